@@ -463,16 +463,13 @@ drf_status launch_bf16_inst(const AttnArgs& a, float scale_log2, hipStream_t st)
     // 8 waves (256 queries) share each staged chunk when there are that many queries.  Up to 256 kv rows
     // go through two buffers of 64 rows (the first MFMAs start after a quarter of the loads and every
     // later chunk is fetched during the steps of the one before; measured the fastest of the 64 / 128 /
-    // 256-row, one / two-buffer combinations), longer sequences through two buffers of 128 rows.
+    // 256-row, one / two-buffer combinations).
     if (a.Nq > 128) {
-        if (a.Nk <= 256) {
-            // more items than workgroups that fit the chip at once: persistent workgroups hide each next
-            // item's first loads; otherwise the plain kernel (fewer registers) is the faster one
-            const long long n_items = (long long)((a.Nq + 255) / 256) * a.heads * a.slots;
-            if (n_items > kPersistGroups) return launch_bf16_cfg<KS, DT, 8, 64, 2, true, true>(a, scale_log2, st);
-            return launch_bf16_cfg<KS, DT, 8, 64, 2, false, true>(a, scale_log2, st);
-        }
-        return launch_bf16_cfg<KS, DT, 8, 128, 2>(a, scale_log2, st);
+        // more items than workgroups that fit the chip at once: persistent workgroups hide each next
+        // item's first loads; otherwise the plain kernel (fewer registers) is the faster one
+        const long long n_items = (long long)((a.Nq + 255) / 256) * a.heads * a.slots;
+        if (n_items > kPersistGroups) return launch_bf16_cfg<KS, DT, 8, 64, 2, true, true>(a, scale_log2, st);
+        return launch_bf16_cfg<KS, DT, 8, 64, 2, false, true>(a, scale_log2, st);
     }
     if (a.Nk <= 256) return launch_bf16_cfg<KS, DT, 4, 256, 1>(a, scale_log2, st);
     return launch_bf16_cfg<KS, DT, 4, 128, 2>(a, scale_log2, st);
@@ -486,7 +483,8 @@ drf_status launch_attn_bf16(const AttnArgs& a, hipStream_t st)
     if (a.Nk < 1 || a.d % 8 != 0 || a.d > 96 || a.ldq % 8 != 0 || a.ldk % 8 != 0 || a.ldo % 8 != 0 ||
         (reinterpret_cast<uintptr_t>(a.out) & 15u) != 0)
         DRF_FAIL(DRF_ESHAPE, "bf16 attention needs head dim %% 8 == 0 and <= 96 (got %d)", a.d);
-    const float sl2 = 1.4426950408889634f / sqrtf((float)a.d);
+    if (attn_long(a.Nq, a.Nk)) return launch_attn_long_bf16(a, st);
+    const float sl2 = attn_scale_log2(a);
     switch ((a.d + 15) / 16) {
     case 1: return launch_bf16_inst<1, 1>(a, sl2, st);
     case 2: return launch_bf16_inst<2, 1>(a, sl2, st);

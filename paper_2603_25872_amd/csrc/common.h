@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <math.h>
 #include <string>
 #include <vector>
 
@@ -108,7 +109,8 @@ struct Epilogue {
     uint32_t rps_magic; int rps_shift;   // m / rows_per_slot == fast_div(m, rps_magic, rps_shift), see set_rows_per_slot
     // EPI_STORE_HEADS (bf16 only): column n = which * hid + head * hd + dd of row m = slot * rows_per_slot + t goes to
     //   out[which * plane + ((slot * heads + head) * rows_per_slot + t) * hd + dd]     (q | k | v planes, head-major)
-    int hid, hd, heads; size_t plane;
+    // with the q plane multiplied by q_scale before it is rounded
+    int hid, hd, heads; size_t plane; float q_scale;
     uint32_t hid_magic, hd_magic; int hid_shift, hd_shift;
     // Optional (bf16 wide-tile kernel only): the last 256 workgroups of the launch (the ones that run in
     // its final round) each load one word of their share of the warm_lines 128-byte lines at `warm`,
@@ -139,8 +141,14 @@ struct AttnArgs {
     void* out; int ldo;             // out row (slot * Nq + i), head h at column h * d
     int Nq, Nk, heads, d, slots;
     int kv_mod;                     // kv_batch = kv_mod ? slot % kv_mod : slot
+    int q_scaled;                   // bf16 path: 1 = the queries have been multiplied by log2(e) / sqrt(d) already
 };
+// Sequences that launch_attn_bf16 hands to launch_attn_long_bf16, which likes its queries scaled by their producer.
+inline bool attn_long(int Nq, int Nk) { return Nq > 128 && Nk > 256; }
+// Factor that turns q . k into an exponent of two.
+inline float attn_scale_log2(const AttnArgs& a) { return a.q_scaled ? 1.f : 1.4426950408889634f / sqrtf((float)a.d); }
 drf_status launch_attn_bf16(const AttnArgs& a, hipStream_t st);
+drf_status launch_attn_long_bf16(const AttnArgs& a, hipStream_t st);
 drf_status launch_attn_f32(const AttnArgs& a, hipStream_t st);
 
 struct DitDims { int D, P, T, gh, gw, C, H, W, patch, heads, d, R, L; };

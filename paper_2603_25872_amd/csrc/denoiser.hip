@@ -278,6 +278,7 @@ Epilogue epi_heads(void* out, int M, const DitDims& dm)
     e.mode = EPI_STORE_HEADS; e.out = out; e.ldo = 3 * dm.D; e.out_f32 = 0;
     set_rows_per_slot(&e, dm.T);
     e.hid = dm.D; e.hd = dm.d; e.heads = dm.heads; e.plane = (size_t)M * dm.D;
+    e.q_scale = attn_long(dm.T, dm.T) ? 1.4426950408889634f / sqrtf((float)dm.d) : 1.f;
     make_fast_div(dm.D, &e.hid_magic, &e.hid_shift);
     make_fast_div(dm.d, &e.hd_magic, &e.hd_shift);
     return e;
@@ -403,6 +404,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
                 aa.k = (char*)ws.qkv + (size_t)M * D * act; aa.v = (char*)ws.qkv + (size_t)2 * M * D * act;
                 aa.ldq = aa.ldk = dm.d;
                 aa.q_slot_stride = aa.kv_batch_stride = (size_t)dm.T * D; aa.q_head_stride = aa.kv_head_stride = (size_t)dm.T * dm.d;
+                aa.q_scaled = attn_long(dm.T, dm.T);
             }
             ProfScope ps(d, st, DRF_PROF_ATTN, 4.0 * slots * dm.heads * (double)dm.T * dm.T * dm.d);
             if ((rc = f32 ? launch_attn_f32(aa, st) : launch_attn_bf16(aa, st)) != DRF_OK) return rc;

@@ -61,6 +61,7 @@ __device__ inline void epilogue4(const Epilogue& e, int m, int n, float v0, floa
         const float4 g = *reinterpret_cast<const float4*>(e.gate + (size_t)fast_div(m, e.rps_magic, e.rps_shift) * e.gate_ld + n);
         v0 *= g.x; v1 *= g.y; v2 *= g.z; v3 *= g.w;
     }
+    if (e.mode == EPI_STORE_HEADS && n < e.hid) { v0 *= e.q_scale; v1 *= e.q_scale; v2 *= e.q_scale; v3 *= e.q_scale; }
     if (e.out_f32) {
         *reinterpret_cast<float4*>((float*)e.out + (size_t)m * e.ldo + n) = make_float4(v0, v1, v2, v3);
     } else {
@@ -570,6 +571,10 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
                         for (int i = 0; i < NI; ++i) {
                             float v0 = acc[i][j][0] + bb[i].x, v1 = acc[i][j][1] + bb[i].y, v2 = acc[i][j][2] + bb[i].z, v3 = acc[i][j][3] + bb[i].w;
                             if (MODE == EPI_STORE_GELU) { v0 = gelu_tanh(v0); v1 = gelu_tanh(v1); v2 = gelu_tanh(v2); v3 = gelu_tanh(v3); }
+                            if constexpr (MODE == EPI_STORE_HEADS) {
+                                const float qs = nw + i * 16 < e.hid ? e.q_scale : 1.f;       // hid is a multiple of 16
+                                v0 *= qs; v1 *= qs; v2 *= qs; v3 *= qs;
+                            }
                             if constexpr (MODE == EPI_STORE_GATED) {
                                 float4 g;
                                 if constexpr (GLDS) {
@@ -739,8 +744,8 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
 {
     if (M == 0 || N == 0) return DRF_OK;
     if (K % 64 != 0 || N % 4 != 0 || e.ldo % 4 != 0) DRF_FAIL(DRF_ESHAPE, "bf16 GEMM needs K %% 64 == 0 and N %% 4 == 0 (M=%d N=%d K=%d)", M, N, K);
-    if (e.mode == EPI_STORE_HEADS && (e.out_f32 || e.hd % 8 != 0 || N % e.hid != 0))
-        DRF_FAIL(DRF_ESHAPE, "head-major store needs bf16 output and head width %% 8 == 0");
+    if (e.mode == EPI_STORE_HEADS && (e.out_f32 || e.hd % 8 != 0 || e.hid % 16 != 0 || N % e.hid != 0))
+        DRF_FAIL(DRF_ESHAPE, "head-major store needs bf16 output, head width %% 8 == 0 and hidden %% 16 == 0");
     if (e.mode == EPI_STORE_GATED && (e.out_f32 || !e.gate)) DRF_FAIL(DRF_ESHAPE, "gated store needs bf16 output and a gate");
     if ((size_t)M * K >= ((size_t)1 << 31) || (size_t)N * K >= ((size_t)1 << 31))
         DRF_FAIL(DRF_ESHAPE, "bf16 GEMM operand exceeds 2^31 elements");

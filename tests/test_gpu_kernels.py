@@ -82,6 +82,20 @@ def test_attention_bf16_shapes(torch, drf, orc, slots, T, H, d):
     assert err < 1.5e-2, err
 
 
+@pytest.mark.parametrize("d", [8, 16, 24, 32, 40, 48, 56, 64, 72, 80, 88, 96])
+@pytest.mark.parametrize("T", [257, 320, 545])
+def test_attention_bf16_long_sequences(torch, drf, orc, d, T):
+    """More than 256 kv rows: every head width, last steps of 1 and 32 rows, a last chunk of one row, and a last query
+    block in which three of four waves have no query."""
+    slots, H = 2, 3
+    rng = np.random.default_rng(1000 * d + T)
+    qkv = bf16_round(torch, rng.standard_normal((slots * T, 3 * H * d)) * 1.5)
+    out = drf.probe_attn_bf16(qkv.cuda(), slots, T, H, d).float().cpu().numpy()
+    want = orc.attention_packed(qkv.float().numpy(), T, H, d)
+    err = np.abs(out - want).max() / np.abs(want).max()
+    assert err < 1.5e-2, err                     # P and the result rounded to bf16: 2^-8 relative each at worst
+
+
 def test_attention_bf16_large_scores_and_lazy_rescale(torch, drf, orc):
     # score ranges far beyond the lazy-rescale headroom, increasing along kv so the reference moves often
     slots, T, H, d = 1, 512, 1, 64
