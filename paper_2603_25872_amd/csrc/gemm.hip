@@ -183,6 +183,8 @@ template <int OFF> __device__ inline void lds_read16(u32x4& dst, uint32_t addr)
 // Waits until at most N LDS reads are outstanding.  The fragments that the following MFMAs consume
 // pass through the statement as in/out operands, so no use of them can be scheduled above the wait.
 template <int N> __device__ inline void wait_frag(u32x4& w) { asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(w) : "n"(N)); }
+// Keeps a fragment's registers its own up to this point.
+__device__ inline void hold_frag(u32x4& w) { asm volatile("" : "+v"(w)); }
 template <int N, int MI> __device__ inline void wait_frags(u32x4& w, u32x4 (&a)[MI])
 {
     static_assert(MI == 2 || MI == 4, "activation fragments per k-step");
@@ -440,7 +442,14 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
         });
         cs = ns;
     }
-    wait_lgkmcnt<0>();                              // the last tile's look-ahead reads
+    // The last tile's look-ahead reads are still on their way into the fragment registers, which nothing consumes
+    // any more: they pass through the wait, so that no register of theirs is given to anything computed above it
+    // (a column index kept there would be overwritten by the data that lands).
+    wait_frag<0>(fw[0]);
+#pragma unroll
+    for (int r = 1; r < R; ++r) hold_frag(fw[r]);
+#pragma unroll
+    for (int j = 0; j < MI; ++j) { hold_frag(fa[0][j]); hold_frag(fa[1][j]); }
 
     if constexpr (SK) {
         // partial tile, straight from the accumulators: acc[i][j][r] is (m = j*16 + l16, n = i*16 + 4*quarter + r)
