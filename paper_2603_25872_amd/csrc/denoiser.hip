@@ -418,7 +418,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         if (d->cfg.cond == DRF_COND_TEXT) {
             const int ctx_rows = map.cond_mod ? map.cond_mod : slots;
             if ((rc = ln(nullptr, nullptr, 0, true)) != DRF_OK) return rc;
-            if ((rc = gemm(d, ws.hbuf, b.xq, M, epi_store(ws.qkv, D, f32), st)) != DRF_OK) return rc;
+            if ((rc = gemm(d, ws.hbuf, b.xq, M, epi_store(ws.qkv, D, f32), st, ws.skpart)) != DRF_OK) return rc;
             const char* kv = (const char*)ws.xkv + (size_t)l * ctx_rows * d->cfg.ctx_len * 2 * D * act;
             AttnArgs aa{};
             aa.q = ws.qkv; aa.ldq = D; aa.k = kv; aa.v = kv + (size_t)D * act; aa.ldk = 2 * D; aa.out = ws.hbuf; aa.ldo = D;
@@ -429,7 +429,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
                 ProfScope ps(d, st, DRF_PROF_ATTN, 4.0 * slots * dm.heads * (double)dm.T * d->cfg.ctx_len * dm.d);
                 if ((rc = f32 ? launch_attn_f32(aa, st) : launch_attn_bf16(aa, st)) != DRF_OK) return rc;
             }
-            if ((rc = gemm(d, ws.hbuf, b.xo, M, epi_resid(ws.resid, D, nullptr, 0, dm.T), st)) != DRF_OK) return rc;
+            if ((rc = gemm(d, ws.hbuf, b.xo, M, epi_resid(ws.resid, D, nullptr, 0, dm.T), st, ws.skpart)) != DRF_OK) return rc;
         }
         const bool last = l == n_blocks - 1;
         if ((rc = ln(mrow + 3 * D, mrow + 4 * D, nm, f32 || last)) != DRF_OK) return rc;
@@ -1079,12 +1079,12 @@ extern "C" drf_status drf_probe_gemm_bf16(const void* A, const void* W, int M, i
     if (!A || !W || !out_bf16 || !bias || M < 0 || N < 0 || K < 0) DRF_FAIL(DRF_EINVAL, "bad argument");
     Epilogue e{};
     e.mode = EPI_STORE; e.out = out_bf16; e.ldo = N; e.out_f32 = 0; e.bias = bias;
-    // variant 10 (the 128 x 128 tile, K split across workgroups where the rule allows): partial tiles in a buffer
-    // that the probe allocates once per process and keeps
+    // split forms (see launch_gemm_bf16): partial tiles in a buffer that the probe allocates once per process and keeps
     static float* probe_splitk = nullptr;
-    if (variant == 10 && !probe_splitk) DRF_HIP(hipMalloc((void**)&probe_splitk, gemm_splitk_scratch_bytes()));
+    const bool split = variant == 10 || variant >= 100;
+    if (split && !probe_splitk) DRF_HIP(hipMalloc((void**)&probe_splitk, gemm_splitk_scratch_bytes()));
     return launch_gemm_bf16((const bf16_t*)A, (const bf16_t*)W, M, N, K, e, (hipStream_t)hip_stream, variant,
-                            variant == 10 ? probe_splitk : nullptr);
+                            split ? probe_splitk : nullptr);
 }
 
 extern "C" drf_status drf_probe_attn_bf16(const void* qkv, void* out, int slots, int tokens, int heads, int head_dim,

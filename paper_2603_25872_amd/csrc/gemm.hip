@@ -1,7 +1,7 @@
 // GEMM C[M][N] = A[M][K] . W[N][K]^T with fused epilogues (bias, GELU-tanh, gated
-// residual).  bf16 path: the wide-tile kernel (16x16x32 MFMAs, operands by LDS-DMA) for the
-// DiT's big GEMMs and a small 32x32x16-MFMA kernel for short or ragged problems, fp32
-// accumulate.  fp32 path: plain LDS-tiled FMA kernel for the fp32 configuration.
+// residual).  bf16 path: one software-pipelined kernel (16x16x32 MFMAs, operands by LDS-DMA, fp32
+// accumulate) at tiles from 32 x 64 to 256 x 288, the tile chosen by a measured time model.
+// fp32 path: plain LDS-tiled FMA kernel for the fp32 configuration.
 #include <type_traits>
 
 #include "common.h"
@@ -12,7 +12,6 @@ namespace {
 
 typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
 typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // GELU (tanh form): 0.5 x (1 + tanh(u)) = x * sigmoid(2u), u = sqrt(2/pi) (x + 0.044715 x^3).
 // One exp2 and one reciprocal (both hardware transcendental ops, ~1 ulp).
@@ -72,103 +71,6 @@ __device__ inline void epilogue4(const Epilogue& e, int m, int n, float v0, floa
 }
 
 // ------------------------------------------------------------------ bf16 MFMA
-// Block tile BM x BN x 64, WM x WN waves, each wave (BM/WM) x (BN/WN) as 32x32 MFMA tiles.
-// The weight tile is the MFMA "A" operand and the activation tile the "B" operand, so a
-// lane ends up with 4 consecutive output columns per register quad (vector stores).
-template <int BM, int BN, int WM, int WN>
-__global__ void __launch_bounds__(WM * WN * 64)
-gemm_bf16_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K, const Epilogue e)
-{
-    constexpr int BK = 64, LDK = BK + 8, NT = WM * WN * 64;
-    constexpr int TM = BM / WM, TN = BN / WN, MI = TM / 32, NI = TN / 32;
-    constexpr int ACH = BM * (BK / 8) / NT, WCH = BN * (BK / 8) / NT;   // 16-byte chunks per thread
-    static_assert(BM * (BK / 8) % NT == 0 && BN * (BK / 8) % NT == 0, "tile/threads mismatch");
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    bf16_t* sA = reinterpret_cast<bf16_t*>(smem_raw);                 // [2][BM][LDK]
-    bf16_t* sW = sA + 2 * BM * LDK;                                     // [2][BN][LDK]
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % WM, wn = wave / WM;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int l32 = lane & 31, half = lane >> 5;
-
-    bf16x8 ra[ACH], rw[WCH];
-    auto load_global = [&](int kt) {
-#pragma unroll
-        for (int c = 0; c < ACH; ++c) {
-            const int id = tid + c * NT, row = id >> 3, kc = id & 7;
-            int gm = m0 + row; gm = gm < M ? gm : M - 1;               // clamp: rows past M are never stored
-            ra[c] = *reinterpret_cast<const bf16x8*>(A + (size_t)gm * K + kt * BK + kc * 8);
-        }
-#pragma unroll
-        for (int c = 0; c < WCH; ++c) {
-            const int id = tid + c * NT, row = id >> 3, kc = id & 7;
-            int gn = n0 + row; gn = gn < N ? gn : N - 1;
-            rw[c] = *reinterpret_cast<const bf16x8*>(W + (size_t)gn * K + kt * BK + kc * 8);
-        }
-    };
-    auto store_lds = [&](int buf) {
-#pragma unroll
-        for (int c = 0; c < ACH; ++c) {
-            const int id = tid + c * NT, row = id >> 3, kc = id & 7;
-            *reinterpret_cast<bf16x8*>(sA + (buf * BM + row) * LDK + kc * 8) = ra[c];
-        }
-#pragma unroll
-        for (int c = 0; c < WCH; ++c) {
-            const int id = tid + c * NT, row = id >> 3, kc = id & 7;
-            *reinterpret_cast<bf16x8*>(sW + (buf * BN + row) * LDK + kc * 8) = rw[c];
-        }
-    };
-
-    f32x16 acc[NI][MI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int j = 0; j < MI; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    const int nk = K / BK;
-    load_global(0);
-    store_lds(0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) load_global(kt + 1);
-        const bf16_t* pa = sA + (buf * BM + wm * TM + l32) * LDK + half * 8;
-        const bf16_t* pw = sW + (buf * BN + wn * TN + l32) * LDK + half * 8;
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            bf16x8 fa[MI], fw[NI];
-#pragma unroll
-            for (int j = 0; j < MI; ++j) fa[j] = *reinterpret_cast<const bf16x8*>(pa + j * 32 * LDK + ks * 16);
-#pragma unroll
-            for (int i = 0; i < NI; ++i) fw[i] = *reinterpret_cast<const bf16x8*>(pw + i * 32 * LDK + ks * 16);
-#pragma unroll
-            for (int i = 0; i < NI; ++i)
-#pragma unroll
-                for (int j = 0; j < MI; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[i], fa[j], acc[i][j], 0, 0, 0);
-        }
-        if (kt + 1 < nk) store_lds(buf ^ 1);
-        __syncthreads();
-    }
-
-    // acc[i][j][r]: n = n0 + wn*TN + i*32 + 8*(r/4) + 4*half + r%4,  m = m0 + wm*TM + j*32 + l32
-#pragma unroll
-    for (int j = 0; j < MI; ++j) {
-        const int m = m0 + wm * TM + j * 32 + l32;
-        if (m >= M) continue;
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = n0 + wn * TN + i * 32 + 8 * q + 4 * half;
-                if (n < N) epilogue4(e, m, n, acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-            }
-    }
-}
-
 #define DRF_GLOBAL_AS __attribute__((address_space(1)))
 #define DRF_LDS_AS __attribute__((address_space(3)))
 template <int N> __device__ inline void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
@@ -199,8 +101,7 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
     }
 }
 
-// ------------------------------------------------ bf16 MFMA 16x16x32, wide tiles
-// The main kernel for the DiT's big GEMMs.  BM x BN x 64 block tile (256 x 288 for hidden
+// The kernel for all of the DiT's GEMMs.  BM x BN x 64 block tile (256 x 288 for hidden
 // 1152: 1152, 3456 and 4608 are all multiples of 288, so at 64 row tiles every GEMM of the
 // block is a whole number of 256-tile rounds), 8 waves as WM x WN, wave tile (BM/WM) x
 // (BN/WN) built from 16x16x32 MFMAs so that widths only need to be multiples of 16.
@@ -221,17 +122,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // copy instructions issued per MFMA group by the in-loop copy of the two-stage kernels (1: measured best; 2, 3 and
 // the whole copy at once are 0.8 % slower per call, one every other group lands too late: 3 % slower)
 constexpr int kSpreadPer = 1;
-// split K across workgroups: at most this many workgroups per launch (one round of the GPU's CUs), and only
-// when the problem has at least this many 64-wide k-tiles (shorter ones do not repay the reduction launch:
-// 36 -> 18 was measured, another 4.5 % off a batch-1 call)
-constexpr int kSplitKMaxGroups = 256, kSplitKMinKTiles = 18;
+// partial tiles of one split-K launch: 256 tiles of 128 x 128
+constexpr size_t kSplitKScratchFloats = (size_t)256 * 128 * 128;
 
-//  - SK (split K across workgroups, for problems with few tiles and a long K: the out-projection of the MLP at
-//    one or two samples per pass): tiles_n counts sk.splits column-tile rows, workgroup (tm, tn) takes k-range
-//    tn / sk.tiles_n of column tile tn % sk.tiles_n and leaves its fp32 partial tile in sk.part
-//    ([split][tiles_m * BM][sk.tiles_n * BN], padded, so no bounds are needed); splitk_reduce_kernel adds the
-//    partial tiles in a fixed order and applies the epilogue.
-struct SplitK { int splits, tiles_n, ksub; float* part; };
+//  - SK (split K across workgroups, for problems with few tiles and a long K): tiles_n counts sk.splits column-tile
+//    rows, workgroup (tm, tn) takes the k-steps of part tn / sk.tiles_n (parts differ by at most one step) of column
+//    tile tn % sk.tiles_n and leaves its fp32 partial tile in sk.part ([split][tiles_m * BM][sk.tiles_n * BN], padded,
+//    so no bounds are needed); splitk_reduce_kernel adds the partial tiles in a fixed order and applies the epilogue.
+struct SplitK { int splits, tiles_n; float* part; };
 
 template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1, bool SK = false>
 __global__ void __launch_bounds__(WM * WN * WK * 64)
@@ -258,7 +156,12 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
     const int tm = first_m + (idx % per_group) % gsz, tn = (idx % per_group) / gsz;
     const int split = SK ? tn / sk.tiles_n : 0;
     const int m0 = tm * BM, n0 = (SK ? tn - split * sk.tiles_n : tn) * BN;
-    if constexpr (SK) { A += split * sk.ksub; W += split * sk.ksub; }   // row stride stays K
+    int nk = K / (BK * WK);                                          // k-steps of this workgroup
+    if constexpr (SK) {
+        const int first = split * nk / sk.splits, last = (split + 1) * nk / sk.splits;
+        A += first * BK * WK; W += first * BK * WK;                  // row stride stays K
+        nk = last - first;
+    }
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform, kept in a scalar register
@@ -338,7 +241,7 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
     // MFMAs of group g it is enough that at most the reads issued after position g's remain.
     static_assert(NS >= 2 && KS == 2, "the pipelined loop assumes LDS stages of two k-steps");
     constexpr int G = KS * NI;
-    constexpr int R = G % 6 == 0 ? 6 : G % 4 == 0 ? 4 : G % 5 == 0 ? 5 : G % 3 == 0 ? 3 : 2, D = R - 1;
+    constexpr int R = G % 6 == 0 && NI >= 6 ? 6 : G % 4 == 0 && NI >= 4 ? 4 : G % 5 == 0 && NI >= 5 ? 5 : G % 3 == 0 && NI >= 3 ? 3 : 2, D = R - 1;
     static_assert(G % R == 0 && D < NI && D + MI <= 15, "ring size");
     // With two stages the copy of tile kt + 2 is not issued as one burst after the barrier of tile kt (72
     // wave-wide loads that the vector-memory path takes one per ~17 cycles, during which the issuing waves
@@ -349,7 +252,6 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
     constexpr int HEAD0 = D * PER < LPT ? D * PER : LPT;
     constexpr bool kSpread = NS == 2 && WK == 1 && (LPT - HEAD0 + PER - 1) / PER <= G - D;
     constexpr int HEAD = kSpread ? HEAD0 : LPT, TAIL = LPT - HEAD;
-    const int nk = (SK ? sk.ksub : K) / (BK * WK);
     u32x4 fa[2][MI], fw[R];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(DRF_LDS_AS unsigned char*)smem_raw;
     uint32_t a_addr[KS], w_addr[KS];                // byte addresses of this lane's fragments in stage 0
@@ -451,17 +353,6 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
 #pragma unroll
     for (int j = 0; j < MI; ++j) { hold_frag(fa[0][j]); hold_frag(fa[1][j]); }
 
-    if constexpr (SK) {
-        // partial tile, straight from the accumulators: acc[i][j][r] is (m = j*16 + l16, n = i*16 + 4*quarter + r)
-        static_assert(WK == 1, "split K across workgroups or across wave groups, not both");
-        float* pt = sk.part + ((size_t)split * tiles_m * BM + m0 + wm * TM) * ((size_t)sk.tiles_n * BN) + n0 + wn * TN;
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-            for (int j = 0; j < MI; ++j)
-                *reinterpret_cast<f32x4*>(pt + (size_t)(j * 16 + l16) * ((size_t)sk.tiles_n * BN) + i * 16 + 4 * quarter) = acc[i][j];
-        return;
-    }
     // ---- epilogue through LDS: acc[i][j][r] is (m = j*16 + l16, n = i*16 + 4*quarter + r) of the wave tile
     __syncthreads();
     constexpr int PART = (WK - 1) * NWT * TM * TN * 4;              // partial sums of the other K groups
@@ -482,6 +373,16 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
             for (int i = 0; i < NI; ++i)
 #pragma unroll
                 for (int j = 0; j < MI; ++j) acc[i][j] += part[((g * NWT + wl) * NI * MI + i * MI + j) * 64 + lane];
+    }
+    if constexpr (SK) {
+        // partial tile, straight from the accumulators: acc[i][j][r] is (m = j*16 + l16, n = i*16 + 4*quarter + r)
+        float* pt = sk.part + ((size_t)split * tiles_m * BM + m0 + wm * TM) * ((size_t)sk.tiles_n * BN) + n0 + wn * TN;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < MI; ++j)
+                *reinterpret_cast<f32x4*>(pt + (size_t)(j * 16 + l16) * ((size_t)sk.tiles_n * BN) + i * 16 + 4 * quarter) = acc[i][j];
+        return;
     }
     constexpr int WBYTES = (NS * STAGE * 2 - PART) / NWT / 16 * 16; // this wave's private slice of the stages
     unsigned char* wbuf = smem_raw + PART + wl * WBYTES;
@@ -684,22 +585,6 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M,
     }
 }
 
-template <int BM, int BN, int WM, int WN>
-drf_status launch_bf16_tile(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st)
-{
-    constexpr size_t smem = (size_t)2 * (BM + BN) * (64 + 8) * sizeof(bf16_t);
-    static bool attr_set = false;
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN>;
-    if (!attr_set) {
-        DRF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-        attr_set = true;
-    }
-    const dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM);
-    hipLaunchKernelGGL(kern, grid, dim3(WM * WN * 64), smem, st, A, W, M, N, K, e);
-    DRF_HIP(hipGetLastError());
-    return DRF_OK;
-}
-
 template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1>
 drf_status launch_bf16_xl(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st)
 {
@@ -718,23 +603,24 @@ drf_status launch_bf16_xl(const bf16_t* A, const bf16_t* W, int M, int N, int K,
     return DRF_OK;
 }
 
-// Split-K form of the 128 x 128 tile: `splits` workgroups per output tile, partial tiles in `part`
-// (splits * tiles * 128 * 128 floats), then the reduction with the epilogue.
+// Split-K form: `splits` workgroups per output tile, partial tiles in `part`, then the reduction with the epilogue.
+template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1>
 drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
                               int splits, float* part)
 {
-    constexpr int BM = 128, BN = 128, BK = 64;
-    constexpr int NS = 4;
-    constexpr size_t smem = (size_t)NS * (BM + BN) * BK * sizeof(bf16_t) + BN * sizeof(float);
+    constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + BN * sizeof(float);
+    static_assert(smem <= 160 * 1024, "LDS of a CU");
     static bool attr_set = false;
-    auto kern = gemm_bf16_xl_kernel<BM, BN, BK, NS, 2, 2, 1, true>;
+    auto kern = gemm_bf16_xl_kernel<BM, BN, BK, NS, WM, WN, WK, true>;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+    if (!part || K % (BK * WK) != 0 || K / (BK * WK) < splits || (size_t)tiles_m * tiles_n * splits * BM * BN > kSplitKScratchFloats)
+        DRF_FAIL(DRF_ESHAPE, "split-K GEMM of %d parts does not fit (M=%d N=%d K=%d)", splits, M, N, K);
     if (!attr_set) {
         DRF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
         attr_set = true;
     }
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    SplitK sk{ splits, tiles_n, K / splits, part };
-    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(256), smem, st, A, W, M, N, K, e, tiles_m, tiles_n * splits, sk);
+    SplitK sk{ splits, tiles_n, part };
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(WM * WN * WK * 64), smem, st, A, W, M, N, K, e, tiles_m, tiles_n * splits, sk);
     DRF_HIP(hipGetLastError());
     const int ldp = tiles_n * BN;
     const long long quads = (long long)M * (N / 4);
@@ -744,9 +630,61 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
     return DRF_OK;
 }
 
+// The tiles, and a time model of a launch of each: base + (per round of workgroups) round + steps * max(lat, c * thr)
+// microseconds, where a round is per_cu workgroups on each of the 256 CUs, c the workgroups that share a CU in it and
+// steps the k-steps of 64 * wk; a split adds red0 + red1 per million partial elements for the reduction launch.
+// The constants are least-squares fits to timings of every tile on 85 shapes (M 2 .. 16384, N 384 .. 195840, K 384 ..
+// 4608, weights cold); the tile that the model picks is 0.7 % slower than the fastest of all on average and 14 % at
+// worst.  Small problems live on small tiles: with weights coming from HBM a launch is a chain of round trips, and what
+// counts is how many of the chip's CUs pull operands at once (M = 512, N = K = 1152: 13.2 us on 36 128 x 128 tiles,
+// 7.0 us on 144 64 x 64 tiles whose two wave groups split K; N = 3456: 15.5 -> 11.2 us on 128 x 64; M = 2048, N = 3456:
+// 32.5 -> 23.9 us with two 128 x 128 workgroups per CU; M = 12288, N = 1536, K = 384: 31.9 -> 22.9 us likewise).
+struct TileModel { int id, bm, bn, wk, per_cu; double base, round, lat, thr, red0, red1; };     // red0 = 0: never split
+const TileModel kTiles[] = {
+    {  2, 256, 288, 1, 1, 0.00, 6.21, 1.52, 0.10, 0.0, 0.0 },
+    {  3, 256, 256, 1, 1, 0.00, 4.69, 1.41, 0.10, 0.0, 0.0 },
+    {  4, 128, 128, 1, 2, 0.00, 2.80, 0.86, 0.03, 0.0, 0.0 },
+    {  5, 128, 128, 1, 1, 0.88, 2.83, 0.51, 0.51, 3.3, 2.3 },
+    {  8, 128, 144, 2, 1, 0.61, 4.06, 0.45, 1.41, 0.0, 0.0 },
+    {  7, 128,  96, 1, 1, 1.38, 2.78, 0.48, 0.48, 0.0, 0.0 },
+    {  6, 128,  64, 1, 1, 0.95, 2.35, 0.17, 0.35, 3.6, 1.8 },
+    { 11,  64,  96, 2, 1, 1.38, 2.33, 0.57, 0.12, 0.0, 0.0 },
+    {  9,  64,  64, 2, 1, 1.42, 1.93, 0.44, 0.10, 3.5, 1.6 },
+    {  1,  64,  64, 1, 2, 1.97, 1.33, 0.26, 0.21, 3.1, 1.9 },
+    { 12,  32,  64, 2, 2, 2.04, 1.43, 0.38, 0.29, 3.1, 1.8 },
+};
+
+double model_us(const TileModel& t, int M, int N, int K, int splits)
+{
+    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
+    const int steps = (K / (64 * t.wk) + splits - 1) / splits;
+    const long long cap = 256LL * t.per_cu, full = tiles / cap, share = (tiles - full * cap + 255) / 256;
+    double us = t.base + full * (t.round + steps * fmax(t.lat, t.per_cu * t.thr));
+    if (share) us += t.round + steps * fmax(t.lat, share * t.thr);
+    if (splits > 1) us += t.red0 + t.red1 * 1e-6 * M * N * splits;
+    return us;
+}
+
+// The tile and split with the least modelled time.  Two K groups need whole pairs of k-tiles; a split leaves every
+// part at least two k-steps and its partial tiles must fit the scratch.
+void pick_tile(int M, int N, int K, bool may_split, int* id, int* splits)
+{
+    double best = 1e300;
+    for (const TileModel& t : kTiles) {
+        if (K % (64 * t.wk) != 0) continue;
+        const size_t tile_floats = (size_t)((M + t.bm - 1) / t.bm) * t.bm * ((size_t)((N + t.bn - 1) / t.bn) * t.bn);
+        const int most = may_split && t.red0 > 0.0 && tile_floats / (t.bm * t.bn) < 512 ? 6 : 1;   // (enough tiles fill the chip unsplit)
+        for (int s2 = 1; s2 <= most; ++s2) {
+            if (s2 > 1 && (K / (64 * t.wk) < 2 * s2 || tile_floats * s2 > kSplitKScratchFloats)) break;
+            const double us = model_us(t, M, N, K, s2);
+            if (us < best) { best = us; *id = t.id; *splits = s2; }
+        }
+    }
+}
+
 }  // namespace
 
-size_t gemm_splitk_scratch_bytes() { return (size_t)kSplitKMaxGroups * 128 * 128 * sizeof(float); }
+size_t gemm_splitk_scratch_bytes() { return kSplitKScratchFloats * sizeof(float); }
 
 drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
                             int variant, float* splitk_scratch)
@@ -758,46 +696,41 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
     if (e.mode == EPI_STORE_GATED && (e.out_f32 || !e.gate)) DRF_FAIL(DRF_ESHAPE, "gated store needs bf16 output and a gate");
     if ((size_t)M * K >= ((size_t)1 << 31) || (size_t)N * K >= ((size_t)1 << 31))
         DRF_FAIL(DRF_ESHAPE, "bf16 GEMM operand exceeds 2^31 elements");
-    int v = variant;
+    int v = variant, splits = 1;
     if (v == 0) {
-        // Pick the tile shape that wastes the least MFMA work: padding of the last tile row /
-        // column, and the idle CUs of the last round of 256 concurrent tiles.
-        struct Cand { int id, bm, bn; double eff; };
-        const Cand cands[] = { { 2, 256, 288, 1.0 }, { 3, 256, 256, 0.97 }, { 4, 128, 288, 0.8 }, { 7, 128, 144, 0.6 },
-                               { 5, 128, 128, 0.55 } };
-        double best = 0.0;
-        v = 1;
-        if (M >= 512) {
-            for (const Cand& c : cands) {
-                const double tm = (M + c.bm - 1) / c.bm, tn = (N + c.bn - 1) / c.bn, tiles = tm * tn;
-                const double rounds = (double)((long long)(tiles + 255) / 256);
-                const double score = c.eff * ((double)M * N) / (rounds * 256.0 * c.bm * c.bn);
-                if (score > best) { best = score; v = c.id; }
-            }
-            // one small tile per CU: let two wave groups split K inside the block
-            if (v == 7 && K % 128 == 0 && K >= 1024) v = 8;
+        pick_tile(M, N, K, splitk_scratch != nullptr, &v, &splits);
+    } else if (v >= 100) {
+        splits = v / 100;
+        v %= 100;
+    } else if (v == 10) {
+        v = 5;
+        const int tiles = ((M + 127) / 128) * ((N + 127) / 128), nk = K / 64;
+        for (int s2 = 2; splitk_scratch && s2 <= 8 && s2 * tiles <= 256; ++s2)
+            if (nk / s2 >= 6) splits = s2;
+    }
+    if (splits > 1) {
+        switch (v) {
+        case 1: return launch_bf16_splitk<64, 64, 64, 4, 2, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
+        case 5: return launch_bf16_splitk<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
+        case 6: return launch_bf16_splitk<128, 64, 64, 4, 4, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
+        case 9: return launch_bf16_splitk<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
+        case 12: return launch_bf16_splitk<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
+        default: DRF_FAIL(DRF_EINVAL, "GEMM tile %d has no split form", v);
         }
     }
-    // Few 128 x 128 tiles and a long K (one or two samples per pass: the MLP's out-projection is 36 tiles of 72
-    // k-tiles on 256 CUs, the attention out-projection 36 of 18): split K over as many workgroups as fit one
-    // round, the k-tiles dividing evenly and at least six to a workgroup.
-    if (v == 10) v = 5;
-    if ((v == 5 || v == 1) && (variant == 0 || variant == 10) && splitk_scratch && K / 64 >= kSplitKMinKTiles) {
-        const int tiles = ((M + 127) / 128) * ((N + 127) / 128), nk = K / 64;
-        int splits = 0;
-        for (int s2 = 2; s2 <= 8 && s2 * tiles <= kSplitKMaxGroups; ++s2)
-            if (nk % s2 == 0 && nk / s2 >= 6) splits = s2;
-        if (splits) return launch_bf16_splitk(A, W, M, N, K, e, st, splits, splitk_scratch);
-    }
     switch (v) {
+    case 1: return launch_bf16_xl<64, 64, 64, 4, 2, 2>(A, W, M, N, K, e, st);
     case 2: return launch_bf16_xl<256, 288, 64, 2, 4, 2>(A, W, M, N, K, e, st);
     case 3: return launch_bf16_xl<256, 256, 64, 2, 4, 2>(A, W, M, N, K, e, st);
-    case 4: return launch_bf16_xl<128, 288, 64, 2, 2, 2>(A, W, M, N, K, e, st);
-    case 5: return launch_bf16_xl<128, 128, 64, 4, 2, 2>(A, W, M, N, K, e, st);
-    case 6: return launch_bf16_xl<256, 288, 64, 2, 4, 3>(A, W, M, N, K, e, st);
-    case 7: return launch_bf16_xl<128, 144, 64, 4, 4, 1>(A, W, M, N, K, e, st);
+    case 4: return launch_bf16_xl<128, 128, 64, 2, 4, 2>(A, W, M, N, K, e, st);
+    case 5: return launch_bf16_xl<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st);
+    case 6: return launch_bf16_xl<128, 64, 64, 4, 4, 2>(A, W, M, N, K, e, st);
+    case 7: return launch_bf16_xl<128, 96, 64, 3, 4, 1>(A, W, M, N, K, e, st);
     case 8: return launch_bf16_xl<128, 144, 64, 2, 4, 1, 2>(A, W, M, N, K, e, st);
-    default: return launch_bf16_tile<128, 128, 2, 2>(A, W, M, N, K, e, st);
+    case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st);
+    case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st);
+    case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st);
+    default: DRF_FAIL(DRF_EINVAL, "unknown GEMM tile %d", v);
     }
 }
 

@@ -63,6 +63,24 @@ def test_gemm_bf16_split_k(torch, drf, orc, M, N, K):
     assert np.abs(out - whole).max() / scale < 6e-3   # both are bf16 roundings of nearly the same fp32 sums
 
 
+@pytest.mark.parametrize("variant", [9, 11, 12, 501, 505, 406, 409, 412])
+@pytest.mark.parametrize("M,N,K", [(300, 292, 1152), (33, 8, 1152), (1, 64, 1280), (130, 100, 1408)])
+def test_gemm_bf16_small_tiles_and_splits(torch, drf, orc, variant, M, N, K):
+    """Tiles of two K groups (9, 11, 12) and 100 s + tile: K in s parts whose k-steps do not divide evenly (18, 20, 22
+    steps in 5 parts; 9, 10, 11 pairs in 4)."""
+    rng = np.random.default_rng(M + N + K)
+    A = bf16_round(torch, rng.standard_normal((M, K)))
+    W = bf16_round(torch, rng.standard_normal((N, K)) * 0.1)
+    b = rng.standard_normal(N).astype(np.float32)
+    out = drf.probe_gemm_bf16(A.cuda(), W.cuda(), torch.from_numpy(b).cuda(), variant=variant).float().cpu().numpy()
+    want = orc.linear(A.float().numpy(), W.float().numpy(), b)
+    err = np.abs(out - want).max() / np.abs(want).max()
+    assert err < 6e-3, err                       # bf16 rounding of the stored result: 2^-8 relative at worst
+    if variant in (9, 11, 12):                   # an odd number of k-tiles has no pairs
+        with pytest.raises(drf.DrfError):
+            drf.probe_gemm_bf16(A[:, :192].contiguous().cuda(), W[:, :192].contiguous().cuda(), torch.from_numpy(b).cuda(), variant=variant)
+
+
 def test_gemm_bf16_rejects_bad_k(torch, drf):
     A = torch.zeros((64, 72), dtype=torch.bfloat16, device="cuda")
     W = torch.zeros((64, 72), dtype=torch.bfloat16, device="cuda")
