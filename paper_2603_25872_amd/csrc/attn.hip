@@ -31,9 +31,7 @@ constexpr float kTau = 8.f;         // lazy-rescale headroom of the online softm
 // KS = ceil(d / 16) k-steps of the score MFMA; DT = ceil(d / 32) row tiles of O^T; NW waves of 32
 // queries per block, all sharing the staged K / V (NW = 8 covers the 256 tokens of a DiT-XL head
 // with one block, so K and V are read and transposed once per head).
-// K and V^T are staged in chunks of KC kv rows, NB chunk buffers: a sequence of up to KC rows is
-// staged once (NB = 1) and the waves then run their steps without any block barrier; longer
-// sequences alternate two buffers with one barrier per chunk.  Between barriers the two waves of
+// K and V^T are staged in chunks of KC kv rows that alternate two buffers, one barrier per chunk.  Between barriers the two waves of
 // a SIMD drift apart, so the MFMAs of one overlap the softmax arithmetic of the other; a barrier
 // per 64-row step would keep every wave in the same phase and leave either the matrix or the
 // vector unit idle.
@@ -50,11 +48,10 @@ constexpr float kTau = 8.f;         // lazy-rescale headroom of the online softm
 // PERSIST a workgroup takes items blockIdx.x, blockIdx.x + gridDim.x, ... and, while it runs the steps
 // of an item's last chunk, already has the next item's Q fragments and first K / V chunk in flight, so
 // only the first item of a workgroup waits for its first loads with nothing else to do.
-template <int KS, int DT, int NW, int KC, int NB, bool PERSIST, bool VTR>
+template <int KS, int DT, int NW, int KC, bool PERSIST, bool VTR>
 __global__ void __launch_bounds__(NW * 64) attn_bf16_kernel(const AttnArgs a, float scale_log2, int nqb, int n_items)
 {
-    static_assert(!PERSIST || NB == 2, "the cross-item prefetch needs two chunk buffers");
-    constexpr int NT = NW * 64;
+    constexpr int NT = NW * 64, NB = 2;
     // VTR row stride of V: 4 consecutive rows x 32 bytes tile the 32 banks
     constexpr int DK = KS * 16, LDKS = DK + 8, LDV = VTR ? DT * 32 + 16 : KC + 8;
     constexpr int KBUF = KC * LDKS, VBUF = VTR ? KC * LDV : DT * 32 * LDV;
@@ -296,11 +293,11 @@ __global__ void __launch_bounds__(NW * 64) attn_bf16_kernel(const AttnArgs a, fl
             for (int r = 0; r < 16; ++r) o[t][r] = 0.f;
         m_run = -INFINITY; l_run = 0.f;
         for (int c0 = 0; c0 < a.Nk; c0 += KC) {
-            // chunk c0 is visible in `buf`; with two buffers the next chunk (of this item, or the first
+            // chunk c0 is visible in `buf`; the next chunk (of this item, or the first
             // one of the workgroup's next item together with that item's Q fragments) is fetched now and
             // staged after this chunk's steps (the other buffer was last read before the previous barrier)
             const bool more = c0 + KC < a.Nk;
-            if (NB == 2 && more) fetch(cur, c0 + KC);
+            if (more) fetch(cur, c0 + KC);
             if (PERSIST && !more && has_next) {
                 np = locate(nxt);
                 fetch(np, 0);
@@ -314,14 +311,8 @@ __global__ void __launch_bounds__(NW * 64) attn_bf16_kernel(const AttnArgs a, fl
                 for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
             }
             if (more || has_next) {
-                if (NB == 2) {
-                    stage(buf ^ 1);
-                    buf ^= 1;
-                } else {                        // single buffer: refill in place
-                    __syncthreads();
-                    fetch(cur, c0 + KC);
-                    stage(0);
-                }
+                stage(buf ^ 1);
+                buf ^= 1;
                 __syncthreads();
             }
         }
@@ -435,13 +426,13 @@ __global__ void __launch_bounds__(kF32Threads) attn_f32_kernel(const AttnArgs a,
     }
 }
 
-template <int KS, int DT, int NW, int KC, int NB, bool PERSIST = false, bool VTR = false>
+template <int KS, int DT, int NW, int KC, bool PERSIST = false, bool VTR = false>
 drf_status launch_bf16_cfg(const AttnArgs& a, float scale_log2, hipStream_t st)
 {
     constexpr int LDKS = KS * 16 + 8, LDV = VTR ? DT * 32 + 16 : KC + 8;
-    constexpr size_t smem = ((size_t)NB * (KC * LDKS + (VTR ? KC : DT * 32) * LDV) + (size_t)NW * 32 * (DT * 32 + 8)) * sizeof(bf16_t);
+    constexpr size_t smem = ((size_t)2 * (KC * LDKS + (VTR ? KC : DT * 32) * LDV) + (size_t)NW * 32 * (DT * 32 + 8)) * sizeof(bf16_t);
     static_assert(smem <= 160 * 1024 && smem % 16 == 0, "LDS budget");
-    auto kern = attn_bf16_kernel<KS, DT, NW, KC, NB, PERSIST, VTR>;
+    auto kern = attn_bf16_kernel<KS, DT, NW, KC, PERSIST, VTR>;
     static bool attr_set = false;
     if (!attr_set) {
         DRF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
@@ -460,7 +451,7 @@ drf_status launch_bf16_cfg(const AttnArgs& a, float scale_log2, hipStream_t st)
 template <int KS, int DT>
 drf_status launch_bf16_inst(const AttnArgs& a, float scale_log2, hipStream_t st)
 {
-    // 8 waves (256 queries) share each staged chunk when there are that many queries.  Up to 256 kv rows
+    // 8 waves (256 queries) share each staged chunk when there are that many queries.  The kv rows (up to 256) then
     // go through two buffers of 64 rows (the first MFMAs start after a quarter of the loads and every
     // later chunk is fetched during the steps of the one before; measured the fastest of the 64 / 128 /
     // 256-row, one / two-buffer combinations).
@@ -468,11 +459,10 @@ drf_status launch_bf16_inst(const AttnArgs& a, float scale_log2, hipStream_t st)
         // more items than workgroups that fit the chip at once: persistent workgroups hide each next
         // item's first loads; otherwise the plain kernel (fewer registers) is the faster one
         const long long n_items = (long long)((a.Nq + 255) / 256) * a.heads * a.slots;
-        if (n_items > kPersistGroups) return launch_bf16_cfg<KS, DT, 8, 64, 2, true, true>(a, scale_log2, st);
-        return launch_bf16_cfg<KS, DT, 8, 64, 2, false, true>(a, scale_log2, st);
+        if (n_items > kPersistGroups) return launch_bf16_cfg<KS, DT, 8, 64, true, true>(a, scale_log2, st);
+        return launch_bf16_cfg<KS, DT, 8, 64, false, true>(a, scale_log2, st);
     }
-    if (a.Nk <= 256) return launch_bf16_cfg<KS, DT, 4, 256, 1>(a, scale_log2, st);
-    return launch_bf16_cfg<KS, DT, 4, 128, 2>(a, scale_log2, st);
+    return launch_bf16_cfg<KS, DT, 4, 128>(a, scale_log2, st);
 }
 
 }  // namespace
@@ -484,6 +474,9 @@ drf_status launch_attn_bf16(const AttnArgs& a, hipStream_t st)
         (reinterpret_cast<uintptr_t>(a.out) & 15u) != 0)
         DRF_FAIL(DRF_ESHAPE, "bf16 attention needs head dim %% 8 == 0 and <= 96 (got %d)", a.d);
     if (attn_long(a.Nq, a.Nk)) return launch_attn_long_bf16(a, st);
+    bool taken = false;
+    const drf_status rc = launch_attn_short_bf16(a, st, &taken);
+    if (rc != DRF_OK || taken) return rc;
     const float sl2 = attn_scale_log2(a);
     switch ((a.d + 15) / 16) {
     case 1: return launch_bf16_inst<1, 1>(a, sl2, st);

@@ -150,6 +150,8 @@ inline bool attn_long(int Nq, int Nk) { return Nq > 128 && Nk > 256; }
 inline float attn_scale_log2(const AttnArgs& a) { return a.q_scaled ? 1.f : 1.4426950408889634f / sqrtf((float)a.d); }
 drf_status launch_attn_bf16(const AttnArgs& a, hipStream_t st);
 drf_status launch_attn_long_bf16(const AttnArgs& a, hipStream_t st);
+// Takes the launch (*taken) when it is the faster kernel for it: Nk <= 256, and few or short query sequences.
+drf_status launch_attn_short_bf16(const AttnArgs& a, hipStream_t st, bool* taken);
 drf_status launch_attn_f32(const AttnArgs& a, hipStream_t st);
 
 struct DitDims { int D, P, T, gh, gw, C, H, W, patch, heads, d, R, L; };

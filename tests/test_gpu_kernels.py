@@ -114,6 +114,20 @@ def test_attention_bf16_long_sequences(torch, drf, orc, d, T):
     assert err < 1.5e-2, err                     # P and the result rounded to bf16: 2^-8 relative each at worst
 
 
+@pytest.mark.parametrize("d", [8, 16, 24, 32, 40, 48, 56, 64, 72, 80, 88, 96])
+@pytest.mark.parametrize("slots,T,H,scale", [(3, 1, 2, 1.5), (2, 31, 3, 1.5), (2, 64, 1, 1.5), (3, 65, 2, 1.5), (1, 193, 2, 1.5),
+                                             (1, 256, 2, 6.0), (300, 40, 8, 1.5)])
+def test_attention_bf16_one_wave_per_64_rows(torch, drf, orc, slots, T, H, scale, d):
+    """Up to 256 kv rows split over the waves of a workgroup: every head width, one to four waves, last waves of 1 and
+    64 rows, partly empty query blocks, large scores (the waves' maxima differ), and enough items for 64-query blocks."""
+    rng = np.random.default_rng(1000 * d + T)
+    qkv = bf16_round(torch, rng.standard_normal((slots * T, 3 * H * d)) * scale)
+    out = drf.probe_attn_bf16(qkv.cuda(), slots, T, H, d).float().cpu().numpy()
+    want = orc.attention_packed(qkv.float().numpy(), T, H, d)
+    err = np.abs(out - want).max() / np.abs(want).max()
+    assert err < 1.5e-2, err                     # P and the result rounded to bf16: 2^-8 relative each at worst
+
+
 def test_attention_bf16_large_scores_and_lazy_rescale(torch, drf, orc):
     # score ranges far beyond the lazy-rescale headroom, increasing along kv so the reference moves often
     slots, T, H, d = 1, 512, 1, 64
