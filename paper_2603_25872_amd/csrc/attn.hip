@@ -2,7 +2,7 @@
 // bf16 path: flash-style, one wave per 32 queries, scores computed transposed
 // (S^T = K Q^T) so that each lane owns one query column and the online softmax needs a
 // single cross-lane exchange; P^T feeds the second MFMA straight from registers.
-// fp32 path: a few lanes per query over kv rows read through the cache, for the fp32 configuration.
+// fp32 path: fp32 MFMA, kv rows split over the waves of a workgroup.
 #include <type_traits>
 
 #include "common.h"
@@ -365,64 +365,122 @@ __global__ void __launch_bounds__(NW * 64) attn_bf16_kernel(const AttnArgs a, fl
     }
 }
 
-// fp32: kLanesPerQuery lanes share a query and split the kv rows between them (lane t takes rows
-// t, t + kLanesPerQuery, ...), each with its own online-softmax state; the states are merged with
-// cross-lane exchanges at the end.  The head width is a template bound so that the per-lane query and
-// output vectors stay in registers.
-constexpr int kF32MaxD = 128, kLanesPerQuery = 8, kF32Threads = 256;
-template <int DMAX>
-__global__ void __launch_bounds__(kF32Threads) attn_f32_kernel(const AttnArgs a, float scale)
+// fp32 on the fp32 matrix instruction (16x16x4).  A workgroup takes 16 queries of one (slot, head), its four waves the
+// kv rows in steps of 32 (wave w: steps w, w + 4, ...), each with its own online softmax; the states are combined through
+// LDS.  Scores are computed transposed (S^T = K Q^T): a lane owns query lane % 16 and, per 16-row tile, kv rows
+// 4 * (lane / 16) + (0..3), which are the k-slices the PV product takes them in.  Operands go from memory straight to
+// registers; a launch of this path is a few round trips (2 slots x 4 heads x 64 rows, d = 32: 46 -> 6 us against eight
+// lanes per query on vector FMAs).  DQ = ceil(d / 16); VEC: head width and strides allow 16-byte loads of Q and K.
+constexpr int kF32MaxD = 128, kF32Waves = 4;
+template <int DQ, bool VEC>
+__global__ void __launch_bounds__(kF32Waves * 64) attn_f32_kernel(const AttnArgs a, float scale, int nqb)
 {
-    const int h = blockIdx.y, d = a.d;
-    const int sub = threadIdx.x % kLanesPerQuery;
-    const int q = blockIdx.x * (kF32Threads / kLanesPerQuery) + threadIdx.x / kLanesPerQuery;
-    const bool live = q < a.Nq;
-    const int qc = live ? q : a.Nq - 1;             // lanes past the end keep their group's exchanges in step
-    for (int slot = blockIdx.z; slot < a.slots; slot += gridDim.z) {
-        const int kvb = a.kv_mod ? slot % a.kv_mod : slot;
-        const float* Q = (const float*)a.q + slot * a.q_slot_stride + h * a.q_head_stride + (size_t)qc * a.ldq;
-        const float* Kp = (const float*)a.k + kvb * a.kv_batch_stride + h * a.kv_head_stride;
-        const float* Vp = (const float*)a.v + kvb * a.kv_batch_stride + h * a.kv_head_stride;
-        float qv[DMAX], o[DMAX];
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    __shared__ f32x4 po[kF32Waves][DQ][64];
+    __shared__ float pm[kF32Waves][16], pl[kF32Waves][16];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, quarter = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int d = a.d, h = blockIdx.x / (unsigned)nqb, q0 = ((int)blockIdx.x - h * nqb) * 16, slot = blockIdx.y;
+    const int kvb = a.kv_mod ? slot % a.kv_mod : slot;
+    const int q = q0 + l16, qc = q < a.Nq ? q : a.Nq - 1;
+    const float* Q = (const float*)a.q + slot * a.q_slot_stride + h * a.q_head_stride + (size_t)qc * a.ldq;
+    const float* Kp = (const float*)a.k + kvb * a.kv_batch_stride + h * a.kv_head_stride;
+    const float* Vp = (const float*)a.v + kvb * a.kv_batch_stride + h * a.kv_head_stride;
+    auto load4 = [&](const float* p, int dd) -> f32x4 {             // elements dd .. dd + 3 of a row, zero past its end
+        f32x4 v = { 0.f, 0.f, 0.f, 0.f };
+        if constexpr (VEC) {
+            if (dd < d) v = *reinterpret_cast<const f32x4*>(p + dd);
+        } else {
 #pragma unroll
-        for (int e = 0; e < DMAX; ++e) { qv[e] = e < d ? Q[e] * scale : 0.f; o[e] = 0.f; }
-        float m_run = -INFINITY, l_run = 0.f;
-        for (int j = sub; j < a.Nk; j += kLanesPerQuery) {
-            const float* kr = Kp + (size_t)j * a.ldk;
-            float s = 0.f;
-#pragma unroll
-            for (int e = 0; e < DMAX; ++e)
-                if (e < d) s = fmaf(qv[e], kr[e], s);
-            const float m_new = fmaxf(m_run, s);
-            const float alpha = expf(m_run - m_new), p = expf(s - m_new);
-            l_run = l_run * alpha + p;
-            m_run = m_new;
-            const float* vr = Vp + (size_t)j * a.ldk;
-#pragma unroll
-            for (int e = 0; e < DMAX; ++e)
-                if (e < d) o[e] = fmaf(o[e], alpha, p * vr[e]);
+            for (int j = 0; j < 4; ++j)
+                if (dd + j < d) v[j] = p[dd + j];
         }
-        // merge the kLanesPerQuery partial states (a lane that saw no row has m = -inf, l = 0)
+        return v;
+    };
+    f32x4 qf[DQ], o[DQ];
 #pragma unroll
-        for (int off = 1; off < kLanesPerQuery; off <<= 1) {
-            const float m_o = __shfl_xor(m_run, off, 64), l_o = __shfl_xor(l_run, off, 64);
-            const float m_new = fmaxf(m_run, m_o);
-            const float ca = m_run == -INFINITY ? 0.f : expf(m_run - m_new), cb = m_o == -INFINITY ? 0.f : expf(m_o - m_new);
-            l_run = l_run * ca + l_o * cb;
+    for (int c = 0; c < DQ; ++c) {
+        qf[c] = load4(Q, c * 16 + 4 * quarter) * scale;
+        o[c] = (f32x4){ 0.f, 0.f, 0.f, 0.f };
+    }
+    float m_run = -INFINITY, l_run = 0.f;                           // l_run: this quarter's share
+    for (int kv0 = wave * 32; kv0 < a.Nk; kv0 += kF32Waves * 32) {
+        f32x4 s[2], kf[2][DQ];
+        float vf[2][4][DQ];
 #pragma unroll
-            for (int e = 0; e < DMAX; ++e) {
-                const float o_o = __shfl_xor(o[e], off, 64);
-                o[e] = o[e] * ca + o_o * cb;
+        for (int t = 0; t < 2; ++t) {
+            const int row = kv0 + t * 16 + l16, rc = row < a.Nk ? row : a.Nk - 1;
+#pragma unroll
+            for (int c = 0; c < DQ; ++c) kf[t][c] = load4(Kp + (size_t)rc * a.ldk, c * 16 + 4 * quarter);
+        }
+        // V^T operand of k-slice (t, r): row t * 16 + 4 * quarter + r, column c * 16 + l16
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = kv0 + t * 16 + 4 * quarter + r;
+#pragma unroll
+                for (int c = 0; c < DQ; ++c)
+                    vf[t][r][c] = row < a.Nk && c * 16 + l16 < d ? Vp[(size_t)row * a.ldk + c * 16 + l16] : 0.f;
             }
-            m_run = m_new;
-        }
-        if (live) {
-            float* op = (float*)a.out + ((size_t)slot * a.Nq + q) * a.ldo + h * d;
-            const float inv = 1.f / l_run;
+        float mx = -INFINITY;
 #pragma unroll
-            for (int e = 0; e < DMAX; ++e)
-                if (e < d && e % kLanesPerQuery == sub) op[e] = o[e] * inv;
+        for (int t = 0; t < 2; ++t) {
+            s[t] = (f32x4){ 0.f, 0.f, 0.f, 0.f };
+#pragma unroll
+            for (int c = 0; c < DQ; ++c)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][c][j], qf[c][j], s[t], 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (kv0 + t * 16 + 4 * quarter + r >= a.Nk) s[t][r] = -INFINITY;
+                mx = fmaxf(mx, s[t][r]);
+            }
         }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m_run, mx), alpha = expf(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int c = 0; c < DQ; ++c) o[c] *= alpha;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float p = expf(s[t][r] - m_new);
+                l_run += p;
+#pragma unroll
+                for (int c = 0; c < DQ; ++c) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][r][c], p, o[c], 0, 0, 0);
+            }
+    }
+    // o[c][r] is O^T[d = 16 c + 4 quarter + r][query l16]
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+    if (quarter == 0) { pm[wave][l16] = m_run; pl[wave][l16] = l_run; }
+#pragma unroll
+    for (int c = 0; c < DQ; ++c) po[wave][c][lane] = o[c];
+    __syncthreads();
+    float m_all = pm[0][l16], l_all = 0.f, f[kF32Waves];
+#pragma unroll
+    for (int w = 1; w < kF32Waves; ++w) m_all = fmaxf(m_all, pm[w][l16]);
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) {                           // a wave that saw no row has m = -inf, l = 0
+        f[w] = pm[w][l16] == -INFINITY ? 0.f : expf(pm[w][l16] - m_all);
+        l_all += pl[w][l16] * f[w];
+    }
+    if (q >= a.Nq) return;
+    const float inv = 1.f / l_all;
+    float* op = (float*)a.out + ((size_t)slot * a.Nq + q) * a.ldo + h * d;
+    for (int c = wave; c < DQ; c += kF32Waves) {
+        f32x4 v = po[0][c][lane] * f[0];
+#pragma unroll
+        for (int w = 1; w < kF32Waves; ++w) v += po[w][c][lane] * f[w];
+        v *= inv;
+        const int dd = c * 16 + 4 * quarter;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (dd + r < d) op[dd + r] = v[r];
     }
 }
 
@@ -492,13 +550,21 @@ drf_status launch_attn_f32(const AttnArgs& a, hipStream_t st)
 {
     if (a.slots == 0 || a.Nq == 0) return DRF_OK;
     if (a.Nk < 1 || a.d > kF32MaxD) DRF_FAIL(DRF_ESHAPE, "fp32 attention needs head dim <= %d (got %d)", kF32MaxD, a.d);
-    constexpr int qpb = kF32Threads / kLanesPerQuery;
-    // slots beyond the grid's z limit are covered by a stride loop inside the kernel
-    const dim3 grid((a.Nq + qpb - 1) / qpb, a.heads, a.slots < 65535 ? a.slots : 65535);
+    const int nqb = (a.Nq + 15) / 16, dq = (a.d + 15) / 16;
+    const dim3 grid((unsigned)nqb * a.heads, a.slots);              // slots: at most 65535, the pass limit
     const float scale = 1.f / sqrtf((float)a.d);
-    if (a.d <= 32) hipLaunchKernelGGL(attn_f32_kernel<32>, grid, dim3(kF32Threads), 0, st, a, scale);
-    else if (a.d <= 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(kF32Threads), 0, st, a, scale);
-    else hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(kF32Threads), 0, st, a, scale);
+    const bool vec = a.d % 4 == 0 && a.ldq % 4 == 0 && a.ldk % 4 == 0 && a.q_slot_stride % 4 == 0 && a.q_head_stride % 4 == 0 &&
+                     a.kv_batch_stride % 4 == 0 && a.kv_head_stride % 4 == 0 &&
+                     ((reinterpret_cast<uintptr_t>(a.q) | reinterpret_cast<uintptr_t>(a.k)) & 15u) == 0;
+    auto go = [&](auto dq_c) {
+        constexpr int DQ = decltype(dq_c)::value;
+        if (vec) hipLaunchKernelGGL((attn_f32_kernel<DQ, true>), grid, dim3(kF32Waves * 64), 0, st, a, scale, nqb);
+        else hipLaunchKernelGGL((attn_f32_kernel<DQ, false>), grid, dim3(kF32Waves * 64), 0, st, a, scale, nqb);
+    };
+    if (dq <= 1) go(std::integral_constant<int, 1>{});
+    else if (dq <= 2) go(std::integral_constant<int, 2>{});
+    else if (dq <= 4) go(std::integral_constant<int, 4>{});
+    else go(std::integral_constant<int, 8>{});
     DRF_HIP(hipGetLastError());
     return DRF_OK;
 }

@@ -241,6 +241,7 @@ drf_status launch_short_inst(const AttnArgs& a, float scale_log2, hipStream_t st
 {
     const long long items = (long long)((a.Nq + 31) / 32) * a.heads * a.slots;
     *taken = a.Nq <= 128 || items <= short_round<KS, DT>((a.Nk + kRows - 1) / kRows);
+    if (items > 1 << 23) *taken = false;            // (threads of a launch are counted in 32 bits)
     if (!*taken) return DRF_OK;
     return items <= 4096 ? launch_short<KS, DT, 1>(a, scale_log2, st) : launch_short<KS, DT, 2>(a, scale_log2, st);
 }

@@ -95,7 +95,9 @@ struct SlotMap {
     int cond_mod;           // cond row of slot j = cond_mod ? j % cond_mod : j
 };
 
-enum EpiMode { EPI_STORE = 0, EPI_STORE_GELU = 1, EPI_RESID = 2, EPI_STORE_HEADS = 3, EPI_STORE_GATED = 4 };
+enum EpiMode { EPI_STORE = 0, EPI_STORE_GELU = 1, EPI_RESID = 2, EPI_STORE_HEADS = 3, EPI_STORE_GATED = 4,
+               EPI_STORE_SILU = 5 /* fp32 path only */ };
+__device__ inline float silu(float v) { return v / (1.f + __expf(-v)); }
 struct Epilogue {
     int mode;
     void* out;              // EPI_STORE*: [M][ldo] of out type; EPI_RESID: float [M][ldo], read-modify-write
@@ -130,7 +132,8 @@ void set_rows_per_slot(Epilogue* e, int rows_per_slot);
 drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
                             int variant = 0, float* splitk_scratch = nullptr);
 size_t gemm_splitk_scratch_bytes();
-drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st);
+// fp32; a_row_mod: row m of C uses row m % a_row_mod of A (0: row m).
+drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int a_row_mod = 0);
 
 struct AttnArgs {
     // query i of (slot, head h) starts at q + slot * q_slot_stride + h * q_head_stride + i * ldq  (elements);

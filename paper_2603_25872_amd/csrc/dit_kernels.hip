@@ -29,14 +29,12 @@ __device__ inline float wave_sum(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-__device__ inline float silu(float v) { return v / (1.f + __expf(-v)); }
-
 __device__ inline int slot_tau(const SlotMap& m, int slot) { return m.t_dev ? m.t_dev[slot] : m.taus[slot / m.group]; }
 __device__ inline int slot_xrow(const SlotMap& m, int slot) { return (slot / m.x_group) * m.x_batch + slot % m.x_batch; }
 __device__ inline int slot_crow(const SlotMap& m, int slot) { return m.cond_mod ? slot % m.cond_mod : slot; }
 
-// Conditioning front-end, four small launches that each fill the chip:
-//   femb(tau) per slot -> skinny Linear + SiLU -> skinny Linear -> add cond embedding, SiLU.
+// Conditioning front-end, four small launches:
+//   femb(tau) per slot -> Linear + SiLU -> Linear -> add cond embedding, SiLU  (fp32 GEMMs).
 
 // femb[slot][256] = [cos(tau f_i) | sin(tau f_i)], f_i = 10000^(-i/128).  Double precision:
 // tau * f reaches ~1e3 rad, beyond what fp32 range reduction keeps to 1e-7.
@@ -48,50 +46,6 @@ __global__ void __launch_bounds__(kTFreq / 2) time_features_kernel(const SlotMap
     const double ang = (double)slot_tau(map, slot) * f;
     femb[(size_t)slot * kTFreq + i] = (float)cos(ang);
     femb[(size_t)slot * kTFreq + kTFreq / 2 + i] = (float)sin(ang);
-}
-
-// y[r][j] = act(sum_k x[row(r)][k] w[j][k] + b[j]) for a handful of rows r (one per slot).
-// A block owns kSkinnyCols output columns of one 64-row chunk (grid.y walks the chunks) and
-// walks K in pieces staged through LDS: thread (row, column pair) accumulates two outputs.
-constexpr int kSkinnyCols = 8, kSkinnyChunk = 128;
-template <bool SILU>
-__global__ void __launch_bounds__(256) skinny_linear_kernel(const float* __restrict__ x, int ldx, int row_mod,
-                                                            const float* __restrict__ w, const float* __restrict__ b,
-                                                            int rows, int K, int N, float* __restrict__ y)
-{
-    __shared__ float xs[64][kSkinnyChunk + 1];
-    __shared__ float ws[kSkinnyCols][kSkinnyChunk + 1];
-    const int tid = threadIdx.x, rl = tid & 63, cg = tid >> 6;
-    const int j0 = blockIdx.x * kSkinnyCols;
-    for (int r0 = blockIdx.y * 64; r0 < rows; r0 += gridDim.y * 64) {
-        float acc0 = 0.f, acc1 = 0.f;
-        for (int k0 = 0; k0 < K; k0 += kSkinnyChunk) {
-            __syncthreads();
-            for (int i = tid; i < 64 * kSkinnyChunk; i += 256) {
-                const int r = i / kSkinnyChunk, k = i % kSkinnyChunk, rr = r0 + r;
-                float v = 0.f;
-                if (rr < rows && k0 + k < K) v = x[(size_t)(row_mod ? rr % row_mod : rr) * ldx + k0 + k];
-                xs[r][k] = v;
-            }
-            for (int i = tid; i < kSkinnyCols * kSkinnyChunk; i += 256) {
-                const int c = i / kSkinnyChunk, k = i % kSkinnyChunk;
-                ws[c][k] = (j0 + c < N && k0 + k < K) ? w[(size_t)(j0 + c) * K + k0 + k] : 0.f;
-            }
-            __syncthreads();
-#pragma unroll 8
-            for (int k = 0; k < kSkinnyChunk; ++k) {
-                const float xv = xs[rl][k];
-                acc0 = fmaf(xv, ws[2 * cg][k], acc0);
-                acc1 = fmaf(xv, ws[2 * cg + 1][k], acc1);
-            }
-        }
-        const int r = r0 + rl;
-        if (r < rows) {
-            const int ja = j0 + 2 * cg, jb = ja + 1;
-            if (ja < N) { const float v = acc0 + b[ja]; y[(size_t)r * N + ja] = SILU ? silu(v) : v; }
-            if (jb < N) { const float v = acc1 + b[jb]; y[(size_t)r * N + jb] = SILU ? silu(v) : v; }
-        }
-    }
 }
 
 // c = t_emb + cond embedding; writes SiLU(c) as float and, if asked, bf16.
@@ -470,14 +424,17 @@ drf_status launch_cond_embed(const CondArgs& a, hipStream_t st)
     float* h1 = femb + (size_t)S * kTFreq;
     float* temb = h1 + (size_t)S * D;
     float* vemb = temb + (size_t)S * D;
-    const dim3 gcol((D + kSkinnyCols - 1) / kSkinnyCols, (S + 63) / 64 < 64 ? (S + 63) / 64 : 64);
     hipLaunchKernelGGL(time_features_kernel, dim3(S), dim3(kTFreq / 2), 0, st, a.map, S, femb);
-    hipLaunchKernelGGL(skinny_linear_kernel<true>, gcol, dim3(256), 0, st, femb, kTFreq, 0, a.t_w1, a.t_b1, S, kTFreq, D, h1);
-    hipLaunchKernelGGL(skinny_linear_kernel<false>, gcol, dim3(256), 0, st, h1, D, 0, a.t_w2, a.t_b2, S, D, D, temb);
+    auto linear = [&](const float* x, int K, const float* w, const float* b, float* y, bool act, int row_mod) -> drf_status {
+        Epilogue e{};
+        e.mode = act ? EPI_STORE_SILU : EPI_STORE; e.out = y; e.ldo = D; e.out_f32 = 1; e.bias = b;
+        return launch_gemm_f32(x, w, S, D, K, e, st, row_mod);
+    };
+    drf_status rc;
+    if ((rc = linear(femb, kTFreq, a.t_w1, a.t_b1, h1, true, 0)) != DRF_OK) return rc;
+    if ((rc = linear(h1, D, a.t_w2, a.t_b2, temb, false, 0)) != DRF_OK) return rc;
     const bool vec = a.cond_kind == DRF_COND_VECTOR;
-    if (vec)
-        hipLaunchKernelGGL(skinny_linear_kernel<false>, gcol, dim3(256), 0, st, (const float*)a.cond, a.cond_dim,
-                           a.map.cond_mod, a.c_w, a.c_b, S, a.cond_dim, D, vemb);
+    if (vec && (rc = linear((const float*)a.cond, a.cond_dim, a.c_w, a.c_b, vemb, false, a.map.cond_mod)) != DRF_OK) return rc;
     const bool cls = a.cond_kind == DRF_COND_CLASS;
     hipLaunchKernelGGL(cond_finish_kernel, dim3((D + 255) / 256, S), dim3(256), 0, st, temb, vec ? vemb : nullptr,
                        cls ? a.table : nullptr, cls ? (const int32_t*)a.cond : nullptr, a.map, a.cond_dim, S, D,

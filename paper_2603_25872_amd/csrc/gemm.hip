@@ -1,7 +1,7 @@
 // GEMM C[M][N] = A[M][K] . W[N][K]^T with fused epilogues (bias, GELU-tanh, gated
 // residual).  bf16 path: one software-pipelined kernel (16x16x32 MFMAs, operands by LDS-DMA, fp32
 // accumulate) at tiles from 32 x 64 to 256 x 288, the tile chosen by a measured time model.
-// fp32 path: plain LDS-tiled FMA kernel for the fp32 configuration.
+// fp32 path: fp32 MFMA, operands straight to registers, K split over the waves of a workgroup.
 #include <type_traits>
 
 #include "common.h"
@@ -56,6 +56,7 @@ __device__ inline void epilogue4(const Epilogue& e, int m, int n, float v0, floa
         return;
     }
     if (e.mode == EPI_STORE_GELU) { v0 = gelu_tanh(v0); v1 = gelu_tanh(v1); v2 = gelu_tanh(v2); v3 = gelu_tanh(v3); }
+    if (e.mode == EPI_STORE_SILU) { v0 = silu(v0); v1 = silu(v1); v2 = silu(v2); v3 = silu(v3); }
     if (e.mode == EPI_STORE_GATED) {
         const float4 g = *reinterpret_cast<const float4*>(e.gate + (size_t)fast_div(m, e.rps_magic, e.rps_shift) * e.gate_ld + n);
         v0 *= g.x; v1 *= g.y; v2 *= g.z; v3 *= g.w;
@@ -550,38 +551,85 @@ splitk_reduce_kernel(const float* __restrict__ part, int splits, size_t split_st
 }
 
 // ------------------------------------------------------------------------ fp32
-// 64 x 64 x 16 tile, 256 threads, 4 x 4 outputs per thread (columns n consecutive).
+// 32 x 32 output tile per workgroup on the fp32 matrix instruction (16x16x4, exact fp32 products and sums); the four
+// waves split K (wave w takes the 16-wide k-steps w, w + 4, ...) and add their partial tiles through LDS.  Operands go
+// from memory straight to registers, kF32Batch steps at a time and one batch ahead: the problems of this path are a few
+// hundred rows, where a launch is one or two round trips to memory, and a staged tile only adds barriers to them
+// (M = 128: K = 512 46 -> 7 us, K = 128 20 -> 5 us against a 64 x 64 x 16 LDS tile on vector FMAs).
+// A lane loads 4 consecutive k of its row; MFMA e of a step takes element e of every lane, that is the k-set
+// {4 quarter + e}, the same for both operands.  The weights are the first operand: a lane ends with 4 consecutive n.
+// VEC: rows are 16-byte aligned and K % 4 == 0; otherwise the four elements are loaded one by one.
+constexpr int kF32Batch = 2;
+template <bool VEC>
 __global__ void __launch_bounds__(256)
-gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, const Epilogue e)
+gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, int a_row_mod, const Epilogue e)
 {
-    constexpr int BM = 64, BN = 64, BK = 16;
-    __shared__ float sA[BK][BM + 1], sW[BK][BN + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += BK) {
-        for (int i = tid; i < BM * BK; i += 256) {
-            const int r = i / BK, k = i % BK;
-            sA[k][r] = (m0 + r < M && k0 + k < K) ? A[(size_t)(m0 + r) * K + k0 + k] : 0.f;
-            sW[k][r] = (n0 + r < N && k0 + k < K) ? W[(size_t)(n0 + r) * K + k0 + k] : 0.f;
+    __shared__ f32x4 part[4][4][64];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, quarter = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n0 = blockIdx.x * 32;
+    for (int m0 = blockIdx.y * 32; m0 < M; m0 += gridDim.y * 32) {   // (more row tiles than the grid's y limit: several each)
+        const float *ap[2], *wp[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            int m = m0 + i * 16 + l16, n = n0 + i * 16 + l16;           // rows past the end repeat the last one, never stored
+            m = m < M ? m : M - 1; n = n < N ? n : N - 1;
+            if (a_row_mod) m %= a_row_mod;
+            ap[i] = A + (size_t)m * K; wp[i] = W + (size_t)n * K;
         }
-        __syncthreads();
+        auto load4 = [&](const float* p, int k) -> f32x4 {
+            f32x4 v = { 0.f, 0.f, 0.f, 0.f };
+            if constexpr (VEC) {
+                if (k < K) v = *reinterpret_cast<const f32x4*>(p + k);
+            } else {
 #pragma unroll
-        for (int k = 0; k < BK; ++k) {
-            float a[4], w[4];
+                for (int j = 0; j < 4; ++j)
+                    if (k + j < K) v[j] = p[k + j];
+            }
+            return v;
+        };
+        f32x4 fa[2][kF32Batch][2], fw[2][kF32Batch][2], acc[2][2];      // [buffer][step][16-row half]; acc[n half][m half]
+        auto load = [&](f32x4 (&a)[kF32Batch][2], f32x4 (&w)[kF32Batch][2], int step) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = sA[k][ty * 4 + i]; w[i] = sW[k][tx * 4 + i]; }
+            for (int u = 0; u < kF32Batch; ++u) {
+                const int k = (step + 4 * u) * 16 + 4 * quarter;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 2; ++i) { a[u][i] = load4(ap[i], k); w[u][i] = load4(wp[i], k); }
+            }
+        };
+        auto multiply = [&](const f32x4 (&a)[kF32Batch][2], const f32x4 (&w)[kF32Batch][2]) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
+            for (int u = 0; u < kF32Batch; ++u)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][i][k], a[u][j][k], acc[i][j], 0, 0, 0);
+        };
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){ 0.f, 0.f, 0.f, 0.f };
+        const int steps = (K + 15) / 16;
+        load(fa[0], fw[0], wave);
+        for (int s = wave; s < steps; s += 8 * kF32Batch) {             // steps past the end are zeros
+            load(fa[1], fw[1], s + 4 * kF32Batch);
+            multiply(fa[0], fw[0]);
+            load(fa[0], fw[0], s + 8 * kF32Batch);
+            multiply(fa[1], fw[1]);
         }
-        __syncthreads();
-    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i, n = n0 + tx * 4;
-        if (m < M && n < N) epilogue4(e, m, n, acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) part[wave][i * 2 + j][lane] = acc[i][j];
+        __syncthreads();
+        // wave f finishes fragment f: acc[i][j][r] is (n = 16 i + 4 quarter + r, m = 16 j + l16) of the tile
+        const f32x4 v = (part[0][wave][lane] + part[1][wave][lane]) + (part[2][wave][lane] + part[3][wave][lane]);
+        const int m = m0 + (wave & 1) * 16 + l16, n = n0 + (wave >> 1) * 16 + 4 * quarter;
+        if (m < M && n < N) epilogue4(e, m, n, v[0], v[1], v[2], v[3]);
+        __syncthreads();
     }
 }
 
@@ -734,12 +782,15 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
     }
 }
 
-drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st)
+drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int a_row_mod)
 {
     if (M == 0 || N == 0) return DRF_OK;
     if (N % 4 != 0 || e.ldo % 4 != 0) DRF_FAIL(DRF_ESHAPE, "fp32 GEMM needs N %% 4 == 0 (N=%d)", N);
-    const dim3 grid((N + 63) / 64, (M + 63) / 64);
-    hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, A, W, M, N, K, e);
+    const bool vec = K % 4 == 0 && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(W)) & 15u) == 0;
+    const int tiles_m = (int)(((long long)M + 31) / 32);
+    const dim3 grid((unsigned)((N + 31LL) / 32), tiles_m < 65535 ? tiles_m : 65535);
+    if (vec) hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, dim3(256), 0, st, A, W, M, N, K, a_row_mod, e);
+    else hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, dim3(256), 0, st, A, W, M, N, K, a_row_mod, e);
     DRF_HIP(hipGetLastError());
     return DRF_OK;
 }

@@ -133,6 +133,30 @@ def test_fp32_forward_odd_shapes(torch, drf, orc):
     check_forward(torch, drf, orc, dit, "loud", slots=5, tol=TOL_F32, seed=7)
 
 
+@pytest.mark.parametrize("kw", [dict(cond=I.COND_VECTOR, hidden=20, heads=4, cond_dim=7, lat_h=6, lat_w=6),          # d = 5
+                                dict(cond=I.COND_TEXT, hidden=36, heads=2, cond_dim=6, ctx_len=35, lat_h=8, lat_w=8),   # d = 18
+                                dict(cond=I.COND_CLASS, hidden=128, heads=1, lat_h=24, lat_w=24, depth=1),              # 144 rows, d = 128
+                                dict(cond=I.COND_CLASS, hidden=132, heads=2, lat_h=14, lat_w=4, patch=1, in_ch=5)])     # d = 66, P = 5
+def test_fp32_forward_operands_that_no_vector_load_takes(torch, drf, orc, kw):
+    """Widths that are not multiples of 4 or 16, K remainders, kv rows beyond one round of the waves."""
+    cond = kw.pop("cond")
+    check_forward(torch, drf, orc, small_dit(cond, I.F32, **kw), "loud", slots=3, tol=TOL_F32, seed=70 + kw["hidden"])
+
+
+def test_fp32_conditioning_from_an_unaligned_buffer(torch, drf, orc):
+    dit = small_dit(I.COND_VECTOR, I.F32)
+    w, cond = I.weights(dit, 3, "loud"), make_cond(dit, 2, 4)
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((2, dit["in_ch"], dit["lat_h"], dit["lat_w"])).astype(np.float32)
+    t = np.array([3, 900], np.int32)
+    den = drf.Denoiser(dit, w)
+    room = torch.zeros(cond.size + 1, device="cuda")
+    room[1:] = dev(torch, cond).ravel()
+    got = den.eps_batched(dev(torch, x), dev(torch, t), room[1:].view(cond.shape)).cpu().numpy()
+    check(got, orc.dit_eps(dit, w, x, t, cond), TOL_F32, "eps")
+    den.close()
+
+
 @pytest.mark.parametrize("cond", [I.COND_VECTOR, I.COND_CLASS, I.COND_TEXT])
 @pytest.mark.parametrize("init", ["paper", "loud"])
 def test_bf16_forward_matches_oracle(torch, drf, orc, cond, init):
