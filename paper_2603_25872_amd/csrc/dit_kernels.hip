@@ -68,42 +68,61 @@ __global__ void __launch_bounds__(256) cond_finish_kernel(const float* __restric
     if (act_bf16) act_bf16[(size_t)slot * D + j] = (bf16_t)s;
 }
 
-// resid[m][j] = sum_k token[m][k] w[j][k] + b[j] + pos[token][j].  One block per kTok tokens.
-constexpr int kTok = 8;
+// resid[m][j] = sum_k token[m][k] w[j][k] + b[j] + pos[token][j], on the fp32 matrix instruction.  A workgroup takes 16
+// tokens and (blockIdx.y) 4 * kPatchTiles tiles of 16 columns, dealt over its four waves; a wave gathers its tokens'
+// patches once, in the operand layout (lane: token lane % 16, k = 4 * (lane / 16) + (0..3) of every 16).  Bound by the
+// store of the stream: the row-per-thread form, whose weight reads touched 64 lines per instruction, took 25 us for 512
+// rows and 44 us for 16384 (hidden 1152), this one 7.6 and 33.5 us.
+// VEC: P % 4 == 0 (16-byte loads of the weight rows).
+constexpr int kPatchTiles = 6;
+typedef float f32x4m __attribute__((ext_vector_type(4)));
+template <bool VEC>
 __global__ void __launch_bounds__(256) patch_embed_kernel(const float* __restrict__ x, const SlotMap map,
                                                           const float* __restrict__ w, const float* __restrict__ b,
                                                           const float* __restrict__ pos, const DitDims dm, int M,
                                                           float* __restrict__ resid)
 {
-    extern __shared__ float tok[];         // [kTok][P]
-    const int m0 = blockIdx.x * kTok, tid = threadIdx.x;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, quarter = lane >> 4, wave = threadIdx.x >> 6;
     const size_t E = (size_t)dm.C * dm.H * dm.W;
-    for (int i = tid; i < kTok * dm.P; i += blockDim.x) {
-        const int tl = i / dm.P, k = i % dm.P, m = m0 + tl;
-        float v = 0.f;
-        if (m < M) {
-            const int slot = m / dm.T, t = m % dm.T, py = t / dm.gw, px = t % dm.gw;
-            const int pp = dm.patch * dm.patch, ch = k / pp, dy = (k % pp) / dm.patch, dx = k % dm.patch;
-            v = x[(size_t)slot_xrow(map, slot) * E + ((size_t)ch * dm.H + py * dm.patch + dy) * dm.W + px * dm.patch + dx];
+    const int row = blockIdx.x * 16 + l16, m = row < M ? row : M - 1;
+    const int slot = m / dm.T, t = m - slot * dm.T, py = t / dm.gw, px = t - py * dm.gw;
+    const float* xp = x + (size_t)slot_xrow(map, slot) * E + (size_t)py * dm.patch * dm.W + px * dm.patch;
+    const int pp = dm.patch * dm.patch, first = (blockIdx.y * 4 + wave) * kPatchTiles * 16;
+    f32x4m acc[kPatchTiles];
+#pragma unroll
+    for (int i = 0; i < kPatchTiles; ++i) acc[i] = (f32x4m){ 0.f, 0.f, 0.f, 0.f };
+    for (int k0 = 0; k0 < dm.P; k0 += 16) {
+        f32x4m tok = { 0.f, 0.f, 0.f, 0.f }, wf[kPatchTiles];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = k0 + 4 * quarter + j, ch = k / pp, dy = (k - ch * pp) / dm.patch, dx = k - ch * pp - dy * dm.patch;
+            if (k < dm.P) tok[j] = xp[((size_t)ch * dm.H + dy) * dm.W + dx];
         }
-        tok[i] = v;
+#pragma unroll
+        for (int i = 0; i < kPatchTiles; ++i) {
+            const int j = first + i * 16 + l16, k = k0 + 4 * quarter;
+            const float* wr = w + (size_t)(j < dm.D ? j : dm.D - 1) * dm.P;
+            wf[i] = (f32x4m){ 0.f, 0.f, 0.f, 0.f };
+            if constexpr (VEC) {
+                if (k < dm.P) wf[i] = *reinterpret_cast<const f32x4m*>(wr + k);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (k + u < dm.P) wf[i][u] = wr[k + u];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int i = 0; i < kPatchTiles; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[i][u], tok[u], acc[i], 0, 0, 0);
     }
-    __syncthreads();
-    for (int j = tid; j < dm.D; j += blockDim.x) {
-        const float* wr = w + (size_t)j * dm.P;
-        const float bj = b[j];
-        float acc[kTok];
+    if (row >= M) return;
 #pragma unroll
-        for (int tl = 0; tl < kTok; ++tl) acc[tl] = 0.f;
-        for (int k = 0; k < dm.P; ++k) {
-            const float wv = wr[k];
-#pragma unroll
-            for (int tl = 0; tl < kTok; ++tl) acc[tl] = fmaf(tok[tl * dm.P + k], wv, acc[tl]);
-        }
-#pragma unroll
-        for (int tl = 0; tl < kTok; ++tl) {
-            const int m = m0 + tl;
-            if (m < M) resid[(size_t)m * dm.D + j] = acc[tl] + bj + pos[(size_t)(m % dm.T) * dm.D + j];
+    for (int i = 0; i < kPatchTiles; ++i) {         // acc[i][r]: column first + 16 i + 4 quarter + r of row l16
+        const int j = first + i * 16 + 4 * quarter;
+        if (j < dm.D) {                             // hidden is a multiple of 4
+            const f32x4m bj = *reinterpret_cast<const f32x4m*>(b + j), pj = *reinterpret_cast<const f32x4m*>(pos + (size_t)t * dm.D + j);
+            *reinterpret_cast<f32x4m*>(resid + (size_t)m * dm.D + j) = acc[i] + bj + pj;
         }
     }
 }
@@ -329,81 +348,74 @@ __global__ void __launch_bounds__(256) final_kernel(const float* __restrict__ re
     }
 }
 
-// Final layer for hidden sizes that are multiples of 128 and weights [P][D] that fit LDS: the weights are
-// staged once per block, half a wave takes a row (16-byte loads, the row stays in registers through the
-// statistics, the modulation and the P dot products), and 16 partial sums per lane are reduced across
-// the half wave by a transposing butterfly (8 + 4 + 2 + 1 + 1 exchanges) that leaves output k on the lane
-// whose bits 4..1 spell k.
-template <int PER4>
-__global__ void __launch_bounds__(256) final4_kernel(const float* __restrict__ resid, const float* __restrict__ shift,
-                                                     const float* __restrict__ scale, int mod_ld,
-                                                     const float* __restrict__ w, const float* __restrict__ b,
-                                                     const DitDims dm, int M, int rows_per_block, float* __restrict__ eps_out)
+// Final layer for hidden sizes that are multiples of 64, on the fp32 matrix instruction: a workgroup takes 16 rows, its
+// four waves a quarter of the columns each (NS steps of 16), a row piece in the operand layout staying in registers
+// through the statistics (two exchanges through LDS), the modulation and the product with 16 output weights at a time;
+// the waves' partial products are added through LDS.  One chain of loads and no weights staged: with the weights in LDS
+// and a row per half wave a launch took 23 us for 512 rows and 42 us for 16384 (hidden 1152, P = 16), this one 15 and 27 us.
+template <int NS>
+__global__ void __launch_bounds__(256) final_mfma_kernel(const float* __restrict__ resid, const float* __restrict__ shift,
+                                                         const float* __restrict__ scale, int mod_ld,
+                                                         const float* __restrict__ w, const float* __restrict__ b,
+                                                         const DitDims dm, int M, float* __restrict__ eps_out)
 {
-    constexpr int D = PER4 * 128;
-    extern __shared__ __attribute__((aligned(16))) float fin_w[];            // [P][D]
-    const int P = dm.P, tid = threadIdx.x, l32 = tid & 31, hw = tid >> 5;
-    for (int i = tid; i < P * (D / 4); i += 256) reinterpret_cast<float4*>(fin_w)[i] = reinterpret_cast<const float4*>(w)[i];
+    constexpr int D = NS * 64;
+    __shared__ float s_sum[4][16], s_sq[4][16];
+    __shared__ f32x4m part[4][64];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, quarter = lane >> 4, wave = threadIdx.x >> 6;
+    const int m0 = blockIdx.x * 16, row = m0 + l16, m = row < M ? row : M - 1;
+    const size_t col0 = (size_t)wave * (NS * 16) + 4 * quarter;
+    f32x4m v[NS];
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) v[i] = *reinterpret_cast<const f32x4m*>(resid + (size_t)m * D + col0 + i * 16);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) sum += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    if (quarter == 0) s_sum[wave][l16] = sum;
     __syncthreads();
+    const float mean = ((s_sum[0][l16] + s_sum[1][l16]) + (s_sum[2][l16] + s_sum[3][l16])) * (1.f / (float)D);
+    float sq = 0.f;
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { v[i][j] -= mean; sq = fmaf(v[i][j], v[i][j], sq); }
+    sq += __shfl_xor(sq, 16, 64);
+    sq += __shfl_xor(sq, 32, 64);
+    if (quarter == 0) s_sq[wave][l16] = sq;
+    __syncthreads();
+    const float rstd = rsqrtf(((s_sq[0][l16] + s_sq[1][l16]) + (s_sq[2][l16] + s_sq[3][l16])) * (1.f / (float)D) + 1e-6f);
+    const int slot = m / dm.T;
+    const float* sh = shift + (size_t)slot * mod_ld + col0;
+    const float* sc = scale + (size_t)slot * mod_ld + col0;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+        const f32x4m s4 = *reinterpret_cast<const f32x4m*>(sc + i * 16), h4 = *reinterpret_cast<const f32x4m*>(sh + i * 16);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[i][j] = fmaf(v[i][j] * rstd, 1.f + s4[j], h4[j]);
+    }
     const size_t E = (size_t)dm.C * dm.H * dm.W;
     const int pp = dm.patch * dm.patch;
-    const int row0 = blockIdx.x * rows_per_block, row_end = min(M, row0 + rows_per_block);
-    for (int row = row0 + hw; row < row_end; row += 8) {
-        const float4* xr = reinterpret_cast<const float4*>(resid + (size_t)row * D);
-        float4 v[PER4];
-        float sum = 0.f;
+    const int orow = m0 + (threadIdx.x & 15), oslot = orow / dm.T, t = orow - oslot * dm.T, py = t / dm.gw, px = t - py * dm.gw;
+    for (int kbase = 0; kbase < dm.P; kbase += 16) {
+        const float* wr = w + (size_t)(kbase + l16 < dm.P ? kbase + l16 : dm.P - 1) * D + col0;
+        f32x4m acc[2] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
 #pragma unroll
-        for (int i = 0; i < PER4; ++i) {
-            v[i] = xr[i * 32 + l32];
-            sum += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+        for (int i = 0; i < NS; ++i) {
+            const f32x4m w4 = *reinterpret_cast<const f32x4m*>(wr + i * 16);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[j], v[i][j], acc[j & 1], 0, 0, 0);
         }
-        const float mean = half_wave_sum(sum) * (1.f / (float)D);
-        float sq = 0.f;
-#pragma unroll
-        for (int i = 0; i < PER4; ++i) {
-            const float dx = v[i].x - mean, dy = v[i].y - mean, dz = v[i].z - mean, dw = v[i].w - mean;
-            sq = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, fmaf(dw, dw, sq))));
+        part[wave][lane] = acc[0] + acc[1];         // element r: output kbase + 4 quarter + r of row l16
+        __syncthreads();
+        const int kk = threadIdx.x >> 4, k = kbase + kk, src = (kk >> 2) * 16 + (threadIdx.x & 15);
+        if (k < dm.P && orow < M) {
+            const float tot = (part[0][src][kk & 3] + part[1][src][kk & 3]) + (part[2][src][kk & 3] + part[3][src][kk & 3]);
+            const int ch = k / pp, dy = (k % pp) / dm.patch, dx = k % dm.patch;
+            eps_out[(size_t)oslot * E + ((size_t)ch * dm.H + py * dm.patch + dy) * dm.W + px * dm.patch + dx] = tot + b[k];
         }
-        const float rstd = rsqrtf(half_wave_sum(sq) * (1.f / (float)D) + 1e-6f);
-        const int slot = row / dm.T, t = row % dm.T, py = t / dm.gw, px = t % dm.gw;
-        const float4* sh = reinterpret_cast<const float4*>(shift + (size_t)slot * mod_ld);
-        const float4* sc = reinterpret_cast<const float4*>(scale + (size_t)slot * mod_ld);
-#pragma unroll
-        for (int i = 0; i < PER4; ++i) {
-            const float4 s4 = sc[i * 32 + l32], h4 = sh[i * 32 + l32];
-            v[i].x = fmaf((v[i].x - mean) * rstd, 1.f + s4.x, h4.x); v[i].y = fmaf((v[i].y - mean) * rstd, 1.f + s4.y, h4.y);
-            v[i].z = fmaf((v[i].z - mean) * rstd, 1.f + s4.z, h4.z); v[i].w = fmaf((v[i].w - mean) * rstd, 1.f + s4.w, h4.w);
-        }
-        for (int kbase = 0; kbase < P; kbase += 16) {
-            float acc[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                acc[q] = 0.f;
-                if (kbase + q < P) {                        // uniform over the block
-                    const float4* wk = reinterpret_cast<const float4*>(fin_w + (size_t)(kbase + q) * D);
-#pragma unroll
-                    for (int i = 0; i < PER4; ++i) {
-                        const float4 w4 = wk[i * 32 + l32];
-                        acc[q] = fmaf(v[i].x, w4.x, fmaf(v[i].y, w4.y, fmaf(v[i].z, w4.z, fmaf(v[i].w, w4.w, acc[q]))));
-                    }
-                }
-            }
-            float a8[8], a4[4], a2[2];
-            const bool b16 = l32 & 16, b8 = l32 & 8, b4 = l32 & 4, b2 = l32 & 2;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) a8[q] = (b16 ? acc[q + 8] : acc[q]) + __shfl_xor(b16 ? acc[q] : acc[q + 8], 16, 64);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) a4[q] = (b8 ? a8[q + 4] : a8[q]) + __shfl_xor(b8 ? a8[q] : a8[q + 4], 8, 64);
-#pragma unroll
-            for (int q = 0; q < 2; ++q) a2[q] = (b4 ? a4[q + 2] : a4[q]) + __shfl_xor(b4 ? a4[q] : a4[q + 2], 4, 64);
-            const float a1 = (b2 ? a2[1] : a2[0]) + __shfl_xor(b2 ? a2[0] : a2[1], 2, 64);
-            const float tot = a1 + __shfl_xor(a1, 1, 64);
-            const int k = kbase + (b16 ? 8 : 0) + (b8 ? 4 : 0) + (b4 ? 2 : 0) + (b2 ? 1 : 0);
-            if (!(l32 & 1) && k < P) {
-                const int ch = k / pp, dy = (k % pp) / dm.patch, dx = k % dm.patch;
-                eps_out[(size_t)slot * E + ((size_t)ch * dm.H + py * dm.patch + dy) * dm.W + px * dm.patch + dx] = tot + b[k];
-            }
-        }
+        __syncthreads();
     }
 }
 
@@ -448,8 +460,12 @@ drf_status launch_patch_embed(const float* x, const SlotMap& map, const float* w
 {
     const int M = slots * dm.T;
     if (M == 0) return DRF_OK;
-    hipLaunchKernelGGL(patch_embed_kernel, dim3((M + kTok - 1) / kTok), dim3(256), sizeof(float) * kTok * dm.P, st, x, map,
-                       w, b, pos, dm, M, resid);
+    const int per = 4 * kPatchTiles * 16;
+    const dim3 grid((M + 15) / 16, (dm.D + per - 1) / per);
+    if (dm.P % 4 == 0 && (reinterpret_cast<uintptr_t>(w) & 15u) == 0)
+        hipLaunchKernelGGL(patch_embed_kernel<true>, grid, dim3(256), 0, st, x, map, w, b, pos, dm, M, resid);
+    else
+        hipLaunchKernelGGL(patch_embed_kernel<false>, grid, dim3(256), 0, st, x, map, w, b, pos, dm, M, resid);
     DRF_HIP(hipGetLastError());
     return DRF_OK;
 }
@@ -523,28 +539,22 @@ drf_status launch_final(const float* resid, const float* shift, const float* sca
     const int M = slots * dm.T;
     if (M == 0) return DRF_OK;
     if (dm.D > 2048) DRF_FAIL(DRF_ESHAPE, "final layer needs hidden <= 2048");
-    const size_t wbytes = (size_t)dm.P * dm.D * sizeof(float);
     const bool al16 = mod_ld % 4 == 0 && ((reinterpret_cast<uintptr_t>(resid) | reinterpret_cast<uintptr_t>(shift) |
                                            reinterpret_cast<uintptr_t>(scale) | reinterpret_cast<uintptr_t>(w)) & 15u) == 0;
-    if (al16 && wbytes <= 96 * 1024 && (dm.D == 1152 || dm.D == 384 || dm.D == 768 || dm.D == 1024 || dm.D == 128)) {
-        const int rpb = M >= 8192 ? 32 : 16;
-        const dim3 grid4((M + rpb - 1) / rpb), block4(256);
+    if (al16) {
         auto go = [&](auto kern) -> drf_status {
-            static bool attr_set = false;                   // one flag per kernel instantiation
-            if (!attr_set) {
-                DRF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024));
-                attr_set = true;
-            }
-            hipLaunchKernelGGL(kern, grid4, block4, wbytes, st, resid, shift, scale, mod_ld, w, b, dm, M, rpb, eps_out);
+            hipLaunchKernelGGL(kern, dim3((M + 15) / 16), dim3(256), 0, st, resid, shift, scale, mod_ld, w, b, dm, M, eps_out);
             DRF_HIP(hipGetLastError());
             return DRF_OK;
         };
-        switch (dm.D / 128) {
-        case 1: return go(final4_kernel<1>);
-        case 3: return go(final4_kernel<3>);
-        case 6: return go(final4_kernel<6>);
-        case 8: return go(final4_kernel<8>);
-        default: return go(final4_kernel<9>);
+        switch (dm.D) {
+        case 128: return go(final_mfma_kernel<2>);
+        case 384: return go(final_mfma_kernel<6>);
+        case 576: return go(final_mfma_kernel<9>);
+        case 768: return go(final_mfma_kernel<12>);
+        case 1024: return go(final_mfma_kernel<16>);
+        case 1152: return go(final_mfma_kernel<18>);
+        default: break;
         }
     }
     const dim3 grid((M + kFinalRowsPerBlock - 1) / kFinalRowsPerBlock), block(256);
