@@ -681,21 +681,25 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
 // The tiles, and a time model of a launch of each: base + (per round of workgroups) round + steps * max(lat, c * thr)
 // microseconds, where a round is per_cu workgroups on each of the 256 CUs, c the workgroups that share a CU in it and
 // steps the k-steps of 64 * wk; a split adds red0 + red1 per million partial elements for the reduction launch.
-// The constants are least-squares fits to timings of every tile on 85 shapes (M 2 .. 16384, N 384 .. 195840, K 384 ..
-// 4608, weights cold); the tile that the model picks is 0.7 % slower than the fastest of all on average and 14 % at
+// The constants are least-squares fits to timings of every tile on 107 shapes (M 2 .. 65536, N 384 .. 195840, K 384 ..
+// 4608, weights cold); the tile that the model picks is 0.8 % slower than the fastest of all on average and 14 % at
 // worst.  Small problems live on small tiles: with weights coming from HBM a launch is a chain of round trips, and what
 // counts is how many of the chip's CUs pull operands at once (M = 512, N = K = 1152: 13.2 us on 36 128 x 128 tiles,
 // 7.0 us on 144 64 x 64 tiles whose two wave groups split K; N = 3456: 15.5 -> 11.2 us on 128 x 64; M = 2048, N = 3456:
 // 32.5 -> 23.9 us with two 128 x 128 workgroups per CU; M = 12288, N = 1536, K = 384: 31.9 -> 22.9 us likewise).
+// Larger ones lose by a part-filled round: the tiles between 128 x 128 and 256 x 256 are there for their counts (M = 8192,
+// N = 1152, K = 4608: 108 us on 160 256 x 256 tiles, 84 us on 256 of 256 x 144).
 struct TileModel { int id, bm, bn, wk, per_cu; double base, round, lat, thr, red0, red1; };     // red0 = 0: never split
 const TileModel kTiles[] = {
-    {  2, 256, 288, 1, 1, 0.00, 6.21, 1.52, 0.10, 0.0, 0.0 },
-    {  3, 256, 256, 1, 1, 0.00, 4.69, 1.41, 0.10, 0.0, 0.0 },
-    {  4, 128, 128, 1, 2, 0.00, 2.80, 0.86, 0.03, 0.0, 0.0 },
-    {  5, 128, 128, 1, 1, 0.88, 2.83, 0.51, 0.51, 3.3, 2.3 },
-    {  8, 128, 144, 2, 1, 0.61, 4.06, 0.45, 1.41, 0.0, 0.0 },
-    {  7, 128,  96, 1, 1, 1.38, 2.78, 0.48, 0.48, 0.0, 0.0 },
-    {  6, 128,  64, 1, 1, 0.95, 2.35, 0.17, 0.35, 3.6, 1.8 },
+    {  2, 256, 288, 1, 1, 0.00, 6.34, 1.55, 0.10, 0.0, 0.0 },
+    {  3, 256, 256, 1, 1, 0.00, 4.89, 1.43, 0.10, 0.0, 0.0 },
+    { 13, 256, 144, 1, 1, 0.00, 5.53, 0.95, 0.95, 0.0, 0.0 },
+    { 14, 256, 128, 1, 1, 0.55, 4.75, 0.83, 0.10, 0.0, 0.0 },
+    {  4, 128, 128, 1, 2, 0.00, 2.84, 0.89, 0.10, 0.0, 0.0 },
+    {  5, 128, 128, 1, 1, 0.90, 2.82, 0.51, 0.48, 3.3, 2.3 },
+    {  8, 128, 144, 2, 1, 0.70, 4.01, 1.40, 1.40, 0.0, 0.0 },
+    {  7, 128,  96, 1, 1, 1.39, 2.88, 0.48, 0.48, 0.0, 0.0 },
+    {  6, 128,  64, 1, 1, 0.95, 2.35, 0.35, 0.35, 3.6, 1.8 },
     { 11,  64,  96, 2, 1, 1.38, 2.33, 0.57, 0.12, 0.0, 0.0 },
     {  9,  64,  64, 2, 1, 1.42, 1.93, 0.44, 0.10, 3.5, 1.6 },
     {  1,  64,  64, 1, 2, 1.97, 1.33, 0.26, 0.21, 3.1, 1.9 },
@@ -778,6 +782,8 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
     case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st);
     case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st);
     case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st);
+    case 13: return launch_bf16_xl<256, 144, 64, 3, 8, 1>(A, W, M, N, K, e, st);
+    case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2>(A, W, M, N, K, e, st);
     default: DRF_FAIL(DRF_EINVAL, "unknown GEMM tile %d", v);
     }
 }

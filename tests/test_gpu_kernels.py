@@ -63,10 +63,10 @@ def test_gemm_bf16_split_k(torch, drf, orc, M, N, K):
     assert np.abs(out - whole).max() / scale < 6e-3   # both are bf16 roundings of nearly the same fp32 sums
 
 
-@pytest.mark.parametrize("variant", [9, 11, 12, 501, 505, 406, 409, 412])
+@pytest.mark.parametrize("variant", [9, 11, 12, 13, 14, 501, 505, 406, 409, 412])
 @pytest.mark.parametrize("M,N,K", [(300, 292, 1152), (33, 8, 1152), (1, 64, 1280), (130, 100, 1408)])
 def test_gemm_bf16_small_tiles_and_splits(torch, drf, orc, variant, M, N, K):
-    """Tiles of two K groups (9, 11, 12) and 100 s + tile: K in s parts whose k-steps do not divide evenly (18, 20, 22
+    """Tiles of two K groups (9, 11, 12), three-stage tiles (13, 14) and 100 s + tile: K in s parts whose k-steps do not divide evenly (18, 20, 22
     steps in 5 parts; 9, 10, 11 pairs in 4)."""
     rng = np.random.default_rng(M + N + K)
     A = bf16_round(torch, rng.standard_normal((M, K)))
