@@ -124,13 +124,18 @@ struct Epilogue {
 void make_fast_div(int d, uint32_t* magic, int* shift);
 // Fills rows_per_slot and its division constants (exact for 0 <= m < 2^31).
 void set_rows_per_slot(Epilogue* e, int rows_per_slot);
+// Partial tiles of a split-K launch that its consumer adds itself: element (m, n) of the product is
+// sum over s < splits of part[s * stride + m * ldp + n].  splits == 0: there are none, the launch has stored its result.
+constexpr int kMaxSplits = 6;       // parts that the choice of tile makes at most
+struct PartialSum { const float* part; int splits, ldp; size_t stride; };
 // C[M][N] = A[M][K] . W[N][K]^T, then the epilogue.  bf16: K % 64 == 0.
 // variant 0: the tile shape and split are chosen from the problem size; > 0 forces one (measurement and tile tests).
 // splitk_scratch: gemm_splitk_scratch_bytes() of device memory, or NULL; with it, problems of few tiles and a long
 // K may be split across workgroups (variant 10 forces the 128 x 128 tile, split when K is long enough; variant
 // 100 s + v forces tile v split in s).
+// leave != NULL: a launch that splits leaves its partial tiles for the caller (in splitk_scratch, the epilogue not applied).
 drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
-                            int variant = 0, float* splitk_scratch = nullptr);
+                            int variant = 0, float* splitk_scratch = nullptr, PartialSum* leave = nullptr);
 size_t gemm_splitk_scratch_bytes();
 // fp32; a_row_mod: row m of C uses row m % a_row_mod of A (0: row m).
 drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int a_row_mod = 0);
@@ -179,6 +184,12 @@ drf_status launch_patch_embed(const float* x, const SlotMap& map, const float* w
 drf_status launch_ln_modulate(float* resid, const bf16_t* add, const bf16_t* add2, bool write_back, const float* shift,
                               const float* scale, int mod_ld, int rows_per_slot, int M, int D, void* out, int out_f32,
                               hipStream_t st);
+// The same with the output of a split GEMM as the last branch: x = (resid + add) + bf16(gate * (sum of the
+// partials + bias)), stored over resid; add may be NULL.  Only for the widths that ln_partial_width accepts; out is bf16.
+bool ln_partial_width(int D);
+struct PartialBranch { PartialSum sum; const float *bias, *gate; };
+drf_status launch_ln_modulate_partial(float* resid, const bf16_t* add, const PartialBranch& br, const float* shift, const float* scale,
+                                      int mod_ld, int rows_per_slot, int M, int D, bf16_t* out, hipStream_t st);
 drf_status launch_final(const float* resid, const float* shift, const float* scale, int mod_ld, const float* w,
                         const float* b, const DitDims& dm, int slots, float* eps_out, hipStream_t st);
 drf_status launch_f32_to_bf16(const float* in, bf16_t* out, size_t n, hipStream_t st);

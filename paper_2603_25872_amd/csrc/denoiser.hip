@@ -257,11 +257,12 @@ drf_status ensure_ctx(drf_denoiser* d, int rows, hipStream_t st)
     return DRF_OK;
 }
 
-drf_status gemm(drf_denoiser* d, const void* A, const LinearW& w, int M, Epilogue e, hipStream_t st, float* splitk_scratch = nullptr)
+drf_status gemm(drf_denoiser* d, const void* A, const LinearW& w, int M, Epilogue e, hipStream_t st, float* splitk_scratch = nullptr,
+                PartialSum* leave = nullptr)
 {
     e.bias = w.b;
     ProfScope ps(d, st, DRF_PROF_GEMM, 2.0 * M * (double)w.N * w.K);
-    if (d->bf16) return launch_gemm_bf16((const bf16_t*)A, w.w16, M, w.N, w.K, e, st, 0, splitk_scratch);
+    if (d->bf16) return launch_gemm_bf16((const bf16_t*)A, w.w16, M, w.N, w.K, e, st, 0, splitk_scratch, leave);
     return launch_gemm_f32((const float*)A, w.w32, M, w.N, w.K, e, st);
 }
 
@@ -376,9 +377,19 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
     // GEMM whose k-loop waits on first-touch weight lines runs measurably slower than the same GEMM with
     // warm weights.  So each bf16 GEMM of the block chain (qkv -> proj -> fc1 -> fc2 -> next block's
     // qkv) touches the weights of its successor while its own last round of tiles starts.
+    // In a thin pass a branch GEMM may split K across workgroups: its partial tiles are then the last pending branch
+    // (part), and the LayerNorm launch that adds them stores the stream.
     const bf16_t *pend1 = nullptr, *pend2 = nullptr;
+    PartialBranch part{};
+    const bool may_leave = !f32 && ln_partial_width(D) && nm % 4 == 0;
     const bool text = d->cfg.cond == DRF_COND_TEXT;
     auto ln = [&](const float* shift, const float* scale, int mod_ld, bool store) -> drf_status {
+        if (part.sum.splits) {
+            ProfScope ps(d, st, DRF_PROF_ELEMWISE, (double)M * D * (10.0 + 4.0 * part.sum.splits + (pend1 ? 2.0 : 0.0)));
+            const drf_status r = launch_ln_modulate_partial(ws.resid, pend1, part, shift, scale, nm, dm.T, M, D, (bf16_t*)ws.hbuf, st);
+            pend1 = pend2 = nullptr; part.sum.splits = 0;
+            return r;
+        }
         const int n_add = (pend1 ? 1 : 0) + (pend2 ? 1 : 0);
         ProfScope ps(d, st, DRF_PROF_ELEMWISE, ln_bytes + (double)M * D * (2.0 * n_add + (n_add && store ? 4.0 : 0.0)));
         const drf_status r = launch_ln_modulate(ws.resid, pend1, pend2, store, shift, scale, mod_ld, dm.T, M, D, ws.hbuf, f32, st);
@@ -412,8 +423,9 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         if (f32) {
             if ((rc = gemm(d, ws.hbuf, b.proj, M, epi_resid(ws.resid, D, mrow + 2 * D, nm, dm.T), st)) != DRF_OK) return rc;
         } else {
-            if ((rc = gemm(d, ws.hbuf, b.proj, M, with_warm(epi_gated(ws.ybuf, D, mrow + 2 * D, nm, dm.T), text ? nullptr : &b.fc1), st, ws.skpart)) != DRF_OK) return rc;
-            pend1 = (const bf16_t*)ws.ybuf;
+            if ((rc = gemm(d, ws.hbuf, b.proj, M, with_warm(epi_gated(ws.ybuf, D, mrow + 2 * D, nm, dm.T), text ? nullptr : &b.fc1), st, ws.skpart, may_leave ? &part.sum : nullptr)) != DRF_OK) return rc;
+            part.bias = b.proj.b; part.gate = mrow + 2 * D;
+            if (!part.sum.splits) pend1 = (const bf16_t*)ws.ybuf;
         }
         if (d->cfg.cond == DRF_COND_TEXT) {
             const int ctx_rows = map.cond_mod ? map.cond_mod : slots;
@@ -439,8 +451,9 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         } else {
             // the attention output may still be pending in ybuf: the MLP output goes to the second buffer
             void* yo = pend1 ? ws.ybuf2 : ws.ybuf;
-            if ((rc = gemm(d, ws.mid, b.fc2, M, with_warm(epi_gated(yo, D, mrow + 5 * D, nm, dm.T), &d->blk[l + 1].qkv), st, ws.skpart)) != DRF_OK) return rc;
-            (pend1 ? pend2 : pend1) = (const bf16_t*)yo;
+            if ((rc = gemm(d, ws.mid, b.fc2, M, with_warm(epi_gated(yo, D, mrow + 5 * D, nm, dm.T), &d->blk[l + 1].qkv), st, ws.skpart, may_leave ? &part.sum : nullptr)) != DRF_OK) return rc;
+            part.bias = b.fc2.b; part.gate = mrow + 5 * D;
+            if (!part.sum.splits) (pend1 ? pend2 : pend1) = (const bf16_t*)yo;
         }
     }
     if (resid_out) {

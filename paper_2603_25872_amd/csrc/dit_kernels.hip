@@ -8,6 +8,7 @@ namespace {
 
 constexpr int kWave = 64;
 constexpr int kTFreq = 256;
+typedef float f32x4m __attribute__((ext_vector_type(4)));
 
 // Sum over the 64 lanes with DPP adds (no LDS traffic): inclusive scan inside each row of 16
 // lanes (row_shr 1, 2, 4, 8 with zero fill), then the row totals are passed on with
@@ -75,7 +76,6 @@ __global__ void __launch_bounds__(256) cond_finish_kernel(const float* __restric
 // rows and 44 us for 16384 (hidden 1152), this one 7.6 and 33.5 us.
 // VEC: P % 4 == 0 (16-byte loads of the weight rows).
 constexpr int kPatchTiles = 6;
-typedef float f32x4m __attribute__((ext_vector_type(4)));
 template <bool VEC>
 __global__ void __launch_bounds__(256) patch_embed_kernel(const float* __restrict__ x, const SlotMap map,
                                                           const float* __restrict__ w, const float* __restrict__ b,
@@ -276,6 +276,84 @@ __global__ void __launch_bounds__(256) ln_modulate4_kernel(float* __restrict__ r
             reinterpret_cast<bf16x4*>(out + (size_t)row * D)[j] = o;
         }
         if constexpr (ADD >= 1 && WB) { const f32x4n t4 = { v[i].x, v[i].y, v[i].z, v[i].w }; __builtin_nontemporal_store(t4, reinterpret_cast<f32x4n*>(xr) + i * 32 + l32); }
+    }
+}
+
+// ln_modulate4_kernel with the output of a split GEMM as the branch to add: the partial tiles are summed here in a fixed
+// order instead of by a reduction launch between the GEMM and this one (thin passes: 4.5 us of a 75 us block at 512
+// rows), and the branch output takes the rounding that a stored one takes, so that a sample's result does not depend on
+// the size of the pass it was part of beyond the order of those sums.  Always stores the stream, since the partials
+// do not outlive the next split launch.  A wave per row: these launches have few rows.
+template <int D, bool ADD>
+__global__ void __launch_bounds__(128) ln_partial_kernel(float* __restrict__ resid, const bf16_t* __restrict__ add, const PartialBranch br,
+                                                         const float* __restrict__ shift, const float* __restrict__ scale, int mod_ld,
+                                                         int rows_per_slot, int M, bf16_t* __restrict__ out)
+{
+    constexpr int D4 = D / 4, PER = (D4 + 63) / 64;                  // float4 pieces of a row, pieces per lane
+    typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, row = blockIdx.x * 2 + (threadIdx.x >> 6);
+    if (row >= M) return;
+    f32x4m* xr = reinterpret_cast<f32x4m*>(resid + (size_t)row * D);
+    const size_t mrow = (size_t)(row / rows_per_slot) * mod_ld;
+    // (a lane without a last piece repeats the row's last one, counts nothing for it and stores nothing)
+    auto at = [&](int i) { const int j = i * 64 + lane; return j < D4 ? j : D4 - 1; };
+    auto mine = [&](int i) { return i * 64 + lane < D4; };
+    f32x4m v[PER], p[PER], g[PER], b[PER];
+    bf16x4 a4[ADD ? PER : 1];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        v[i] = xr[at(i)];
+        if constexpr (ADD) a4[i] = reinterpret_cast<const bf16x4*>(add + (size_t)row * D)[at(i)];
+        p[i] = reinterpret_cast<const f32x4m*>(br.sum.part + (size_t)row * br.sum.ldp)[at(i)];
+        g[i] = reinterpret_cast<const f32x4m*>(br.gate + mrow)[at(i)];
+        b[i] = reinterpret_cast<const f32x4m*>(br.bias)[at(i)];
+    }
+    // every partial tile's row is asked for before the first is added: added one by one they were five round trips
+    f32x4m more[kMaxSplits - 1][PER];
+#pragma unroll
+    for (int s = 1; s < kMaxSplits; ++s)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            more[s - 1][i] = (f32x4m){ 0.f, 0.f, 0.f, 0.f };
+            if (s < br.sum.splits) more[s - 1][i] = reinterpret_cast<const f32x4m*>(br.sum.part + s * br.sum.stride + (size_t)row * br.sum.ldp)[at(i)];
+        }
+    f32x4m s4[PER], h4[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        s4[i] = h4[i] = (f32x4m){ 0.f, 0.f, 0.f, 0.f };
+        if (shift) {
+            s4[i] = reinterpret_cast<const f32x4m*>(scale + mrow)[at(i)];
+            h4[i] = reinterpret_cast<const f32x4m*>(shift + mrow)[at(i)];
+        }
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+#pragma unroll
+        for (int s = 1; s < kMaxSplits; ++s) p[i] += more[s - 1][i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if constexpr (ADD) v[i][j] += (float)a4[i][j];
+            v[i][j] += (float)(bf16_t)(g[i][j] * (p[i][j] + b[i][j]));      // rounded as a stored branch output is
+        }
+        if (mine(i)) sum += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
+    }
+    const float mean = wave_sum(sum) * (1.f / (float)D);
+    float sq = 0.f;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { const float c = mine(i) ? v[i][j] - mean : 0.f; sq = fmaf(c, c, sq); }
+    const float rstd = rsqrtf(wave_sum(sq) * (1.f / (float)D) + 1e-6f);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        bf16x4 o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = (bf16_t)fmaf((v[i][j] - mean) * rstd, 1.f + s4[i][j], h4[i][j]);
+        if (mine(i)) {
+            reinterpret_cast<bf16x4*>(out + (size_t)row * D)[at(i)] = o;
+            xr[at(i)] = v[i];
+        }
     }
 }
 
@@ -531,6 +609,29 @@ drf_status launch_ln_modulate(float* resid, const bf16_t* add, const bf16_t* add
     else launch_ln_inst<16>(resid, add, add2, wb, shift, scale, mod_ld, rows_per_slot, M, D, out, out_f32, st);
     DRF_HIP(hipGetLastError());
     return DRF_OK;
+}
+
+bool ln_partial_width(int D) { return D == 128 || D == 384 || D == 768 || D == 1024 || D == 1152; }
+
+drf_status launch_ln_modulate_partial(float* resid, const bf16_t* add, const PartialBranch& br, const float* shift, const float* scale,
+                                      int mod_ld, int rows_per_slot, int M, int D, bf16_t* out, hipStream_t st)
+{
+    if (M == 0) return DRF_OK;
+    if (!ln_partial_width(D) || mod_ld % 4 != 0 || br.sum.ldp % 4 != 0 || br.sum.splits < 1 || br.sum.splits > kMaxSplits) DRF_FAIL(DRF_ESHAPE, "LayerNorm of partial tiles: hidden %d", D);
+    const dim3 grid((M + 1) / 2), block(128);
+    auto go = [&](auto with, auto without) -> drf_status {
+        if (add) hipLaunchKernelGGL(with, grid, block, 0, st, resid, add, br, shift, scale, mod_ld, rows_per_slot, M, out);
+        else hipLaunchKernelGGL(without, grid, block, 0, st, resid, add, br, shift, scale, mod_ld, rows_per_slot, M, out);
+        DRF_HIP(hipGetLastError());
+        return DRF_OK;
+    };
+    switch (D) {
+    case 128: return go(ln_partial_kernel<128, true>, ln_partial_kernel<128, false>);
+    case 384: return go(ln_partial_kernel<384, true>, ln_partial_kernel<384, false>);
+    case 768: return go(ln_partial_kernel<768, true>, ln_partial_kernel<768, false>);
+    case 1024: return go(ln_partial_kernel<1024, true>, ln_partial_kernel<1024, false>);
+    default: return go(ln_partial_kernel<1152, true>, ln_partial_kernel<1152, false>);
+    }
 }
 
 drf_status launch_final(const float* resid, const float* shift, const float* scale, int mod_ld, const float* w,

@@ -654,7 +654,7 @@ drf_status launch_bf16_xl(const bf16_t* A, const bf16_t* W, int M, int N, int K,
 // Split-K form: `splits` workgroups per output tile, partial tiles in `part`, then the reduction with the epilogue.
 template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1>
 drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
-                              int splits, float* part)
+                              int splits, float* part, PartialSum* leave)
 {
     constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + BN * sizeof(float);
     static_assert(smem <= 160 * 1024, "LDS of a CU");
@@ -671,6 +671,10 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(WM * WN * WK * 64), smem, st, A, W, M, N, K, e, tiles_m, tiles_n * splits, sk);
     DRF_HIP(hipGetLastError());
     const int ldp = tiles_n * BN;
+    if (leave) {
+        *leave = PartialSum{ part, splits, ldp, (size_t)tiles_m * BM * ldp };
+        return DRF_OK;
+    }
     const long long quads = (long long)M * (N / 4);
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, part, splits,
                        (size_t)tiles_m * BM * ldp, ldp, M, N, e);
@@ -706,29 +710,30 @@ const TileModel kTiles[] = {
     { 12,  32,  64, 2, 2, 2.04, 1.43, 0.38, 0.29, 3.1, 1.8 },
 };
 
-double model_us(const TileModel& t, int M, int N, int K, int splits)
+double model_us(const TileModel& t, int M, int N, int K, int splits, bool leave)
 {
     const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
     const int steps = (K / (64 * t.wk) + splits - 1) / splits;
     const long long cap = 256LL * t.per_cu, full = tiles / cap, share = (tiles - full * cap + 255) / 256;
     double us = t.base + full * (t.round + steps * fmax(t.lat, t.per_cu * t.thr));
     if (share) us += t.round + steps * fmax(t.lat, share * t.thr);
-    if (splits > 1) us += t.red0 + t.red1 * 1e-6 * M * N * splits;
+    // partials left to the next launch cost it their bytes, and the store of the row that it would not make otherwise
+    if (splits > 1) us += leave ? 0.5 + 0.8e-6 * M * N * splits : t.red0 + t.red1 * 1e-6 * M * N * splits;
     return us;
 }
 
 // The tile and split with the least modelled time.  Two K groups need whole pairs of k-tiles; a split leaves every
 // part at least two k-steps and its partial tiles must fit the scratch.
-void pick_tile(int M, int N, int K, bool may_split, int* id, int* splits)
+void pick_tile(int M, int N, int K, bool may_split, bool leave, int* id, int* splits)
 {
     double best = 1e300;
     for (const TileModel& t : kTiles) {
         if (K % (64 * t.wk) != 0) continue;
         const size_t tile_floats = (size_t)((M + t.bm - 1) / t.bm) * t.bm * ((size_t)((N + t.bn - 1) / t.bn) * t.bn);
-        const int most = may_split && t.red0 > 0.0 && tile_floats / (t.bm * t.bn) < 512 ? 6 : 1;   // (enough tiles fill the chip unsplit)
+        const int most = may_split && t.red0 > 0.0 && tile_floats / (t.bm * t.bn) < 512 ? kMaxSplits : 1;   // (enough tiles fill the chip unsplit)
         for (int s2 = 1; s2 <= most; ++s2) {
             if (s2 > 1 && (K / (64 * t.wk) < 2 * s2 || tile_floats * s2 > kSplitKScratchFloats)) break;
-            const double us = model_us(t, M, N, K, s2);
+            const double us = model_us(t, M, N, K, s2, leave);
             if (us < best) { best = us; *id = t.id; *splits = s2; }
         }
     }
@@ -739,8 +744,9 @@ void pick_tile(int M, int N, int K, bool may_split, int* id, int* splits)
 size_t gemm_splitk_scratch_bytes() { return kSplitKScratchFloats * sizeof(float); }
 
 drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
-                            int variant, float* splitk_scratch)
+                            int variant, float* splitk_scratch, PartialSum* leave)
 {
+    if (leave) leave->splits = 0;
     if (M == 0 || N == 0) return DRF_OK;
     if (K % 64 != 0 || N % 4 != 0 || e.ldo % 4 != 0) DRF_FAIL(DRF_ESHAPE, "bf16 GEMM needs K %% 64 == 0 and N %% 4 == 0 (M=%d N=%d K=%d)", M, N, K);
     if (e.mode == EPI_STORE_HEADS && (e.out_f32 || e.hd % 8 != 0 || e.hid % 16 != 0 || N % e.hid != 0))
@@ -750,7 +756,7 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
         DRF_FAIL(DRF_ESHAPE, "bf16 GEMM operand exceeds 2^31 elements");
     int v = variant, splits = 1;
     if (v == 0) {
-        pick_tile(M, N, K, splitk_scratch != nullptr, &v, &splits);
+        pick_tile(M, N, K, splitk_scratch != nullptr, leave != nullptr, &v, &splits);
     } else if (v >= 100) {
         splits = v / 100;
         v %= 100;
@@ -762,11 +768,11 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
     }
     if (splits > 1) {
         switch (v) {
-        case 1: return launch_bf16_splitk<64, 64, 64, 4, 2, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
-        case 5: return launch_bf16_splitk<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
-        case 6: return launch_bf16_splitk<128, 64, 64, 4, 4, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
-        case 9: return launch_bf16_splitk<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
-        case 12: return launch_bf16_splitk<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, splits, splitk_scratch);
+        case 1: return launch_bf16_splitk<64, 64, 64, 4, 2, 2>(A, W, M, N, K, e, st, splits, splitk_scratch, leave);
+        case 5: return launch_bf16_splitk<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st, splits, splitk_scratch, leave);
+        case 6: return launch_bf16_splitk<128, 64, 64, 4, 4, 2>(A, W, M, N, K, e, st, splits, splitk_scratch, leave);
+        case 9: return launch_bf16_splitk<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, splits, splitk_scratch, leave);
+        case 12: return launch_bf16_splitk<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, splits, splitk_scratch, leave);
         default: DRF_FAIL(DRF_EINVAL, "GEMM tile %d has no split form", v);
         }
     }

@@ -175,6 +175,14 @@ def test_bf16_forward_head_dims_and_tiles(torch, drf, orc, hidden, heads, lat):
     check_forward(torch, drf, orc, dit, "loud", slots=5, tol=TOL_BF16, seed=20 + heads)
 
 
+@pytest.mark.parametrize("cond", [I.COND_CLASS, I.COND_TEXT])
+@pytest.mark.parametrize("hidden,heads", [(128, 4), (384, 6), (768, 8), (1024, 16), (1152, 16)])
+def test_bf16_thin_pass_branch_outputs_left_as_partial_tiles(torch, drf, orc, hidden, heads, cond):
+    # 45 rows: the branch GEMMs split K and the LayerNorm launches add their partial tiles; odd row count
+    dit = small_dit(cond, I.BF16, hidden=hidden, heads=heads, depth=2)
+    check_forward(torch, drf, orc, dit, "loud", slots=3, tol=TOL_BF16, seed=80 + heads)
+
+
 def test_bf16_text_cross_attention_77(torch, drf, orc):
     dit = small_dit(I.COND_TEXT, I.BF16, hidden=576, heads=8, lat_h=12, lat_w=12, depth=2, cond_dim=128, ctx_len=77)
     check_forward(torch, drf, orc, dit, "loud", slots=2, tol=TOL_BF16, seed=31)
