@@ -135,7 +135,7 @@ struct SplitK { int splits, tiles_n; float* part; };
 template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1, bool SK = false>
 __global__ void __launch_bounds__(WM * WN * WK * 64)
 gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K, const Epilogue e,
-                    int tiles_m, int tiles_n, const SplitK sk)
+                    int tiles_m, int tiles_n, int m_first, const SplitK sk)
 {
     // WK > 1: the waves form WK groups that share the output tile and split K between them (group g
     // takes the k-tiles g, g + WK, ...); the groups' partial sums are added through LDS before the
@@ -156,7 +156,7 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
     const int gsz = tiles_m - first_m < GROUP_M ? tiles_m - first_m : GROUP_M;
     const int tm = first_m + (idx % per_group) % gsz, tn = (idx % per_group) / gsz;
     const int split = SK ? tn / sk.tiles_n : 0;
-    const int m0 = tm * BM, n0 = (SK ? tn - split * sk.tiles_n : tn) * BN;
+    const int m0 = m_first + tm * BM, n0 = (SK ? tn - split * sk.tiles_n : tn) * BN;
     int nk = K / (BK * WK);                                          // k-steps of this workgroup
     if constexpr (SK) {
         const int first = split * nk / sk.splits, last = (split + 1) * nk / sk.splits;
@@ -634,7 +634,7 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M,
 }
 
 template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1>
-drf_status launch_bf16_xl(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st)
+drf_status launch_bf16_xl(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first = 0)
 {
     constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + BN * sizeof(float);   // stages + gate row
     static_assert(smem <= 160 * 1024, "LDS of a CU");
@@ -645,8 +645,8 @@ drf_status launch_bf16_xl(const bf16_t* A, const bf16_t* W, int M, int N, int K,
         DRF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
         attr_set = true;
     }
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(WM * WN * WK * 64), smem, st, A, W, M, N, K, e, tiles_m, tiles_n, SplitK{});
+    const int tiles_m = (M - m_first + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(WM * WN * WK * 64), smem, st, A, W, M, N, K, e, tiles_m, tiles_n, m_first, SplitK{});
     DRF_HIP(hipGetLastError());
     return DRF_OK;
 }
@@ -668,7 +668,7 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
         attr_set = true;
     }
     SplitK sk{ splits, tiles_n, part };
-    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(WM * WN * WK * 64), smem, st, A, W, M, N, K, e, tiles_m, tiles_n * splits, sk);
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * splits), dim3(WM * WN * WK * 64), smem, st, A, W, M, N, K, e, tiles_m, tiles_n * splits, 0, sk);
     DRF_HIP(hipGetLastError());
     const int ldp = tiles_n * BN;
     if (leave) {
@@ -722,9 +722,52 @@ double model_us(const TileModel& t, int M, int N, int K, int splits, bool leave)
     return us;
 }
 
+// Rows m_first .. M - 1 of the problem with tile v (m_first a multiple of the tile's height).
+drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first)
+{
+    switch (v) {
+    case 1: return launch_bf16_xl<64, 64, 64, 4, 2, 2>(A, W, M, N, K, e, st, m_first);
+    case 2: return launch_bf16_xl<256, 288, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 3: return launch_bf16_xl<256, 256, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 4: return launch_bf16_xl<128, 128, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 5: return launch_bf16_xl<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 6: return launch_bf16_xl<128, 64, 64, 4, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 7: return launch_bf16_xl<128, 96, 64, 3, 4, 1>(A, W, M, N, K, e, st, m_first);
+    case 8: return launch_bf16_xl<128, 144, 64, 2, 4, 1, 2>(A, W, M, N, K, e, st, m_first);
+    case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
+    case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
+    case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, m_first);
+    case 13: return launch_bf16_xl<256, 144, 64, 3, 8, 1>(A, W, M, N, K, e, st, m_first);
+    case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2>(A, W, M, N, K, e, st, m_first);
+    default: DRF_FAIL(DRF_EINVAL, "unknown GEMM tile %d", v);
+    }
+}
+
+// A problem that fills some rounds of a tile and part of another runs as two launches where that is modelled at least 5 %
+// faster: the rows of the full rounds with that tile, the rest with whatever suits it (24576 x 1152: 1.5 rounds of 256 x 288
+// tiles, or one of them and one of 256 x 144: 232 -> ~217 us at K = 4608; a call of 4096-token slots 430.1 -> 421.7 ms).  Returns the rows of the first launch, 0 for one launch.
+int pick_row_split(int M, int N, int K, double one_us, int* id_a, int* id_b)
+{
+    double best = 0.95 * one_us;
+    int rows = 0;
+    for (const TileModel& a : kTiles) {
+        const long long tn = (N + a.bn - 1) / a.bn, cap = 256LL * a.per_cu, rounds = M / a.bm * tn / cap;
+        if (rounds < 1 || K % (64 * a.wk) != 0) continue;
+        const int ra = (int)(rounds * cap / tn) * a.bm;
+        if (ra == 0 || ra >= M) continue;
+        const double ua = model_us(a, ra, N, K, 1, false);
+        for (const TileModel& b : kTiles) {
+            if (K % (64 * b.wk) != 0 || ra % b.bm != 0) continue;
+            const double us = ua + model_us(b, M - ra, N, K, 1, false);
+            if (us < best) { best = us; rows = ra; *id_a = a.id; *id_b = b.id; }
+        }
+    }
+    return rows;
+}
+
 // The tile and split with the least modelled time.  Two K groups need whole pairs of k-tiles; a split leaves every
 // part at least two k-steps and its partial tiles must fit the scratch.
-void pick_tile(int M, int N, int K, bool may_split, bool leave, int* id, int* splits)
+double pick_tile(int M, int N, int K, bool may_split, bool leave, int* id, int* splits)
 {
     double best = 1e300;
     for (const TileModel& t : kTiles) {
@@ -737,6 +780,7 @@ void pick_tile(int M, int N, int K, bool may_split, bool leave, int* id, int* sp
             if (us < best) { best = us; *id = t.id; *splits = s2; }
         }
     }
+    return best;
 }
 
 }  // namespace
@@ -754,9 +798,10 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
     if (e.mode == EPI_STORE_GATED && (e.out_f32 || !e.gate)) DRF_FAIL(DRF_ESHAPE, "gated store needs bf16 output and a gate");
     if ((size_t)M * K >= ((size_t)1 << 31) || (size_t)N * K >= ((size_t)1 << 31))
         DRF_FAIL(DRF_ESHAPE, "bf16 GEMM operand exceeds 2^31 elements");
-    int v = variant, splits = 1;
+    int v = variant, splits = 1, va = 0, rows_a = 0;
     if (v == 0) {
-        pick_tile(M, N, K, splitk_scratch != nullptr, leave != nullptr, &v, &splits);
+        const double us = pick_tile(M, N, K, splitk_scratch != nullptr, leave != nullptr, &v, &splits);
+        if (splits == 1 && M >= 2048) rows_a = pick_row_split(M, N, K, us, &va, &v);
     } else if (v >= 100) {
         splits = v / 100;
         v %= 100;
@@ -776,22 +821,13 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
         default: DRF_FAIL(DRF_EINVAL, "GEMM tile %d has no split form", v);
         }
     }
-    switch (v) {
-    case 1: return launch_bf16_xl<64, 64, 64, 4, 2, 2>(A, W, M, N, K, e, st);
-    case 2: return launch_bf16_xl<256, 288, 64, 2, 4, 2>(A, W, M, N, K, e, st);
-    case 3: return launch_bf16_xl<256, 256, 64, 2, 4, 2>(A, W, M, N, K, e, st);
-    case 4: return launch_bf16_xl<128, 128, 64, 2, 4, 2>(A, W, M, N, K, e, st);
-    case 5: return launch_bf16_xl<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st);
-    case 6: return launch_bf16_xl<128, 64, 64, 4, 4, 2>(A, W, M, N, K, e, st);
-    case 7: return launch_bf16_xl<128, 96, 64, 3, 4, 1>(A, W, M, N, K, e, st);
-    case 8: return launch_bf16_xl<128, 144, 64, 2, 4, 1, 2>(A, W, M, N, K, e, st);
-    case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st);
-    case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st);
-    case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st);
-    case 13: return launch_bf16_xl<256, 144, 64, 3, 8, 1>(A, W, M, N, K, e, st);
-    case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2>(A, W, M, N, K, e, st);
-    default: DRF_FAIL(DRF_EINVAL, "unknown GEMM tile %d", v);
+    if (rows_a) {
+        Epilogue ea = e;
+        ea.warm_lines = 0;                          // the second launch is the one whose last round warms the caches
+        const drf_status rc = launch_tile(va, A, W, rows_a, N, K, ea, st, 0);
+        if (rc != DRF_OK) return rc;
     }
+    return launch_tile(v, A, W, M, N, K, e, st, rows_a);
 }
 
 drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int a_row_mod)

@@ -81,6 +81,18 @@ def test_gemm_bf16_small_tiles_and_splits(torch, drf, orc, variant, M, N, K):
             drf.probe_gemm_bf16(A[:, :192].contiguous().cuda(), W[:, :192].contiguous().cuda(), torch.from_numpy(b).cuda(), variant=variant)
 
 
+@pytest.mark.parametrize("M,N,K", [(20011, 1152, 384), (12289, 1540, 384)])
+def test_gemm_bf16_rows_in_two_launches(torch, drf, M, N, K):
+    """Full rounds of one tile and the remaining rows with another: same sums in the same order as one launch of a
+    third tile (neither splits K), so the same bits; ragged last row and column tiles."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+    A = torch.randn((M, K), generator=g, device="cuda").bfloat16()
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.1).bfloat16()
+    b = torch.randn((N,), generator=g, device="cuda")
+    out = drf.probe_gemm_bf16(A, W, b)
+    assert torch.equal(out, drf.probe_gemm_bf16(A, W, b, variant=1))
+
+
 def test_gemm_bf16_rejects_bad_k(torch, drf):
     A = torch.zeros((64, 72), dtype=torch.bfloat16, device="cuda")
     W = torch.zeros((64, 72), dtype=torch.bfloat16, device="cuda")
