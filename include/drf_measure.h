@@ -60,6 +60,23 @@ drf_status drf_probe_attn_bf16(const void* qkv, void* out, int slots, int tokens
                                void* hip_stream);
 
 /*
+ * The same kernels in the layout of the cross-attention: q DEVICE bf16 [slots * q_rows][heads * head_dim], kv DEVICE bf16
+ * [kv_slots * kv_rows][2 * heads * head_dim] (k | v), slot j attends to kv slot j % kv_slots.  q_scaled = 1: the queries have been
+ * multiplied by log2(e) / sqrt(head_dim), as the forward pass stores them for long sequences.
+ */
+drf_status drf_probe_cross_attn_bf16(const void* q, const void* kv, void* out, int slots, int kv_slots, int q_rows, int kv_rows,
+                                     int heads, int head_dim, int q_scaled, void* hip_stream);
+
+/*
+ * Which bf16 attention kernel takes a launch of these sizes (host only; 0 for sizes that are refused):
+ *   1 | 2  up to 256 kv rows, one wave per 64 of them, 32 | 64 queries per workgroup;
+ *   3 | 4  kv rows in chunks of 64, 256 queries per workgroup, plain | persistent;
+ *   5      the same with chunks of 128 for more than 256 kv rows;      6  128 queries per workgroup;
+ *   7      more than 256 kv rows, 64 queries per wave.
+ */
+int drf_probe_attn_route(int slots, int q_rows, int kv_rows, int heads, int head_dim, int q_scaled);
+
+/*
  * Introspection for the graph-replay tests: how many drf_sample launch sequences the handle holds as
  * instantiated graphs, how many captures failed (those argument sets launch kernel by kernel), and how
  * many calls were served by a graph launch since the handle was created.

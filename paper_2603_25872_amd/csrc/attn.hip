@@ -506,24 +506,56 @@ drf_status launch_bf16_cfg(const AttnArgs& a, float scale_log2, hipStream_t st)
     return DRF_OK;
 }
 
+// Up to 256 kv rows go through two buffers of 64 (the first MFMAs start after a quarter of the loads and every later chunk
+// is fetched during the steps of the one before; measured the fastest of the 64 / 128 / 256-row, one / two-buffer
+// combinations), more of them through two buffers of 128.
 template <int KS, int DT>
-drf_status launch_bf16_inst(const AttnArgs& a, float scale_log2, hipStream_t st)
+drf_status launch_bf16_inst(const AttnArgs& a, AttnRoute route, float scale_log2, hipStream_t st)
 {
-    // 8 waves (256 queries) share each staged chunk when there are that many queries.  The kv rows (up to 256) then
-    // go through two buffers of 64 rows (the first MFMAs start after a quarter of the loads and every
-    // later chunk is fetched during the steps of the one before; measured the fastest of the 64 / 128 /
-    // 256-row, one / two-buffer combinations).
-    if (a.Nq > 128) {
-        // more items than workgroups that fit the chip at once: persistent workgroups hide each next
-        // item's first loads; otherwise the plain kernel (fewer registers) is the faster one
-        const long long n_items = (long long)((a.Nq + 255) / 256) * a.heads * a.slots;
-        if (n_items > kPersistGroups) return launch_bf16_cfg<KS, DT, 8, 64, true, true>(a, scale_log2, st);
-        return launch_bf16_cfg<KS, DT, 8, 64, false, true>(a, scale_log2, st);
+    switch (route) {
+    case ATTN_CHUNKED_PERSIST: return launch_bf16_cfg<KS, DT, 8, 64, true, true>(a, scale_log2, st);
+    case ATTN_CHUNKED: return launch_bf16_cfg<KS, DT, 8, 64, false, true>(a, scale_log2, st);
+    case ATTN_CHUNKED_LONG: return launch_bf16_cfg<KS, DT, 8, 128>(a, scale_log2, st);
+    default: return launch_bf16_cfg<KS, DT, 4, 128>(a, scale_log2, st);
     }
-    return launch_bf16_cfg<KS, DT, 4, 128>(a, scale_log2, st);
 }
 
+// Workgroups (256 queries each) from which the kernel for long sequences is the faster one, by head width / 8, for queries
+// that come scaled and for others; 0: never.  Against the 8-wave chunked kernel, 300 to 2048 rows, 8 to 4096 workgroups:
+//  - up to 256 of them, one to a CU, it has one wave per SIMD and nothing runs beside a wave's softmax.  Where the head width
+//    leaves spare columns for the reference score it wins all the same (72: 1.08-1.17x scaled, 1.03-1.10x not); at 16, 32
+//    and 64 it loses (64 scaled: 0.89x at 2048 rows, 31.6 against 25.3 us for 4 slots x 1024 rows x 6 heads unscaled);
+//  - from the second workgroup of a CU on it wins at every width up to 80 (64: 1.2-1.6x scaled), unscaled later at 16 and 32;
+//  - at 88 and 96 its registers do not suffice and it loses at most sizes (96: 81 against 35 us for 4 slots x 1024 rows x 12).
+constexpr int kLongFrom[2][12] = { { 257, 1024, 257, 768, 257, 257, 1, 257, 1, 257, 0, 0 }, { 1, 257, 1, 257, 1, 1, 1, 257, 1, 1, 0, 0 } };
+
 }  // namespace
+
+// Nk > 256 and more than 128 queries: see kLongFrom.  Up to 256 kv rows and more than 128 queries the short kernel takes what
+// fits the chip at once: from the second round on, staging K and V once per 256 queries beats reading them once per 32 (12
+// slots x 6 heads x 256 rows, d = 64: 8.9 us there, 10.6 here; 8 slots x 16 heads, d = 72: two rounds, 17.7 there, 14.6
+// here), with persistent workgroups once there are more items than CUs, which hide each next item's first loads (otherwise
+// the plain kernel, with fewer registers, is the faster one).  Up to 128 queries the chunked kernel has nothing to share and the
+// short one takes all (40 slots x 64 rows: 10.4 against 29.0 us), 64 queries at a time once there are many (128 slots x 128
+// rows: 51.5 against 58.0 us with 32, 91.8 chunked); beyond 2^23 items the threads of its launch would not fit 32 bits.
+AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled)
+{
+    if (Nk > 256) {
+        if (Nq <= 128) return ATTN_CHUNKED_FEW;
+        const long long groups = (long long)((Nq + 255) / 256) * heads * slots;
+        const int from = kLongFrom[q_scaled ? 1 : 0][d / 8 - 1];
+        return from && groups >= from ? ATTN_LONG : ATTN_CHUNKED_LONG;
+    }
+    const long long items = (long long)((Nq + 31) / 32) * heads * slots;
+    if (items <= 1 << 23 && (Nq <= 128 || items <= attn_short_items_at_once(Nk, d))) return items <= 4096 ? ATTN_SHORT : ATTN_SHORT_64;
+    if (Nq <= 128) return ATTN_CHUNKED_FEW;
+    return (long long)((Nq + 255) / 256) * heads * slots > kPersistGroups ? ATTN_CHUNKED_PERSIST : ATTN_CHUNKED;
+}
+
+bool attn_wants_scaled(int tokens, int heads, int d, int slots)
+{
+    return attn_route(tokens, tokens, heads, d, slots, true) == ATTN_LONG;
+}
 
 drf_status launch_attn_bf16(const AttnArgs& a, hipStream_t st)
 {
@@ -531,18 +563,17 @@ drf_status launch_attn_bf16(const AttnArgs& a, hipStream_t st)
     if (a.Nk < 1 || a.d % 8 != 0 || a.d > 96 || a.ldq % 8 != 0 || a.ldk % 8 != 0 || a.ldo % 8 != 0 ||
         (reinterpret_cast<uintptr_t>(a.out) & 15u) != 0)
         DRF_FAIL(DRF_ESHAPE, "bf16 attention needs head dim %% 8 == 0 and <= 96 (got %d)", a.d);
-    if (attn_long(a.Nq, a.Nk)) return launch_attn_long_bf16(a, st);
-    bool taken = false;
-    const drf_status rc = launch_attn_short_bf16(a, st, &taken);
-    if (rc != DRF_OK || taken) return rc;
+    const AttnRoute route = attn_route(a.Nq, a.Nk, a.heads, a.d, a.slots, a.q_scaled != 0);
+    if (route == ATTN_LONG) return launch_attn_long_bf16(a, st);
+    if (route == ATTN_SHORT || route == ATTN_SHORT_64) return launch_attn_short_bf16(a, route == ATTN_SHORT ? 32 : 64, st);
     const float sl2 = attn_scale_log2(a);
     switch ((a.d + 15) / 16) {
-    case 1: return launch_bf16_inst<1, 1>(a, sl2, st);
-    case 2: return launch_bf16_inst<2, 1>(a, sl2, st);
-    case 3: return launch_bf16_inst<3, 2>(a, sl2, st);
-    case 4: return launch_bf16_inst<4, 2>(a, sl2, st);
-    case 5: return launch_bf16_inst<5, 3>(a, sl2, st);
-    default: return launch_bf16_inst<6, 3>(a, sl2, st);
+    case 1: return launch_bf16_inst<1, 1>(a, route, sl2, st);
+    case 2: return launch_bf16_inst<2, 1>(a, route, sl2, st);
+    case 3: return launch_bf16_inst<3, 2>(a, route, sl2, st);
+    case 4: return launch_bf16_inst<4, 2>(a, route, sl2, st);
+    case 5: return launch_bf16_inst<5, 3>(a, route, sl2, st);
+    default: return launch_bf16_inst<6, 3>(a, route, sl2, st);
     }
 }
 

@@ -231,36 +231,35 @@ template <int KS, int DT> int short_round(int nw)
     return 256 * (by_lds < by_regs ? by_lds : by_regs);
 }
 
-// Above 128 queries this kernel takes what fits the chip at once: from the second round on, staging K and V once per
-// 256 queries beats reading them once per 32 (12 slots x 6 heads x 256 rows, d = 64: 8.9 us here, 10.6 there; 8 slots x 16
-// heads, d = 72: two rounds, 17.7 here, 14.6 there).  Up to 128 queries the chunked kernel has nothing to share and this one
-// takes all (40 slots x 64 rows: 10.4 against 29.0 us), 64 queries at a time once there are many (128 slots x 128 rows:
-// 51.5 against 58.0 us with 32, 91.8 chunked).
-template <int KS, int DT>
-drf_status launch_short_inst(const AttnArgs& a, float scale_log2, hipStream_t st, bool* taken)
-{
-    const long long items = (long long)((a.Nq + 31) / 32) * a.heads * a.slots;
-    *taken = a.Nq <= 128 || items <= short_round<KS, DT>((a.Nk + kRows - 1) / kRows);
-    if (items > 1 << 23) *taken = false;            // (threads of a launch are counted in 32 bits)
-    if (!*taken) return DRF_OK;
-    return items <= 4096 ? launch_short<KS, DT, 1>(a, scale_log2, st) : launch_short<KS, DT, 2>(a, scale_log2, st);
-}
-
 }  // namespace
 
-drf_status launch_attn_short_bf16(const AttnArgs& a, hipStream_t st, bool* taken)
+int attn_short_items_at_once(int Nk, int d)
 {
-    *taken = false;
-    if (a.Nk > kRows * kMaxWaves) return DRF_OK;
-    const float sl2 = attn_scale_log2(a);
-    switch ((a.d + 15) / 16) {
-    case 1: return launch_short_inst<1, 1>(a, sl2, st, taken);
-    case 2: return launch_short_inst<2, 1>(a, sl2, st, taken);
-    case 3: return launch_short_inst<3, 2>(a, sl2, st, taken);
-    case 4: return launch_short_inst<4, 2>(a, sl2, st, taken);
-    case 5: return launch_short_inst<5, 3>(a, sl2, st, taken);
-    default: return launch_short_inst<6, 3>(a, sl2, st, taken);
+    const int nw = (Nk + kRows - 1) / kRows;
+    switch ((d + 15) / 16) {
+    case 1: return short_round<1, 1>(nw);
+    case 2: return short_round<2, 1>(nw);
+    case 3: return short_round<3, 2>(nw);
+    case 4: return short_round<4, 2>(nw);
+    case 5: return short_round<5, 3>(nw);
+    default: return short_round<6, 3>(nw);
     }
+}
+
+drf_status launch_attn_short_bf16(const AttnArgs& a, int queries, hipStream_t st)
+{
+    if (a.Nk > kRows * kMaxWaves) DRF_FAIL(DRF_ESHAPE, "one wave per 64 rows: at most %d kv rows", kRows * kMaxWaves);
+    const float sl2 = attn_scale_log2(a);
+#define DRF_SHORT(KS, DT) (queries == 32 ? launch_short<KS, DT, 1>(a, sl2, st) : launch_short<KS, DT, 2>(a, sl2, st))
+    switch ((a.d + 15) / 16) {
+    case 1: return DRF_SHORT(1, 1);
+    case 2: return DRF_SHORT(2, 1);
+    case 3: return DRF_SHORT(3, 2);
+    case 4: return DRF_SHORT(4, 2);
+    case 5: return DRF_SHORT(5, 3);
+    default: return DRF_SHORT(6, 3);
+    }
+#undef DRF_SHORT
 }
 
 }  // namespace drf

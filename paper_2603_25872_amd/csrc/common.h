@@ -152,14 +152,25 @@ struct AttnArgs {
     int kv_mod;                     // kv_batch = kv_mod ? slot % kv_mod : slot
     int q_scaled;                   // bf16 path: 1 = the queries have been multiplied by log2(e) / sqrt(d) already
 };
-// Sequences that launch_attn_bf16 hands to launch_attn_long_bf16, which likes its queries scaled by their producer.
-inline bool attn_long(int Nq, int Nk) { return Nq > 128 && Nk > 256; }
 // Factor that turns q . k into an exponent of two.
 inline float attn_scale_log2(const AttnArgs& a) { return a.q_scaled ? 1.f : 1.4426950408889634f / sqrtf((float)a.d); }
+// Which bf16 kernel takes a launch (see attn_route in attn.hip for the rules).
+enum AttnRoute {
+    ATTN_SHORT = 1,         // up to 256 kv rows, one wave per 64 of them; 32 queries per workgroup (attn_short.hip)
+    ATTN_SHORT_64 = 2,      // the same with 64 queries
+    ATTN_CHUNKED = 3,       // chunks of kv rows, 8 waves of 32 queries, up to 256 kv rows (attn.hip)
+    ATTN_CHUNKED_PERSIST = 4,   // the same, persistent workgroups
+    ATTN_CHUNKED_LONG = 5,  // 8 waves, more than 256 kv rows
+    ATTN_CHUNKED_FEW = 6,   // 4 waves, up to 128 queries
+    ATTN_LONG = 7,          // more than 256 kv rows, 64 queries per wave (attn_long.hip)
+};
+AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled);
+// Self-attention whose queries their producer should multiply by log2(e) / sqrt(d): what ATTN_LONG takes with them scaled.
+bool attn_wants_scaled(int tokens, int heads, int d, int slots);
 drf_status launch_attn_bf16(const AttnArgs& a, hipStream_t st);
 drf_status launch_attn_long_bf16(const AttnArgs& a, hipStream_t st);
-// Takes the launch (*taken) when it is the faster kernel for it: Nk <= 256, and few or short query sequences.
-drf_status launch_attn_short_bf16(const AttnArgs& a, hipStream_t st, bool* taken);
+drf_status launch_attn_short_bf16(const AttnArgs& a, int queries, hipStream_t st);
+int attn_short_items_at_once(int Nk, int d);    // work items of 32 queries that the chip holds of ATTN_SHORT
 drf_status launch_attn_f32(const AttnArgs& a, hipStream_t st);
 
 struct DitDims { int D, P, T, gh, gw, C, H, W, patch, heads, d, R, L; };

@@ -273,13 +273,13 @@ Epilogue epi_store(void* out, int ldo, bool f32, bool gelu = false)
     return e;
 }
 
-Epilogue epi_heads(void* out, int M, const DitDims& dm)
+Epilogue epi_heads(void* out, int slots, const DitDims& dm)
 {
     Epilogue e{};
     e.mode = EPI_STORE_HEADS; e.out = out; e.ldo = 3 * dm.D; e.out_f32 = 0;
     set_rows_per_slot(&e, dm.T);
-    e.hid = dm.D; e.hd = dm.d; e.heads = dm.heads; e.plane = (size_t)M * dm.D;
-    e.q_scale = attn_long(dm.T, dm.T) ? 1.4426950408889634f / sqrtf((float)dm.d) : 1.f;
+    e.hid = dm.D; e.hd = dm.d; e.heads = dm.heads; e.plane = (size_t)slots * dm.T * dm.D;
+    e.q_scale = attn_wants_scaled(dm.T, dm.heads, dm.d, slots) ? 1.4426950408889634f / sqrtf((float)dm.d) : 1.f;
     make_fast_div(dm.D, &e.hid_magic, &e.hid_shift);
     make_fast_div(dm.d, &e.hd_magic, &e.hd_shift);
     return e;
@@ -402,7 +402,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         if ((rc = ln(mrow, mrow + D, nm, true)) != DRF_OK) return rc;
         // bf16: q | k | v are stored head-major ([slot][head][token][d] planes) so that attention reads
         // whole contiguous tiles; fp32: packed rows
-        if ((rc = gemm(d, ws.hbuf, b.qkv, M, f32 ? epi_store(ws.qkv, 3 * D, true) : with_warm(epi_heads(ws.qkv, M, dm), &b.proj), st, ws.skpart)) != DRF_OK) return rc;
+        if ((rc = gemm(d, ws.hbuf, b.qkv, M, f32 ? epi_store(ws.qkv, 3 * D, true) : with_warm(epi_heads(ws.qkv, slots, dm), &b.proj), st, ws.skpart)) != DRF_OK) return rc;
         {
             AttnArgs aa{};
             aa.q = ws.qkv; aa.out = ws.hbuf; aa.ldo = D; aa.Nq = dm.T; aa.Nk = dm.T; aa.heads = dm.heads; aa.d = dm.d;
@@ -415,7 +415,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
                 aa.k = (char*)ws.qkv + (size_t)M * D * act; aa.v = (char*)ws.qkv + (size_t)2 * M * D * act;
                 aa.ldq = aa.ldk = dm.d;
                 aa.q_slot_stride = aa.kv_batch_stride = (size_t)dm.T * D; aa.q_head_stride = aa.kv_head_stride = (size_t)dm.T * dm.d;
-                aa.q_scaled = attn_long(dm.T, dm.T);
+                aa.q_scaled = attn_wants_scaled(dm.T, dm.heads, dm.d, slots);
             }
             ProfScope ps(d, st, DRF_PROF_ATTN, 4.0 * slots * dm.heads * (double)dm.T * dm.T * dm.d);
             if ((rc = f32 ? launch_attn_f32(aa, st) : launch_attn_bf16(aa, st)) != DRF_OK) return rc;
@@ -1110,4 +1110,23 @@ extern "C" drf_status drf_probe_attn_bf16(const void* qkv, void* out, int slots,
     aa.q_slot_stride = aa.kv_batch_stride = (size_t)tokens * 3 * D; aa.q_head_stride = aa.kv_head_stride = head_dim;
     aa.out = out; aa.ldo = D; aa.Nq = tokens; aa.Nk = tokens; aa.heads = heads; aa.d = head_dim; aa.slots = slots; aa.kv_mod = 0;
     return launch_attn_bf16(aa, (hipStream_t)hip_stream);
+}
+
+extern "C" drf_status drf_probe_cross_attn_bf16(const void* q, const void* kv, void* out, int slots, int kv_slots, int q_rows, int kv_rows,
+                                                int heads, int head_dim, int q_scaled, void* hip_stream)
+{
+    if (!q || !kv || !out || slots < 0 || kv_slots < 1 || q_rows < 1 || kv_rows < 1 || heads < 1 || head_dim < 1 || q_scaled < 0 || q_scaled > 1)
+        DRF_FAIL(DRF_EINVAL, "bad argument");
+    const int D = heads * head_dim;
+    AttnArgs aa{};
+    aa.q = q; aa.ldq = D; aa.k = kv; aa.v = (const bf16_t*)kv + D; aa.ldk = 2 * D; aa.out = out; aa.ldo = D;
+    aa.q_slot_stride = (size_t)q_rows * D; aa.kv_batch_stride = (size_t)kv_rows * 2 * D; aa.q_head_stride = aa.kv_head_stride = head_dim;
+    aa.Nq = q_rows; aa.Nk = kv_rows; aa.heads = heads; aa.d = head_dim; aa.slots = slots; aa.kv_mod = kv_slots; aa.q_scaled = q_scaled;
+    return launch_attn_bf16(aa, (hipStream_t)hip_stream);
+}
+
+extern "C" int drf_probe_attn_route(int slots, int q_rows, int kv_rows, int heads, int head_dim, int q_scaled)
+{
+    if (slots < 1 || q_rows < 1 || kv_rows < 1 || heads < 1 || head_dim < 8 || head_dim > 96 || head_dim % 8 != 0) return 0;
+    return attn_route(q_rows, kv_rows, heads, head_dim, slots, q_scaled != 0);
 }

@@ -25,7 +25,7 @@ SYMBOLS = ["drf_denoiser_weight_count", "drf_denoiser_create", "drf_denoiser_des
            "drf_plan_build", "drf_last_error"]
 # include/drf_measure.h: test and measurement hooks
 MEASURE_SYMBOLS = ["drf_eps_trace", "drf_profile_enable", "drf_profile_read", "drf_probe_gemm_bf16",
-                   "drf_probe_attn_bf16", "drf_probe_update_fused", "drf_graph_stats", "drf_calibrate_mfma_bf16", "drf_calibrate_copy"]
+                   "drf_probe_attn_bf16", "drf_probe_cross_attn_bf16", "drf_probe_attn_route", "drf_probe_update_fused", "drf_graph_stats", "drf_calibrate_mfma_bf16", "drf_calibrate_copy"]
 STATIC_SCRATCH_BYTES = 48 << 20
 
 
@@ -93,6 +93,8 @@ def lib():
         L.drf_probe_gemm_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p,
                                           C.c_int, C.c_void_p]
         L.drf_probe_attn_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]
+        L.drf_probe_cross_attn_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p] + [C.c_int] * 7 + [C.c_void_p]
+        L.drf_probe_attn_route.argtypes = [C.c_int] * 6
         L.drf_last_error.restype = C.c_char_p
         _lib = L
     return _lib
@@ -235,6 +237,22 @@ def probe_attn_bf16(qkv, slots, tokens, heads, head_dim, out=None):
     _check(lib().drf_probe_attn_bf16(_dev(qkv, torch.bfloat16), _dev(out, torch.bfloat16), slots, tokens, heads, head_dim,
                                      _stream()))
     return out
+
+
+def probe_cross_attn_bf16(q, kv, slots, kv_slots, q_rows, kv_rows, heads, head_dim, q_scaled=False, out=None):
+    """Attention of bf16 q [slots*q_rows, heads*head_dim] over bf16 kv [kv_slots*kv_rows, 2*heads*head_dim], slot j over kv
+    slot j % kv_slots (measurement hook)."""
+    import torch
+    if out is None:
+        out = torch.empty((slots * q_rows, heads * head_dim), dtype=torch.bfloat16, device=q.device)
+    _check(lib().drf_probe_cross_attn_bf16(_dev(q, torch.bfloat16), _dev(kv, torch.bfloat16), _dev(out, torch.bfloat16), slots, kv_slots,
+                                           q_rows, kv_rows, heads, head_dim, int(q_scaled), _stream()))
+    return out
+
+
+def probe_attn_route(slots, q_rows, kv_rows, heads, head_dim, q_scaled=False):
+    """Number of the bf16 attention kernel that takes a launch of these sizes (host only, see include/drf_measure.h)."""
+    return lib().drf_probe_attn_route(slots, q_rows, kv_rows, heads, head_dim, int(q_scaled))
 
 
 def probe_update_fused(sched, s_from, n_chain, n_draft, g, w, x_base, eps, x_out=None, draft_out=None):

@@ -171,3 +171,28 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0
     assert "one GPU" in (r.stderr + r.stdout)
+
+
+@pytest.mark.parametrize("d", range(8, 97, 8))
+@pytest.mark.parametrize("scaled", [0, 1])
+def test_long_attention_goes_to_the_kernel_that_measured_faster(d, scaled):
+    """More than 256 kv rows.  One workgroup of 256 queries to a CU (here 4 and 256 of them): 64 queries per wave lose at widths
+    16, 32 and 64 (0.76-0.95x of the chunked kernel, queries scaled or not) and never beyond 80; many workgroups: they win at every
+    width up to 80."""
+    few, full, many = (drf.probe_attn_route(s, 1024, 1024, h, d, scaled) for s, h in ((1, 1), (8, 8), (64, 8)))
+    assert many == (7 if d <= 80 else 5)
+    if d in (16, 32, 64, 88, 96):
+        assert (few, full) == (5, 5)
+    elif scaled or d in (56, 72):
+        assert (few, full) == (7, 7)
+
+
+def test_attention_routes_by_rows():
+    route = drf.probe_attn_route
+    for d in range(8, 97, 8):
+        assert route(2, 64, 64, 4, d) == 1 and route(300, 40, 40, 16, d) == 2         # up to 128 queries: 32 at a time, 64 of many
+        assert route(2, 256, 256, 4, d) == 1                                            # fits the chip at once
+        assert route(32, 256, 256, 8, d) == 3 and route(64, 256, 256, 8, d) == 4
+        assert route(2, 128, 257, 4, d) == 6 and route(2, 128, 256, 4, d) == 1
+        assert route(3, 129, 257, 4, d) in (5, 7)
+    assert route(0, 64, 64, 4, 64) == route(1, 64, 64, 4, 12) == route(1, 64, 64, 4, 104) == 0
