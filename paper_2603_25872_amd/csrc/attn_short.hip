@@ -131,12 +131,14 @@ attn_short_kernel(const AttnArgs a, float scale_log2, int nqb, int n_items, uint
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         m_own[b] = mx * scale_log2;
         if (half == 0) s_max[wave][b][l32] = m_own[b];
+        // (a wave whose 64 rows all score -infinity has no reference: its numerators are zero against any)
+        const float ref = m_own[b] == -INFINITY ? 0.f : m_own[b];
         float sum = 0.f;
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(s[b][t][r], scale_log2, -m_own[b]));
+                const float p = __builtin_amdgcn_exp2f(fmaf(s[b][t][r], scale_log2, -ref));
                 sum += p;
                 pf[b][t][r >> 3][r & 7] = (bf16_t)p;
             }

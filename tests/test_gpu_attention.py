@@ -127,3 +127,23 @@ def test_one_wave_per_64_rows_over_shared_kv(torch, drf, d, Nq, Nk):
     args = (5, 2, Nq, Nk, 3, d)
     run(torch, drf, 1, *normal(np.random.default_rng(d + Nq), *args), *args, False, 1.5e-2, look=(0, 3, 4))
     run(torch, drf, 1, *growing(np.random.default_rng(d + Nq), *args), *args, False, 2e-2)
+
+
+def overflowing(rng, slots, kv_slots, Nq, Nk, H, d, rows):
+    """Finite queries and keys whose products with the keys of `rows` are below the range of fp32 (scores of -inf); the other
+    scores are of order one."""
+    q, kv = normal(rng, slots, kv_slots, Nq, Nk, H, d, 1)
+    q = np.abs(q) * 1e19 + 1e19
+    kv[:, :H * d] *= 1e-19
+    for s in range(kv_slots):
+        kv[s * Nk + rows.start:s * Nk + rows.stop, :H * d] = -1e25
+    return q, kv
+
+
+@pytest.mark.parametrize("d", [16, 64, 72, 96])
+@pytest.mark.parametrize("slots,Nq,Nk,rows,route", [(3, 40, 128, range(64, 128), 1), (3, 40, 200, range(0, 64), 1), (131, 256, 70, range(64, 70), 4),
+                                                    (180, 96, 256, range(64, 192), 2)])
+def test_scores_of_minus_infinity_in_a_whole_wave(torch, drf, d, slots, Nq, Nk, rows, route):
+    """The rows of one wave have no finite score: they get no weight, and the rest of the row is what it is without them."""
+    args = (slots, 2, Nq, Nk, 8, d)
+    run(torch, drf, route, *overflowing(np.random.default_rng(d), *args, rows), *args, False, 1.5e-2)
