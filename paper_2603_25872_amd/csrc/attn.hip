@@ -439,7 +439,9 @@ __global__ void __launch_bounds__(kF32Waves * 64) attn_f32_kernel(const AttnArgs
         }
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float m_new = fmaxf(m_run, mx), alpha = expf(m_run - m_new);
+        const float m_new = fmaxf(m_run, mx);
+        // (while no row of this wave has scored above -infinity there is no reference: numerators are zero against any)
+        const float ref = m_new == -INFINITY ? 0.f : m_new, alpha = expf(m_run - ref);
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll
@@ -448,7 +450,7 @@ __global__ void __launch_bounds__(kF32Waves * 64) attn_f32_kernel(const AttnArgs
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float p = expf(s[t][r] - m_new);
+                const float p = expf(s[t][r] - ref);
                 l_run += p;
 #pragma unroll
                 for (int c = 0; c < DQ; ++c) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][r][c], p, o[c], 0, 0, 0);

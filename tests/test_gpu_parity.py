@@ -143,6 +143,27 @@ def test_fp32_forward_operands_that_no_vector_load_takes(torch, drf, orc, kw):
     check_forward(torch, drf, orc, small_dit(cond, I.F32, **kw), "loud", slots=3, tol=TOL_F32, seed=70 + kw["hidden"])
 
 
+def test_fp32_attention_scores_of_minus_infinity_in_one_waves_rows(torch, drf, orc):
+    """Context rows 32-63, one wave's share, score below the range of fp32: they get no weight."""
+    dit = small_dit(I.COND_TEXT, I.F32, depth=1, ctx_len=70)
+    w, D = I.weights(dit, 11, "loud"), dit["hidden"]
+    p = I.param_views(dit, w)
+    p["blk0.xq_w"][:], p["blk0.xq_b"][:] = 0, 1e19
+    p["blk0.xkv_w"][:D] *= 1e-19
+    p["blk0.xkv_b"][:D] = 0
+    p["blk0.xkv_w"][:D, 0] = -1e25
+    rng = np.random.default_rng(12)
+    ctx = rng.standard_normal((2, 70, dit["cond_dim"])).astype(np.float32)
+    ctx[:, :, 0] = 0
+    ctx[:, 32:64, 0] = 1
+    x = rng.standard_normal((2, dit["in_ch"], dit["lat_h"], dit["lat_w"])).astype(np.float32)
+    t = np.array([3, 900], np.int32)
+    den = drf.Denoiser(dit, w)
+    got = den.eps_trace(dev(torch, x), dev(torch, t), dev(torch, ctx), 1).cpu().numpy()
+    den.close()
+    check(got, orc.dit_eps(dit, w, x, t, ctx, stop_blocks=1), TOL_F32, "resid1")
+
+
 def test_fp32_conditioning_from_an_unaligned_buffer(torch, drf, orc):
     dit = small_dit(I.COND_VECTOR, I.F32)
     w, cond = I.weights(dit, 3, "loud"), make_cond(dit, 2, 4)
