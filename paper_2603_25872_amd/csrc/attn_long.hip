@@ -18,6 +18,7 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 constexpr int kWaves = 4, kQpw = 64, kQpg = kWaves * kQpw;     // waves, queries per wave and per workgroup
 constexpr int kStep = 32;                                       // kv rows per softmax step
 constexpr float kTau = 8.f;                                     // lazy-rescale headroom of the online softmax, in log2 units
+constexpr float kFar = 1024.f;                                  // see settle: scores closer than this to the reference keep 2^-13
 
 __device__ inline float max3(float a, float b, float c) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c); }
 
@@ -218,6 +219,12 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_long_kernel(const AttnArg
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[b][ks], ks == 0 ? zero16 : s[b], 0, 0, 0);
         };
+        auto largest = [&](const f32x16& v) {
+            float mx = max3(v[0], v[1], v[2]);
+#pragma unroll
+            for (int r = 3; r < 15; r += 2) mx = max3(mx, v[r], v[r + 1]);
+            return __builtin_elementwise_maximum(mx, v[15]);
+        };
         // Largest score of this lane's kv rows.  Register r of s[b] holds kv row 8 (r / 4) + 4 half + r % 4 of the step.
         auto top = [&](int b, int kv0) {
             if constexpr (!C::ONES) {
@@ -228,25 +235,44 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_long_kernel(const AttnArg
                         if (8 * (r >> 2) + (r & 3) >= left) s[b][r] = -INFINITY;
                 }
             }
-            float mx = max3(s[b][0], s[b][1], s[b][2]);
+            return largest(s[b]);
+        };
+        // Scores of block b and a step without any reference, with K straight from memory (its LDS rows may be gone): for the
+        // rare case of settle.  The spare columns meet zeros.
+        auto raw = [&](int b, int step, f32x16& v) {
+            const int row = step * kStep + l32;
+            const bf16_t* kr = Kp + (size_t)(row < Nk ? row : Nk - 1) * ldk;
 #pragma unroll
-            for (int r = 3; r < 15; r += 2) mx = max3(mx, s[b][r], s[b][r + 1]);
-            return __builtin_elementwise_maximum(mx, s[b][15]);
+            for (int ks = 0; ks < KS; ++ks) {
+                const int dd = ks * 16 + half * 8;
+                const bf16x8 kk = dd < d ? *reinterpret_cast<const bf16x8*>(kr + dd) : zero8;
+                v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk, qf[b][ks], ks == 0 ? zero16 : v, 0, 0, 0);
+            }
         };
         // PADM: the reference is subtracted by the score MFMA itself, as three bf16 parts in Q's spare columns (24 bits: all
         // of m_run) against ones in K's, so scores arrive relative to it and need no arithmetic before the exponential.
-        auto settle = [&](int b, float mx, bool first) {
+        auto settle = [&](int b, float mx, int step, bool first) {
             const float rel = C::PADM ? mx : mx - m_run[b];
             if (__any(rel > (first ? -INFINITY : tau))) {
-                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(rel), __float_as_uint(rel), false, false);
-                const float m_new = m_run[b] + max3(__uint_as_float(sw[0]), __uint_as_float(sw[1]), first ? -INFINITY : 0.f);
-                const float delta = m_new - m_run[b];
+                // the largest of both halves' rows; m_new: never below the reference so far
+                auto both = [&](float v, float least) {
+                    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+                    return max3(__uint_as_float(sw[0]), __uint_as_float(sw[1]), least);
+                };
+                float m_new = C::PADM ? m_run[b] + both(rel, first ? -INFINITY : 0.f) : both(mx, first ? -INFINITY : m_run[b]);
+                float delta = m_new - m_run[b], shift = delta;
+                // scores far above the reference have lost their low bits to it (2^-24 of the distance): formed anew
+                if (C::PADM && !first && __any(delta > kFar)) {
+                    raw(b, step, s[b]);
+                    shift = m_new = both(largest(s[b]), m_run[b]);
+                    delta = m_new - m_run[b];
+                }
                 const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(PRE ? -delta : -delta * scale_log2);
                 m_run[b] = m_new;
                 l_run[b] *= alpha;
                 if constexpr (C::PADM) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) s[b][r] -= delta;
+                    for (int r = 0; r < 16; ++r) s[b][r] -= shift;
                     const bf16_t hi = (bf16_t)-m_new, mid = (bf16_t)(-m_new - (float)hi), lo = (bf16_t)((-m_new - (float)hi) - (float)mid);
                     const bf16x8 parts = { hi, mid, lo, 0, 0, 0, 0, 0 };
                     qf[b][KS - 1] = half ? parts : qf[b][KS - 1];
@@ -299,7 +325,7 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_long_kernel(const AttnArg
         load_k(base + koff);
         load_v(base);
         qk(0);
-        settle(0, top(0, 0), true);
+        settle(0, top(0, 0), 0, true);
         static_assert(SPC > 1, "the pipeline runs one step ahead");
         for (int kv = 0; kv < nsteps; ++kv) {
             // position n's fragments are read as soon as the last MFMA that needs this one's is issued (past the end: the
@@ -310,12 +336,12 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_long_kernel(const AttnArg
             load_k(nb + (n % SPC) * (kStep * KP * 8) + koff);
             pin();
             soft_pv(0);
-            settle(1, top(1, kv * kStep), kv == 0);
+            settle(1, top(1, kv * kStep), kv, kv == 0);
             qk(0);
             soft_pv(1);
             load_v(nb + (n % SPC) * (kStep * VP * 8));
             pin();
-            settle(0, top(0, n * kStep), false);
+            settle(0, top(0, n * kStep), n, false);
             // every fragment of this chunk has been read when step kv + 2 opens the next one
             if ((kv + 2) % SPC == 0 && kv + 2 < nsteps) next_chunk((kv + 2) / SPC);
         }

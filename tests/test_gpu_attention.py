@@ -147,3 +147,18 @@ def test_scores_of_minus_infinity_in_a_whole_wave(torch, drf, d, slots, Nq, Nk, 
     """The rows of one wave have no finite score: they get no weight, and the rest of the row is what it is without them."""
     args = (slots, 2, Nq, Nk, 8, d)
     run(torch, drf, route, *overflowing(np.random.default_rng(d), *args, rows), *args, False, 1.5e-2)
+
+
+@pytest.mark.parametrize("scaled", [False, True])
+@pytest.mark.parametrize("d", [w for w in WIDTHS if w <= 80])
+@pytest.mark.parametrize("far", [1e3, 1e5, 1e8, 1e20])
+def test_scores_far_above_the_reference_so_far(torch, drf, d, scaled, far):
+    """The first rows, as many as a step or a little more, score far below the rest, whose differences decide the result: they
+    must not be rounded to the distance."""
+    args = (130 if d in (16, 32) and not scaled else 34, 2, 300, 300, 8, d)
+    q, kv = normal(np.random.default_rng(d), *args, 1)
+    q = np.abs(q) + 1
+    for s in range(2):
+        kv[s * 300:s * 300 + 32, :8 * d] = -far
+        kv[s * 300 + 32:s * 300 + 40, :8 * d] = -far / 2
+    run(torch, drf, 7, q, kv, *args, scaled, 1.5e-2)
