@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_long_kernel(const AttnArg
             return largest(s[b]);
         };
         // Scores of block b and a step without any reference, with K straight from memory (its LDS rows may be gone): for the
-        // rare case of settle.  The spare columns meet zeros.
+        // rare cases of settle.  The spare columns meet zeros.
         auto raw = [&](int b, int step, f32x16& v) {
             const int row = step * kStep + l32;
             const bf16_t* kr = Kp + (size_t)(row < Nk ? row : Nk - 1) * ldk;
@@ -253,13 +253,20 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_long_kernel(const AttnArg
         // of m_run) against ones in K's, so scores arrive relative to it and need no arithmetic before the exponential.
         auto settle = [&](int b, float mx, int step, bool first) {
             const float rel = C::PADM ? mx : mx - m_run[b];
-            if (__any(rel > (first ? -INFINITY : tau))) {
+            if (__any(rel >= (first ? -INFINITY : tau))) {
                 // the largest of both halves' rows; m_new: never below the reference so far
                 auto both = [&](float v, float least) {
                     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
                     return max3(__uint_as_float(sw[0]), __uint_as_float(sw[1]), least);
                 };
                 float m_new = C::PADM ? m_run[b] + both(rel, first ? -INFINITY : 0.f) : both(mx, first ? -INFINITY : m_run[b]);
+                if (first && __any(m_new == -INFINITY)) {
+                    // a query that scores -infinity against all of the first 32 rows takes its reference from the next 32, in
+                    // the registers of the other block's scores, which hold nothing yet; failing that, 0
+                    raw(b, 1, s[1 - b]);
+                    const float m2 = both(largest(s[1 - b]), -INFINITY);
+                    if (m_new == -INFINITY) m_new = m2 == -INFINITY ? 0.f : m2;
+                }
                 float delta = m_new - m_run[b], shift = delta;
                 // scores far above the reference have lost their low bits to it (2^-24 of the distance): formed anew
                 if (C::PADM && !first && __any(delta > kFar)) {

@@ -151,6 +151,22 @@ def test_scores_of_minus_infinity_in_a_whole_wave(torch, drf, d, slots, Nq, Nk, 
 
 @pytest.mark.parametrize("scaled", [False, True])
 @pytest.mark.parametrize("d", [w for w in WIDTHS if w <= 80])
+@pytest.mark.parametrize("rows", [range(0, 32), range(32, 96), range(256, 300)])
+@pytest.mark.parametrize("every", [1, 2])
+def test_scores_of_minus_infinity_in_a_step_of_64_queries(torch, drf, d, scaled, rows, every):
+    """The same for steps of the kernel for long sequences, the first of which sets the reference: for every query, and for
+    every second one while the others' scores stay finite; the scores of all other rows are far below zero."""
+    args = (130 if d in (16, 32) and not scaled else 34, 2, 300, 300, 8, d)
+    q, kv = overflowing(np.random.default_rng(d), *args, rows)
+    for r in set(range(300)) - set(rows):
+        kv[[r, 300 + r], :8 * d] -= 1.5e-17 * d ** -0.5
+    if every == 2:
+        q[::2] *= 1e-9
+    run(torch, drf, 7, q, kv, *args, scaled, 1.5e-2)
+
+
+@pytest.mark.parametrize("scaled", [False, True])
+@pytest.mark.parametrize("d", [w for w in WIDTHS if w <= 80])
 @pytest.mark.parametrize("far", [1e3, 1e5, 1e8, 1e20])
 def test_scores_far_above_the_reference_so_far(torch, drf, d, scaled, far):
     """The first rows, as many as a step or a little more, score far below the rest, whose differences decide the result: they
