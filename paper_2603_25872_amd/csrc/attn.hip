@@ -539,7 +539,9 @@ constexpr int kLongFrom[2][12] = { { 257, 1024, 257, 768, 257, 257, 1, 257, 1, 2
 // here), with persistent workgroups once there are more items than CUs, which hide each next item's first loads (otherwise
 // the plain kernel, with fewer registers, is the faster one).  Up to 128 queries the chunked kernel has nothing to share and the
 // short one takes all (40 slots x 64 rows: 10.4 against 29.0 us), 64 queries at a time once there are many (128 slots x 128
-// rows: 51.5 against 58.0 us with 32, 91.8 chunked); beyond 2^23 items the threads of its launch would not fit 32 bits.
+// rows: 51.5 against 58.0 us with 32, 91.8 chunked), at widths beyond 80 from the second round of a launch of more than 96
+// queries on (64 slots x 128 queries x 256 rows x 4 heads of 96: 15.9 against 18.9 us, 17.1 in one chunk per head; from 32 to
+// 96 queries one form or the other is ahead by up to 20 %); beyond 2^23 items the threads of its launch would not fit 32 bits.
 AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled)
 {
     if (Nk > 256) {
@@ -549,7 +551,8 @@ AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled)
         return from && groups >= from ? ATTN_LONG : ATTN_CHUNKED_LONG;
     }
     const long long items = (long long)((Nq + 31) / 32) * heads * slots;
-    if (items <= 1 << 23 && (Nq <= 128 || items <= attn_short_items_at_once(Nk, d))) return items <= 4096 ? ATTN_SHORT : ATTN_SHORT_64;
+    const bool at_once = items <= attn_short_items_at_once(Nk, d);
+    if (items <= 1 << 23 && (Nq <= 128 || at_once)) return items > 4096 || (d > 80 && Nq > 96 && !at_once) ? ATTN_SHORT_64 : ATTN_SHORT;
     if (Nq <= 128) return ATTN_CHUNKED_FEW;
     return (long long)((Nq + 255) / 256) * heads * slots > kPersistGroups ? ATTN_CHUNKED_PERSIST : ATTN_CHUNKED;
 }

@@ -196,3 +196,12 @@ def test_attention_routes_by_rows():
         assert route(2, 128, 257, 4, d) == 6 and route(2, 128, 256, 4, d) == 1
         assert route(3, 129, 257, 4, d) in (5, 7)
     assert route(0, 64, 64, 4, 64) == route(1, 64, 64, 4, 12) == route(1, 64, 64, 4, 104) == 0
+
+
+@pytest.mark.parametrize("d", range(8, 97, 8))
+def test_wide_heads_share_kv_between_two_query_blocks_from_the_second_round_on(d):
+    """Up to 256 rows and 97 to 128 queries at widths 88 and 96: with 32 queries per workgroup a launch that does not fit the chip at once is
+    slower than with 64 (18.9 against 15.9 us) and than one chunk per head was (17.1 us)."""
+    route = drf.probe_attn_route
+    assert route(64, 128, 256, 4, d) == route(16, 128, 200, 16, d) == (2 if d > 80 else 1)
+    assert route(64, 96, 256, 4, d) == 1 and route(8, 128, 256, 4, d) == 1
