@@ -45,8 +45,9 @@ drf_status drf_profile_read(drf_denoiser* den, int which, long long* launches, d
 /*
  * Measurement hook: one launch of the library's bf16 GEMM on caller buffers,
  * out[M][N] (bf16) = A[M][K] (bf16) . W[N][K]^T (bf16) + bias[N] (fp32), all DEVICE.
- * variant 0 = the tile shape the forward pass would pick unsplit, > 0 forces one (for sweeps); 10 = the 128 x 128 tile
- * with K split across workgroups as far as parts of six 64-wide k-tiles go; 100 s + v = tile v with K in s parts.
+ * variant 0 = the tile shape the forward pass would pick unsplit, > 0 forces one (for sweeps; a number that names none takes
+ * the 128 x 128 tile); 10 = the 128 x 128 tile with K split across workgroups as far as parts of six 64-wide k-tiles go;
+ * 100 s + v = tile v with K in s parts.
  * K % 64 == 0 and N % 4 == 0 are required.
  */
 drf_status drf_probe_gemm_bf16(const void* A, const void* W, int M, int N, int K, void* out_bf16, const float* bias,

@@ -93,6 +93,16 @@ def test_gemm_bf16_rows_in_two_launches(torch, drf, M, N, K):
     assert torch.equal(out, drf.probe_gemm_bf16(A, W, b, variant=1))
 
 
+@pytest.mark.parametrize("variant", [-1, 15, 99, 100])
+def test_gemm_bf16_number_that_names_no_tile(torch, drf, variant):
+    """Taken by the 128 x 128 tile, as such numbers always were by a general one."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randn((130, 192), generator=g, device="cuda").bfloat16()
+    W = (torch.randn((100, 192), generator=g, device="cuda") * 0.1).bfloat16()
+    b = torch.randn((100,), generator=g, device="cuda")
+    assert torch.equal(drf.probe_gemm_bf16(A, W, b, variant=variant), drf.probe_gemm_bf16(A, W, b, variant=5))
+
+
 def test_gemm_bf16_rejects_bad_k(torch, drf):
     A = torch.zeros((64, 72), dtype=torch.bfloat16, device="cuda")
     W = torch.zeros((64, 72), dtype=torch.bfloat16, device="cuda")
