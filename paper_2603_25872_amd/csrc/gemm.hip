@@ -795,6 +795,7 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
     if (e.mode == EPI_STORE_HEADS && (e.out_f32 || e.hd % 8 != 0 || e.hid % 16 != 0 || N % e.hid != 0))
         DRF_FAIL(DRF_ESHAPE, "head-major store needs bf16 output, head width %% 8 == 0 and hidden %% 16 == 0");
     if (e.mode == EPI_STORE_GATED && (e.out_f32 || !e.gate)) DRF_FAIL(DRF_ESHAPE, "gated store needs bf16 output and a gate");
+    if (e.mode == EPI_STORE_SILU) DRF_FAIL(DRF_ESHAPE, "the SiLU store is an epilogue of the fp32 GEMM");
     if ((size_t)M * K >= ((size_t)1 << 31) || (size_t)N * K >= ((size_t)1 << 31))
         DRF_FAIL(DRF_ESHAPE, "bf16 GEMM operand exceeds 2^31 elements");
     int v = variant, splits = 1, va = 0, rows_a = 0;

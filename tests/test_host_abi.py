@@ -205,3 +205,13 @@ def test_wide_heads_share_kv_between_two_query_blocks_from_the_second_round_on(d
     route = drf.probe_attn_route
     assert route(64, 128, 256, 4, d) == route(16, 128, 200, 16, d) == (2 if d > 80 else 1)
     assert route(64, 96, 256, 4, d) == 1 and route(8, 128, 256, 4, d) == 1
+
+
+def test_bf16_gemm_refuses_the_fp32_paths_activation():
+    """SiLU is an epilogue of the fp32 GEMM only: the bf16 launch must say so (checked on the host, before anything else is looked
+    at) instead of storing without it."""
+    launch = drf.lib()._ZN3drf16launch_gemm_bf16EPKDF16bS1_iiiRKNS_8EpilogueEP12ihipStream_tiPfPNS_10PartialSumE
+    launch.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_void_p]
+    epilogue = (C.c_int * 128)(5)                # Epilogue starts with its mode: EPI_STORE_SILU
+    assert launch(None, None, 64, 64, 64, epilogue, None, 0, None, None) == -2
+    assert b"SiLU" in drf.lib().drf_last_error()
