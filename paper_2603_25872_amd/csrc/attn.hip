@@ -522,14 +522,21 @@ drf_status launch_bf16_inst(const AttnArgs& a, AttnRoute route, float scale_log2
     }
 }
 
-// Workgroups (256 queries each) from which the kernel for long sequences is the faster one, by head width / 8, for queries
-// that come scaled and for others; 0: never.  Against the 8-wave chunked kernel, 300 to 2048 rows, 8 to 4096 workgroups:
+// Workgroups (256 queries each) from which the kernel for long sequences is the faster one, by head width / 8; 0: never.
+// Against the 8-wave chunked kernel, 264 to 2048 rows, 8 to 4096 workgroups:
 //  - up to 256 of them, one to a CU, it has one wave per SIMD and nothing runs beside a wave's softmax.  Where the head width
-//    leaves spare columns for the reference score it wins all the same (72: 1.08-1.17x scaled, 1.03-1.10x not); at 16, 32
-//    and 64 it loses (64 scaled: 0.89x at 2048 rows, 31.6 against 25.3 us for 4 slots x 1024 rows x 6 heads unscaled);
+//    leaves spare columns for the reference score it wins all the same (72: 1.05-1.17x scaled, 1.01-1.12x not); at 16, 32
+//    and 64 it loses (64 scaled: 0.89x at 2048 rows; 31.6 against 25.3 us for 4 slots x 1024 rows x 6 heads unscaled);
 //  - from the second workgroup of a CU on it wins at every width up to 80 (64: 1.2-1.6x scaled), unscaled later at 16 and 32;
-//  - at 88 and 96 its registers do not suffice and it loses at most sizes (96: 81 against 35 us for 4 slots x 1024 rows x 12).
-constexpr int kLongFrom[2][12] = { { 257, 1024, 257, 768, 257, 257, 1, 257, 1, 257, 0, 0 }, { 1, 257, 1, 257, 1, 1, 1, 257, 1, 1, 0, 0 } };
+//  - at 88 and 96 its registers do not suffice and it loses at most sizes (96: 81 against 35 us for 4 slots x 1024 rows x 12);
+//  - up to 352 rows, a third chunk of at most 96, it is 5 to 10 % better off than beyond.
+constexpr int kLongFewRows = 352;
+constexpr int kLongFrom[2][2][12] = {
+    { { 257, 1024, 257, 768, 257, 257, 1, 257, 1, 257, 0, 0 },         // more rows: queries as they are
+      { 1, 257, 1, 257, 1, 1, 1, 257, 1, 1, 0, 0 } },                   //            queries scaled
+    { { 1, 257, 1, 768, 1, 1, 1, 257, 1, 1, 257, 0 },                   // up to kLongFewRows
+      { 1, 1, 1, 257, 1, 1, 1, 257, 1, 1, 257, 0 } },
+};
 
 }  // namespace
 
@@ -547,7 +554,7 @@ AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled)
     if (Nk > 256) {
         if (Nq <= 128) return ATTN_CHUNKED_FEW;
         const long long groups = (long long)((Nq + 255) / 256) * heads * slots;
-        const int from = kLongFrom[q_scaled ? 1 : 0][d / 8 - 1];
+        const int from = kLongFrom[Nk <= kLongFewRows][q_scaled ? 1 : 0][d / 8 - 1];
         return from && groups >= from ? ATTN_LONG : ATTN_CHUNKED_LONG;
     }
     const long long items = (long long)((Nq + 31) / 32) * heads * slots;

@@ -433,7 +433,8 @@ template <bool PRE> drf_status launch_width(const AttnArgs& a, hipStream_t st)
     case 8: return launch_inst<8, PRE>(a, st);
     case 9: return launch_inst<9, PRE>(a, st);
     case 10: return launch_inst<10, PRE>(a, st);
-    default: DRF_FAIL(DRF_ESHAPE, "attention with 64 queries per wave: head dim <= 80 (got %d)", a.d);
+    case 11: return launch_inst<11, PRE>(a, st);
+    default: DRF_FAIL(DRF_ESHAPE, "attention with 64 queries per wave: head dim <= 88 (got %d)", a.d);
     }
 }
 

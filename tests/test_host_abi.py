@@ -187,6 +187,13 @@ def test_long_attention_goes_to_the_kernel_that_measured_faster(d, scaled):
         assert (few, full) == (7, 7)
 
 
+@pytest.mark.parametrize("d", range(8, 97, 8))
+def test_long_attention_of_a_few_rows_more_than_256(d):
+    """Up to 352 rows the chunked kernel fills its third chunk of 128 in part and keeps fewer widths."""
+    few, many = drf.probe_attn_route(2, 300, 300, 4, d, 0), drf.probe_attn_route(64, 300, 300, 8, d, 0)
+    assert few == (5 if d in (16, 32, 64, 88, 96) else 7) and many == (7 if d <= 88 else 5)
+
+
 def test_attention_routes_by_rows():
     route = drf.probe_attn_route
     for d in range(8, 97, 8):
