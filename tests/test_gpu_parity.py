@@ -204,6 +204,22 @@ def test_bf16_thin_pass_branch_outputs_left_as_partial_tiles(torch, drf, orc, hi
     check_forward(torch, drf, orc, dit, "loud", slots=3, tol=TOL_BF16, seed=80 + heads)
 
 
+@pytest.mark.parametrize("lat", [(10, 6), (24, 24)])
+def test_bf16_text_context_of_300_rows(torch, drf, orc, lat):
+    # 15 and 144 queries over 300 kv rows: the chunked kernel's forms with four and with eight waves
+    dit = small_dit(I.COND_TEXT, I.BF16, lat_h=lat[0], lat_w=lat[1], ctx_len=300)
+    check_forward(torch, drf, orc, dit, "loud", slots=3, tol=TOL_BF16, seed=90 + lat[0])
+
+
+@pytest.mark.parametrize("hidden,heads,slots", [(64, 8, 2), (192, 8, 2), (320, 8, 2), (384, 8, 1), (448, 8, 1), (576, 8, 2), (640, 8, 1), (1152, 16, 1),
+                                                (128, 8, 17), (256, 8, 17)])
+def test_bf16_long_self_attention_with_scaled_queries(torch, drf, orc, hidden, heads, slots):
+    """272 tokens at head widths 8 to 80: the projection stores q multiplied by log2(e) / sqrt(d), whole and split GEMMs."""
+    dit = small_dit(I.COND_CLASS, I.BF16, hidden=hidden, heads=heads, depth=1, lat_h=32, lat_w=34)
+    assert drf.probe_attn_route(slots, 272, 272, heads, hidden // heads, 1) == 7
+    check_forward(torch, drf, orc, dit, "loud", slots=slots, tol=TOL_BF16, seed=100 + heads, trace=slots < 17)
+
+
 def test_bf16_text_cross_attention_77(torch, drf, orc):
     dit = small_dit(I.COND_TEXT, I.BF16, hidden=576, heads=8, lat_h=12, lat_w=12, depth=2, cond_dim=128, ctx_len=77)
     check_forward(torch, drf, orc, dit, "loud", slots=2, tol=TOL_BF16, seed=31)
