@@ -1,5 +1,6 @@
 // Multi-head attention softmax(q k^T / sqrt(d)) v without mask.
-// bf16 path: flash-style, one wave per 32 queries, scores computed transposed
+// Which bf16 kernel takes a launch (attn_route; the ones for short and for long sequences are in attn_short.hip and
+// attn_long.hip), and the chunked one: flash-style, one wave per 32 queries, scores computed transposed
 // (S^T = K Q^T) so that each lane owns one query column and the online softmax needs a
 // single cross-lane exchange; P^T feeds the second MFMA straight from registers.
 // fp32 path: fp32 MFMA, kv rows split over the waves of a workgroup.

@@ -687,7 +687,8 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
 // steps the k-steps of 64 * wk; a split adds red0 + red1 per million partial elements for the reduction launch.
 // The constants are least-squares fits to timings of every tile on 107 shapes (M 2 .. 65536, N 384 .. 195840, K 384 ..
 // 4608, weights cold); the tile that the model picks is 0.8 % slower than the fastest of all on average and 14 % at
-// worst.  Small problems live on small tiles: with weights coming from HBM a launch is a chain of round trips, and what
+// worst, on those shapes and back to back (inside a pass launches take longer: 53 against 43 modelled us for the four of a
+// 512-row block of hidden 1152).  Small problems live on small tiles: with weights coming from HBM a launch is a chain of round trips, and what
 // counts is how many of the chip's CUs pull operands at once (M = 512, N = K = 1152: 13.2 us on 36 128 x 128 tiles,
 // 7.0 us on 144 64 x 64 tiles whose two wave groups split K; N = 3456: 15.5 -> 11.2 us on 128 x 64; M = 2048, N = 3456:
 // 32.5 -> 23.9 us with two 128 x 128 workgroups per CU; M = 12288, N = 1536, K = 384: 31.9 -> 22.9 us likewise).
@@ -744,7 +745,8 @@ drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, in
 
 // A problem that fills some rounds of a tile and part of another runs as two launches where that is modelled at least 5 %
 // faster: the rows of the full rounds with that tile, the rest with whatever suits it (24576 x 1152: 1.5 rounds of 256 x 288
-// tiles, or one of them and one of 256 x 144: 232 -> ~217 us at K = 4608; a call of 4096-token slots 430.1 -> 421.7 ms).  Returns the rows of the first launch, 0 for one launch.
+// tiles, or one of them and one of 256 x 144: 232 -> ~217 us at K = 4608; a call of 4096-token slots 430.1 -> 421.7 ms).
+// Returns the rows of the first launch, 0 for one launch.
 int pick_row_split(int M, int N, int K, double one_us, int* id_a, int* id_b)
 {
     double best = 0.95 * one_us;
