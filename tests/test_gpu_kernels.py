@@ -189,6 +189,26 @@ def test_config3_pass_at_benchmark_size_sampled_slots(torch, drf, orc):
         assert err < 2e-2, (j, err)
 
 
+@pytest.mark.parametrize("slots,seam", [(34, 33), (23, 21)])
+def test_pass_whose_gemms_run_in_two_launches_sampled_slots(torch, drf, orc, slots, seam):
+    """247-token slots, no multiple of any tile: out-projection, fc1 and fc2 (34 slots) or QKV (23) run as full rounds of one tile and
+    the remaining rows with another, whose first row lies inside slot `seam`: gates, head-major planes and GELU across it."""
+    dit = dict(I.CONFIGS[3]["dit"], depth=2, lat_h=26, lat_w=38)
+    w = I.weights(dit, 3, "loud")
+    den = drf.Denoiser(dit, w)
+    rng = np.random.default_rng(slots)
+    x = rng.standard_normal((slots, 4, 26, 38)).astype(np.float32)
+    t = rng.integers(0, 1000, size=slots).astype(np.int32)
+    cls = I.conditioning(dit, slots, 3)
+    got = den.eps_batched(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda(), torch.from_numpy(cls).cuda()).cpu().numpy()
+    den.close()
+    wd = orc.prepare_weights(w)
+    for j in (0, seam - 1, seam, slots - 1):
+        want = orc.dit_eps(dit, wd, x[j:j + 1], t[j:j + 1], cls[j:j + 1])[0]
+        err = np.abs(got[j] - want).max() / np.abs(want).max()
+        assert err < 2e-2, (j, err)
+
+
 @pytest.mark.parametrize("g,n_chain,n_draft", [(2, 4, 4), (1, 3, 0), (2, 0, 4), (1, 1, 1)])
 def test_fused_update_probe_equals_its_parts(torch, drf, orc, g, n_chain, n_draft):
     """The measurement hook that launches the fused guidance + chain + draft update once, against the same steps
