@@ -136,6 +136,10 @@ struct PartialSum { const float* part; int splits, ldp; size_t stride; };
 // leave != NULL: a launch that splits leaves its partial tiles for the caller (in splitk_scratch, the epilogue not applied).
 drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
                             int variant = 0, float* splitk_scratch = nullptr, PartialSum* leave = nullptr);
+// The 256-row tiles of 288 and of 256 columns on rows m_first .. M - 1; called by launch_gemm_bf16, which checks the shapes
+// (no GELU with fp32 output).
+drf_status launch_gemm_wide_288(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first);
+drf_status launch_gemm_wide_256(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first);
 size_t gemm_splitk_scratch_bytes();
 // fp32; a_row_mod: row m of C uses row m % a_row_mod of A (0: row m).
 drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int a_row_mod = 0);

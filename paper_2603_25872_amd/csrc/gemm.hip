@@ -2,41 +2,11 @@
 // residual).  bf16 path: one software-pipelined kernel (16x16x32 MFMAs, operands by LDS-DMA, fp32
 // accumulate) at tiles from 32 x 64 to 256 x 288, the tile chosen by a measured time model.
 // fp32 path: fp32 MFMA, operands straight to registers, K split over the waves of a workgroup.
-#include <type_traits>
-
-#include "common.h"
+#include "gemm_device.h"
 
 namespace drf {
 
 namespace {
-
-typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
-typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
-
-// GELU (tanh form): 0.5 x (1 + tanh(u)) = x * sigmoid(2u), u = sqrt(2/pi) (x + 0.044715 x^3).
-// One exp2 and one reciprocal (both hardware transcendental ops, ~1 ulp).
-__device__ inline float gelu_tanh(float x)
-{
-    const float t = x * x;
-    const float m2u_log2e = x * fmaf(t, -0.1029432f, -2.3022082f);   // -2 u log2(e)
-    return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(m2u_log2e));
-}
-
-// floor(n / d) for 0 <= n < 2^31 with a host-made magic number (d >= 1).
-__device__ inline int fast_div(int n, uint32_t magic, int shift)
-{
-    return magic ? (int)(__umulhi((uint32_t)n, magic) >> shift) : (n >> shift);
-}
-
-// Element offset of (row m, column n) in the head-major q | k | v planes (n is a multiple of 4 or 8
-// and the head width a multiple of 8, so a vector never straddles a head).
-__device__ inline size_t heads_offset(const Epilogue& e, int m, int n)
-{
-    const int which = fast_div(n, e.hid_magic, e.hid_shift), c = n - which * e.hid;
-    const int head = fast_div(c, e.hd_magic, e.hd_shift), dd = c - head * e.hd;
-    const int slot = fast_div(m, e.rps_magic, e.rps_shift), t = m - slot * e.rows_per_slot;
-    return (size_t)which * e.plane + ((size_t)(slot * e.heads + head) * e.rows_per_slot + t) * e.hd + dd;
-}
 
 // Applies the epilogue to 4 consecutive columns n..n+3 of row m (n % 4 == 0, n + 3 < N).
 __device__ inline void epilogue4(const Epilogue& e, int m, int n, float v0, float v1, float v2, float v3)
@@ -72,36 +42,6 @@ __device__ inline void epilogue4(const Epilogue& e, int m, int n, float v0, floa
 }
 
 // ------------------------------------------------------------------ bf16 MFMA
-#define DRF_GLOBAL_AS __attribute__((address_space(1)))
-#define DRF_LDS_AS __attribute__((address_space(3)))
-template <int N> __device__ inline void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-template <int N> __device__ inline void wait_lgkmcnt() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory"); }
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-// 16 bytes per lane from LDS byte address addr + OFF, asynchronously: dst is valid only after an
-// s_waitcnt lgkmcnt that covers it.
-template <int OFF> __device__ inline void lds_read16(u32x4& dst, uint32_t addr)
-{
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
-}
-// Waits until at most N LDS reads are outstanding.  The fragments that the following MFMAs consume
-// pass through the statement as in/out operands, so no use of them can be scheduled above the wait.
-template <int N> __device__ inline void wait_frag(u32x4& w) { asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(w) : "n"(N)); }
-// Keeps a fragment's registers its own up to this point.
-__device__ inline void hold_frag(u32x4& w) { asm volatile("" : "+v"(w)); }
-template <int N, int MI> __device__ inline void wait_frags(u32x4& w, u32x4 (&a)[MI])
-{
-    static_assert(MI == 2 || MI == 4, "activation fragments per k-step");
-    if constexpr (MI == 2) asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(w), "+v"(a[0]), "+v"(a[1]) : "n"(N));
-    else asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(w), "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]) : "n"(N));
-}
-template <int I, int N, typename F> __device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
 // The kernel for all of the DiT's GEMMs.  BM x BN x 64 block tile (256 x 288 for hidden
 // 1152: 1152, 3456 and 4608 are all multiples of 288, so at 64 row tiles every GEMM of the
 // block is a whole number of 256-tile rounds), 8 waves as WM x WN, wave tile (BM/WM) x
@@ -119,7 +59,6 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
 //  - epilogue: each wave transposes its accumulators through its own slice of the (now
 //    idle) LDS stages and then touches global memory in whole rows: 16 bytes per lane,
 //    consecutive lanes on consecutive addresses.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 // copy instructions issued per MFMA group by the in-loop copy of the two-stage kernels (1: measured best; 2, 3 and
 // the whole copy at once are 0.8 % slower per call, one every other group lands too late: 3 % slower)
 constexpr int kSpreadPer = 1;
@@ -132,7 +71,7 @@ constexpr size_t kSplitKScratchFloats = (size_t)256 * 128 * 128;
 //    so no bounds are needed); splitk_reduce_kernel adds the partial tiles in a fixed order and applies the epilogue.
 struct SplitK { int splits, tiles_n; float* part; };
 
-template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1, bool SK = false>
+template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1, bool SK = false, bool RS = false>
 __global__ void __launch_bounds__(WM * WN * WK * 64)
 gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N, int K, const Epilogue e,
                     int tiles_m, int tiles_n, int m_first, const SplitK sk)
@@ -147,7 +86,6 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
     constexpr int GROUP_M = 8;
     static_assert(TM % 16 == 0 && TN % 16 == 0 && (BM + BN) % RPI == 0 && BM % 16 == 0, "tile shape");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    bf16_t* smem = reinterpret_cast<bf16_t*>(smem_raw);
 
     const int nb = tiles_m * tiles_n, b = blockIdx.x;
     const int xcd = b & 7, local = b >> 3, q = nb >> 3, rem = nb & 7;
@@ -273,24 +211,17 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
     };
 
     // tiles 0 .. NS-2 are in flight before the loop; tile kt + NS - 1 is requested once tile kt - 1 has been read
+    const GateRows gr = gate_rows<BM>(e, m0, M);
+    if constexpr (!SK) stage_epilogue_rows<BN>(e, gr, lds_base + NS * STAGE * 2, wave, NW, n0, N);
     issue(0, 0);
-    // Gated store, all rows of the tile in one slot (the slot length is a multiple of BM): the tile's BN gate
-    // values go to LDS behind the stages, once, and the epilogue reads them from there.  Read from global memory
-    // in the epilogue they would be loaded per 16 x 16 piece, each load waited for on the spot (and, from the
-    // second transposition pass on, behind the stores of the pass before: loads and stores share a counter).
-    const bool gate_lds = e.mode == EPI_STORE_GATED && e.rows_per_slot % BM == 0;
-    float* sgate = reinterpret_cast<float*>(smem_raw + NS * STAGE * 2);
-    if (gate_lds && tid < BN / 4) {
-        const int n = n0 + tid * 4;
-        const float4 gv = *reinterpret_cast<const float4*>(e.gate + (size_t)fast_div(m0, e.rps_magic, e.rps_shift) * e.gate_ld + (n < N ? n : 0));
-        *reinterpret_cast<float4*>(sgate + tid * 4) = gv;   // (the compiler waits for every load before this write:
-    }                                                       //  the later stages are requested only now)
 #pragma unroll
     for (int t = 1; t < NS - 1; ++t)
         if (t < nk) issue(t, t);
     if (NS > 2 && nk >= NS - 1) wait_vmcnt<LPT * (NS - 2)>(); else wait_vmcnt<0>();
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     asm volatile("" ::"v"(warm_val));
+    static_for<0, NI * MI>([&](auto pc) { constexpr int p = decltype(pc)::value; hold_acc<false>(acc[p / MI][p % MI]); });
+    settle_mfma();
     if (NS - 1 < nk) issue(NS - 1, NS - 1);
     static_for<0, D>([&](auto pc) { fetch(pc, a_addr, w_addr); });
     int cs = 0;                                     // stage of tile kt
@@ -336,9 +267,7 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
                 else wait_frag<later>(fw[g % R]);
                 static_for<0, MI>([&](auto jc) {
                     constexpr int j = (g & 1) ? MI - 1 - decltype(jc)::value : decltype(jc)::value;   // snake: one operand changes per MFMA
-                    acc[g % NI][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fw[g % R]),
-                                                                             __builtin_bit_cast(bf16x8, fa[(g / NI) & 1][j]),
-                                                                             acc[g % NI][j], 0, 0, 0);
+                    mfma<false>(acc[g % NI][j], fw[g % R], fa[(g / NI) & 1][j]);
                 });
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -349,16 +278,18 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
     // any more: they pass through the wait, so that no register of theirs is given to anything computed above it
     // (a column index kept there would be overwritten by the data that lands).
     wait_frag<0>(fw[0]);
+    settle_mfma();
+    static_for<0, NI * MI>([&](auto pc) { constexpr int p = decltype(pc)::value; hold_acc<false>(acc[p / MI][p % MI]); });
 #pragma unroll
     for (int r = 1; r < R; ++r) hold_frag(fw[r]);
 #pragma unroll
     for (int j = 0; j < MI; ++j) { hold_frag(fa[0][j]); hold_frag(fa[1][j]); }
 
-    // ---- epilogue through LDS: acc[i][j][r] is (m = j*16 + l16, n = i*16 + 4*quarter + r) of the wave tile
-    __syncthreads();
+    // ---- epilogue: acc[i][j][r] is (m = j*16 + l16, n = i*16 + 4*quarter + r) of the wave tile
     constexpr int PART = (WK - 1) * NWT * TM * TN * 4;              // partial sums of the other K groups
     if constexpr (WK > 1) {
         static_assert(PART < NS * STAGE * 2, "LDS too small for the split-K partial sums");
+        __syncthreads();                                            // the stages are idle
         f32x4* part = reinterpret_cast<f32x4*>(smem_raw);
         if (wk > 0) {
 #pragma unroll
@@ -385,153 +316,21 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
                 *reinterpret_cast<f32x4*>(pt + (size_t)(j * 16 + l16) * ((size_t)sk.tiles_n * BN) + i * 16 + 4 * quarter) = acc[i][j];
         return;
     }
-    constexpr int WBYTES = (NS * STAGE * 2 - PART) / NWT / 16 * 16; // this wave's private slice of the stages
-    unsigned char* wbuf = smem_raw + PART + wl * WBYTES;
-    const int mw = m0 + wm * TM, nw = n0 + wn * TN;
-    // bias of this lane's columns, fetched in one batch (kept in registers: reading it from LDS per 16 x 16 piece
-    // like the gate was measured 1 % slower per call)
-    float4 bb[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int n = nw + i * 16 + 4 * quarter;
-        bb[i] = *reinterpret_cast<const float4*>(e.bias + (n < N ? n : 0));
+    if constexpr (RS) {
+        if (may_store_rows<BM, BN>(e, m0, n0, M, N, gr)) {
+            static_assert(PART + NWT * rows_tile_bytes(TM, TN) <= NS * STAGE * 2, "LDS too small for the waves' tiles in rows");
+            if constexpr (WK == 1) asm volatile("s_barrier" ::: "memory");      // every wave has read its last fragments
+            const int mw = m0 + wm * TM, nw = n0 + wn * TN;
+            unsigned char* wbuf = smem_raw + PART + wl * rows_tile_bytes(TM, TN);
+            const unsigned char* erows = smem_raw + NS * STAGE * 2 + wn * TN * 4;
+            if (e.mode == EPI_STORE_GELU) store_rows<TM, TN, EPI_STORE_GELU, 0>(acc, e, mw, nw, wbuf, erows, 0);
+            else if (e.mode == EPI_STORE_HEADS) store_rows<TM, TN, EPI_STORE_HEADS, 0>(acc, e, mw, nw, wbuf, erows, 0);
+            else if (e.mode == EPI_STORE_GATED) store_rows<TM, TN, EPI_STORE_GATED, 1>(acc, e, mw, nw, wbuf, erows, epi_row_bytes(BN));
+            else store_rows<TM, TN, EPI_STORE, 0>(acc, e, mw, nw, wbuf, erows, 0);
+            return;
+        }
     }
-    if (e.mode == EPI_RESID || e.out_f32) {
-        constexpr int ROWB = TN * 4 + ((TN * 4) % 128 == 0 ? 16 : 0);
-        constexpr int RPP = (WBYTES / ROWB) / 16 * 16 < TM ? (WBYTES / ROWB) / 16 * 16 : TM;   // rows per pass
-        static_assert(RPP >= 16, "LDS slice too small for the fp32 epilogue");
-        constexpr int CH = TN / 4, IT = (RPP * CH + 63) / 64;       // float4 chunks per row, chunks per lane and pass
-        auto run = [&](auto mode_c) {
-            constexpr int MODE = decltype(mode_c)::value;
-#pragma unroll
-            for (int j0 = 0; j0 < MI; j0 += RPP / 16) {
-#pragma unroll
-                for (int jj = 0; jj < RPP / 16; ++jj) {
-                    const int j = j0 + jj;
-                    if (j < MI) {
-#pragma unroll
-                        for (int i = 0; i < NI; ++i) {
-                            float4 v = make_float4(acc[i][j][0] + bb[i].x, acc[i][j][1] + bb[i].y, acc[i][j][2] + bb[i].z,
-                                                   acc[i][j][3] + bb[i].w);
-                            if (MODE == EPI_STORE_GELU) { v.x = gelu_tanh(v.x); v.y = gelu_tanh(v.y); v.z = gelu_tanh(v.z); v.w = gelu_tanh(v.w); }
-                            *reinterpret_cast<float4*>(wbuf + (jj * 16 + l16) * ROWB + (i * 16 + 4 * quarter) * 4) = v;
-                        }
-                    }
-                }
-                // rows back out, kBatch chunks per lane at a time: their loads are all issued before
-                // the first dependent store
-                constexpr int kBatch = 3;
-#pragma unroll
-                for (int it0 = 0; it0 < IT; it0 += kBatch) {
-                    float4 vv[kBatch], xx[kBatch], gg[kBatch];
-                    bool ok[kBatch];
-#pragma unroll
-                    for (int u = 0; u < kBatch; ++u) {
-                        const int id = lane + (it0 + u) * 64, rl = id / CH, c = id % CH;
-                        const int m = mw + j0 * 16 + rl, n = nw + c * 4;
-                        ok[u] = it0 + u < IT && id < RPP * CH && j0 * 16 + rl < TM && m < M && n < N;
-                        if (ok[u]) {
-                            vv[u] = *reinterpret_cast<const float4*>(wbuf + rl * ROWB + c * 16);
-                            if (MODE == EPI_RESID) {
-                                xx[u] = *reinterpret_cast<const float4*>((const float*)e.out + (size_t)m * e.ldo + n);
-                                gg[u] = e.gate ? *reinterpret_cast<const float4*>(e.gate + (size_t)fast_div(m, e.rps_magic, e.rps_shift) * e.gate_ld + n)
-                                               : make_float4(1.f, 1.f, 1.f, 1.f);
-                            }
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < kBatch; ++u) {
-                        const int id = lane + (it0 + u) * 64, rl = id / CH, c = id % CH;
-                        const int m = mw + j0 * 16 + rl, n = nw + c * 4;
-                        if (ok[u]) {
-                            float4 o = vv[u];
-                            if (MODE == EPI_RESID) {
-                                o.x = fmaf(gg[u].x, vv[u].x, xx[u].x); o.y = fmaf(gg[u].y, vv[u].y, xx[u].y);
-                                o.z = fmaf(gg[u].z, vv[u].z, xx[u].z); o.w = fmaf(gg[u].w, vv[u].w, xx[u].w);
-                            }
-                            *reinterpret_cast<float4*>((float*)e.out + (size_t)m * e.ldo + n) = o;
-                        }
-                    }
-                }
-            }
-        };
-        if (e.mode == EPI_RESID) run(std::integral_constant<int, EPI_RESID>{});
-        else if (e.mode == EPI_STORE_GELU) run(std::integral_constant<int, EPI_STORE_GELU>{});
-        else run(std::integral_constant<int, EPI_STORE>{});
-    } else {
-        constexpr int ROWB = TN * 2 + ((TN * 2) % 128 == 0 ? 16 : 0);
-        constexpr int RPP = (WBYTES / ROWB) / 16 * 16 < TM ? (WBYTES / ROWB) / 16 * 16 : TM;
-        static_assert(RPP >= 16, "LDS slice too small for the bf16 epilogue");
-        constexpr int CH = TN / 8, IT = (RPP * CH + 63) / 64;       // 16-byte chunks per row, chunks per lane and pass
-        auto run = [&](auto mode_c, auto gate_lds_c) {
-            constexpr int MODE = decltype(mode_c)::value;
-            constexpr bool GLDS = decltype(gate_lds_c)::value;
-#pragma unroll
-            for (int j0 = 0; j0 < MI; j0 += RPP / 16) {
-#pragma unroll
-                for (int jj = 0; jj < RPP / 16; ++jj) {
-                    const int j = j0 + jj;
-                    if (j < MI) {
-                        // EPI_STORE_GATED: the gate row of this lane's output row (rows past M use the last one)
-                        const float* grow = nullptr;
-                        if constexpr (MODE == EPI_STORE_GATED && !GLDS) {
-                            const int mr = mw + j * 16 + l16;
-                            grow = e.gate + (size_t)fast_div(mr < M ? mr : M - 1, e.rps_magic, e.rps_shift) * e.gate_ld;
-                        }
-#pragma unroll
-                        for (int i = 0; i < NI; ++i) {
-                            float v0 = acc[i][j][0] + bb[i].x, v1 = acc[i][j][1] + bb[i].y, v2 = acc[i][j][2] + bb[i].z, v3 = acc[i][j][3] + bb[i].w;
-                            if (MODE == EPI_STORE_GELU) { v0 = gelu_tanh(v0); v1 = gelu_tanh(v1); v2 = gelu_tanh(v2); v3 = gelu_tanh(v3); }
-                            if constexpr (MODE == EPI_STORE_HEADS) {
-                                const float qs = nw + i * 16 < e.hid ? e.q_scale : 1.f;       // hid is a multiple of 16
-                                v0 *= qs; v1 *= qs; v2 *= qs; v3 *= qs;
-                            }
-                            if constexpr (MODE == EPI_STORE_GATED) {
-                                float4 g;
-                                if constexpr (GLDS) {
-                                    g = *reinterpret_cast<const float4*>(sgate + wn * TN + i * 16 + 4 * quarter);
-                                } else {
-                                    const int ng = nw + i * 16 + 4 * quarter;
-                                    g = *reinterpret_cast<const float4*>(grow + (ng < N ? ng : 0));
-                                }
-                                v0 *= g.x; v1 *= g.y; v2 *= g.z; v3 *= g.w;
-                            }
-                            bf16x4 o = { (bf16_t)v0, (bf16_t)v1, (bf16_t)v2, (bf16_t)v3 };
-                            *reinterpret_cast<bf16x4*>(wbuf + (jj * 16 + l16) * ROWB + (i * 16 + 4 * quarter) * 2) = o;
-                        }
-                    }
-                }
-                // rows back out: all of a pass's LDS reads first (reading is harmless where nothing is stored), then the stores
-                constexpr int kRB = 4;                                  // LDS reads in flight before their stores
-#pragma unroll
-                for (int it0 = 0; it0 < IT; it0 += kRB) {
-                    bf16x8 rv[kRB];
-#pragma unroll
-                    for (int u = 0; u < kRB; ++u) {
-                        const int id = lane + (it0 + u) * 64, idc = id < RPP * CH ? id : RPP * CH - 1;
-                        if (it0 + u < IT) rv[u] = *reinterpret_cast<const bf16x8*>(wbuf + (idc / CH) * ROWB + (idc % CH) * 16);
-                    }
-#pragma unroll
-                    for (int u = 0; u < kRB; ++u) {
-                        const int id = lane + (it0 + u) * 64, rl = id / CH, c = id % CH;
-                        const int m = mw + j0 * 16 + rl, n = nw + c * 8;
-                        if (it0 + u < IT && id < RPP * CH && j0 * 16 + rl < TM && m < M && n < N) {
-                            const size_t off = MODE == EPI_STORE_HEADS ? heads_offset(e, m, n) : (size_t)m * e.ldo + n;
-                            if (n + 8 <= N)
-                                *reinterpret_cast<bf16x8*>((bf16_t*)e.out + off) = rv[u];
-                            else            // N is a multiple of 4: the last chunk of a row may be half valid
-                                *reinterpret_cast<bf16x4*>((bf16_t*)e.out + off) = __builtin_shufflevector(rv[u], rv[u], 0, 1, 2, 3);
-                        }
-                    }
-                }
-            }
-        };
-        if (e.mode == EPI_STORE_GELU) run(std::integral_constant<int, EPI_STORE_GELU>{}, std::false_type{});
-        else if (e.mode == EPI_STORE_HEADS) run(std::integral_constant<int, EPI_STORE_HEADS>{}, std::false_type{});
-        else if (e.mode == EPI_STORE_GATED && gate_lds) run(std::integral_constant<int, EPI_STORE_GATED>{}, std::true_type{});
-        else if (e.mode == EPI_STORE_GATED) run(std::integral_constant<int, EPI_STORE_GATED>{}, std::false_type{});
-        else run(std::integral_constant<int, EPI_STORE>{}, std::false_type{});
-    }
+    store_tile<TM, TN>(acc, e, m0 + wm * TM, n0 + wn * TN, M, N, smem_raw + NS * STAGE * 2 + wn * TN * 4, epi_row_bytes(BN), gr);
 }
 
 // Sum of the split-K partial tiles (fixed order: deterministic), then the epilogue; one thread per 4 columns.
@@ -633,13 +432,13 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M,
     }
 }
 
-template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1>
+template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1, bool RS = false>
 drf_status launch_bf16_xl(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first = 0)
 {
-    constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + BN * sizeof(float);   // stages + gate row
+    constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + epi_lds_bytes(BN);
     static_assert(smem <= 160 * 1024, "LDS of a CU");
     static bool attr_set = false;
-    auto kern = gemm_bf16_xl_kernel<BM, BN, BK, NS, WM, WN, WK>;
+    auto kern = gemm_bf16_xl_kernel<BM, BN, BK, NS, WM, WN, WK, false, RS>;
     if (K % (BK * WK) != 0) DRF_FAIL(DRF_ESHAPE, "bf16 GEMM tile needs K %% %d == 0 (K=%d)", BK * WK, K);
     if (!attr_set) {
         DRF_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
@@ -656,7 +455,7 @@ template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1>
 drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
                               int splits, float* part, PartialSum* leave)
 {
-    constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + BN * sizeof(float);
+    constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + epi_lds_bytes(BN);
     static_assert(smem <= 160 * 1024, "LDS of a CU");
     static bool attr_set = false;
     auto kern = gemm_bf16_xl_kernel<BM, BN, BK, NS, WM, WN, WK, true>;
@@ -726,19 +525,20 @@ double model_us(const TileModel& t, int M, int N, int K, int splits, bool leave)
 // Rows m_first .. M - 1 of the problem with tile v (m_first a multiple of the tile's height).
 drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first)
 {
+    if (e.mode == EPI_STORE_GELU && e.out_f32 && (v == 2 || v == 3)) v = 14;      // (the 4-wave tiles have no such store)
     switch (v) {
     case 1: return launch_bf16_xl<64, 64, 64, 4, 2, 2>(A, W, M, N, K, e, st, m_first);
-    case 2: return launch_bf16_xl<256, 288, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
-    case 3: return launch_bf16_xl<256, 256, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
-    case 4: return launch_bf16_xl<128, 128, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 2: return launch_gemm_wide_288(A, W, M, N, K, e, st, m_first);
+    case 3: return launch_gemm_wide_256(A, W, M, N, K, e, st, m_first);
+    case 4: return launch_bf16_xl<128, 128, 64, 2, 4, 2, 1, true>(A, W, M, N, K, e, st, m_first);
     case 6: return launch_bf16_xl<128, 64, 64, 4, 4, 2>(A, W, M, N, K, e, st, m_first);
     case 7: return launch_bf16_xl<128, 96, 64, 3, 4, 1>(A, W, M, N, K, e, st, m_first);
-    case 8: return launch_bf16_xl<128, 144, 64, 2, 4, 1, 2>(A, W, M, N, K, e, st, m_first);
+    case 8: return launch_bf16_xl<128, 144, 64, 2, 4, 1, 2, true>(A, W, M, N, K, e, st, m_first);
     case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, m_first);
-    case 13: return launch_bf16_xl<256, 144, 64, 3, 8, 1>(A, W, M, N, K, e, st, m_first);
-    case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 13: return launch_bf16_xl<256, 144, 64, 3, 8, 1, 1, true>(A, W, M, N, K, e, st, m_first);
+    case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2, 1, true>(A, W, M, N, K, e, st, m_first);
     default: return launch_bf16_xl<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st, m_first);      // 5, or a number that names no tile
     }
 }

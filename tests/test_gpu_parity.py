@@ -204,6 +204,25 @@ def test_bf16_thin_pass_branch_outputs_left_as_partial_tiles(torch, drf, orc, hi
     check_forward(torch, drf, orc, dit, "loud", slots=3, tol=TOL_BF16, seed=80 + heads)
 
 
+@pytest.mark.parametrize("cond,lat,slots", [(I.COND_CLASS, (32, 32), 65), (I.COND_TEXT, (36, 28), 67), (I.COND_CLASS, (18, 14), 261),
+                                            (I.COND_CLASS, (8, 8), 1030)])
+def test_bf16_whole_and_edge_tiles_of_a_fat_pass(torch, drf, orc, cond, lat, slots):
+    """More rows than one round of the largest GEMM tiles: 256 tokens (whole tiles, one gate row each), 252 and 63 (tiles over
+    two to six slots, a ragged last row tile), 16 (more slots to a tile than gate rows are kept); slots at both ends, at a
+    seam of the first tiles and in the middle against the oracle."""
+    dit = small_dit(cond, I.BF16, hidden=1152, heads=16, depth=2, lat_h=lat[0], lat_w=lat[1])
+    w = I.weights(dit, 47, "loud")
+    rng = np.random.default_rng(57)
+    x = rng.standard_normal((slots, dit["in_ch"], dit["lat_h"], dit["lat_w"])).astype(np.float32)
+    t = rng.integers(0, 1000, size=slots).astype(np.int32)
+    c = make_cond(dit, slots, 67)
+    den = drf.Denoiser(dit, w)
+    got = den.eps_batched(dev(torch, x), dev(torch, t), dev(torch, c)).cpu().numpy()
+    den.close()
+    pick = [0, 1, slots // 2, slots - 1]
+    check(got[pick], orc.dit_eps(dit, w, x[pick], t[pick], c[pick]), TOL_BF16, "eps")
+
+
 @pytest.mark.parametrize("lat", [(10, 6), (24, 24)])
 def test_bf16_text_context_of_300_rows(torch, drf, orc, lat):
     # 15 and 144 queries over 300 kv rows: the chunked kernel's forms with four and with eight waves
