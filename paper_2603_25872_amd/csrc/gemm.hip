@@ -1,6 +1,7 @@
 // GEMM C[M][N] = A[M][K] . W[N][K]^T with fused epilogues (bias, GELU-tanh, gated
-// residual).  bf16 path: one software-pipelined kernel (16x16x32 MFMAs, operands by LDS-DMA, fp32
-// accumulate) at tiles from 32 x 64 to 256 x 288, the tile chosen by a measured time model.
+// residual).  bf16 path: software-pipelined kernels (16x16x32 MFMAs, operands by LDS-DMA, fp32 accumulate) at tiles from
+// 32 x 64 to 256 x 288, the tile chosen by a measured time model: 256 columns and more in gemm_wide.h, 144 in gemm_pair.h, the
+// others here.
 // fp32 path: fp32 MFMA, operands straight to registers, K split over the waves of a workgroup.
 #include "gemm_device.h"
 
@@ -42,13 +43,10 @@ __device__ inline void epilogue4(const Epilogue& e, int m, int n, float v0, floa
 }
 
 // ------------------------------------------------------------------ bf16 MFMA
-// The kernel for all of the DiT's GEMMs.  BM x BN x 64 block tile (256 x 288 for hidden
-// 1152: 1152, 3456 and 4608 are all multiples of 288, so at 64 row tiles every GEMM of the
-// block is a whole number of 256-tile rounds), 8 waves as WM x WN, wave tile (BM/WM) x
-// (BN/WN) built from 16x16x32 MFMAs so that widths only need to be multiples of 16.
+// The kernel for small problems and for what the 4-wave kernels leave: BM x BN x 64 block tile, waves as WM x WN (x WK), wave
+// tile (BM/WM) x (BN/WN) built from 16x16x32 MFMAs so that widths only need to be multiples of 16.
 //  - operands go HBM -> LDS directly (global_load_lds_dwordx4: every lane supplies its own
-//    global address and the wave's 64 x 16 bytes land contiguously in LDS), NS stages (two
-//    for the wide tiles: all that 160 KB of LDS hold), so the copy of the next k-tiles overlaps
+//    global address and the wave's 64 x 16 bytes land contiguously in LDS), NS stages so the copy of the next k-tiles overlaps
 //    the MFMAs of k-tile t.  A tile row is 128 bytes = 8
 //    chunks; chunk c of row r sits at position c ^ ((r / 2) % 8), which keeps both the DMA
 //    writes and the ds_read_b128 operand fetches free of bank conflicts;
@@ -56,9 +54,7 @@ __device__ inline void epilogue4(const Epilogue& e, int m, int n, float v0, floa
 //    works on a compact group of tiles and shares A/W slices through its own L2;
 //  - the weight tile is the MFMA A operand: a lane ends with 4 consecutive columns n of one
 //    row m per accumulator;
-//  - epilogue: each wave transposes its accumulators through its own slice of the (now
-//    idle) LDS stages and then touches global memory in whole rows: 16 bytes per lane,
-//    consecutive lanes on consecutive addresses.
+//  - epilogue: store_tile, or (RS: the tiles that fill the chip) store_rows through the idle LDS stages.
 // copy instructions issued per MFMA group by the in-loop copy of the two-stage kernels (1: measured best; 2, 3 and
 // the whole copy at once are 0.8 % slower per call, one every other group lands too late: 3 % slower)
 constexpr int kSpreadPer = 1;
@@ -484,30 +480,28 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
 // The tiles, and a time model of a launch of each: base + (per round of workgroups) round + steps * max(lat, c * thr)
 // microseconds, where a round is per_cu workgroups on each of the 256 CUs, c the workgroups that share a CU in it and
 // steps the k-steps of 64 * wk; a split adds red0 + red1 per million partial elements for the reduction launch.
-// The constants are least-squares fits to timings of every tile on 107 shapes (M 2 .. 65536, N 384 .. 195840, K 384 ..
-// 4608, weights cold); the tile that the model picks is 0.8 % slower than the fastest of all on average and 14 % at
-// worst, on those shapes and back to back (inside a pass launches take longer: 53 against 43 modelled us for the four of a
-// 512-row block of hidden 1152).  Small problems live on small tiles: with weights coming from HBM a launch is a chain of round trips, and what
-// counts is how many of the chip's CUs pull operands at once (M = 512, N = K = 1152: 13.2 us on 36 128 x 128 tiles,
-// 7.0 us on 144 64 x 64 tiles whose two wave groups split K; N = 3456: 15.5 -> 11.2 us on 128 x 64; M = 2048, N = 3456:
-// 32.5 -> 23.9 us with two 128 x 128 workgroups per CU; M = 12288, N = 1536, K = 384: 31.9 -> 22.9 us likewise).
-// Larger ones lose by a part-filled round: the tiles between 128 x 128 and 256 x 256 are there for their counts (M = 8192,
-// N = 1152, K = 4608: 108 us on 160 256 x 256 tiles, 84 us on 256 of 256 x 144).
+// The constants are least-squares fits to timings of every tile on 134 shapes (M 16 .. 65536, N 384 .. 195840, K 384 ..
+// 4608, weights cold); the tile that the model picks is 0.6 % slower than the fastest of all on average and 8 % at
+// worst but for 24576 x 384 x 1536, where it takes the second best.  Back to back, that is: inside a pass launches take longer.
+// Small problems live on small tiles: with weights coming from HBM a launch is a chain of round trips, and what counts is
+// how many of the chip's CUs pull operands at once (M = 512, N = K = 1152: 7.1 us on 144 64 x 64 tiles whose two wave
+// groups split K, 12.5 on 36 128 x 128 tiles).  Larger ones lose by a part-filled round: the tiles between 128 x 128 and 256 x 256
+// are there for their counts (M = 8192, N = 1152, K = 4608: 77.6 us on 256 tiles of 256 x 144, 88.1 on 160 of 256 x 256).
 struct TileModel { int id, bm, bn, wk, per_cu; double base, round, lat, thr, red0, red1; };     // red0 = 0: never split
 const TileModel kTiles[] = {
-    {  2, 256, 288, 1, 1, 0.00, 6.34, 1.55, 0.10, 0.0, 0.0 },
-    {  3, 256, 256, 1, 1, 0.00, 4.89, 1.43, 0.10, 0.0, 0.0 },
-    { 13, 256, 144, 1, 1, 0.00, 5.53, 0.95, 0.95, 0.0, 0.0 },
-    { 14, 256, 128, 1, 1, 0.55, 4.75, 0.83, 0.10, 0.0, 0.0 },
-    {  4, 128, 128, 1, 2, 0.00, 2.84, 0.89, 0.10, 0.0, 0.0 },
-    {  5, 128, 128, 1, 1, 0.90, 2.82, 0.51, 0.48, 3.3, 2.3 },
-    {  8, 128, 144, 2, 1, 0.70, 4.01, 1.40, 1.40, 0.0, 0.0 },
-    {  7, 128,  96, 1, 1, 1.39, 2.88, 0.48, 0.48, 0.0, 0.0 },
-    {  6, 128,  64, 1, 1, 0.95, 2.35, 0.35, 0.35, 3.6, 1.8 },
-    { 11,  64,  96, 2, 1, 1.38, 2.33, 0.57, 0.12, 0.0, 0.0 },
-    {  9,  64,  64, 2, 1, 1.42, 1.93, 0.44, 0.10, 3.5, 1.6 },
-    {  1,  64,  64, 1, 2, 1.97, 1.33, 0.26, 0.21, 3.1, 1.9 },
-    { 12,  32,  64, 2, 2, 2.04, 1.43, 0.38, 0.29, 3.1, 1.8 },
+    {  2, 256, 288, 1, 1, 0.00, 8.99, 1.59, 0.00, 0.0, 0.0 },
+    {  3, 256, 256, 1, 1, 0.00, 7.66, 1.31, 0.00, 0.0, 0.0 },
+    { 13, 256, 144, 1, 1, 0.10, 8.17, 0.94, 0.00, 0.0, 0.0 },
+    { 14, 256, 128, 1, 1, 0.24, 4.29, 0.85, 0.00, 0.0, 0.0 },
+    { 16, 128, 144, 1, 1, 0.51, 4.58, 0.54, 0.00, 0.0, 0.0 },
+    {  4, 128, 128, 1, 2, 0.98, 2.65, 0.64, 0.51, 0.0, 0.0 },
+    {  5, 128, 128, 1, 1, 1.29, 2.95, 0.48, 0.00, 2.9, 1.8 },
+    { 17,  64, 144, 1, 1, 1.51, 3.13, 0.31, 0.00, 0.0, 0.0 },
+    {  6, 128,  64, 1, 1, 1.50, 2.12, 0.32, 0.00, 2.9, 1.9 },
+    { 11,  64,  96, 2, 1, 1.43, 2.65, 0.44, 0.00, 0.0, 0.0 },
+    {  9,  64,  64, 2, 1, 1.47, 2.08, 0.37, 0.00, 2.9, 1.8 },
+    {  1,  64,  64, 1, 2, 1.91, 1.40, 0.22, 0.19, 2.7, 1.8 },
+    { 12,  32,  64, 2, 2, 1.98, 1.34, 0.29, 0.26, 2.9, 1.7 },
 };
 
 double model_us(const TileModel& t, int M, int N, int K, int splits, bool leave)
@@ -532,12 +526,13 @@ drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, in
     case 3: return launch_gemm_wide_256(A, W, M, N, K, e, st, m_first);
     case 4: return launch_bf16_xl<128, 128, 64, 2, 4, 2, 1, true>(A, W, M, N, K, e, st, m_first);
     case 6: return launch_bf16_xl<128, 64, 64, 4, 4, 2>(A, W, M, N, K, e, st, m_first);
-    case 7: return launch_bf16_xl<128, 96, 64, 3, 4, 1>(A, W, M, N, K, e, st, m_first);
-    case 8: return launch_bf16_xl<128, 144, 64, 2, 4, 1, 2, true>(A, W, M, N, K, e, st, m_first);
+    case 8:                                         // (16 for whole pairs of k-tiles only, as this number has always been)
+        if (K % 128 != 0) DRF_FAIL(DRF_ESHAPE, "bf16 GEMM tile needs K %% 128 == 0 (K=%d)", K);
+        [[fallthrough]];
+    case 13: case 16: case 17: return launch_gemm_pair(v, A, W, M, N, K, e, st, m_first);
     case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, m_first);
-    case 13: return launch_bf16_xl<256, 144, 64, 3, 8, 1, 1, true>(A, W, M, N, K, e, st, m_first);
     case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2, 1, true>(A, W, M, N, K, e, st, m_first);
     default: return launch_bf16_xl<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st, m_first);      // 5, or a number that names no tile
     }

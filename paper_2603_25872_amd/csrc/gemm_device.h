@@ -339,19 +339,19 @@ __device__ __forceinline__ void store_rows(const f32x4 (&acc)[TN / 16][TM / 16],
 }
 
 // The epilogue's mode found at run time.
-template <int TM, int TN>
+template <int TM, int TN, bool EDGES_ONLY = false>
 __device__ __forceinline__ void store_tile(const f32x4 (&acc)[TN / 16][TM / 16], const Epilogue& e, int mw, int nw, int M, int N,
                                            const unsigned char* erows, int rstride, const GateRows& gr)
 {
     const int lane = threadIdx.x & 63;
-    if (e.mode == EPI_RESID) store_tile_as<TM, TN, EPI_RESID, true>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
+    if (e.mode == EPI_RESID) store_tile_as<TM, TN, EPI_RESID, true, EDGES_ONLY>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
     else if (e.out_f32) {
-        if (e.mode == EPI_STORE_GELU) store_tile_as<TM, TN, EPI_STORE_GELU, true>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
-        else store_tile_as<TM, TN, EPI_STORE, true>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
-    } else if (e.mode == EPI_STORE_GELU) store_tile_as<TM, TN, EPI_STORE_GELU, false>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
-    else if (e.mode == EPI_STORE_HEADS) store_tile_as<TM, TN, EPI_STORE_HEADS, false>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
-    else if (e.mode == EPI_STORE_GATED) store_tile_as<TM, TN, EPI_STORE_GATED, false>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
-    else store_tile_as<TM, TN, EPI_STORE, false>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
+        if (e.mode == EPI_STORE_GELU) store_tile_as<TM, TN, EPI_STORE_GELU, true, EDGES_ONLY>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
+        else store_tile_as<TM, TN, EPI_STORE, true, EDGES_ONLY>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
+    } else if (e.mode == EPI_STORE_GELU) store_tile_as<TM, TN, EPI_STORE_GELU, false, EDGES_ONLY>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
+    else if (e.mode == EPI_STORE_HEADS) store_tile_as<TM, TN, EPI_STORE_HEADS, false, EDGES_ONLY>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
+    else if (e.mode == EPI_STORE_GATED) store_tile_as<TM, TN, EPI_STORE_GATED, false, EDGES_ONLY>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
+    else store_tile_as<TM, TN, EPI_STORE, false, EDGES_ONLY>(acc, e, mw, nw, M, N, erows, rstride, gr, lane);
 }
 
 // Whether the workgroup's tile (rows m0 .., columns n0 ..) may go through store_rows.

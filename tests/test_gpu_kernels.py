@@ -81,6 +81,20 @@ def test_gemm_bf16_small_tiles_and_splits(torch, drf, orc, variant, M, N, K):
             drf.probe_gemm_bf16(A[:, :192].contiguous().cuda(), W[:, :192].contiguous().cuda(), torch.from_numpy(b).cuda(), variant=variant)
 
 
+@pytest.mark.parametrize("variant", [2, 3, 13, 16, 17])
+@pytest.mark.parametrize("M,N,K", [(300, 292, 64), (33, 8, 128), (256, 288, 192), (517, 580, 256), (130, 148, 320), (512, 576, 1088)])
+def test_gemm_bf16_four_wave_tiles(torch, drf, orc, variant, M, N, K):
+    """1 to 5 and 17 k-tiles: fewer than the stages, as many, one more, odd and even numbers; whole and ragged tiles."""
+    rng = np.random.default_rng(M + N + K)
+    A = bf16_round(torch, rng.standard_normal((M, K)))
+    W = bf16_round(torch, rng.standard_normal((N, K)) * 0.1)
+    b = rng.standard_normal(N).astype(np.float32)
+    out = drf.probe_gemm_bf16(A.cuda(), W.cuda(), torch.from_numpy(b).cuda(), variant=variant).float().cpu().numpy()
+    want = orc.linear(A.float().numpy(), W.float().numpy(), b)
+    err = np.abs(out - want).max() / np.abs(want).max()
+    assert err < 6e-3, err                       # bf16 rounding of the stored result: 2^-8 relative at worst
+
+
 @pytest.mark.parametrize("M,N,K", [(20011, 1152, 384), (12289, 1540, 384)])
 def test_gemm_bf16_rows_in_two_launches(torch, drf, M, N, K):
     """Full rounds of one tile and the remaining rows with another: same sums in the same order as one launch of a
