@@ -367,13 +367,13 @@ __global__ void __launch_bounds__(NW * 64) attn_bf16_kernel(const AttnArgs a, fl
 }
 
 // fp32 on the fp32 matrix instruction (16x16x4).  A workgroup takes 16 queries of one (slot, head), its four waves the
-// kv rows in steps of 32 (wave w: steps w, w + 4, ...), each with its own online softmax; the states are combined through
+// kv rows in steps of 16 TS (wave w: steps w, w + 4, ...; TS == 1 for up to 64 rows, where two of the waves had none), each with its own online softmax; the states are combined through
 // LDS.  Scores are computed transposed (S^T = K Q^T): a lane owns query lane % 16 and, per 16-row tile, kv rows
 // 4 * (lane / 16) + (0..3), which are the k-slices the PV product takes them in.  Operands go from memory straight to
 // registers; a launch of this path is a few round trips (2 slots x 4 heads x 64 rows, d = 32: 46 -> 6 us against eight
 // lanes per query on vector FMAs).  DQ = ceil(d / 16); VEC: head width and strides allow 16-byte loads of Q and K.
 constexpr int kF32MaxD = 128, kF32Waves = 4;
-template <int DQ, bool VEC>
+template <int DQ, bool VEC, int TS>
 __global__ void __launch_bounds__(kF32Waves * 64) attn_f32_kernel(const AttnArgs a, float scale, int nqb)
 {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -405,18 +405,18 @@ __global__ void __launch_bounds__(kF32Waves * 64) attn_f32_kernel(const AttnArgs
         o[c] = (f32x4){ 0.f, 0.f, 0.f, 0.f };
     }
     float m_run = -INFINITY, l_run = 0.f;                           // l_run: this quarter's share
-    for (int kv0 = wave * 32; kv0 < a.Nk; kv0 += kF32Waves * 32) {
-        f32x4 s[2], kf[2][DQ];
-        float vf[2][4][DQ];
+    for (int kv0 = wave * 16 * TS; kv0 < a.Nk; kv0 += kF32Waves * 16 * TS) {
+        f32x4 s[TS], kf[TS][DQ];
+        float vf[TS][4][DQ];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < TS; ++t) {
             const int row = kv0 + t * 16 + l16, rc = row < a.Nk ? row : a.Nk - 1;
 #pragma unroll
             for (int c = 0; c < DQ; ++c) kf[t][c] = load4(Kp + (size_t)rc * a.ldk, c * 16 + 4 * quarter);
         }
         // V^T operand of k-slice (t, r): row t * 16 + 4 * quarter + r, column c * 16 + l16
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < TS; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = kv0 + t * 16 + 4 * quarter + r;
@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(kF32Waves * 64) attn_f32_kernel(const AttnArgs
             }
         float mx = -INFINITY;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
+        for (int t = 0; t < TS; ++t) {
             s[t] = (f32x4){ 0.f, 0.f, 0.f, 0.f };
 #pragma unroll
             for (int c = 0; c < DQ; ++c)
@@ -448,7 +448,7 @@ __global__ void __launch_bounds__(kF32Waves * 64) attn_f32_kernel(const AttnArgs
 #pragma unroll
         for (int c = 0; c < DQ; ++c) o[c] *= alpha;
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < TS; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float p = expf(s[t][r] - ref);
@@ -602,8 +602,13 @@ drf_status launch_attn_f32(const AttnArgs& a, hipStream_t st)
                      ((reinterpret_cast<uintptr_t>(a.q) | reinterpret_cast<uintptr_t>(a.k)) & 15u) == 0;
     auto go = [&](auto dq_c) {
         constexpr int DQ = decltype(dq_c)::value;
-        if (vec) hipLaunchKernelGGL((attn_f32_kernel<DQ, true>), grid, dim3(kF32Waves * 64), 0, st, a, scale, nqb);
-        else hipLaunchKernelGGL((attn_f32_kernel<DQ, false>), grid, dim3(kF32Waves * 64), 0, st, a, scale, nqb);
+        auto with = [&](auto ts_c) {
+            constexpr int TS = decltype(ts_c)::value;
+            if (vec) hipLaunchKernelGGL((attn_f32_kernel<DQ, true, TS>), grid, dim3(kF32Waves * 64), 0, st, a, scale, nqb);
+            else hipLaunchKernelGGL((attn_f32_kernel<DQ, false, TS>), grid, dim3(kF32Waves * 64), 0, st, a, scale, nqb);
+        };
+        if (a.Nk <= kF32Waves * 16) with(std::integral_constant<int, 1>{});
+        else with(std::integral_constant<int, 2>{});
     };
     if (dq <= 1) go(std::integral_constant<int, 1>{});
     else if (dq <= 2) go(std::integral_constant<int, 2>{});

@@ -145,6 +145,11 @@ drf_status launch_gemm_pair(int tile, const bf16_t* A, const bf16_t* W, int M, i
 size_t gemm_splitk_scratch_bytes();
 // fp32; a_row_mod: row m of C uses row m % a_row_mod of A (0: row m).
 drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int a_row_mod = 0);
+// fp32, with LayerNorm and modulation of the rows of A computed on the way (K is the row length):
+// A = (x - mean) / sqrt(var + 1e-6) * (1 + scale) + shift of row m's slot; shift NULL: no modulation.
+struct RowNorm { const float *shift, *scale; int mod_ld, rows_per_slot; };
+bool gemm_f32_folds_ln(int M, int N, int K);       // whether that is the faster way (and one that the launch takes)
+drf_status launch_gemm_f32_ln(const float* resid, const RowNorm& ln, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st);
 
 struct AttnArgs {
     // query i of (slot, head h) starts at q + slot * q_slot_stride + h * q_head_stride + i * ldq  (elements);

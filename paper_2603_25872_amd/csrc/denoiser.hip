@@ -396,13 +396,23 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         if (store) pend1 = pend2 = nullptr;
         return r;
     };
+    // LayerNorm, then a Linear of its output; on the fp32 path one launch where the GEMM can normalise its rows itself
+    auto ln_linear = [&](const float* shift, const float* scale, int mod_ld, bool store, const LinearW& w, const Epilogue& ep) -> drf_status {
+        if (f32 && gemm_f32_folds_ln(M, w.N, w.K)) {
+            Epilogue e = ep;
+            e.bias = w.b;
+            ProfScope ps(d, st, DRF_PROF_GEMM, 2.0 * M * (double)w.N * w.K);
+            return launch_gemm_f32_ln(ws.resid, RowNorm{ shift, scale, mod_ld, dm.T }, w.w32, M, w.N, w.K, e, st);
+        }
+        const drf_status r = ln(shift, scale, mod_ld, store);
+        return r != DRF_OK ? r : gemm(d, ws.hbuf, w, M, ep, st, ws.skpart);
+    };
     for (int l = 0; l < n_blocks; ++l) {
         const BlockW& b = d->blk[l];
         const float* mrow = mod + (size_t)l * 6 * D;        // shift1 | scale1 | gate1 | shift2 | scale2 | gate2
-        if ((rc = ln(mrow, mrow + D, nm, true)) != DRF_OK) return rc;
         // bf16: q | k | v are stored head-major ([slot][head][token][d] planes) so that attention reads
         // whole contiguous tiles; fp32: packed rows
-        if ((rc = gemm(d, ws.hbuf, b.qkv, M, f32 ? epi_store(ws.qkv, 3 * D, true) : with_warm(epi_heads(ws.qkv, slots, dm), &b.proj), st, ws.skpart)) != DRF_OK) return rc;
+        if ((rc = ln_linear(mrow, mrow + D, nm, true, b.qkv, f32 ? epi_store(ws.qkv, 3 * D, true) : with_warm(epi_heads(ws.qkv, slots, dm), &b.proj))) != DRF_OK) return rc;
         {
             AttnArgs aa{};
             aa.q = ws.qkv; aa.out = ws.hbuf; aa.ldo = D; aa.Nq = dm.T; aa.Nk = dm.T; aa.heads = dm.heads; aa.d = dm.d;
@@ -429,8 +439,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         }
         if (d->cfg.cond == DRF_COND_TEXT) {
             const int ctx_rows = map.cond_mod ? map.cond_mod : slots;
-            if ((rc = ln(nullptr, nullptr, 0, true)) != DRF_OK) return rc;
-            if ((rc = gemm(d, ws.hbuf, b.xq, M, epi_store(ws.qkv, D, f32), st, ws.skpart)) != DRF_OK) return rc;
+            if ((rc = ln_linear(nullptr, nullptr, 0, true, b.xq, epi_store(ws.qkv, D, f32))) != DRF_OK) return rc;
             const char* kv = (const char*)ws.xkv + (size_t)l * ctx_rows * d->cfg.ctx_len * 2 * D * act;
             AttnArgs aa{};
             aa.q = ws.qkv; aa.ldq = D; aa.k = kv; aa.v = kv + (size_t)D * act; aa.ldk = 2 * D; aa.out = ws.hbuf; aa.ldo = D;
@@ -444,8 +453,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
             if ((rc = gemm(d, ws.hbuf, b.xo, M, epi_resid(ws.resid, D, nullptr, 0, dm.T), st, ws.skpart)) != DRF_OK) return rc;
         }
         const bool last = l == n_blocks - 1;
-        if ((rc = ln(mrow + 3 * D, mrow + 4 * D, nm, f32 || last)) != DRF_OK) return rc;
-        if ((rc = gemm(d, ws.hbuf, b.fc1, M, with_warm(epi_store(ws.mid, dm.R * D, f32, true), f32 ? nullptr : &b.fc2), st, ws.skpart)) != DRF_OK) return rc;
+        if ((rc = ln_linear(mrow + 3 * D, mrow + 4 * D, nm, f32 || last, b.fc1, with_warm(epi_store(ws.mid, dm.R * D, f32, true), f32 ? nullptr : &b.fc2))) != DRF_OK) return rc;
         if (f32 || last) {
             if ((rc = gemm(d, ws.mid, b.fc2, M, epi_resid(ws.resid, D, mrow + 5 * D, nm, dm.T), st, ws.skpart)) != DRF_OK) return rc;
         } else {

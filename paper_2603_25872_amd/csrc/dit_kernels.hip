@@ -1,5 +1,7 @@
 // Bandwidth-bound pieces of the DiT forward: conditioning front-end, patch embedding,
 // LayerNorm + adaLN modulation, final projection + unpatchify.
+#include <type_traits>
+
 #include "common.h"
 
 namespace drf {
@@ -75,8 +77,7 @@ __global__ void __launch_bounds__(256) cond_finish_kernel(const float* __restric
 // store of the stream: the row-per-thread form, whose weight reads touched 64 lines per instruction, took 25 us for 512
 // rows and 44 us for 16384 (hidden 1152), this one 7.6 and 33.5 us.
 // VEC: P % 4 == 0 (16-byte loads of the weight rows).
-constexpr int kPatchTiles = 6;
-template <bool VEC>
+template <bool VEC, int kPatchTiles>
 __global__ void __launch_bounds__(256) patch_embed_kernel(const float* __restrict__ x, const SlotMap map,
                                                           const float* __restrict__ w, const float* __restrict__ b,
                                                           const float* __restrict__ pos, const DitDims dm, int M,
@@ -91,6 +92,13 @@ __global__ void __launch_bounds__(256) patch_embed_kernel(const float* __restric
     f32x4m acc[kPatchTiles];
 #pragma unroll
     for (int i = 0; i < kPatchTiles; ++i) acc[i] = (f32x4m){ 0.f, 0.f, 0.f, 0.f };
+    // bias and position code are asked for with the operands, not after them
+    f32x4m add[kPatchTiles];
+#pragma unroll
+    for (int i = 0; i < kPatchTiles; ++i) {
+        const int j = first + i * 16 + 4 * quarter, jc = j < dm.D ? j : 0;      // hidden is a multiple of 4
+        add[i] = *reinterpret_cast<const f32x4m*>(pos + (size_t)t * dm.D + jc);
+    }
     for (int k0 = 0; k0 < dm.P; k0 += 16) {
         f32x4m tok = { 0.f, 0.f, 0.f, 0.f }, wf[kPatchTiles];
 #pragma unroll
@@ -120,9 +128,9 @@ __global__ void __launch_bounds__(256) patch_embed_kernel(const float* __restric
 #pragma unroll
     for (int i = 0; i < kPatchTiles; ++i) {         // acc[i][r]: column first + 16 i + 4 quarter + r of row l16
         const int j = first + i * 16 + 4 * quarter;
-        if (j < dm.D) {                             // hidden is a multiple of 4
-            const f32x4m bj = *reinterpret_cast<const f32x4m*>(b + j), pj = *reinterpret_cast<const f32x4m*>(pos + (size_t)t * dm.D + j);
-            *reinterpret_cast<f32x4m*>(resid + (size_t)m * dm.D + j) = acc[i] + bj + pj;
+        if (j < dm.D) {
+            const f32x4m bj = *reinterpret_cast<const f32x4m*>(b + j);
+            *reinterpret_cast<f32x4m*>(resid + (size_t)m * dm.D + j) = acc[i] + bj + add[i];
         }
     }
 }
@@ -538,12 +546,16 @@ drf_status launch_patch_embed(const float* x, const SlotMap& map, const float* w
 {
     const int M = slots * dm.T;
     if (M == 0) return DRF_OK;
-    const int per = 4 * kPatchTiles * 16;
-    const dim3 grid((M + 15) / 16, (dm.D + per - 1) / per);
-    if (dm.P % 4 == 0 && (reinterpret_cast<uintptr_t>(w) & 15u) == 0)
-        hipLaunchKernelGGL(patch_embed_kernel<true>, grid, dim3(256), 0, st, x, map, w, b, pos, dm, M, resid);
-    else
-        hipLaunchKernelGGL(patch_embed_kernel<false>, grid, dim3(256), 0, st, x, map, w, b, pos, dm, M, resid);
+    auto go = [&](auto tiles_c) {
+        constexpr int TILES = decltype(tiles_c)::value, per = 4 * TILES * 16;
+        const dim3 grid((M + 15) / 16, (dm.D + per - 1) / per);
+        if (dm.P % 4 == 0 && (reinterpret_cast<uintptr_t>(w) & 15u) == 0)
+            hipLaunchKernelGGL((patch_embed_kernel<true, TILES>), grid, dim3(256), 0, st, x, map, w, b, pos, dm, M, resid);
+        else
+            hipLaunchKernelGGL((patch_embed_kernel<false, TILES>), grid, dim3(256), 0, st, x, map, w, b, pos, dm, M, resid);
+    };
+    if ((M + 15) / 16 < 64) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 6>{});
     DRF_HIP(hipGetLastError());
     return DRF_OK;
 }

@@ -42,6 +42,31 @@ __device__ inline void epilogue4(const Epilogue& e, int m, int n, float v0, floa
     }
 }
 
+// The same for the fp32 path's modes, in two parts: what it reads, asked for ahead of the product, and the rest.
+struct EpilogueOperands { f32x4 bias, gate, x; };
+__device__ inline EpilogueOperands load_epilogue4(const Epilogue& e, int m, int n)
+{
+    EpilogueOperands o;
+    o.bias = *reinterpret_cast<const f32x4*>(e.bias + n);
+    o.gate = (f32x4){ 1.f, 1.f, 1.f, 1.f };
+    if (e.mode == EPI_RESID) {
+        o.x = *reinterpret_cast<const f32x4*>((const float*)e.out + (size_t)m * e.ldo + n);
+        if (e.gate) o.gate = *reinterpret_cast<const f32x4*>(e.gate + (size_t)fast_div(m, e.rps_magic, e.rps_shift) * e.gate_ld + n);
+    }
+    return o;
+}
+__device__ inline void store_epilogue4(const Epilogue& e, int m, int n, f32x4 v, const EpilogueOperands& o)
+{
+    v += o.bias;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (e.mode == EPI_RESID) v[j] = fmaf(o.gate[j], v[j], o.x[j]);
+        if (e.mode == EPI_STORE_GELU) v[j] = gelu_tanh(v[j]);
+        if (e.mode == EPI_STORE_SILU) v[j] = silu(v[j]);
+    }
+    *reinterpret_cast<f32x4*>((float*)e.out + (size_t)m * e.ldo + n) = v;
+}
+
 // ------------------------------------------------------------------ bf16 MFMA
 // The kernel for small problems and for what the 4-wave kernels leave: BM x BN x 64 block tile, waves as WM x WN (x WK), wave
 // tile (BM/WM) x (BN/WN) built from 16x16x32 MFMAs so that widths only need to be multiples of 16.
@@ -346,31 +371,38 @@ splitk_reduce_kernel(const float* __restrict__ part, int splits, size_t split_st
 }
 
 // ------------------------------------------------------------------------ fp32
-// 32 x 32 output tile per workgroup on the fp32 matrix instruction (16x16x4, exact fp32 products and sums); the four
-// waves split K (wave w takes the 16-wide k-steps w, w + 4, ...) and add their partial tiles through LDS.  Operands go
-// from memory straight to registers, kF32Batch steps at a time and one batch ahead: the problems of this path are a few
-// hundred rows, where a launch is one or two round trips to memory, and a staged tile only adds barriers to them
-// (M = 128: K = 512 46 -> 7 us, K = 128 20 -> 5 us against a 64 x 64 x 16 LDS tile on vector FMAs).
+// 32 x 32 (F == 2) or 16 x 16 (F == 1) output tile per workgroup on the fp32 matrix instruction (16x16x4, exact fp32 products and sums); the NW
+// waves split K (wave w takes the 16-wide k-steps w, w + NW, ...) and add their partial tiles through LDS.  Operands go
+// from memory straight to registers, B steps at a time and one batch ahead: the problems of this path are a few
+// hundred rows, where a launch is a chain of round trips to memory, and a staged tile only adds barriers to them.  What the
+// epilogue adds to the product is asked for before the first of its operands is used.  Two forms (f32_small): 16 x 16 tiles
+// with K dealt over enough waves that one batch takes all of it up to 512, and 32 x 32 tiles of four waves for more rows.
 // A lane loads 4 consecutive k of its row; MFMA e of a step takes element e of every lane, that is the k-set
 // {4 quarter + e}, the same for both operands.  The weights are the first operand: a lane ends with 4 consecutive n.
 // VEC: rows are 16-byte aligned and K % 4 == 0; otherwise the four elements are loaded one by one.
-constexpr int kF32Batch = 2;
-template <bool VEC>
-__global__ void __launch_bounds__(256)
-gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, int a_row_mod, const Epilogue e)
+// LN: A is the residual stream, and its rows are normalised and modulated here (statistics over all K, in one batch), in
+// place of a launch that does it once for all column tiles: for a few rows reading and normalising them again costs less than
+// that launch (M = 64, K = 128: 3.2 + 5.3 us as two launches, 4.4 as one; 2304 rows of 256: 1.7 times the two).
+// (32 x 32 tiles: three workgroups a CU; a fourth evicts the lines that they share from L1, 5 % slower at 16384 x 1024 and more.)
+template <bool VEC, int F, int NW, int B, bool LN>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(F == 2 ? 3 : 1, F == 2 ? 3 : 8)))
+gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K, int a_row_mod, const Epilogue e, const RowNorm ln)
 {
-    __shared__ f32x4 part[4][4][64];
+    constexpr int T = 16 * F;
+    __shared__ f32x4 part[NW][F * F][64];
+    __shared__ float red[LN ? 2 : 1][NW][T];
     const int lane = threadIdx.x & 63, l16 = lane & 15, quarter = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n0 = blockIdx.x * 32;
-    for (int m0 = blockIdx.y * 32; m0 < M; m0 += gridDim.y * 32) {   // (more row tiles than the grid's y limit: several each)
-        const float *ap[2], *wp[2];
+    const int n0 = blockIdx.x * T;
+    for (int m0 = blockIdx.y * T; m0 < M; m0 += gridDim.y * T) {   // (more row tiles than the grid's y limit: several each)
+        const float *ap[F], *wp[F], *sc[F], *sh[F];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < F; ++i) {
             int m = m0 + i * 16 + l16, n = n0 + i * 16 + l16;           // rows past the end repeat the last one, never stored
             m = m < M ? m : M - 1; n = n < N ? n : N - 1;
             if (a_row_mod) m %= a_row_mod;
             ap[i] = A + (size_t)m * K; wp[i] = W + (size_t)n * K;
+            if (LN && ln.shift) { const size_t mr = (size_t)(m / ln.rows_per_slot) * ln.mod_ld; sc[i] = ln.scale + mr; sh[i] = ln.shift + mr; }
         }
         auto load4 = [&](const float* p, int k) -> f32x4 {
             f32x4 v = { 0.f, 0.f, 0.f, 0.f };
@@ -383,47 +415,120 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M,
             }
             return v;
         };
-        f32x4 fa[2][kF32Batch][2], fw[2][kF32Batch][2], acc[2][2];      // [buffer][step][16-row half]; acc[n half][m half]
-        auto load = [&](f32x4 (&a)[kF32Batch][2], f32x4 (&w)[kF32Batch][2], int step) {
+        f32x4 fa[2][B][F], fw[2][B][F], acc[F][F];      // [buffer][step][16-row part]; acc[n part][m part]
+        auto load = [&](f32x4 (&a)[B][F], f32x4 (&w)[B][F], int step) {
 #pragma unroll
-            for (int u = 0; u < kF32Batch; ++u) {
-                const int k = (step + 4 * u) * 16 + 4 * quarter;
+            for (int u = 0; u < B; ++u) {
+                const int k = (step + NW * u) * 16 + 4 * quarter;
 #pragma unroll
-                for (int i = 0; i < 2; ++i) { a[u][i] = load4(ap[i], k); w[u][i] = load4(wp[i], k); }
+                for (int i = 0; i < F; ++i) { a[u][i] = load4(ap[i], k); w[u][i] = load4(wp[i], k); }
             }
         };
-        auto multiply = [&](const f32x4 (&a)[kF32Batch][2], const f32x4 (&w)[kF32Batch][2]) {
+        auto multiply = [&](const f32x4 (&a)[B][F], const f32x4 (&w)[B][F], int left) {
 #pragma unroll
-            for (int u = 0; u < kF32Batch; ++u)
+            for (int u = 0; u < B; ++u)
+                if (F == 2 || u == 0 || NW * u < left)                  // (steps past the end are zeros)
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
+                    for (int k = 0; k < 4; ++k)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
+                        for (int i = 0; i < F; ++i)
 #pragma unroll
-                        for (int j = 0; j < 2; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][i][k], a[u][j][k], acc[i][j], 0, 0, 0);
+                            for (int j = 0; j < F; ++j)
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][i][k], a[u][j][k], acc[i][j], 0, 0, 0);
         };
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < F; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){ 0.f, 0.f, 0.f, 0.f };
+            for (int j = 0; j < F; ++j) acc[i][j] = (f32x4){ 0.f, 0.f, 0.f, 0.f };
         const int steps = (K + 15) / 16;
         load(fa[0], fw[0], wave);
-        for (int s = wave; s < steps; s += 8 * kF32Batch) {             // steps past the end are zeros
-            load(fa[1], fw[1], s + 4 * kF32Batch);
-            multiply(fa[0], fw[0]);
-            load(fa[0], fw[0], s + 8 * kF32Batch);
-            multiply(fa[1], fw[1]);
+        f32x4 s4[LN ? B : 1][F], h4[LN ? B : 1][F];
+        if constexpr (LN) {
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+#pragma unroll
+                for (int i = 0; i < F; ++i) {
+                    const int k = (wave + NW * u) * 16 + 4 * quarter;
+                    s4[u][i] = h4[u][i] = (f32x4){ 0.f, 0.f, 0.f, 0.f };
+                    if (ln.shift) { s4[u][i] = load4(sc[i], k); h4[u][i] = load4(sh[i], k); }
+                }
+        }
+        // wave f < F F finishes fragment f: acc[i][j][r] is (n = 16 i + 4 quarter + r, m = 16 j + l16) of the tile
+        const int em = m0 + wave % F * 16 + l16, en = n0 + wave / F * 16 + 4 * quarter;
+        const bool mine = wave < F * F && em < M && en < N;
+        EpilogueOperands ops;
+        if (F == 1 && mine) ops = load_epilogue4(e, em, en);
+        if constexpr (LN) {
+            // mean, then the centred squares: two exchanges between the quarters and the waves
+            float mean[F], rstd[F];
+            auto total = [&](const float (&v)[F], float (&out)[F], int which) {
+#pragma unroll
+                for (int i = 0; i < F; ++i) {
+                    float t = v[i];
+                    t += __shfl_xor(t, 16, 64); t += __shfl_xor(t, 32, 64);
+                    if (quarter == 0) red[which][wave][i * 16 + l16] = t;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < F; ++i) {
+                    float t = 0.f;
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) t += red[which][w][i * 16 + l16];
+                    out[i] = t;
+                }
+            };
+            float v[F] = {};
+#pragma unroll
+            for (int u = 0; u < B; ++u)
+#pragma unroll
+                for (int i = 0; i < F; ++i) v[i] += (fa[0][u][i][0] + fa[0][u][i][1]) + (fa[0][u][i][2] + fa[0][u][i][3]);
+            total(v, mean, 0);
+#pragma unroll
+            for (int i = 0; i < F; ++i) {
+                v[i] = 0.f;
+                mean[i] *= 1.f / (float)K;
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const bool in = (wave + NW * u) * 16 + 4 * quarter + j < K;
+                        fa[0][u][i][j] = in ? fa[0][u][i][j] - mean[i] : 0.f;
+                        v[i] = fmaf(fa[0][u][i][j], fa[0][u][i][j], v[i]);
+                    }
+            }
+            total(v, rstd, LN ? 1 : 0);
+#pragma unroll
+            for (int i = 0; i < F; ++i) {
+                rstd[i] = rsqrtf(rstd[i] * (1.f / (float)K) + 1e-6f);
+#pragma unroll
+                for (int u = 0; u < B; ++u)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float y = fa[0][u][i][j] * rstd[i];
+                        fa[0][u][i][j] = ln.shift ? fmaf(y, 1.f + s4[u][i][j], h4[u][i][j]) : y;
+                    }
+            }
+            multiply(fa[0], fw[0], steps - wave);
+        } else {
+            for (int s = wave; s < steps; s += 2 * NW * B) {
+                if (F == 2 || s + NW * B < steps) load(fa[1], fw[1], s + NW * B);
+                multiply(fa[0], fw[0], steps - s);
+                if (F == 2 || s + 2 * NW * B < steps) load(fa[0], fw[0], s + 2 * NW * B);
+                if (F == 2 || s + NW * B < steps) multiply(fa[1], fw[1], steps - s - NW * B);
+            }
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < F; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) part[wave][i * 2 + j][lane] = acc[i][j];
+            for (int j = 0; j < F; ++j) part[wave][i * F + j][lane] = acc[i][j];
         __syncthreads();
-        // wave f finishes fragment f: acc[i][j][r] is (n = 16 i + 4 quarter + r, m = 16 j + l16) of the tile
-        const f32x4 v = (part[0][wave][lane] + part[1][wave][lane]) + (part[2][wave][lane] + part[3][wave][lane]);
-        const int m = m0 + (wave & 1) * 16 + l16, n = n0 + (wave >> 1) * 16 + 4 * quarter;
-        if (m < M && n < N) epilogue4(e, m, n, v[0], v[1], v[2], v[3]);
+        if (mine) {
+            if (F == 2) ops = load_epilogue4(e, em, en);                // (registers that the loop needs, where there are many tiles)
+            f32x4 v = part[0][wave][lane];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) v += part[w][wave][lane];
+            store_epilogue4(e, em, en, v, ops);
+        }
         __syncthreads();
     }
 }
@@ -627,17 +732,49 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
     return launch_tile(v, A, W, M, N, K, e, st, rows_a);
 }
 
-drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int a_row_mod)
+// Whether a problem is for the 16 x 16 tiles: so few 32 x 32 tiles that a launch is one chain of round trips, which then only
+// gets shorter with more and smaller workgroups.  (M = 64: K = 512, N = 128 7.2 -> 5.1 us, K = N = 128 5.3 -> 3.6;
+// a call of configuration 1 1047 -> 675 us.  With the small tiles' waves and batches on 32 x 32 tiles, 16384 rows of 1024 lose 23 %.)
+bool f32_small(int M, int N) { return ((M + 31LL) / 32) * ((N + 31LL) / 32) <= 128; }
+
+template <bool LN>
+static drf_status launch_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int a_row_mod, const RowNorm& ln)
 {
     if (M == 0 || N == 0) return DRF_OK;
     if (N % 4 != 0 || e.ldo % 4 != 0) DRF_FAIL(DRF_ESHAPE, "fp32 GEMM needs N %% 4 == 0 (N=%d)", N);
-    const bool vec = K % 4 == 0 && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(W)) & 15u) == 0;
-    const int tiles_m = (int)(((long long)M + 31) / 32);
-    const dim3 grid((unsigned)((N + 31LL) / 32), tiles_m < 65535 ? tiles_m : 65535);
-    if (vec) hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, dim3(256), 0, st, A, W, M, N, K, a_row_mod, e);
-    else hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, dim3(256), 0, st, A, W, M, N, K, a_row_mod, e);
+    if (!e.out_f32 || e.mode == EPI_STORE_HEADS || e.mode == EPI_STORE_GATED) DRF_FAIL(DRF_ESHAPE, "epilogue mode of the bf16 GEMM");
+    uintptr_t bases = reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(W);
+    if (LN) bases |= reinterpret_cast<uintptr_t>(ln.shift) | reinterpret_cast<uintptr_t>(ln.scale) | (uintptr_t)(ln.mod_ld % 4);
+    const bool vec = K % 4 == 0 && (bases & 15u) == 0;
+    auto go = [&](auto f_c, auto nw_c, auto b_c) {
+        constexpr int F = decltype(f_c)::value, NW = decltype(nw_c)::value, B = decltype(b_c)::value, T = 16 * F;
+        const long long tiles_m = ((long long)M + T - 1) / T;
+        const dim3 grid((unsigned)((N + T - 1LL) / T), (unsigned)(tiles_m < 65535 ? tiles_m : 65535));
+        if (vec) hipLaunchKernelGGL((gemm_f32_kernel<true, F, NW, B, LN>), grid, dim3(NW * 64), 0, st, A, W, M, N, K, a_row_mod, e, ln);
+        else hipLaunchKernelGGL((gemm_f32_kernel<false, F, NW, B, LN>), grid, dim3(NW * 64), 0, st, A, W, M, N, K, a_row_mod, e, ln);
+    };
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 4> four{};
+    if (LN || f32_small(M, N)) {
+        if (K <= 128) go(one, four, four);
+        else go(one, std::integral_constant<int, 8>{}, four);
+    } else if constexpr (!LN) go(two, four, two);
     DRF_HIP(hipGetLastError());
     return DRF_OK;
+}
+
+drf_status launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int a_row_mod)
+{
+    return launch_f32<false>(A, W, M, N, K, e, st, a_row_mod, RowNorm{});
+}
+
+bool gemm_f32_folds_ln(int M, int N, int K) { return K <= 512 && f32_small(M, N); }
+
+drf_status launch_gemm_f32_ln(const float* resid, const RowNorm& ln, const float* W, int M, int N, int K, const Epilogue& e, hipStream_t st)
+{
+    if (!gemm_f32_folds_ln(M, N, K)) DRF_FAIL(DRF_ESHAPE, "LayerNorm inside the fp32 GEMM is for few rows of at most 512 (M=%d N=%d K=%d)", M, N, K);
+    return launch_f32<true>(resid, W, M, N, K, e, st, 0, ln);
 }
 
 }  // namespace drf

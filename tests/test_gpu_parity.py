@@ -204,6 +204,14 @@ def test_bf16_thin_pass_branch_outputs_left_as_partial_tiles(torch, drf, orc, hi
     check_forward(torch, drf, orc, dit, "loud", slots=3, tol=TOL_BF16, seed=80 + heads)
 
 
+@pytest.mark.parametrize("hidden,heads,slots", [(4, 1, 1), (20, 1, 3), (128, 4, 1), (260, 4, 3), (512, 8, 1), (516, 6, 1), (256, 4, 20)])
+def test_fp32_forward_rows_normalised_in_the_gemm(torch, drf, orc, hidden, heads, slots):
+    """Rows of 4 to 512 (one wave's single step, ragged steps, every wave's full batch) inside the GEMM; 516 and 300 rows of
+    256 through a LayerNorm launch; 15 tokens a slot, so row tiles run over slots."""
+    check_forward(torch, drf, orc, small_dit(I.COND_CLASS, I.F32, hidden=hidden, heads=heads), "loud", slots=slots, tol=TOL_F32, seed=70 + heads)
+    check_forward(torch, drf, orc, small_dit(I.COND_TEXT, I.F32, hidden=hidden, heads=heads, depth=1), "loud", slots=slots, tol=TOL_F32, seed=71)
+
+
 @pytest.mark.parametrize("cond,lat,slots", [(I.COND_CLASS, (32, 32), 65), (I.COND_TEXT, (36, 28), 67), (I.COND_CLASS, (18, 14), 261),
                                             (I.COND_CLASS, (8, 8), 1030)])
 def test_bf16_whole_and_edge_tiles_of_a_fat_pass(torch, drf, orc, cond, lat, slots):
