@@ -128,20 +128,6 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
     const int wk = wave / NWT, wl = wave % NWT, wm = wl % WM, wn = wl / WM;
     const int l16 = lane & 15, quarter = lane >> 4;
 
-    // Cache warm-up for a later launch (see Epilogue::warm): the lines are dealt over the workgroups of
-    // the last round, a thread loads one word per line; the values are only consumed by an empty asm
-    // after the first barrier, so the loads complete together with the first operand tiles.
-    unsigned warm_val = 0;
-    if (e.warm_lines) {
-        const uint32_t first = nb > 256 ? (uint32_t)nb - 256u : 0u, cnt = (uint32_t)nb - first;
-        const uint32_t per = (e.warm_lines + cnt - 1u) / cnt;
-        if ((uint32_t)b >= first)
-            for (uint32_t t = (uint32_t)tid; t < per; t += NW * 64) {
-                const uint32_t line = ((uint32_t)b - first) * per + t;
-                if (line < e.warm_lines) warm_val ^= reinterpret_cast<const unsigned*>(e.warm)[(size_t)line * 32];
-            }
-    }
-
     // DMA: the A rows and W rows of a k-tile form one row space [0, BM + BN), and a stage holds WK
     // k-tiles one after the other.  A wave-wide instruction covers RPI rows (never straddling the
     // A/W boundary).  Every wave issues LPT instructions; when SEG is not a multiple of the wave
@@ -232,15 +218,15 @@ gemm_bf16_xl_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, 
     };
 
     // tiles 0 .. NS-2 are in flight before the loop; tile kt + NS - 1 is requested once tile kt - 1 has been read
+    issue(0, 0);
     const GateRows gr = gate_rows<BM>(e, m0, M);
     if constexpr (!SK) stage_epilogue_rows<BN>(e, gr, lds_base + NS * STAGE * 2, wave, NW, n0, N);
-    issue(0, 0);
 #pragma unroll
     for (int t = 1; t < NS - 1; ++t)
         if (t < nk) issue(t, t);
     if (NS > 2 && nk >= NS - 1) wait_vmcnt<LPT * (NS - 2)>(); else wait_vmcnt<0>();
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    asm volatile("" ::"v"(warm_val));
+    warm_caches(e, lds_base + NS * STAGE * 2 + epi_lds_bytes(BN), nb, b, wave, NW);     // (the last k-tile's wait covers it)
     static_for<0, NI * MI>([&](auto pc) { constexpr int p = decltype(pc)::value; hold_acc<false>(acc[p / MI][p % MI]); });
     settle_mfma();
     if (NS - 1 < nk) issue(NS - 1, NS - 1);
@@ -536,7 +522,7 @@ gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W, int M,
 template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1, bool RS = false>
 drf_status launch_bf16_xl(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first = 0)
 {
-    constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + epi_lds_bytes(BN);
+    constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + epi_lds_bytes(BN) + 256;
     static_assert(smem <= 160 * 1024, "LDS of a CU");
     static bool attr_set = false;
     auto kern = gemm_bf16_xl_kernel<BM, BN, BK, NS, WM, WN, WK, false, RS>;
@@ -556,7 +542,7 @@ template <int BM, int BN, int BK, int NS, int WM, int WN, int WK = 1>
 drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
                               int splits, float* part, PartialSum* leave)
 {
-    constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + epi_lds_bytes(BN);
+    constexpr size_t smem = (size_t)NS * WK * (BM + BN) * BK * sizeof(bf16_t) + epi_lds_bytes(BN) + 256;
     static_assert(smem <= 160 * 1024, "LDS of a CU");
     static bool attr_set = false;
     auto kern = gemm_bf16_xl_kernel<BM, BN, BK, NS, WM, WN, WK, true>;

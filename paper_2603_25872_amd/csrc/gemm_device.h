@@ -86,7 +86,7 @@ template <int I, int N, typename F> __device__ __forceinline__ void static_for(F
 
 // Rows of epilogue operands that a workgroup keeps in LDS behind its stages: the bias of its columns, then the gate rows
 // of the slots that its rows belong to (up to kGateRows; beyond, gates are read from global memory).  They are copied
-// ahead of the first stage, so the wait for that stage covers them and the epilogue meets no memory round trip.
+// between the first stage and the second, so the wait for the first covers them and the epilogue meets no memory round trip.
 constexpr int kGateRows = 4;
 __host__ __device__ constexpr int epi_row_bytes(int BN) { return (BN + 63) / 64 * 256; }
 __host__ __device__ constexpr int epi_lds_bytes(int BN) { return (1 + kGateRows) * epi_row_bytes(BN); }
@@ -113,6 +113,23 @@ template <int BN> __device__ inline void stage_epilogue_rows(const Epilogue& e, 
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                          :: "s"(lds + (uint32_t)(r * epi_row_bytes(BN) + c * 256)), "v"((uint32_t)n * 4u), "s"(src) : "memory");
         }
+    }
+}
+
+// Cache warm-up for a later launch (see Epilogue::warm): the lines are dealt over the workgroups of the last round, one word
+// per line and lane, into 256 bytes of LDS that nobody reads (a register destination would be waited for: with it the
+// prologue took the time of its stages and of these lines from HBM).  Whoever calls it waits for vmcnt 0 once before
+// its workgroup ends: nothing may land in LDS after that.
+__device__ inline void warm_caches(const Epilogue& e, uint32_t lds, int nb, int b, int wave, int n_waves)
+{
+    if (!e.warm_lines) return;
+    const uint32_t first = nb > 256 ? (uint32_t)nb - 256u : 0u, cnt = (uint32_t)nb - first;
+    const uint32_t per = (e.warm_lines + cnt - 1u) / cnt;
+    if ((uint32_t)b < first) return;
+    for (uint32_t t = (uint32_t)wave * 64u; t < per; t += (uint32_t)n_waves * 64u) {
+        uint32_t line = ((uint32_t)b - first) * per + t + (threadIdx.x & 63u);
+        line = line < e.warm_lines ? line : e.warm_lines - 1u;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" :: "s"(lds), "v"(line * 128u), "s"(e.warm) : "memory");
     }
 }
 

@@ -82,23 +82,16 @@ gemm_bf16_pair_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W
         static_for<0, NI>([&](auto ic) { hold_frag(fw[s][decltype(ic)::value]); });
     };
 
+    static_for<0, NL>([&](auto ic) { copy_one(ic, 0, 0u); });
     const GateRows gr = gate_rows<BM>(e, m0, M);
     stage_epilogue_rows<BN>(e, gr, lds0 + ROWS, wave, 4, n0, N);
 #pragma unroll
-    for (int t = 0; t < NS; ++t)
+    for (int t = 1; t < NS; ++t)
         if (t < nk) static_for<0, NL>([&](auto ic) { copy_one(ic, t, (uint32_t)(t * STAGE)); });
     if (nk >= NS) wait_vmcnt<NL * (NS - 1)>(); else wait_vmcnt<0>();
     asm volatile("s_barrier" ::: "memory");
-    if (e.warm_lines) {                             // cache warm-up for a later launch, as in the 256-row tiles of four waves
-        const uint32_t first = nb > 256 ? (uint32_t)nb - 256u : 0u, cnt = (uint32_t)nb - first;
-        const uint32_t per = (e.warm_lines + cnt - 1u) / cnt;
-        if ((uint32_t)b >= first)
-            for (uint32_t t = (uint32_t)wave * 64u; t < per; t += 256) {
-                uint32_t line = ((uint32_t)b - first) * per + t + (uint32_t)lane;
-                line = line < e.warm_lines ? line : e.warm_lines - 1u;
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" :: "s"(lds0 + DUMMY), "v"(line * 128u), "s"(e.warm) : "memory");
-            }
-    }
+    warm_caches(e, lds0 + DUMMY, nb, b, wave, 4);
+    if (nk == 1) wait_vmcnt<0>();                   // (otherwise the last k-tile's wait covers it)
     static_for<0, S>([&](auto pc) { constexpr int p = decltype(pc)::value; hold_acc<(p < AGPR)>(acc[p / MI][p % MI]); });
     settle_mfma();
 

@@ -113,26 +113,16 @@ gemm_bf16_wide_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W
     constexpr auto C0 = std::integral_constant<int, 0>{};
     constexpr auto C1 = std::integral_constant<int, 1>{};
 
+    static_for<0, NL>([&](auto ic) { copy_one(ic, 0, 0); });
     const GateRows gr = gate_rows<BM>(e, m0, M);
     stage_epilogue_rows<BN>(e, gr, lds0 + ROWS, wave, 4, n0, N);
-    static_for<0, NL>([&](auto ic) { copy_one(ic, 0, 0); });
     if (nk > 1) {
         static_for<0, FIRST_TILE>([&](auto ic) { copy_one(ic, 1, STAGE); });
         wait_vmcnt<FIRST_TILE>();
     } else wait_vmcnt<0>();
     asm volatile("s_barrier" ::: "memory");
-    // Cache warm-up for a later launch (see Epilogue::warm): the lines are dealt over the workgroups of the last round, one
-    // word per line and lane, into LDS that nobody reads (a register destination would be waited for).
-    if (e.warm_lines) {
-        const uint32_t first = nb > 256 ? (uint32_t)nb - 256u : 0u, cnt = (uint32_t)nb - first;
-        const uint32_t per = (e.warm_lines + cnt - 1u) / cnt;
-        if ((uint32_t)b >= first)
-            for (uint32_t t = (uint32_t)wave * 64u; t < per; t += 256) {
-                uint32_t line = ((uint32_t)b - first) * per + t + (uint32_t)lane;
-                line = line < e.warm_lines ? line : e.warm_lines - 1u;
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" :: "s"(lds0 + DUMMY), "v"(line * 128u), "s"(e.warm) : "memory");
-            }
-    }
+    warm_caches(e, lds0 + DUMMY, nb, b, wave, 4);
+    if (nk == 1) wait_vmcnt<0>();                   // (otherwise the last k-tile's wait covers it)
     static_for<0, RD>([&](auto rc) { read_one(rc, C0, a0, w0); });
     static_for<0, S>([&](auto pc) { constexpr int p = decltype(pc)::value; hold_acc<(p < kAgprPieces)>(acc[p / MI][p % MI]); });
     settle_mfma();
