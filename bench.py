@@ -258,7 +258,7 @@ def main():
         peaks = calibrate(torch, drf)
         gm = fam["gemm"]
         g_ach = gm["work"] / (gm["ms"] * 1e-3) / 1e12 if gm["ms"] > 0 else 0.0
-        gemm = {"kernel": "gemm_bf16_xl_kernel (all bf16 GEMM launches of one drf_sample call)", "achieved": g_ach,
+        gemm = {"kernel": "gemm_bf16_*_kernel (all bf16 GEMM launches of one drf_sample call)", "achieved": g_ach,
                 "frac": g_ach / PEAK_BF16_TFLOPS, "launches": gm["launches"],
                 "avg_launch_us": gm["ms"] * 1e3 / max(gm["launches"], 1), "flops_per_launch": gm["work"] / max(gm["launches"], 1),
                 "traffic": GEMM_TRAFFIC_BYTES_PER_LAUNCH.get(args.config) if default_workload else None}

@@ -367,8 +367,8 @@ __global__ void __launch_bounds__(NW * 64) attn_bf16_kernel(const AttnArgs a, fl
 }
 
 // fp32 on the fp32 matrix instruction (16x16x4).  A workgroup takes 16 queries of one (slot, head), its four waves the
-// kv rows in steps of 16 TS (wave w: steps w, w + 4, ...; TS == 1 for up to 64 rows, where two of the waves had none), each with its own online softmax; the states are combined through
-// LDS.  Scores are computed transposed (S^T = K Q^T): a lane owns query lane % 16 and, per 16-row tile, kv rows
+// kv rows in steps of 16 TS (wave w: steps w, w + 4, ...; TS == 1 for up to 64 rows, where with 2 two of the waves have
+// none), each with its own online softmax; the states are combined through LDS.  Scores are computed transposed (S^T = K Q^T): a lane owns query lane % 16 and, per 16-row tile, kv rows
 // 4 * (lane / 16) + (0..3), which are the k-slices the PV product takes them in.  Operands go from memory straight to
 // registers; a launch of this path is a few round trips (2 slots x 4 heads x 64 rows, d = 32: 46 -> 6 us against eight
 // lanes per query on vector FMAs).  DQ = ceil(d / 16); VEC: head width and strides allow 16-byte loads of Q and K.

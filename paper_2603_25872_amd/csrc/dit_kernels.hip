@@ -92,12 +92,11 @@ __global__ void __launch_bounds__(256) patch_embed_kernel(const float* __restric
     f32x4m acc[kPatchTiles];
 #pragma unroll
     for (int i = 0; i < kPatchTiles; ++i) acc[i] = (f32x4m){ 0.f, 0.f, 0.f, 0.f };
-    // bias and position code are asked for with the operands, not after them
-    f32x4m add[kPatchTiles];
+    f32x4m code[kPatchTiles];                       // position code, asked for with the operands and not after them
 #pragma unroll
     for (int i = 0; i < kPatchTiles; ++i) {
         const int j = first + i * 16 + 4 * quarter, jc = j < dm.D ? j : 0;      // hidden is a multiple of 4
-        add[i] = *reinterpret_cast<const f32x4m*>(pos + (size_t)t * dm.D + jc);
+        code[i] = *reinterpret_cast<const f32x4m*>(pos + (size_t)t * dm.D + jc);
     }
     for (int k0 = 0; k0 < dm.P; k0 += 16) {
         f32x4m tok = { 0.f, 0.f, 0.f, 0.f }, wf[kPatchTiles];
@@ -130,7 +129,7 @@ __global__ void __launch_bounds__(256) patch_embed_kernel(const float* __restric
         const int j = first + i * 16 + 4 * quarter;
         if (j < dm.D) {
             const f32x4m bj = *reinterpret_cast<const f32x4m*>(b + j);
-            *reinterpret_cast<f32x4m*>(resid + (size_t)m * dm.D + j) = acc[i] + bj + add[i];
+            *reinterpret_cast<f32x4m*>(resid + (size_t)m * dm.D + j) = acc[i] + bj + code[i];
         }
     }
 }
