@@ -553,7 +553,10 @@ drf_status launch_patch_embed(const float* x, const SlotMap& map, const float* w
         else
             hipLaunchKernelGGL((patch_embed_kernel<false, TILES>), grid, dim3(256), 0, st, x, map, w, b, pos, dm, M, resid);
     };
-    if ((M + 15) / 16 < 64) go(std::integral_constant<int, 2>{});
+    // Few rows: narrower column groups, so that more CUs pull the weights (two tiles against six a wave, hidden 1152: 1024 rows 6.1
+    // and 7.2 us, 3072 rows 10.1 and 10.5; 4096 rows 13.0 and 11.5, where every group gathers the patches again; hidden 384: 3072
+    // rows 6.2 and 7.0; hidden 128: 64 rows 3.9 and 4.8).
+    if (M < 4096) go(std::integral_constant<int, 2>{});
     else go(std::integral_constant<int, 6>{});
     DRF_HIP(hipGetLastError());
     return DRF_OK;
