@@ -1108,6 +1108,14 @@ extern "C" drf_status drf_probe_gemm_bf16(const void* A, const void* W, int M, i
                             split ? probe_splitk : nullptr);
 }
 
+extern "C" drf_status drf_probe_gemm_route(int M, int N, int K, int split, int* route)
+{
+    if (!route || M < 1 || N < 1 || K < 1 || K % 64 != 0 || split < 0 || split > 2) DRF_FAIL(DRF_EINVAL, "bad argument");
+    const GemmRoute r = gemm_route(M, N, K, split > 0, split > 1);
+    route[0] = r.tile; route[1] = r.splits; route[2] = r.first_tile; route[3] = r.first_rows;
+    return DRF_OK;
+}
+
 extern "C" drf_status drf_probe_attn_bf16(const void* qkv, void* out, int slots, int tokens, int heads, int head_dim,
                                           void* hip_stream)
 {

@@ -674,6 +674,14 @@ double pick_tile(int M, int N, int K, bool may_split, bool leave, int* id, int* 
 
 size_t gemm_splitk_scratch_bytes() { return kSplitKScratchFloats * sizeof(float); }
 
+GemmRoute gemm_route(int M, int N, int K, bool may_split, bool leave)
+{
+    GemmRoute r{ 0, 1, 0, 0 };
+    const double us = pick_tile(M, N, K, may_split, leave, &r.tile, &r.splits);
+    if (r.splits == 1 && M >= 2048) r.first_rows = pick_row_split(M, N, K, us, &r.first_tile, &r.tile);
+    return r;
+}
+
 drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st,
                             int variant, float* splitk_scratch, PartialSum* leave)
 {
@@ -688,8 +696,8 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
         DRF_FAIL(DRF_ESHAPE, "bf16 GEMM operand exceeds 2^31 elements");
     int v = variant, splits = 1, va = 0, rows_a = 0;
     if (v == 0) {
-        const double us = pick_tile(M, N, K, splitk_scratch != nullptr, leave != nullptr, &v, &splits);
-        if (splits == 1 && M >= 2048) rows_a = pick_row_split(M, N, K, us, &va, &v);
+        const GemmRoute r = gemm_route(M, N, K, splitk_scratch != nullptr, leave != nullptr);
+        v = r.tile; splits = r.splits; va = r.first_tile; rows_a = r.first_rows;
     } else if (v >= 100) {
         splits = v / 100;
         v %= 100;

@@ -25,7 +25,7 @@ SYMBOLS = ["drf_denoiser_weight_count", "drf_denoiser_create", "drf_denoiser_des
            "drf_plan_build", "drf_last_error"]
 # include/drf_measure.h: test and measurement hooks
 MEASURE_SYMBOLS = ["drf_eps_trace", "drf_profile_enable", "drf_profile_read", "drf_probe_gemm_bf16",
-                   "drf_probe_attn_bf16", "drf_probe_cross_attn_bf16", "drf_probe_attn_route", "drf_probe_update_fused", "drf_graph_stats", "drf_calibrate_mfma_bf16", "drf_calibrate_copy"]
+                   "drf_probe_attn_bf16", "drf_probe_cross_attn_bf16", "drf_probe_attn_route", "drf_probe_gemm_route", "drf_probe_update_fused", "drf_graph_stats", "drf_calibrate_mfma_bf16", "drf_calibrate_copy"]
 STATIC_SCRATCH_BYTES = 48 << 20
 
 
@@ -95,6 +95,7 @@ def lib():
         L.drf_probe_attn_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]
         L.drf_probe_cross_attn_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p] + [C.c_int] * 7 + [C.c_void_p]
         L.drf_probe_attn_route.argtypes = [C.c_int] * 6
+        L.drf_probe_gemm_route.argtypes = [C.c_int] * 4 + [C.c_void_p]
         L.drf_last_error.restype = C.c_char_p
         _lib = L
     return _lib
@@ -227,6 +228,13 @@ def probe_gemm_bf16(A, W, bias, out=None, variant=0):
     _check(lib().drf_probe_gemm_bf16(_dev(A, torch.bfloat16), _dev(W, torch.bfloat16), M, N, K,
                                      _dev(out, torch.bfloat16), _dev(bias, torch.float32), variant, _stream()))
     return out
+
+
+def probe_gemm_route(M, N, K, split=1):
+    """(tile, parts of K, tile of the first rows, first rows) of a bf16 GEMM (host only, see include/drf_measure.h)."""
+    route = (C.c_int * 4)()
+    _check(lib().drf_probe_gemm_route(M, N, K, split, route))
+    return tuple(route)
 
 
 def probe_attn_bf16(qkv, slots, tokens, heads, head_dim, out=None):

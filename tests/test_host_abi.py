@@ -214,6 +214,16 @@ def test_wide_heads_share_kv_between_two_query_blocks_from_the_second_round_on(d
     assert route(64, 96, 256, 4, d) == 1 and route(8, 128, 256, 4, d) == 1
 
 
+def test_gemm_routes_are_readable():
+    """Small problems split K where they may, a part-filled last round goes to a second launch, bad arguments are refused."""
+    tile, parts, first_tile, first_rows = drf.probe_gemm_route(512, 1152, 4608, 1)
+    assert parts > 1 and (first_tile, first_rows) == (0, 0)
+    assert drf.probe_gemm_route(512, 1152, 4608, 0)[1] == 1
+    for args in ((0, 64, 64, 0), (64, 64, 72, 0), (64, 64, 64, 3)):
+        with pytest.raises(drf.DrfError):
+            drf.probe_gemm_route(*args)
+
+
 def test_bf16_gemm_refuses_the_fp32_paths_activation():
     """SiLU is an epilogue of the fp32 GEMM only: the bf16 launch must say so (checked on the host, before anything else is looked
     at) instead of storing without it."""
