@@ -216,7 +216,7 @@ def test_wide_heads_share_kv_between_two_query_blocks_from_the_second_round_on(d
 
 def test_gemm_routes_are_readable():
     """Small problems split K where they may, a part-filled last round goes to a second launch, bad arguments are refused."""
-    tile, parts, first_tile, first_rows = drf.probe_gemm_route(512, 1152, 4608, 1)
+    tile, parts, first_tile, first_rows = drf.probe_gemm_route(512, 1152, 4608, 2)
     assert parts > 1 and (first_tile, first_rows) == (0, 0)
     assert drf.probe_gemm_route(512, 1152, 4608, 0)[1] == 1
     for args in ((0, 64, 64, 0), (64, 64, 72, 0), (64, 64, 64, 3)):
