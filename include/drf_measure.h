@@ -54,12 +54,12 @@ drf_status drf_probe_gemm_bf16(const void* A, const void* W, int M, int N, int K
                                int variant, void* hip_stream);
 
 /*
- * How the forward pass runs a bf16 GEMM of these sizes (host only): route[0] = tile number, route[1] = parts that K is split
- * in, route[2], route[3] = tile of the first rows and how many they are, when the rest follows in a second launch (0: one launch).
- * split: 0 = K is not split (the probe above), 1 = it may be, 2 = it may be and the launch that follows adds the partial tiles
- * (attention projection, second MLP layer).
+ * How a bf16 GEMM of these sizes is run (host only): route[0] = tile number, route[1] = parts that K is split in, route[2],
+ * route[3] = tile of the first rows and how many they are, when the rest follows in a second launch (0: one launch).
+ * kind: 0 = the probe above, unsplit; the forward pass's 1 = QKV projection, 2 = attention projection and second MLP layer where
+ * the LayerNorm that follows can add partial tiles, 3 = first MLP layer, 4 = others.
  */
-drf_status drf_probe_gemm_route(int M, int N, int K, int split, int* route);
+drf_status drf_probe_gemm_route(int M, int N, int K, int kind, int rows_per_slot, int* route);
 
 /*
  * Measurement hook: one launch of the bf16 self-attention kernel.  qkv: DEVICE bf16

@@ -131,7 +131,7 @@ struct PartialSum { const float* part; int splits, ldp; size_t stride; };
 // How variant 0 of the launch below runs: `tile` (a number of kTiles in gemm.hip) with K in `splits` parts, the first
 // first_rows rows (0: none) ahead of the others with first_tile.
 struct GemmRoute { int tile, splits, first_tile, first_rows; };
-GemmRoute gemm_route(int M, int N, int K, bool may_split, bool leave);
+GemmRoute gemm_route(int M, int N, int K, const Epilogue& e, bool may_split, bool leave);
 // C[M][N] = A[M][K] . W[N][K]^T, then the epilogue.  bf16: K % 64 == 0.
 // variant 0: the tile shape and split are chosen from the problem size; > 0 forces one (measurement and tile tests).
 // splitk_scratch: gemm_splitk_scratch_bytes() of device memory, or NULL; with it, problems of few tiles and a long

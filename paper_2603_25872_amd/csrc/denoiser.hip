@@ -1108,10 +1108,13 @@ extern "C" drf_status drf_probe_gemm_bf16(const void* A, const void* W, int M, i
                             split ? probe_splitk : nullptr);
 }
 
-extern "C" drf_status drf_probe_gemm_route(int M, int N, int K, int split, int* route)
+extern "C" drf_status drf_probe_gemm_route(int M, int N, int K, int kind, int rows_per_slot, int* route)
 {
-    if (!route || M < 1 || N < 1 || K < 1 || K % 64 != 0 || split < 0 || split > 2) DRF_FAIL(DRF_EINVAL, "bad argument");
-    const GemmRoute r = gemm_route(M, N, K, split > 0, split > 1);
+    if (!route || M < 1 || N < 1 || K < 1 || K % 64 != 0 || kind < 0 || kind > 4 || rows_per_slot < 1) DRF_FAIL(DRF_EINVAL, "bad argument");
+    Epilogue e{};
+    e.mode = kind == 1 ? EPI_STORE_HEADS : kind == 2 ? EPI_STORE_GATED : kind == 3 ? EPI_STORE_GELU : EPI_STORE;
+    e.rows_per_slot = rows_per_slot;
+    const GemmRoute r = gemm_route(M, N, K, e, kind != 0, kind == 2);
     route[0] = r.tile; route[1] = r.splits; route[2] = r.first_tile; route[3] = r.first_rows;
     return DRF_OK;
 }

@@ -68,7 +68,7 @@ __device__ inline void store_epilogue4(const Epilogue& e, int m, int n, f32x4 v,
 }
 
 // ------------------------------------------------------------------ bf16 MFMA
-// The kernel for small problems and for what the 4-wave kernels leave: BM x BN x 64 block tile, waves as WM x WN (x WK), wave
+// The kernel for small problems and for what the 4-wave kernels leave (see wide_form): BM x BN x 64 block tile, waves as WM x WN (x WK), wave
 // tile (BM/WM) x (BN/WN) built from 16x16x32 MFMAs so that widths only need to be multiples of 16.
 //  - operands go HBM -> LDS directly (global_load_lds_dwordx4: every lane supplies its own
 //    global address and the wave's 64 x 16 bytes land contiguously in LDS), NS stages so the copy of the next k-tiles overlaps
@@ -607,6 +607,22 @@ double model_us(const TileModel& t, int M, int N, int K, int splits, bool leave)
     return us;
 }
 
+// The 256-row tiles 2 and 3 on eight waves (20, 19) where the epilogue weighs more than the loop: four waves gain 5-10 % in the
+// loop, but a SIMD's one wave has nothing to run beside its epilogue's arithmetic and address work.  Inside a pass, eight waves
+// against four, 256 x 256 | 256 x 288 tiles:
+//  - GELU: 8192 x 1536 x 384 18.1 : 20.5 | 20.1 : 22.0 us, 16384 x 4608 x 1152 163.7 : 170.2 | 155.3 : 162.1; K = 2048 even (2048 to 8192
+//    rows of 8192 columns 59.8 : 59.0, 112.9 : 113.8, 226.1 : 219.7 | 63.6 : 62.2, 119.7 : 124.7, 241.7 : 233.7);
+//  - head-major planes, slots of whole 32-row passes: K = 384 17.9 : 18.8 | 21.1 : 21.6, K = 512 even (19.60 : 19.56 | 21.0 : 21.9),
+//    K = 768 22.5 : 22.2 | 25.0 : 24.7, K = 1152 34.5 : 31.8 | 121.1 : 110.1;
+//  - other slot lengths: K = 768 42.9 : 43.8 | 30.3 : 32.1, K = 1152 128.6 : 138.9 | 112.4 : 118.9, K = 2048 101.9 : 96.2 | 110.9 : 106.6.
+// Gated, residual and plain stores stay on four at every K (24576 x 1152 x 1152 plain 70.8 : 63.0, residual 106.8 : 102.5, gated even).
+int wide_form(int tile, int K, const Epilogue& e)
+{
+    if (tile != 2 && tile != 3) return tile;
+    const bool eight = e.mode == EPI_STORE_GELU ? K < 2048 : e.mode == EPI_STORE_HEADS && K < (e.rows_per_slot % 32 == 0 ? 512 : 1536);
+    return !eight ? tile : tile == 2 ? 20 : 19;
+}
+
 // Rows m_first .. M - 1 of the problem with tile v (m_first a multiple of the tile's height).
 drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first)
 {
@@ -624,6 +640,8 @@ drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, in
     case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, m_first);
+    case 19: return launch_bf16_xl<256, 256, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 20: return launch_bf16_xl<256, 288, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
     case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2, 1, true>(A, W, M, N, K, e, st, m_first);
     default: return launch_bf16_xl<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st, m_first);      // 5, or a number that names no tile
     }
@@ -674,11 +692,13 @@ double pick_tile(int M, int N, int K, bool may_split, bool leave, int* id, int* 
 
 size_t gemm_splitk_scratch_bytes() { return kSplitKScratchFloats * sizeof(float); }
 
-GemmRoute gemm_route(int M, int N, int K, bool may_split, bool leave)
+GemmRoute gemm_route(int M, int N, int K, const Epilogue& e, bool may_split, bool leave)
 {
     GemmRoute r{ 0, 1, 0, 0 };
     const double us = pick_tile(M, N, K, may_split, leave, &r.tile, &r.splits);
     if (r.splits == 1 && M >= 2048) r.first_rows = pick_row_split(M, N, K, us, &r.first_tile, &r.tile);
+    r.tile = wide_form(r.tile, K, e);
+    r.first_tile = wide_form(r.first_tile, K, e);
     return r;
 }
 
@@ -696,7 +716,7 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
         DRF_FAIL(DRF_ESHAPE, "bf16 GEMM operand exceeds 2^31 elements");
     int v = variant, splits = 1, va = 0, rows_a = 0;
     if (v == 0) {
-        const GemmRoute r = gemm_route(M, N, K, splitk_scratch != nullptr, leave != nullptr);
+        const GemmRoute r = gemm_route(M, N, K, e, splitk_scratch != nullptr, leave != nullptr);
         v = r.tile; splits = r.splits; va = r.first_tile; rows_a = r.first_rows;
     } else if (v >= 100) {
         splits = v / 100;

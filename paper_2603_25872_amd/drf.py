@@ -95,7 +95,7 @@ def lib():
         L.drf_probe_attn_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]
         L.drf_probe_cross_attn_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p] + [C.c_int] * 7 + [C.c_void_p]
         L.drf_probe_attn_route.argtypes = [C.c_int] * 6
-        L.drf_probe_gemm_route.argtypes = [C.c_int] * 4 + [C.c_void_p]
+        L.drf_probe_gemm_route.argtypes = [C.c_int] * 5 + [C.c_void_p]
         L.drf_last_error.restype = C.c_char_p
         _lib = L
     return _lib
@@ -230,10 +230,10 @@ def probe_gemm_bf16(A, W, bias, out=None, variant=0):
     return out
 
 
-def probe_gemm_route(M, N, K, split=1):
+def probe_gemm_route(M, N, K, kind=0, rows_per_slot=256):
     """(tile, parts of K, tile of the first rows, first rows) of a bf16 GEMM (host only, see include/drf_measure.h)."""
     route = (C.c_int * 4)()
-    _check(lib().drf_probe_gemm_route(M, N, K, split, route))
+    _check(lib().drf_probe_gemm_route(M, N, K, kind, rows_per_slot, route))
     return tuple(route)
 
 

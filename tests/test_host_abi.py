@@ -219,9 +219,23 @@ def test_gemm_routes_are_readable():
     tile, parts, first_tile, first_rows = drf.probe_gemm_route(512, 1152, 4608, 2)
     assert parts > 1 and (first_tile, first_rows) == (0, 0)
     assert drf.probe_gemm_route(512, 1152, 4608, 0)[1] == 1
-    for args in ((0, 64, 64, 0), (64, 64, 72, 0), (64, 64, 64, 3)):
+    for args in ((0, 64, 64, 0), (64, 64, 72, 0), (64, 64, 64, 5), (64, 64, 64, 1, 0)):
         with pytest.raises(drf.DrfError):
             drf.probe_gemm_route(*args)
+
+
+@pytest.mark.parametrize("tile,eight,M,N", [(2, 20, 16384, 0), (3, 19, 16384, 256)])
+def test_gemm_256_row_tiles_take_the_form_that_measured_faster(tile, eight, M, N):
+    """One round of 256 x 288 or 256 x 256 tiles: eight waves where GELU or the head-major store weighs more than the loop, four
+    elsewhere (times inside a pass beside the rule)."""
+    def route(K, kind, rows_per_slot=256):
+        cols = N or 288
+        return drf.probe_gemm_route(M, 4 * cols, K, kind, rows_per_slot)[0]
+    for K in (384, 512, 768, 1152, 1536, 2048, 4608):
+        assert route(K, 3) == (eight if K < 2048 else tile)
+        assert route(K, 1) == (eight if K < 512 else tile)
+        assert route(K, 1, 252) == (eight if K < 1536 else tile)
+        assert route(K, 2) == route(K, 4) == route(K, 0) == tile
 
 
 def test_bf16_gemm_refuses_the_fp32_paths_activation():
