@@ -578,11 +578,15 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
 // how many of the chip's CUs pull operands at once (M = 512, N = K = 1152: 7.1 us on 144 64 x 64 tiles whose two wave
 // groups split K, 12.5 on 36 128 x 128 tiles).  Larger ones lose by a part-filled round: the tiles between 128 x 128 and 256 x 256
 // are there for their counts (M = 8192, N = 1152, K = 4608: 77.6 us on 256 tiles of 256 x 144, 88.1 on 160 of 256 x 256).
+// 13 and 18 are the 256 x 144 tile on two pairs of waves and on eight.  Inside a pass, eight against pairs: K = 384 (8192 x 1152) 14.0 : 17.2
+// us, K = 768 (4096 x 2304) 19.7 : 22.0, K = 1152 (2560 x 3456) 24.6 : 26.9, K = 1536 (16384 x 384) 28.5 : 29.2, K = 2048 (4096 x 2048)
+// 42.9 : 42.4, K = 3072 (8192 x 768) 52.5 : 48.2, K = 4608 (8192 x 1152) 81.3 : 71.8; 18's constants put the line at K = 1344.
 struct TileModel { int id, bm, bn, wk, per_cu; double base, round, lat, thr, red0, red1; };     // red0 = 0: never split
 const TileModel kTiles[] = {
     {  2, 256, 288, 1, 1, 0.00, 8.99, 1.59, 0.00, 0.0, 0.0 },
     {  3, 256, 256, 1, 1, 0.00, 7.66, 1.31, 0.00, 0.0, 0.0 },
     { 13, 256, 144, 1, 1, 0.10, 8.17, 0.94, 0.00, 0.0, 0.0 },
+    { 18, 256, 144, 1, 1, 0.10, 6.50, 1.02, 0.00, 0.0, 0.0 },
     { 14, 256, 128, 1, 1, 0.24, 4.29, 0.85, 0.00, 0.0, 0.0 },
     { 16, 128, 144, 1, 1, 0.51, 4.58, 0.54, 0.00, 0.0, 0.0 },
     {  4, 128, 128, 1, 2, 0.98, 2.65, 0.64, 0.51, 0.0, 0.0 },
@@ -640,6 +644,7 @@ drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, in
     case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, m_first);
+    case 18: return launch_bf16_xl<256, 144, 64, 3, 8, 1, 1, true>(A, W, M, N, K, e, st, m_first);
     case 19: return launch_bf16_xl<256, 256, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
     case 20: return launch_bf16_xl<256, 288, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
     case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2, 1, true>(A, W, M, N, K, e, st, m_first);

@@ -81,10 +81,10 @@ def test_gemm_bf16_small_tiles_and_splits(torch, drf, orc, variant, M, N, K):
             drf.probe_gemm_bf16(A[:, :192].contiguous().cuda(), W[:, :192].contiguous().cuda(), torch.from_numpy(b).cuda(), variant=variant)
 
 
-@pytest.mark.parametrize("variant", [2, 3, 13, 16, 17, 19, 20])
+@pytest.mark.parametrize("variant", [2, 3, 13, 16, 17, 18, 19, 20])
 @pytest.mark.parametrize("M,N,K", [(300, 292, 64), (33, 8, 128), (256, 288, 192), (517, 580, 256), (130, 148, 320), (512, 576, 1088)])
 def test_gemm_bf16_four_wave_tiles(torch, drf, orc, variant, M, N, K):
-    """With the eight-wave forms of the 256-row ones (19, 20).  1 to 5 and 17 k-tiles: fewer than the stages, as many, one more, odd and even numbers; whole and ragged tiles."""
+    """With the eight-wave forms of the 256-row ones (18, 19, 20).  1 to 5 and 17 k-tiles: fewer than the stages, as many, one more, odd and even numbers; whole and ragged tiles."""
     rng = np.random.default_rng(M + N + K)
     A = bf16_round(torch, rng.standard_normal((M, K)))
     W = bf16_round(torch, rng.standard_normal((N, K)) * 0.1)

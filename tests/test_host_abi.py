@@ -238,6 +238,12 @@ def test_gemm_256_row_tiles_take_the_form_that_measured_faster(tile, eight, M, N
         assert route(K, 2) == route(K, 4) == route(K, 0) == tile
 
 
+@pytest.mark.parametrize("K,tile", [(384, 18), (768, 18), (1152, 18), (2048, 13), (4608, 13)])
+def test_gemm_one_round_of_256_x_144_tiles(K, tile):
+    """Eight waves for short K, two pairs of waves for long K (times inside a pass beside the tile table)."""
+    assert drf.probe_gemm_route(8192, 1152, K, 2) == (tile, 1, 0, 0)
+
+
 def test_bf16_gemm_refuses_the_fp32_paths_activation():
     """SiLU is an epilogue of the fp32 GEMM only: the bf16 launch must say so (checked on the host, before anything else is looked
     at) instead of storing without it."""
