@@ -615,15 +615,20 @@ double model_us(const TileModel& t, int M, int N, int K, int splits, bool leave)
 // loop, but a SIMD's one wave has nothing to run beside its epilogue's arithmetic and address work.  Inside a pass, eight waves
 // against four, 256 x 256 | 256 x 288 tiles:
 //  - GELU: 8192 x 1536 x 384 18.1 : 20.5 | 20.1 : 22.0 us, 16384 x 4608 x 1152 163.7 : 170.2 | 155.3 : 162.1; K = 2048 even (2048 to 8192
-//    rows of 8192 columns 59.8 : 59.0, 112.9 : 113.8, 226.1 : 219.7 | 63.6 : 62.2, 119.7 : 124.7, 241.7 : 233.7);
+//    rows of 8192 columns 59.8 : 59.0, 112.9 : 113.8, 226.1 : 219.7 | 63.6 : 62.2, 119.7 : 124.7, 241.7 : 233.7).  A single round of K = 1152
+//    gains 1 us with its weights in the cache (2816 rows 32.5 : 33.6) and loses 3 with weights from HBM, which two stages wait for at
+//    every k-tile (the text model, whose MLP no launch warms: 2520 to 3276 rows 36.9 : 33.6 to 36.9 : 35.4): it stays on four;
 //  - head-major planes, slots of whole 32-row passes: K = 384 17.9 : 18.8 | 21.1 : 21.6, K = 512 even (19.60 : 19.56 | 21.0 : 21.9),
 //    K = 768 22.5 : 22.2 | 25.0 : 24.7, K = 1152 34.5 : 31.8 | 121.1 : 110.1;
 //  - other slot lengths: K = 768 42.9 : 43.8 | 30.3 : 32.1, K = 1152 128.6 : 138.9 | 112.4 : 118.9, K = 2048 101.9 : 96.2 | 110.9 : 106.6.
 // Gated, residual and plain stores stay on four at every K (24576 x 1152 x 1152 plain 70.8 : 63.0, residual 106.8 : 102.5, gated even).
-int wide_form(int tile, int K, const Epilogue& e)
+int wide_form(int tile, int rows, int N, int K, const Epilogue& e)
 {
     if (tile != 2 && tile != 3) return tile;
-    const bool eight = e.mode == EPI_STORE_GELU ? K < 2048 : e.mode == EPI_STORE_HEADS && K < (e.rows_per_slot % 32 == 0 ? 512 : 1536);
+    const int cols = tile == 2 ? 288 : 256;
+    const bool one_round = ((rows + 255) / 256) * (long long)((N + cols - 1) / cols) <= 256;
+    const bool eight = e.mode == EPI_STORE_GELU ? K < (one_round ? 1024 : 2048)
+                                                : e.mode == EPI_STORE_HEADS && K < (e.rows_per_slot % 32 == 0 ? 512 : 1536);
     return !eight ? tile : tile == 2 ? 20 : 19;
 }
 
@@ -702,8 +707,8 @@ GemmRoute gemm_route(int M, int N, int K, const Epilogue& e, bool may_split, boo
     GemmRoute r{ 0, 1, 0, 0 };
     const double us = pick_tile(M, N, K, may_split, leave, &r.tile, &r.splits);
     if (r.splits == 1 && M >= 2048) r.first_rows = pick_row_split(M, N, K, us, &r.first_tile, &r.tile);
-    r.tile = wide_form(r.tile, K, e);
-    r.first_tile = wide_form(r.first_tile, K, e);
+    r.tile = wide_form(r.tile, M - r.first_rows, N, K, e);
+    r.first_tile = wide_form(r.first_tile, r.first_rows, N, K, e);
     return r;
 }
 

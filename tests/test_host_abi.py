@@ -224,18 +224,18 @@ def test_gemm_routes_are_readable():
             drf.probe_gemm_route(*args)
 
 
-@pytest.mark.parametrize("tile,eight,M,N", [(2, 20, 16384, 0), (3, 19, 16384, 256)])
-def test_gemm_256_row_tiles_take_the_form_that_measured_faster(tile, eight, M, N):
-    """One round of 256 x 288 or 256 x 256 tiles: eight waves where GELU or the head-major store weighs more than the loop, four
-    elsewhere (times inside a pass beside the rule)."""
-    def route(K, kind, rows_per_slot=256):
-        cols = N or 288
-        return drf.probe_gemm_route(M, 4 * cols, K, kind, rows_per_slot)[0]
-    for K in (384, 512, 768, 1152, 1536, 2048, 4608):
-        assert route(K, 3) == (eight if K < 2048 else tile)
-        assert route(K, 1) == (eight if K < 512 else tile)
-        assert route(K, 1, 252) == (eight if K < 1536 else tile)
-        assert route(K, 2) == route(K, 4) == route(K, 0) == tile
+@pytest.mark.parametrize("tile,eight,cols", [(2, 20, 288), (3, 19, 256)])
+def test_gemm_256_row_tiles_take_the_form_that_measured_faster(tile, eight, cols):
+    """One and two rounds of 256 x 288 or 256 x 256 tiles: eight waves where GELU or the head-major store weighs more than the
+    loop, four elsewhere (times inside a pass beside the rule)."""
+    for rounds in (1, 2):
+        def route(K, kind, rows_per_slot=256):
+            return drf.probe_gemm_route(16384, 4 * rounds * cols, K, kind, rows_per_slot)[0]
+        for K in (384, 512, 768, 1152, 1536, 2048, 4608):
+            assert route(K, 3) == (eight if K < 1024 * rounds else tile)
+            assert route(K, 1) == (eight if K < 512 else tile)
+            assert route(K, 1, 252) == (eight if K < 1536 else tile)
+            assert route(K, 2) == route(K, 4) == route(K, 0) == tile
 
 
 @pytest.mark.parametrize("K,tile", [(384, 18), (768, 18), (1152, 18), (2048, 13), (4608, 13)])
