@@ -581,6 +581,8 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
 // 13 and 18 are the 256 x 144 tile on two pairs of waves and on eight.  Inside a pass, eight against pairs: K = 384 (8192 x 1152) 14.0 : 17.2
 // us, K = 768 (4096 x 2304) 19.7 : 22.0, K = 1152 (2560 x 3456) 24.6 : 26.9, K = 1536 (16384 x 384) 28.5 : 29.2, K = 2048 (4096 x 2048)
 // 42.9 : 42.4, K = 3072 (8192 x 768) 52.5 : 48.2, K = 4608 (8192 x 1152) 81.3 : 71.8; 18's constants put the line at K = 1344.
+// 7 has the launches of 193 to 256 tiles of 128 x 96 (inside a pass, against the next best: 2560 x 1152 x 4608 33.7 us, 128 x 144 35.8, 128 x
+// 128 39.8; 8192 x 384 x 1536 14.4, 128 x 128 15.8; 8192 x 384 x 384 7.0 and 7.6), on four waves by two (four by one: 35.7, 15.4, 7.6).
 struct TileModel { int id, bm, bn, wk, per_cu; double base, round, lat, thr, red0, red1; };     // red0 = 0: never split
 const TileModel kTiles[] = {
     {  2, 256, 288, 1, 1, 0.00, 8.99, 1.59, 0.00, 0.0, 0.0 },
@@ -591,6 +593,7 @@ const TileModel kTiles[] = {
     { 16, 128, 144, 1, 1, 0.51, 4.58, 0.54, 0.00, 0.0, 0.0 },
     {  4, 128, 128, 1, 2, 0.98, 2.65, 0.64, 0.51, 0.0, 0.0 },
     {  5, 128, 128, 1, 1, 1.29, 2.95, 0.48, 0.00, 2.9, 1.8 },
+    {  7, 128,  96, 1, 1, 1.39, 2.96, 0.41, 0.00, 0.0, 0.0 },
     { 17,  64, 144, 1, 1, 1.51, 3.13, 0.31, 0.00, 0.0, 0.0 },
     {  6, 128,  64, 1, 1, 1.50, 2.12, 0.32, 0.00, 2.9, 1.9 },
     { 11,  64,  96, 2, 1, 1.43, 2.65, 0.44, 0.00, 0.0, 0.0 },
@@ -642,6 +645,7 @@ drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, in
     case 3: return launch_gemm_wide_256(A, W, M, N, K, e, st, m_first);
     case 4: return launch_bf16_xl<128, 128, 64, 2, 4, 2, 1, true>(A, W, M, N, K, e, st, m_first);
     case 6: return launch_bf16_xl<128, 64, 64, 4, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 7: return launch_bf16_xl<128, 96, 64, 3, 4, 2>(A, W, M, N, K, e, st, m_first);
     case 8:                                         // (16 for whole pairs of k-tiles only, as this number has always been)
         if (K % 128 != 0) DRF_FAIL(DRF_ESHAPE, "bf16 GEMM tile needs K %% 128 == 0 (K=%d)", K);
         [[fallthrough]];
