@@ -580,7 +580,8 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
 // are there for their counts (M = 8192, N = 1152, K = 4608: 77.6 us on 256 tiles of 256 x 144, 88.1 on 160 of 256 x 256).
 // 13 and 18 are the 256 x 144 tile on two pairs of waves and on eight.  Inside a pass, eight against pairs: K = 384 (8192 x 1152) 14.0 : 17.2
 // us, K = 768 (4096 x 2304) 19.7 : 22.0, K = 1152 (2560 x 3456) 24.6 : 26.9, K = 1536 (16384 x 384) 28.5 : 29.2, K = 2048 (4096 x 2048)
-// 42.9 : 42.4, K = 3072 (8192 x 768) 52.5 : 48.2, K = 4608 (8192 x 1152) 81.3 : 71.8; 18's constants put the line at K = 1344.
+// 42.9 : 42.4, K = 3072 (8192 x 768) 52.5 : 48.2, K = 4608 (8192 x 1152) 81.3 : 71.8; 18's constants put the line at K = 1344.  (18 stores by
+// lane swaps; with store_rows QKV of 8192 and 16384 rows of 384 13.1 -> 13.7 and 24.1 -> 25.4, GELU 22.4 -> 23.4, gated even.)
 // 7 has the launches of 193 to 256 tiles of 128 x 96 (inside a pass, against the next best: 2560 x 1152 x 4608 33.7 us, 128 x 144 35.8, 128 x
 // 128 39.8; 8192 x 384 x 1536 14.4, 128 x 128 15.8; 8192 x 384 x 384 7.0 and 7.6), on four waves by two (four by one: 35.7, 15.4, 7.6).
 struct TileModel { int id, bm, bn, wk, per_cu; double base, round, lat, thr, red0, red1; };     // red0 = 0: never split
@@ -653,7 +654,7 @@ drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, in
     case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, m_first);
-    case 18: return launch_bf16_xl<256, 144, 64, 3, 8, 1, 1, true>(A, W, M, N, K, e, st, m_first);
+    case 18: return launch_bf16_xl<256, 144, 64, 3, 8, 1>(A, W, M, N, K, e, st, m_first);
     case 19: return launch_bf16_xl<256, 256, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
     case 20: return launch_bf16_xl<256, 288, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
     case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2, 1, true>(A, W, M, N, K, e, st, m_first);
