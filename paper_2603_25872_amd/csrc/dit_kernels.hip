@@ -553,10 +553,14 @@ drf_status launch_patch_embed(const float* x, const SlotMap& map, const float* w
         else
             hipLaunchKernelGGL((patch_embed_kernel<false, TILES>), grid, dim3(256), 0, st, x, map, w, b, pos, dm, M, resid);
     };
-    // Few rows: narrower column groups, so that more CUs pull the weights (two tiles against six a wave, hidden 1152: 1024 rows 6.1
-    // and 7.2 us, 3072 rows 10.1 and 10.5; 4096 rows 13.0 and 11.5, where every group gathers the patches again; hidden 384: 3072
-    // rows 6.2 and 7.0; hidden 128: 64 rows 3.9 and 4.8).
-    if (M < 4096) go(std::integral_constant<int, 2>{});
+    // Two column tiles a wave or six.  Six gather the patches once for 24 tiles, two put more workgroups on the chip and waste less of a
+    // last group: where a third of the six-tile groups' columns are padding, two are the faster form at every size (us, two against
+    // six: hidden 128 4.5 : 5.6 at 4096 rows, 14.9 : 19.1 at 24576; 256 14.8 : 16.8 at 16384; 512 9.1 : 9.3 and 25.8 : 28.0), otherwise up
+    // to about 2.2 million elements of the stream (384: 9.0 : 9.6 at 5120 rows, 10.3 : 10.1 at 6144, 12.6 : 11.5 at 8192; 640: 8.9 : 9.4 at 3072,
+    // 10.5 : 10.0 at 4096; 768: 7.7 : 8.3 at 2048, 9.6 : 9.4 at 3072, 14.4 : 13.4 at 8192; 1152: 6.3 : 6.9 at 1024, 8.1 : 8.2 at 2048,
+    // 10.8 : 10.6 at 3328, 12.0 : 11.1 at 4096, 36.9 : 34.4 at 16384; 1536: 6.0 : 6.6 at 1024, 9.1 : 8.2 at 2048).
+    const int tiles = (dm.D + 15) / 16, padded = (tiles + 23) / 24 * 24;
+    if (3 * tiles <= 2 * padded || (long long)M * dm.D < 2200000) go(std::integral_constant<int, 2>{});
     else go(std::integral_constant<int, 6>{});
     DRF_HIP(hipGetLastError());
     return DRF_OK;

@@ -212,6 +212,22 @@ def test_fp32_forward_rows_normalised_in_the_gemm(torch, drf, orc, hidden, heads
     check_forward(torch, drf, orc, small_dit(I.COND_TEXT, I.F32, hidden=hidden, heads=heads, depth=1), "loud", slots=slots, tol=TOL_F32, seed=71)
 
 
+@pytest.mark.parametrize("hidden,heads,in_ch,patch,lat,slots", [
+    (276, 4, 5, 1, (33, 31), 8), (276, 4, 4, 2, (66, 62), 8),       # six column tiles a wave, the last group part-filled, scalar and 16-byte weights
+    (276, 4, 5, 1, (33, 31), 7), (132, 2, 5, 1, (33, 31), 17)])     # two: few rows; a group that six would leave mostly empty
+def test_patch_embedding_of_ragged_rows_and_columns(torch, drf, orc, hidden, heads, in_ch, patch, lat, slots):
+    dit = small_dit(I.COND_CLASS, I.F32, hidden=hidden, heads=heads, in_ch=in_ch, patch=patch, lat_h=lat[0], lat_w=lat[1], depth=1)
+    w = I.weights(dit, 48, "loud")
+    rng = np.random.default_rng(58)
+    x = rng.standard_normal((slots, in_ch, *lat)).astype(np.float32)
+    t = rng.integers(0, 1000, size=slots).astype(np.int32)
+    c = make_cond(dit, slots, 68)
+    den = drf.Denoiser(dit, w)
+    got = den.eps_trace(dev(torch, x), dev(torch, t), dev(torch, c), 0).cpu().numpy()
+    den.close()
+    check(got, orc.dit_eps(dit, w, x, t, c, stop_blocks=0), TOL_F32, "resid0")
+
+
 @pytest.mark.parametrize("cond,lat,slots", [(I.COND_CLASS, (32, 32), 65), (I.COND_TEXT, (36, 28), 67), (I.COND_CLASS, (18, 14), 261),
                                             (I.COND_CLASS, (8, 8), 1030)])
 def test_bf16_whole_and_edge_tiles_of_a_fat_pass(torch, drf, orc, cond, lat, slots):
