@@ -594,7 +594,7 @@ const TileModel kTiles[] = {
     { 16, 128, 144, 1, 1, 0.51, 4.58, 0.54, 0.00, 0.0, 0.0 },
     {  4, 128, 128, 1, 2, 0.98, 2.65, 0.64, 0.51, 0.0, 0.0 },
     {  5, 128, 128, 1, 1, 1.29, 2.95, 0.48, 0.00, 2.9, 1.8 },
-    {  7, 128,  96, 1, 1, 1.39, 2.96, 0.41, 0.00, 0.0, 0.0 },
+    {  7, 128,  96, 1, 1, 1.39, 2.96, 0.42, 0.00, 0.0, 0.0 },
     { 17,  64, 144, 1, 1, 1.51, 3.13, 0.31, 0.00, 0.0, 0.0 },
     {  6, 128,  64, 1, 1, 1.50, 2.12, 0.32, 0.00, 2.9, 1.9 },
     { 11,  64,  96, 2, 1, 1.43, 2.65, 0.44, 0.00, 0.0, 0.0 },
@@ -618,8 +618,8 @@ double model_us(const TileModel& t, int M, int N, int K, int splits, bool leave)
 // The 256-row tiles 2 and 3 on eight waves (20, 19) where the epilogue weighs more than the loop: four waves gain 5-10 % in the
 // loop, but a SIMD's one wave has nothing to run beside its epilogue's arithmetic and address work.  Inside a pass, eight waves
 // against four, 256 x 256 | 256 x 288 tiles:
-//  - GELU: 8192 x 1536 x 384 18.1 : 20.5 | 20.1 : 22.0 us, 16384 x 4608 x 1152 163.7 : 170.2 | 155.3 : 162.1; K = 2048 even (2048 to 8192
-//    rows of 8192 columns 59.8 : 59.0, 112.9 : 113.8, 226.1 : 219.7 | 63.6 : 62.2, 119.7 : 124.7, 241.7 : 233.7).  A single round of K = 1152
+//  - GELU: 8192 x 1536 x 384 18.1 : 20.5 | 20.1 : 22.0 us, 16384 x 4608 x 1152 163.7 : 170.2 | 155.3 : 162.1; 16384 x 6144 x 1536
+//    281.6 : 262.6 | 303.0 : 277.8, 8192 x 8192 x 2048 226.1 : 219.7 | 241.7 : 233.7.  A single round of K = 1152
 //    gains 1 us with its weights in the cache (2816 rows 32.5 : 33.6) and loses 3 with weights from HBM, which two stages wait for at
 //    every k-tile (the text model, whose MLP no launch warms: 2520 to 3276 rows 36.9 : 33.6 to 36.9 : 35.4): it stays on four;
 //  - head-major planes, slots of whole 32-row passes: K = 384 17.9 : 18.8 | 21.1 : 21.6, K = 512 even (19.60 : 19.56 | 21.0 : 21.9),
@@ -631,7 +631,7 @@ int wide_form(int tile, int rows, int N, int K, const Epilogue& e)
     if (tile != 2 && tile != 3) return tile;
     const int cols = tile == 2 ? 288 : 256;
     const bool one_round = ((rows + 255) / 256) * (long long)((N + cols - 1) / cols) <= 256;
-    const bool eight = e.mode == EPI_STORE_GELU ? K < (one_round ? 1024 : 2048)
+    const bool eight = e.mode == EPI_STORE_GELU ? K < (one_round ? 1024 : 1536)
                                                 : e.mode == EPI_STORE_HEADS && K < (e.rows_per_slot % 32 == 0 ? 512 : 1536);
     return !eight ? tile : tile == 2 ? 20 : 19;
 }

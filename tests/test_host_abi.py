@@ -232,7 +232,7 @@ def test_gemm_256_row_tiles_take_the_form_that_measured_faster(tile, eight, cols
         def route(K, kind, rows_per_slot=256):
             return drf.probe_gemm_route(16384, 4 * rounds * cols, K, kind, rows_per_slot)[0]
         for K in (384, 512, 768, 1152, 1536, 2048, 4608):
-            assert route(K, 3) == (eight if K < 1024 * rounds else tile)
+            assert route(K, 3) == (eight if K < (1024 if rounds == 1 else 1536) else tile)
             assert route(K, 1) == (eight if K < 512 else tile)
             assert route(K, 1, 252) == (eight if K < 1536 else tile)
             assert route(K, 2) == route(K, 4) == route(K, 0) == tile
@@ -248,6 +248,7 @@ def test_gemm_one_round_of_256_x_144_tiles(K, tile):
 def test_gemm_one_round_of_128_x_96_tiles(M, N, K):
     """193 to 256 of them, where 128 x 128 tiles leave CUs idle and smaller ones need a second round."""
     assert drf.probe_gemm_route(M, N, K, 2) == (7, 1, 0, 0)
+    assert drf.probe_gemm_route(4096, 1536, 6144, 2)[0] != 7       # two rounds: 84 us, one of 256 x 128 75
 
 
 def test_bf16_gemm_refuses_the_fp32_paths_activation():
