@@ -583,7 +583,9 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
 // 42.9 : 42.4, K = 3072 (8192 x 768) 52.5 : 48.2, K = 4608 (8192 x 1152) 81.3 : 71.8; 18's constants put the line at K = 1344.  (18 stores by
 // lane swaps; with store_rows QKV of 8192 and 16384 rows of 384 13.1 -> 13.7 and 24.1 -> 25.4, GELU 22.4 -> 23.4, gated even.)
 // 7 has the launches of 193 to 256 tiles of 128 x 96 (inside a pass, against the next best: 2560 x 1152 x 4608 33.7 us, 128 x 144 35.8, 128 x
-// 128 39.8; 8192 x 384 x 1536 14.4, 128 x 128 15.8; 8192 x 384 x 384 7.0 and 7.6), on four waves by two (four by one: 35.7, 15.4, 7.6).
+// 128 39.8; 8192 x 384 x 1536 14.4, 128 x 128 15.8), on four waves by two (four by one: 35.7, 15.4).  Its base keeps launches of K <= 512 on
+// 128 x 128: they would gain 0.2-0.6 us, and the other launches of a block, which then find another kernel's code in the instruction
+// caches, lose as much or more (4096 rows of 256: QKV 7.1 -> 6.9, the other three 20.0 -> 21.4).
 struct TileModel { int id, bm, bn, wk, per_cu; double base, round, lat, thr, red0, red1; };     // red0 = 0: never split
 const TileModel kTiles[] = {
     {  2, 256, 288, 1, 1, 0.00, 8.99, 1.59, 0.00, 0.0, 0.0 },
@@ -594,7 +596,7 @@ const TileModel kTiles[] = {
     { 16, 128, 144, 1, 1, 0.51, 4.58, 0.54, 0.00, 0.0, 0.0 },
     {  4, 128, 128, 1, 2, 0.98, 2.65, 0.64, 0.51, 0.0, 0.0 },
     {  5, 128, 128, 1, 1, 1.29, 2.95, 0.48, 0.00, 2.9, 1.8 },
-    {  7, 128,  96, 1, 1, 1.39, 2.96, 0.42, 0.00, 0.0, 0.0 },
+    {  7, 128,  96, 1, 1, 1.90, 2.96, 0.42, 0.00, 0.0, 0.0 },
     { 17,  64, 144, 1, 1, 1.51, 3.13, 0.31, 0.00, 0.0, 0.0 },
     {  6, 128,  64, 1, 1, 1.50, 2.12, 0.32, 0.00, 2.9, 1.9 },
     { 11,  64,  96, 2, 1, 1.43, 2.65, 0.44, 0.00, 0.0, 0.0 },

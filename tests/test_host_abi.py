@@ -244,11 +244,12 @@ def test_gemm_one_round_of_256_x_144_tiles(K, tile):
     assert drf.probe_gemm_route(8192, 1152, K, 2) == (tile, 1, 0, 0)
 
 
-@pytest.mark.parametrize("M,N,K", [(2560, 1152, 4608), (2470, 1152, 1152), (8192, 384, 1536), (7904, 384, 384)])
+@pytest.mark.parametrize("M,N,K", [(2560, 1152, 4608), (2470, 1152, 1152), (8192, 384, 1536), (7904, 384, 1536)])
 def test_gemm_one_round_of_128_x_96_tiles(M, N, K):
     """193 to 256 of them, where 128 x 128 tiles leave CUs idle and smaller ones need a second round."""
     assert drf.probe_gemm_route(M, N, K, 2) == (7, 1, 0, 0)
     assert drf.probe_gemm_route(4096, 1536, 6144, 2)[0] != 7       # two rounds: 84 us, one of 256 x 128 75
+    assert drf.probe_gemm_route(8192, 384, 384, 2)[0] != 7         # a short launch: 0.6 us, which the next kernels' code loads cost
 
 
 def test_bf16_gemm_refuses_the_fp32_paths_activation():
