@@ -28,6 +28,12 @@ def bf16_round(torch, a):
     return torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(torch.bfloat16)
 
 
+def block_routes(drf, M, D, tokens):
+    """How the four GEMMs of a bf16 block of M rows are run (see drf.probe_gemm_route)."""
+    gemms = dict(qkv=(3 * D, D, 1), proj=(D, D, 2), fc1=(4 * D, D, 3), fc2=(D, 4 * D, 2))
+    return {name: drf.probe_gemm_route(M, N, K, kind, tokens) for name, (N, K, kind) in gemms.items()}
+
+
 @pytest.mark.parametrize("variant", [0, 1, 2, 3, 4, 5, 6, 7, 8])
 @pytest.mark.parametrize("M,N,K", [(300, 292, 128), (517, 1156, 192), (1024, 576, 64), (33, 8, 64), (260, 148, 384)])
 def test_gemm_bf16_every_tile_shape(torch, drf, orc, variant, M, N, K):
@@ -35,7 +41,7 @@ def test_gemm_bf16_every_tile_shape(torch, drf, orc, variant, M, N, K):
     A = bf16_round(torch, rng.standard_normal((M, K)))
     W = bf16_round(torch, rng.standard_normal((N, K)) * 0.1)
     b = rng.standard_normal(N).astype(np.float32)
-    if variant == 8 and K % 128:                 # the split-K tile takes two 64-wide k-tiles per step
+    if variant == 8 and K % 128:                 # 16's tile for whole pairs of k-tiles only
         with pytest.raises(drf.DrfError):
             drf.probe_gemm_bf16(A.cuda(), W.cuda(), torch.from_numpy(b).cuda(), variant=variant)
         return
@@ -95,10 +101,12 @@ def test_gemm_bf16_four_wave_tiles(torch, drf, orc, variant, M, N, K):
     assert err < 6e-3, err                       # bf16 rounding of the stored result: 2^-8 relative at worst
 
 
-@pytest.mark.parametrize("M,N,K", [(20011, 1152, 384), (12289, 1540, 384)])
+@pytest.mark.parametrize("M,N,K", [(20011, 1152, 384), (12803, 1540, 384), (10957, 1540, 384)])
 def test_gemm_bf16_rows_in_two_launches(torch, drf, M, N, K):
     """Full rounds of one tile and the remaining rows with another: same sums in the same order as one launch of a
     third tile (neither splits K), so the same bits; ragged last row and column tiles."""
+    tile, _, first_tile, first_rows = drf.probe_gemm_route(M, N, K)
+    assert 0 < first_rows < M and not {tile, first_tile} & {9, 11, 12, 13, 16, 17}      # (those add two halves of the sums)
     g = torch.Generator(device="cuda").manual_seed(M)
     A = torch.randn((M, K), generator=g, device="cuda").bfloat16()
     W = (torch.randn((N, K), generator=g, device="cuda") * 0.1).bfloat16()
@@ -203,11 +211,13 @@ def test_config3_pass_at_benchmark_size_sampled_slots(torch, drf, orc):
         assert err < 2e-2, (j, err)
 
 
-@pytest.mark.parametrize("slots,seam", [(34, 33), (23, 21)])
-def test_pass_whose_gemms_run_in_two_launches_sampled_slots(torch, drf, orc, slots, seam):
-    """247-token slots, no multiple of any tile: out-projection, fc1 and fc2 (34 slots) or QKV (23) run as full rounds of one tile and
-    the remaining rows with another, whose first row lies inside slot `seam`: gates, head-major planes and GELU across it."""
+@pytest.mark.parametrize("slots,gemms", [(34, {"proj", "fc1", "fc2"}), (23, {"qkv", "fc1"})])
+def test_pass_whose_gemms_run_in_two_launches_sampled_slots(torch, drf, orc, slots, gemms):
+    """247-token slots, no multiple of any tile: the GEMMs named run as full rounds of one tile and the remaining rows with another,
+    whose first row lies inside a slot: gates, head-major planes and GELU across it.  The slots at each seam are compared."""
     dit = dict(I.CONFIGS[3]["dit"], depth=2, lat_h=26, lat_w=38)
+    seams = {name: r[3] // 247 for name, r in block_routes(drf, slots * 247, 1152, 247).items() if r[3]}
+    assert set(seams) == gemms
     w = I.weights(dit, 3, "loud")
     den = drf.Denoiser(dit, w)
     rng = np.random.default_rng(slots)
@@ -217,7 +227,39 @@ def test_pass_whose_gemms_run_in_two_launches_sampled_slots(torch, drf, orc, slo
     got = den.eps_batched(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda(), torch.from_numpy(cls).cuda()).cpu().numpy()
     den.close()
     wd = orc.prepare_weights(w)
-    for j in (0, seam - 1, seam, slots - 1):
+    for j in sorted({0, slots - 1} | set(seams.values()) | {j - 1 for j in seams.values()}):
+        want = orc.dit_eps(dit, wd, x[j:j + 1], t[j:j + 1], cls[j:j + 1])[0]
+        err = np.abs(got[j] - want).max() / np.abs(want).max()
+        assert err < 2e-2, (j, err)
+
+
+@pytest.mark.parametrize("lat,slots,tiles", [
+    ((36, 28), 5, dict(qkv=16)), ((36, 28), 8, dict(proj=17, fc1=18, fc2=17)), ((36, 28), 10, dict(qkv=18, proj=7, fc1=3, fc2=7)),
+    ((36, 28), 15, dict(qkv=19, proj=16, fc1=2, fc2=16)), ((36, 28), 19, dict(qkv=20)), ((36, 28), 31, dict(proj=18, fc1=20, fc2=13)),
+    ((36, 28), 24, dict(fc1=19)),
+    ((18, 14), 10, dict(qkv=17, fc1=7)), ((18, 14), 15, dict(fc1=16)), ((18, 14), 19, dict(qkv=16)), ((18, 14), 29, dict(proj=17, fc1=18, fc2=17)),
+    ((18, 14), 57, dict(qkv=19, proj=16, fc1=2, fc2=16)), ((18, 14), 122, dict(qkv=19, proj=18, fc1=20, fc2=13)),
+    ((8, 8), 37, dict(qkv=17)), ((8, 8), 41, dict(qkv=7)), ((8, 8), 73, dict(qkv=16)), ((8, 8), 113, dict(proj=17, fc1=18, fc2=17)),
+    ((8, 8), 145, dict(qkv=18, fc1=3)), ((8, 8), 225, dict(proj=16, fc1=2, fc2=16)), ((8, 8), 481, dict(proj=18, fc1=20, fc2=13))])
+def test_pass_of_ragged_slots_on_every_middle_tile_sampled_slots(torch, drf, orc, lat, slots, tiles):
+    """252, 63 and 16 tokens a slot at row counts that no tile divides: the tiles of two pairs of waves (13, 16, 17), 256-row ones on
+    four and eight waves (2, 3, 18, 19, 20) and 128 x 96 with head-major stores whose 32 rows cross slots, gates of two to four
+    rows in LDS and of more from memory, GELU, and the last block's gated update of the stream; slots at tile edges are compared."""
+    T = lat[0] * lat[1] // 4
+    M = slots * T
+    routes = block_routes(drf, M, 1152, T)
+    assert {name: routes[name][:2] for name in tiles} == {name: (tile, 1) for name, tile in tiles.items()}
+    dit = dict(I.CONFIGS[3]["dit"], depth=2, lat_h=lat[0], lat_w=lat[1])
+    w = I.weights(dit, 3, "loud")
+    den = drf.Denoiser(dit, w)
+    rng = np.random.default_rng(slots)
+    x = rng.standard_normal((slots, 4, *lat)).astype(np.float32)
+    t = rng.integers(0, 1000, size=slots).astype(np.int32)
+    cls = I.conditioning(dit, slots, 3)
+    got = den.eps_batched(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda(), torch.from_numpy(cls).cuda()).cpu().numpy()
+    den.close()
+    wd = orc.prepare_weights(w)
+    for j in sorted({r // T for r in (0, 64, 128, 255, 256, M // 256 * 256 - 1, M - 1) if r < M}):
         want = orc.dit_eps(dit, wd, x[j:j + 1], t[j:j + 1], cls[j:j + 1])[0]
         err = np.abs(got[j] - want).max() / np.abs(want).max()
         assert err < 2e-2, (j, err)
