@@ -114,13 +114,12 @@ struct Epilogue {
     // with the q plane multiplied by q_scale before it is rounded
     int hid, hd, heads; size_t plane; float q_scale;
     uint32_t hid_magic, hd_magic; int hid_shift, hd_shift;
-    // Optional (bf16 wide-tile kernel only): the last 256 workgroups of the launch (the ones that run in
-    // its final round) each load one word of their share of the warm_lines 128-byte lines at `warm`,
-    // typically the weights of the GEMM that runs next, so that those are already on the near side of
-    // HBM when that GEMM asks for them.  Values are not used.
+    // Optional (bf16 kernels): the last 256 workgroups of the launch (the ones that run in its final round) each ask for
+    // their share of the warm_lines 128-byte lines at `warm`, typically the weights of the GEMM that runs next, so that
+    // those are already on the near side of HBM when that GEMM asks for them (see warm_caches in gemm_device.h).
     const void* warm; uint32_t warm_lines;
 };
-// Division constants for floor(n / d), 0 <= n < 2^31 (see fast_div in gemm.hip).
+// Division constants for floor(n / d), 0 <= n < 2^31 (see fast_div in gemm_device.h).
 void make_fast_div(int d, uint32_t* magic, int* shift);
 // Fills rows_per_slot and its division constants (exact for 0 <= m < 2^31).
 void set_rows_per_slot(Epilogue* e, int rows_per_slot);

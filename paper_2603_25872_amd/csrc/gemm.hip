@@ -1,7 +1,7 @@
 // GEMM C[M][N] = A[M][K] . W[N][K]^T with fused epilogues (bias, GELU-tanh, gated
 // residual).  bf16 path: software-pipelined kernels (16x16x32 MFMAs, operands by LDS-DMA, fp32 accumulate) at tiles from
-// 32 x 64 to 256 x 288, the tile chosen by a measured time model: 256 columns and more in gemm_wide.h, 144 in gemm_pair.h, the
-// others here.
+// 32 x 64 to 256 x 288, the tile chosen by a measured time model.  The 256-row tiles of 256 and 288 columns have a four-wave form
+// (gemm_wide.h) beside the one here, the 144-column tiles one of two pairs of waves (gemm_pair.h).
 // fp32 path: fp32 MFMA, operands straight to registers, K split over the waves of a workgroup.
 #include "gemm_device.h"
 
@@ -27,7 +27,6 @@ __device__ inline void epilogue4(const Epilogue& e, int m, int n, float v0, floa
         return;
     }
     if (e.mode == EPI_STORE_GELU) { v0 = gelu_tanh(v0); v1 = gelu_tanh(v1); v2 = gelu_tanh(v2); v3 = gelu_tanh(v3); }
-    if (e.mode == EPI_STORE_SILU) { v0 = silu(v0); v1 = silu(v1); v2 = silu(v2); v3 = silu(v3); }
     if (e.mode == EPI_STORE_GATED) {
         const float4 g = *reinterpret_cast<const float4*>(e.gate + (size_t)fast_div(m, e.rps_magic, e.rps_shift) * e.gate_ld + n);
         v0 *= g.x; v1 *= g.y; v2 *= g.z; v3 *= g.w;
@@ -572,12 +571,12 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
 // microseconds, where a round is per_cu workgroups on each of the 256 CUs, c the workgroups that share a CU in it and
 // steps the k-steps of 64 * wk; a split adds red0 + red1 per million partial elements for the reduction launch.
 // The constants are least-squares fits to timings of every tile on 134 shapes (M 16 .. 65536, N 384 .. 195840, K 384 ..
-// 4608, weights cold); the tile that the model picks is 0.6 % slower than the fastest of all on average and 8 % at
-// worst but for 24576 x 384 x 1536, where it takes the second best.  Back to back, that is: inside a pass launches take longer.
+// 4608, weights cold, back to back), those of 7 and 18 to timings inside a pass, where launches take longer and short ones the
+// more: there the choice is within 5 % of the best single launch at most sizes of hidden 384 and 1152, up to 20 % behind at others.
 // Small problems live on small tiles: with weights coming from HBM a launch is a chain of round trips, and what counts is
 // how many of the chip's CUs pull operands at once (M = 512, N = K = 1152: 7.1 us on 144 64 x 64 tiles whose two wave
 // groups split K, 12.5 on 36 128 x 128 tiles).  Larger ones lose by a part-filled round: the tiles between 128 x 128 and 256 x 256
-// are there for their counts (M = 8192, N = 1152, K = 4608: 77.6 us on 256 tiles of 256 x 144, 88.1 on 160 of 256 x 256).
+// are there for their counts (M = 8192, N = 1152, K = 4608 inside a pass: 71.8 us on 256 tiles of 256 x 144, 89.8 on 160 of 256 x 256).
 // 13 and 18 are the 256 x 144 tile on two pairs of waves and on eight.  Inside a pass, eight against pairs: K = 384 (8192 x 1152) 14.0 : 17.2
 // us, K = 768 (4096 x 2304) 19.7 : 22.0, K = 1152 (2560 x 3456) 24.6 : 26.9, K = 1536 (16384 x 384) 28.5 : 29.2, K = 2048 (4096 x 2048)
 // 42.9 : 42.4, K = 3072 (8192 x 768) 52.5 : 48.2, K = 4608 (8192 x 1152) 81.3 : 71.8; 18's constants put the line at K = 1344.  (18 stores by
@@ -665,8 +664,8 @@ drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, in
 }
 
 // A problem that fills some rounds of a tile and part of another runs as two launches where that is modelled at least 5 %
-// faster: the rows of the full rounds with that tile, the rest with whatever suits it (24576 x 1152: 1.5 rounds of 256 x 288
-// tiles, or one of them and one of 256 x 144: 232 -> ~217 us at K = 4608; a call of 4096-token slots 430.1 -> 421.7 ms).
+// faster: the rows of the full rounds with that tile, the rest with whatever suits it (6144 x 3456 x 1152 inside a pass: 5376 rows of
+// 256 x 288 tiles and the rest of 128 x 96 50.5 us, the best single launch 57.5).
 // Returns the rows of the first launch, 0 for one launch.
 int pick_row_split(int M, int N, int K, double one_us, int* id_a, int* id_b)
 {

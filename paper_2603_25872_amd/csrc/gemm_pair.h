@@ -5,10 +5,11 @@
 // 0.37 without the reads, 0.60 with both; the MFMAs 0.26).  Halving K between the pairs makes the waves' tiles as large as
 // the accumulators allow, 64 x 144 of a 128 x 144 tile, where four row blocks that share K by k-tiles read 90 KB a k-tile; now
 // 53.  Fragments are double-buffered a k-tile ahead, so a stage is free as soon as its k-tile begins and one block
-// barrier a k-tile does for both hand-overs.  Weights warm, 8-wave forms before: 8192 x 1152 x 4608 77.9 -> 66.0 us (256 x 144),
-// 4096 x 1152 x 4608 44.3 -> 38.7 (128 x 144), 2048 x 1152 x 4608 33.7 (128 x 96) -> 26.0 (64 x 144), 4096 x 1152 x 1152 15.6 -> 15.0.
-// Those are launches of K = 4608; below K = 1400 the exchange of the partial sums and the one wave's epilogue cost the 256 x 144
-// tile more than the loop gains, and it runs on eight waves (tile 18 in gemm.hip).
+// barrier a k-tile does for both hand-overs.  Back to back with warm weights, 8-wave forms before: 8192 x 1152 x 4608 77.9 -> 66.0 us
+// (256 x 144), 4096 x 1152 x 4608 44.3 -> 38.7 (128 x 144), 2048 x 1152 x 4608 33.7 (128 x 96) -> 26.0 (64 x 144).
+// Inside a pass of 4096 rows: 128 x 144 at K = 4608 48.7 -> 43.1, at K = 1152 19.1 -> 17.5.  Below K = 1400 the exchange of the
+// partial sums and the one wave's epilogue cost the 256 x 144 tile more than the loop gains, and it runs on eight waves (tile 18
+// in gemm.hip).
 // Four more waves that only copy gained nothing (38.7 -> 42.8, 66.0 -> 64.0), copies by way of registers lost 20-40 %.
 #pragma once
 #include "gemm_device.h"

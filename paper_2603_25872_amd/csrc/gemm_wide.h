@@ -2,9 +2,11 @@
 // quarter of the tile (128 x 144 or 128 x 128) and a SIMD's whole register file.
 //
 // Against the 8-wave form of the same tile (64 x 144 per wave) the fragment reads of a k-tile fall from 213 to 139 KB, which
-// with the 70 KB that the copies write was 96 % of what the LDS port moves in the k-tile's MFMA time and is now 70 %; what
-// is left is held by power (8192 x 8192 x 8192, 256 columns: 1310 -> 1520 TFLOP/s with random operands, 1420 -> 1850 with
-// zeros).  16384 x 4608 x 1152: 156 -> 142 us, 16384 x 1152 x 4608: 134 -> 123 us, 65536 x 4608 x 1152: 639 -> 562 us.
+// with the 70 KB that the copies write was 96 % of what the LDS port moves in the k-tile's MFMA time and is now 70 %.  What is
+// left of a long loop is held by power (8192 x 8192 x 8192, 256 columns: 1310 -> 1520 TFLOP/s with random operands, 1420 -> 1850 with
+// zeros).  Inside a pass of 16384 rows (hidden 1152): gated K = 4608 135.1 -> 122.4 us and K = 1152 43.2 -> 39.8, QKV 120.6 -> 114.1;
+// the GELU launch did not gain (166.3 and 166.7, 639 -> 562 back to back at 65536 rows): a quarter of a K = 1152 round lies outside the
+// loop, where one wave per SIMD has nothing beside it, and such launches run on eight waves (wide_form in gemm.hip).
 //  - one wave per SIMD hides nothing behind another wave, so the loop is a fixed sequence: both k-steps' fragments are
 //    double-buffered in registers, every MFMA slot has at most one LDS read or one copy beside it, and nothing but the two
 //    block barriers of a k-tile waits.  Accumulators are named by inline assembly (AGPRs as far as they go): left to the
