@@ -625,7 +625,8 @@ double model_us(const TileModel& t, int M, int N, int K, int splits, bool leave)
 //    every k-tile (the text model, whose MLP no launch warms: 2520 to 3276 rows 36.9 : 33.6 to 36.9 : 35.4): it stays on four;
 //  - head-major planes, slots of whole 32-row passes: K = 384 17.9 : 18.8 | 21.1 : 21.6, K = 512 even (19.60 : 19.56 | 21.0 : 21.9),
 //    K = 768 22.5 : 22.2 | 25.0 : 24.7, K = 1152 34.5 : 31.8 | 121.1 : 110.1;
-//  - other slot lengths: K = 768 42.9 : 43.8 | 30.3 : 32.1, K = 1152 128.6 : 138.9 | 112.4 : 118.9, K = 2048 101.9 : 96.2 | 110.9 : 106.6.
+//  - other slot lengths: K = 768 42.9 : 43.8 | 30.3 : 32.1, K = 1152 128.6 : 138.9 | 112.4 : 118.9, K = 2048 101.9 : 96.2 | 110.9 : 106.6; a
+//    single round of K = 1152 30.7 : 31.2 | 39.7 : 42.0, and a whole evaluation with the former 4.74 : 4.69 ms.
 // Gated, residual and plain stores stay on four at every K (24576 x 1152 x 1152 plain 70.8 : 63.0, residual 106.8 : 102.5, gated even).
 int wide_form(int tile, int rows, int N, int K, const Epilogue& e)
 {
@@ -633,7 +634,7 @@ int wide_form(int tile, int rows, int N, int K, const Epilogue& e)
     const int cols = tile == 2 ? 288 : 256;
     const bool one_round = ((rows + 255) / 256) * (long long)((N + cols - 1) / cols) <= 256;
     const bool eight = e.mode == EPI_STORE_GELU ? K < (one_round ? 1024 : 1536)
-                                                : e.mode == EPI_STORE_HEADS && K < (e.rows_per_slot % 32 == 0 ? 512 : 1536);
+                                                : e.mode == EPI_STORE_HEADS && K < (e.rows_per_slot % 32 == 0 ? 512 : tile == 3 && one_round ? 1024 : 1536);
     return !eight ? tile : tile == 2 ? 20 : 19;
 }
 

@@ -235,10 +235,10 @@ def test_pass_whose_gemms_run_in_two_launches_sampled_slots(torch, drf, orc, slo
 
 @pytest.mark.parametrize("lat,slots,tiles", [
     ((36, 28), 5, dict(qkv=16)), ((36, 28), 8, dict(proj=17, fc1=18, fc2=17)), ((36, 28), 10, dict(qkv=18, proj=7, fc1=3, fc2=7)),
-    ((36, 28), 15, dict(qkv=19, proj=16, fc1=2, fc2=16)), ((36, 28), 19, dict(qkv=20)), ((36, 28), 31, dict(proj=18, fc1=20, fc2=13)),
+    ((36, 28), 15, dict(qkv=3, proj=16, fc1=2, fc2=16)), ((36, 28), 19, dict(qkv=20)), ((36, 28), 31, dict(qkv=19, proj=18, fc1=20, fc2=13)),
     ((36, 28), 24, dict(fc1=19)),
     ((18, 14), 10, dict(qkv=17, fc1=7)), ((18, 14), 15, dict(fc1=16)), ((18, 14), 19, dict(qkv=16)), ((18, 14), 29, dict(proj=17, fc1=18, fc2=17)),
-    ((18, 14), 57, dict(qkv=19, proj=16, fc1=2, fc2=16)), ((18, 14), 122, dict(qkv=19, proj=18, fc1=20, fc2=13)),
+    ((18, 14), 57, dict(qkv=3, proj=16, fc1=2, fc2=16)), ((18, 14), 122, dict(qkv=19, proj=18, fc1=20, fc2=13)),
     ((8, 8), 37, dict(qkv=17)), ((8, 8), 41, dict(qkv=7)), ((8, 8), 73, dict(qkv=16)), ((8, 8), 113, dict(proj=17, fc1=18, fc2=17)),
     ((8, 8), 145, dict(qkv=18, fc1=3)), ((8, 8), 225, dict(proj=16, fc1=2, fc2=16)), ((8, 8), 481, dict(proj=18, fc1=20, fc2=13))])
 def test_pass_of_ragged_slots_on_every_middle_tile_sampled_slots(torch, drf, orc, lat, slots, tiles):
