@@ -86,6 +86,12 @@ drf_status drf_probe_cross_attn_bf16(const void* q, const void* kv, void* out, i
 int drf_probe_attn_route(int slots, int q_rows, int kv_rows, int heads, int head_dim, int q_scaled);
 
 /*
+ * How a bf16 pass without text conditioning runs its blocks (host only): 0 = launch by launch; otherwise everything that works on
+ * rows alone in one launch of so many rows a workgroup (16, 32 or 64), plus 1000 if that launch computes the self-attention too.
+ */
+int drf_probe_block_route(int slots, int tokens, int hidden, int heads, int mlp_ratio);
+
+/*
  * Introspection for the graph-replay tests: how many drf_sample launch sequences the handle holds as
  * instantiated graphs, how many captures failed (those argument sets launch kernel by kernel), and how
  * many calls were served by a graph launch since the handle was created.

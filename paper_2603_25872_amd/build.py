@@ -8,14 +8,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdrf.so")
-SOURCES = ["plan.cpp", "update.hip", "dit_kernels.hip", "gemm.hip", "gemm_wide_288.hip", "gemm_wide_256.hip", "gemm_pair.hip", "attn.hip", "attn_long.hip", "attn_short.hip", "denoiser.hip", "calibrate.hip"]
+SOURCES = ["plan.cpp", "update.hip", "dit_kernels.hip", "gemm.hip", "gemm_wide_288.hip", "gemm_wide_256.hip", "gemm_pair.hip", "attn.hip", "attn_long.hip", "attn_short.hip", "block_chain.hip", "denoiser.hip", "calibrate.hip"]
 FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
 # Per-file extras.  Attention: keep MFMA accumulators in ordinary VGPRs; the online softmax reads
 # every score right after the MFMA, and AGPR accumulators would cost one move per value per tile.
-EXTRA = {name: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for name in ("attn.hip", "attn_long.hip", "attn_short.hip")}
+EXTRA = {name: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for name in ("attn.hip", "attn_long.hip", "attn_short.hip", "block_chain.hip")}
 
 
 def _compile(src):

@@ -187,6 +187,35 @@ drf_status launch_attn_short_bf16(const AttnArgs& a, int queries, hipStream_t st
 int attn_short_items_at_once(int Nk, int d);    // work items of 32 queries that the chip holds of ATTN_SHORT
 drf_status launch_attn_f32(const AttnArgs& a, hipStream_t st);
 
+// The row-local part of a bf16 block as one launch (block_chain.hip): from the attention output, rows of the stream resid become
+// x = resid + gate1 (proj(attn)), x += gate2 fc2(gelu(fc1(LN(x)))), stored over resid, then the next block's q | k | v of LN(x).
+struct ChainArgs {
+    const bf16_t* attn;             // [M][D]: the attention output, or NULL
+    const bf16_t* kv_in;            // keys and values that the self-attention is computed from in the launch itself (heads of 64), with the queries
+                                    // at q, or NULL; with neither, only the last part runs, of resid as it is
+    float* resid;                   // [M][D]
+    const bf16_t* weights;          // packed units in the order of their use (launch_chain_pack): proj, (fc1, fc2) of every D hidden units, q, k, v
+    const float *b_proj, *b_fc1, *b_fc2, *b_qkv;
+    const float* mod;               // slot 0's gate1 | shift2 | scale2 | gate2 | next shift1 | next scale1, D each (the first four not read for the last part alone)
+    int mod_ld, tokens, slots, mlp_ratio;
+    bf16_t* qkv;                    // head-major planes of `plane` elements as EPI_STORE_HEADS writes them, or NULL
+    // The form that the next launch computes its self-attention from; neither this nor qkv: no last part.  Keys, then values, of every slot and
+    // head in groups of 32 keys of 64, as operand fragments: the first 16-byte piece of lane (l, quarter) in fragment (b, s) of the
+    // keys is columns 32 s + 8 quarter .. + 7 of key 8 (l / 4) + l % 4 + 4 b, in fragment d of the values column 16 d + l of keys
+    // 8 quarter .. + 7.  Other memory than kv_in.  The queries go to q (a workgroup reads and writes its own rows).
+    bf16_t *q, *kv_out;
+    size_t plane; int heads, hd; uint32_t hd_magic; int hd_shift; float q_scale;
+};
+bool chain_width(int D, int mlp_ratio);             // hidden sizes and ratios that have the kernel
+// How a pass uses it: rows a workgroup takes (0: the block's launches one by one are faster), and whether with the self-attention, which
+// then wants its queries scaled by chain_q_scale().
+struct ChainRoute { int rows; bool attention; };
+ChainRoute chain_route(int slots, int D, int mlp_ratio, int tokens, int hd);
+float chain_q_scale();
+// One D x D unit, rows n of w[n][0 .. D) at stride ld, into the kernel's layout.
+drf_status launch_chain_pack(const bf16_t* w, int ld, int D, bf16_t* out, hipStream_t st);
+drf_status launch_block_chain(const ChainArgs& a, int D, int rows, hipStream_t st);
+
 struct DitDims { int D, P, T, gh, gw, C, H, W, patch, heads, d, R, L; };
 
 // c = MLP(femb(tau)) + cond embedding; writes SiLU(c) as float [slots][D] and, if act_bf16 != NULL, bf16.

@@ -66,6 +66,7 @@ struct drf_denoiser {
                 *t_b2 = nullptr, *c_w = nullptr, *c_b = nullptr, *table = nullptr, *fin_w = nullptr, *fin_b = nullptr;
     LinearW ada;                    // all blocks' adaLN projections and the final one, stacked [n_mod][D]
     std::vector<BlockW> blk;
+    bf16_t* chain_w = nullptr;      // the blocks' weights once more, in the layout and order block_chain.hip streams them (NULL: not for this model)
     float* pos = nullptr;           // [T][D]
     // workspace (owned)
     Workspace ws;
@@ -407,29 +408,68 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         const drf_status r = ln(shift, scale, mod_ld, store);
         return r != DRF_OK ? r : gemm(d, ws.hbuf, w, M, ep, st, ws.skpart);
     };
-    for (int l = 0; l < n_blocks; ++l) {
+    auto self_attention = [&]() -> drf_status {
+        AttnArgs aa{};
+        aa.q = ws.qkv; aa.out = ws.hbuf; aa.ldo = D; aa.Nq = dm.T; aa.Nk = dm.T; aa.heads = dm.heads; aa.d = dm.d;
+        aa.slots = slots; aa.kv_mod = 0;
+        if (f32) {
+            aa.k = (char*)ws.qkv + (size_t)D * act; aa.v = (char*)ws.qkv + (size_t)2 * D * act;
+            aa.ldq = aa.ldk = 3 * D;
+            aa.q_slot_stride = aa.kv_batch_stride = (size_t)dm.T * 3 * D; aa.q_head_stride = aa.kv_head_stride = dm.d;
+        } else {
+            aa.k = (char*)ws.qkv + (size_t)M * D * act; aa.v = (char*)ws.qkv + (size_t)2 * M * D * act;
+            aa.ldq = aa.ldk = dm.d;
+            aa.q_slot_stride = aa.kv_batch_stride = (size_t)dm.T * D; aa.q_head_stride = aa.kv_head_stride = (size_t)dm.T * dm.d;
+            aa.q_scaled = attn_wants_scaled(dm.T, dm.heads, dm.d, slots);
+        }
+        ProfScope ps(d, st, DRF_PROF_ATTN, 4.0 * slots * dm.heads * (double)dm.T * dm.T * dm.d);
+        return f32 ? launch_attn_f32(aa, st) : launch_attn_bf16(aa, st);
+    };
+    const ChainRoute chain = d->chain_w ? chain_route(slots, D, dm.R, dm.T, dm.d) : ChainRoute{ 0, false };
+    if (chain.rows) {
+        // narrow models: everything of a block that works on its rows alone in one launch, and the self-attention before it too where that
+        // pays; the keys and values that the launch writes for the next block are then others than those that it reads
+        const size_t unit = (size_t)D * D, per_block = (4 + 2 * (size_t)dm.R) * unit;       // qkv | proj | (fc1, fc2) pieces
+        const Epilogue h = epi_heads(ws.qkv, slots, dm);
+        bf16_t* kv[2] = { (bf16_t*)ws.qkv, (bf16_t*)ws.mid };
+        ChainArgs ca{};
+        ca.resid = ws.resid; ca.mod_ld = nm; ca.tokens = dm.T; ca.slots = slots; ca.mlp_ratio = dm.R;
+        ca.plane = h.plane; ca.heads = h.heads; ca.hd = h.hd; ca.hd_magic = h.hd_magic; ca.hd_shift = h.hd_shift;
+        ca.q_scale = chain.attention ? chain_q_scale() : h.q_scale;
+        ca.q = (bf16_t*)ws.hbuf;
+        for (int l = -1; l < n_blocks; ++l) {               // the launch behind block l's attention, with block l + 1's projection
+            double flops = 0.0;
+            if (l >= 0) {
+                const BlockW& b = d->blk[l];
+                if (chain.attention) {
+                    ca.kv_in = kv[l & 1];
+                    flops += 4.0 * M * dm.T * D;
+                } else {
+                    if ((rc = self_attention()) != DRF_OK) return rc;
+                    ca.attn = (const bf16_t*)ws.hbuf;
+                }
+                ca.b_proj = b.proj.b; ca.b_fc1 = b.fc1.b; ca.b_fc2 = b.fc2.b;
+                flops += 2.0 * M * D * D * (1.0 + 2.0 * dm.R);
+            }
+            ca.mod = mod + (ptrdiff_t)l * 6 * D + 2 * D;    // gate1 | shift2 | scale2 | gate2 of block l, shift1 | scale1 of block l + 1 (of the final layer behind the last)
+            ca.weights = d->chain_w + (l >= 0 ? (size_t)l * per_block + 3 * unit : 0);
+            ca.qkv = ca.kv_out = nullptr;
+            if (l + 1 < n_blocks) {
+                (chain.attention ? ca.kv_out : ca.qkv) = chain.attention ? kv[(l + 1) & 1] : (bf16_t*)ws.qkv;
+                ca.b_qkv = d->blk[l + 1].qkv.b;
+                flops += 6.0 * M * D * D;
+            }
+            ProfScope ps(d, st, DRF_PROF_GEMM, flops);
+            if ((rc = launch_block_chain(ca, D, chain.rows, st)) != DRF_OK) return rc;
+        }
+    }
+    for (int l = chain.rows ? n_blocks : 0; l < n_blocks; ++l) {
         const BlockW& b = d->blk[l];
         const float* mrow = mod + (size_t)l * 6 * D;        // shift1 | scale1 | gate1 | shift2 | scale2 | gate2
         // bf16: q | k | v are stored head-major ([slot][head][token][d] planes) so that attention reads
         // whole contiguous tiles; fp32: packed rows
         if ((rc = ln_linear(mrow, mrow + D, nm, true, b.qkv, f32 ? epi_store(ws.qkv, 3 * D, true) : with_warm(epi_heads(ws.qkv, slots, dm), &b.proj))) != DRF_OK) return rc;
-        {
-            AttnArgs aa{};
-            aa.q = ws.qkv; aa.out = ws.hbuf; aa.ldo = D; aa.Nq = dm.T; aa.Nk = dm.T; aa.heads = dm.heads; aa.d = dm.d;
-            aa.slots = slots; aa.kv_mod = 0;
-            if (f32) {
-                aa.k = (char*)ws.qkv + (size_t)D * act; aa.v = (char*)ws.qkv + (size_t)2 * D * act;
-                aa.ldq = aa.ldk = 3 * D;
-                aa.q_slot_stride = aa.kv_batch_stride = (size_t)dm.T * 3 * D; aa.q_head_stride = aa.kv_head_stride = dm.d;
-            } else {
-                aa.k = (char*)ws.qkv + (size_t)M * D * act; aa.v = (char*)ws.qkv + (size_t)2 * M * D * act;
-                aa.ldq = aa.ldk = dm.d;
-                aa.q_slot_stride = aa.kv_batch_stride = (size_t)dm.T * D; aa.q_head_stride = aa.kv_head_stride = (size_t)dm.T * dm.d;
-                aa.q_scaled = attn_wants_scaled(dm.T, dm.heads, dm.d, slots);
-            }
-            ProfScope ps(d, st, DRF_PROF_ATTN, 4.0 * slots * dm.heads * (double)dm.T * dm.T * dm.d);
-            if ((rc = f32 ? launch_attn_f32(aa, st) : launch_attn_bf16(aa, st)) != DRF_OK) return rc;
-        }
+        if ((rc = self_attention()) != DRF_OK) return rc;
         if (f32) {
             if ((rc = gemm(d, ws.hbuf, b.proj, M, epi_resid(ws.resid, D, mrow + 2 * D, nm, dm.T), st)) != DRF_OK) return rc;
         } else {
@@ -787,6 +827,24 @@ extern "C" drf_status drf_denoiser_create(const drf_dit_config* cfg, const float
             if ((rc = dev_alloc(d, (void**)&w16, n * 2)) != DRF_OK) return fail(rc);
             if ((rc = launch_f32_to_bf16(pm.lw->w32, w16, n, st)) != DRF_OK) return fail(rc);   // exact: values are bf16 already
             pm.lw->w16 = w16;
+        }
+    }
+
+    if (d->bf16 && cfg->cond != DRF_COND_TEXT && chain_width(dm.D, dm.R)) {
+        const size_t unit = D * D;
+        if ((rc = dev_alloc(d, (void**)&d->chain_w, (size_t)dm.L * (4 + 2 * R) * unit * 2)) != DRF_OK) return fail(rc);
+        bf16_t* out = d->chain_w;
+        auto pack = [&](const LinearW& w, size_t row, size_t col) {
+            const drf_status r = launch_chain_pack(w.w16 + row * w.K + col, w.K, dm.D, out, st);
+            out += unit;
+            return r;
+        };
+        for (const BlockW& b : d->blk) {
+            for (size_t p = 0; p < 3; ++p)
+                if ((rc = pack(b.qkv, p * D, 0)) != DRF_OK) return fail(rc);
+            if ((rc = pack(b.proj, 0, 0)) != DRF_OK) return fail(rc);
+            for (size_t c = 0; c < R; ++c)
+                if ((rc = pack(b.fc1, c * D, 0)) != DRF_OK || (rc = pack(b.fc2, 0, c * D)) != DRF_OK) return fail(rc);
         }
     }
 
@@ -1148,4 +1206,11 @@ extern "C" int drf_probe_attn_route(int slots, int q_rows, int kv_rows, int head
 {
     if (slots < 1 || q_rows < 1 || kv_rows < 1 || heads < 1 || head_dim < 8 || head_dim > 96 || head_dim % 8 != 0) return 0;
     return attn_route(q_rows, kv_rows, heads, head_dim, slots, q_scaled != 0);
+}
+
+extern "C" int drf_probe_block_route(int slots, int tokens, int hidden, int heads, int mlp_ratio)
+{
+    if (slots < 1 || tokens < 1 || heads < 1 || mlp_ratio < 1 || hidden < 1 || hidden % heads != 0 || !chain_width(hidden, mlp_ratio)) return 0;
+    const ChainRoute r = chain_route(slots, hidden, mlp_ratio, tokens, hidden / heads);
+    return r.rows + (r.attention ? 1000 : 0);
 }

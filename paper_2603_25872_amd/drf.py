@@ -25,7 +25,7 @@ SYMBOLS = ["drf_denoiser_weight_count", "drf_denoiser_create", "drf_denoiser_des
            "drf_plan_build", "drf_last_error"]
 # include/drf_measure.h: test and measurement hooks
 MEASURE_SYMBOLS = ["drf_eps_trace", "drf_profile_enable", "drf_profile_read", "drf_probe_gemm_bf16",
-                   "drf_probe_attn_bf16", "drf_probe_cross_attn_bf16", "drf_probe_attn_route", "drf_probe_gemm_route", "drf_probe_update_fused", "drf_graph_stats", "drf_calibrate_mfma_bf16", "drf_calibrate_copy"]
+                   "drf_probe_attn_bf16", "drf_probe_cross_attn_bf16", "drf_probe_attn_route", "drf_probe_gemm_route", "drf_probe_block_route", "drf_probe_update_fused", "drf_graph_stats", "drf_calibrate_mfma_bf16", "drf_calibrate_copy"]
 STATIC_SCRATCH_BYTES = 48 << 20
 
 
@@ -95,6 +95,7 @@ def lib():
         L.drf_probe_attn_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]
         L.drf_probe_cross_attn_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p] + [C.c_int] * 7 + [C.c_void_p]
         L.drf_probe_attn_route.argtypes = [C.c_int] * 6
+        L.drf_probe_block_route.argtypes = [C.c_int] * 5
         L.drf_probe_gemm_route.argtypes = [C.c_int] * 5 + [C.c_void_p]
         L.drf_last_error.restype = C.c_char_p
         _lib = L
@@ -261,6 +262,11 @@ def probe_cross_attn_bf16(q, kv, slots, kv_slots, q_rows, kv_rows, heads, head_d
 def probe_attn_route(slots, q_rows, kv_rows, heads, head_dim, q_scaled=False):
     """Number of the bf16 attention kernel that takes a launch of these sizes (host only, see include/drf_measure.h)."""
     return lib().drf_probe_attn_route(slots, q_rows, kv_rows, heads, head_dim, int(q_scaled))
+
+
+def probe_block_route(slots, tokens, hidden, heads, mlp_ratio=4):
+    """How a bf16 pass of these sizes runs its blocks (host only, see include/drf_measure.h)."""
+    return lib().drf_probe_block_route(slots, tokens, hidden, heads, mlp_ratio)
 
 
 def probe_update_fused(sched, s_from, n_chain, n_draft, g, w, x_base, eps, x_out=None, draft_out=None):

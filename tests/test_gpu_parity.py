@@ -247,6 +247,37 @@ def test_bf16_whole_and_edge_tiles_of_a_fat_pass(torch, drf, orc, cond, lat, slo
     check(got[pick], orc.dit_eps(dit, w, x[pick], t[pick], c[pick]), TOL_BF16, "eps")
 
 
+@pytest.mark.parametrize("hidden,heads,lat,slots,ratio,route", [
+    (256, 4, (10, 6), 3, 4, 16),        # 15 tokens: one part-filled row tile a slot; no room for whole key groups in the buffers
+    (256, 4, (2, 2), 5, 2, 16),         # one token
+    (256, 4, (16, 16), 5, 2, 1016), (256, 4, (8, 16), 4, 3, 1016),
+    (384, 6, (26, 38), 12, 4, 1016),    # 247 tokens: a row tile and a key group of 15 and 23
+    (384, 6, (26, 38), 25, 4, 1032), (256, 4, (26, 38), 30, 4, 1032), (512, 8, (26, 38), 25, 4, 1032),
+    (512, 8, (26, 38), 16, 4, 1016),
+    (384, 12, (26, 38), 10, 4, 16), (384, 12, (26, 38), 25, 4, 32), (384, 4, (26, 38), 50, 4, 64), (256, 8, (26, 38), 60, 4, 64),
+    (512, 16, (26, 38), 30, 1, 32),
+    (384, 6, (48, 50), 8, 4, 1032),     # 600 tokens
+    (384, 6, (8, 8), 5, 4, 0)])
+def test_bf16_rows_of_a_block_in_one_launch(torch, drf, orc, hidden, heads, lat, slots, ratio, route):
+    """Narrow models: the launch of a block's row-local part at 16, 32 and 64 rows, with and without the self-attention, whole and
+    part-filled row tiles and key groups, every MLP ratio; slots at both ends and in the middle against the oracle."""
+    dit = small_dit(I.COND_CLASS, I.BF16, hidden=hidden, heads=heads, depth=2, mlp_ratio=ratio, lat_h=lat[0], lat_w=lat[1])
+    w = I.weights(dit, 49, "loud")
+    assert drf.probe_block_route(slots, lat[0] * lat[1] // 4, hidden, heads, ratio) == route
+    rng = np.random.default_rng(59)
+    x = rng.standard_normal((slots, dit["in_ch"], dit["lat_h"], dit["lat_w"])).astype(np.float32)
+    t = rng.integers(0, 1000, size=slots).astype(np.int32)
+    c = make_cond(dit, slots, 69)
+    den = drf.Denoiser(dit, w)
+    args = dev(torch, x), dev(torch, t), dev(torch, c)
+    got, resid = den.eps_batched(*args).cpu().numpy(), den.eps_trace(*args, 1).cpu().numpy()
+    assert np.array_equal(got, den.eps_batched(*args).cpu().numpy())
+    den.close()
+    pick = [0, slots // 2, slots - 1]
+    check(resid.reshape(slots, -1)[pick], orc.dit_eps(dit, w, x[pick], t[pick], c[pick], stop_blocks=1).reshape(len(pick), -1), TOL_BF16, "resid1")
+    check(got[pick], orc.dit_eps(dit, w, x[pick], t[pick], c[pick]), TOL_BF16, "eps")
+
+
 @pytest.mark.parametrize("lat", [(10, 6), (24, 24)])
 def test_bf16_text_context_of_300_rows(torch, drf, orc, lat):
     # 15 and 144 queries over 300 kv rows: the chunked kernel's forms with four and with eight waves
