@@ -128,8 +128,9 @@ def _noise(z=None, seed=None, field0=0):
 
 
 def _stream():
+    """Handle of the current stream (torch.cuda.current_stream() makes a Stream object of it: 3.0 us a call against 0.2)."""
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev(t, dtype=None):
@@ -139,7 +140,7 @@ def _dev(t, dtype=None):
     assert t.is_cuda and t.is_contiguous(), "need a contiguous device tensor"
     if dtype is not None:
         assert t.dtype == dtype, "expected %s, got %s" % (dtype, t.dtype)
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def denoiser_weight_count(dit):
