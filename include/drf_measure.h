@@ -87,7 +87,8 @@ int drf_probe_attn_route(int slots, int q_rows, int kv_rows, int heads, int head
 
 /*
  * How a bf16 pass without text conditioning runs its blocks (host only): 0 = launch by launch; otherwise everything that works on
- * rows alone in one launch of so many rows a workgroup (16, 32 or 64), plus 1000 if that launch computes the self-attention too.
+ * rows alone in one launch of so many rows a workgroup (16, 32 or 64), plus 1000 if that launch computes the self-attention too,
+ * plus 10000 p if the hidden units are dealt over p workgroups and a second launch adds their shares.
  */
 int drf_probe_block_route(int slots, int tokens, int hidden, int heads, int mlp_ratio);
 

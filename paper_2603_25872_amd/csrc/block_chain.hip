@@ -171,7 +171,10 @@ __device__ __forceinline__ void head_attention(const bf16_t* const (&q)[MI], con
 //  - ATT: the self-attention of these rows' queries, a head a wave, from keys and values that the launch before left as operand fragments:
 //    3 us more at 256 keys, where a launch of its own takes 10; from head-major planes, transposing values through LDS in every
 //    workgroup, it took 7.5 us.
-// dit_s (3072 rows of hidden 384, 12 blocks) 11.66 -> 9.09 ms a call; passes of 6176 rows 998 -> 618 us, of 16384 1756 -> 1129.
+//  - few rows leave CUs idle, each of the others streaming all weights: the hidden units are then dealt over two or four workgroups a row
+//    tile, and a second launch adds their shares of the stream and deals q, k and v over two or three (5 slots of 247 rows 525 -> 431 us an
+//    evaluation, one by one 510).
+// dit_s (3072 rows of hidden 384, 12 blocks) 11.66 -> 8.93 ms a call; passes of 6176 rows 998 -> 618 us, of 16384 1756 -> 1129.
 template <int NI, int MI, bool ATT>
 __global__ void __launch_bounds__(kChainWaves * 64)
 block_chain_kernel(const ChainArgs a, int tiles)
@@ -191,10 +194,13 @@ block_chain_kernel(const ChainArgs a, int tiles)
     // a workgroup's rows belong to one slot; the tiles of a slot run on one XCD (ids are dealt round-robin over the 8 of them)
     const int nb = gridDim.x, xcd = blockIdx.x & 7, per = nb >> 3, rem = nb & 7;
     const int idx = xcd * per + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);
-    const int slot = idx / tiles, t0 = (idx - slot * tiles) * ROWS, T = a.tokens, row0 = slot * T + t0;
+    const int part = a.parts > 1 ? idx % a.parts : 0, tile = a.parts > 1 ? idx / a.parts : idx;
+    const int slot = tile / tiles, t0 = (tile - slot * tiles) * ROWS, T = a.tokens, row0 = slot * T + t0;
     const int left = T - t0;                        // rows of the tile that exist
     const int col = wave * (16 * NI) + 4 * quarter;             // this lane's columns of a unit: col + 16 i .. + 3
     const bool has_mlp = ATT || a.attn, has_qkv = a.qkv || a.kv_out;
+    // this workgroup's pieces of D hidden units, and of q, k, v
+    const int c0 = part * a.mlp_ratio / a.parts, c1 = (part + 1) * a.mlp_ratio / a.parts, p0 = has_mlp ? 0 : part * 3 / a.parts, p1 = has_mlp ? 3 : (part + 1) * 3 / a.parts;
 
     // every operand is asked for before the first is used, in the order of their use
     constexpr int PIECES = ROWS * D / 8, PU = (PIECES + NT - 1) / NT;             // 16-byte pieces of a bf16 row tile
@@ -228,7 +234,7 @@ block_chain_kernel(const ChainArgs a, int tiles)
 #pragma unroll
         for (int i = 0; i < NI; ++i) dst[i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, lane16 + i * 1024, p, 0));
     };
-    int wp = wave * (KS * NI * 1024);
+    int wp = wave * (KS * NI * 1024) + p0 * UNIT;
     float* xp[MI];
     f32x4 x[NI][MI];
 #pragma unroll
@@ -247,6 +253,7 @@ block_chain_kernel(const ChainArgs a, int tiles)
             for (int j = 0; j < MI; ++j) x[i][j] = *reinterpret_cast<const f32x4*>(xp[j] + i * 16);
         __builtin_amdgcn_sched_barrier(0);
     };
+    const size_t part_len = (size_t)a.slots * T * D;
     if constexpr (ATT) {
         const size_t head = (size_t)((T + 31) / 32 * 32) * kChainHead;          // elements of a head's keys
         for (int h = wave; h < a.heads; h += kChainWaves) {
@@ -371,12 +378,12 @@ block_chain_kernel(const ChainArgs a, int tiles)
         f32x4 acc[NI][MI], sum[NI][MI];
         zero(sum);
         lds_barrier();
-        unit(sum, ybuf, wp, wp + UNIT);
-        wp += UNIT;
+        unit(sum, ybuf, wp, wp + (1 + 2 * c0) * UNIT);
+        wp += (1 + 2 * c0) * UNIT;
         add_branch(sum, 0, 0);
         norm(1, 2);
         zero(sum);
-        for (int c = 0; c < a.mlp_ratio; ++c) {
+        for (int c = c0; c < c1; ++c) {
             unsigned char* const h = hbuf + (HB == 2 && (c & 1) ? C::TILE : 0);
             zero(acc);
             unit(acc, ybuf, wp, wp + UNIT);
@@ -393,24 +400,55 @@ block_chain_kernel(const ChainArgs a, int tiles)
                 }
             }
             lds_barrier();
-            const bool more = has_qkv || c + 1 < a.mlp_ratio;
+            const bool more = has_qkv || c + 1 < c1;
             unit(sum, h, wp, more ? wp + UNIT : wp);
             wp += UNIT;
         }
-        add_branch(sum, 1 + a.mlp_ratio, 3);
+        if (part == 0) add_branch(sum, 1 + a.mlp_ratio, 3);
+        else {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const f32x4 g = mod_at(3, i);
+#pragma unroll
+                for (int j = 0; j < MI; ++j) x[i][j] = g * sum[i][j];
+            }
+        }
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int j = 0; j < MI; ++j)
-                if (j * 16 + l16 < left) *reinterpret_cast<f32x4*>(xp[j] + i * 16) = x[i][j];
-    } else lds_barrier();
+                if (j * 16 + l16 < left) {
+                    float* to = a.part_out ? a.part_out + part * part_len + (xp[j] - a.resid) : xp[j];
+                    *reinterpret_cast<f32x4*>(to + i * 16) = x[i][j];
+                }
+    } else {
+        if constexpr (MI == 1) {
+            if (a.part_in) {                        // the stream is the sum of the parts' shares, added in their order
+                f32x4 more[kChainRatio][NI];
+#pragma unroll
+                for (int s = 0; s < kChainRatio; ++s)
+#pragma unroll
+                    for (int i = 0; i < NI; ++i)
+                        if (s < a.n_in) more[s][i] = *reinterpret_cast<const f32x4*>(a.part_in + s * part_len + (xp[0] - a.resid) + i * 16);
+#pragma unroll
+                for (int i = 0; i < NI; ++i) {
+                    x[i][0] = more[0][i];
+#pragma unroll
+                    for (int s = 1; s < kChainRatio; ++s)
+                        if (s < a.n_in) x[i][0] += more[s][i];
+                    if (part == 0 && l16 < left) *reinterpret_cast<f32x4*>(xp[0] + i * 16) = x[i][0];
+                }
+            }
+        }
+        lds_barrier();
+    }
     if (!has_qkv) { drain(); return; }
     norm(4, 5);
-    for (int p = 0; p < 3; ++p) {
+    for (int p = p0; p < p1; ++p) {
         f32x4 acc[NI][MI];
         unsigned char* const h = hbuf + (HB == 2 && (p & 1) ? C::TILE : 0);
         zero(acc);
-        unit(acc, ybuf, wp, p < 2 ? wp + UNIT : wp);
+        unit(acc, ybuf, wp, p + 1 < p1 ? wp + UNIT : wp);
         wp += UNIT;
         const float scale = p == 0 ? a.q_scale : 1.f;
         if (HB == 1) lds_barrier();
@@ -492,7 +530,7 @@ template <int NI, int MI, bool ATT> drf_status launch_inst(const ChainArgs& a, h
         attr_set = true;
     }
     const int tiles = (a.tokens + C::ROWS - 1) / C::ROWS;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(a.slots * tiles)), dim3(kChainWaves * 64), C::SMEM, st, a, tiles);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.slots * tiles * a.parts)), dim3(kChainWaves * 64), C::SMEM, st, a, tiles);
     DRF_HIP(hipGetLastError());
     return DRF_OK;
 }
@@ -518,16 +556,19 @@ bool chain_width(int D, int mlp_ratio) { return (D == 256 || D == 384 || D == 51
 //   hidden 384: 256 rows 408 | 535 | 622 | 560, 1024 488 | 512 | 600 | 539, 2048 591 | 514 | 597 | 554, 6176 (247 tokens a slot) 998 | 1016 | 618 | 683,
 //               16384 1756 | 2000 | 1229 | 1129 (64 rows), 64 x 1024 6453 | 10570 | 6773 | 5066 (64 rows)
 //   hidden 512: 2048 rows 701 | 829 | 912 | 861, 4096 998 | 875 | 925 | 949, 8192 1367 | 1655 | 1012 | 1063, 64 x 1024 9731 | 16532 | 10265 | 9405 (32 rows)
-struct ChainModel { int D; double att16, att16_key, att32, att32_key, plain16, plain32, plain64, apart, apart_row; };
+// With few rows most CUs would idle while each workgroup streams all weights; the hidden units in two or four parts cost a second launch and
+// a repeated attention and projection: hidden 384, one launch | two parts | four: 1 x 256 rows 535 | 426 | 382 (one by one 410), 4 x 256 518 |
+// 421 | 390 (487), 5 x 247 525 | 431 | 563 (510), 1 x 1024 627 | 528 | 502; hidden 256, 4 x 256 322 | 300 | 288; hidden 512 825 | 625 | 567 (609).
+struct ChainModel { int D; double att16, att16_key, att32, att32_key, plain16, plain32, plain64, two, two_key, four, four_key, apart, apart_row; };
 const ChainModel kChainModels[] = {
-    { 256, 23.0,  9.5, 27.5, 13.5, 23.0, 29.0, 40.0, 27.0, 3.0 },
-    { 384, 38.5, 12.0, 44.0, 20.0, 38.5, 45.0, 70.0, 25.5, 6.3 },
-    { 512, 66.5, 16.0, 78.0, 27.0, 67.0, 77.0, 0.00, 36.0, 10.0 },
+    { 256, 23.0,  9.5, 27.5, 13.5, 23.0, 29.0, 40.0, 20.3,  9.8, 18.6, 10.8, 27.0, 3.0 },
+    { 384, 38.5, 12.0, 44.0, 20.0, 38.5, 45.0, 70.0, 30.6, 11.5, 26.6, 12.9, 25.5, 6.3 },
+    { 512, 66.5, 16.0, 78.0, 27.0, 67.0, 77.0, 0.00, 46.0, 15.6, 40.0, 17.0, 36.0, 10.0 },
 };
 
 ChainRoute chain_route(int slots, int D, int mlp_ratio, int tokens, int hd)
 {
-    ChainRoute best{ 0, false };
+    ChainRoute best{ 0, false, 1, 1 };
     for (const ChainModel& m : kChainModels) {
         if (m.D != D) continue;
         const double rows = (double)slots * tokens, keys = 1e-3 * tokens;
@@ -536,7 +577,7 @@ ChainRoute chain_route(int slots, int D, int mlp_ratio, int tokens, int hd)
         double us = m.apart + m.apart_row * 1e-3 * rows + attn;
         auto consider = [&](int r, bool att, double round) {
             const double tiles = (double)slots * ((tokens + r - 1) / r), t = ceil(tiles / 256.0) * round + (att ? 0.0 : attn);
-            if (round > 0.0 && t < us) { us = t; best = ChainRoute{ r, att }; }
+            if (round > 0.0 && t < us) { us = t; best = ChainRoute{ r, att, 1, 1 }; }
         };
         consider(16, false, m.plain16);
         consider(32, false, m.plain32);
@@ -545,6 +586,12 @@ ChainRoute chain_route(int slots, int D, int mlp_ratio, int tokens, int hd)
         if (hd == kChainHead && 2 * ((tokens + 31) / 32 * 32) <= (mlp_ratio < 3 ? mlp_ratio : 3) * tokens) {
             consider(16, true, m.att16 + m.att16_key * keys);
             consider(32, true, m.att32 + m.att32_key * keys);
+            // two launches a block, each of all its workgroups at once
+            const double tiles = (double)slots * ((tokens + 15) / 16);
+            for (int p = 2; p <= 4; p += 2) {
+                const double t = p == 2 ? m.two + m.two_key * keys : m.four + m.four_key * keys;
+                if (p <= mlp_ratio && tiles * p <= 256.0 && t < us) { us = t; best = ChainRoute{ 16, true, p, tiles * 3 <= 256.0 ? 3 : 2 }; }
+            }
         }
     }
     return best;
@@ -564,6 +611,10 @@ drf_status launch_block_chain(const ChainArgs& a, int D, int rows, hipStream_t s
     if (a.slots == 0) return DRF_OK;
     if (a.mod_ld % 4 != 0 || !chain_width(D, a.mlp_ratio) || (a.attn && a.kv_in) || (a.qkv && a.kv_out) || ((a.kv_in || a.kv_out) && (a.hd != kChainHead || !a.q || rows > 32)))
         DRF_FAIL(DRF_ESHAPE, "block chain: hidden %d, MLP ratio %d, head width %d", D, a.mlp_ratio, a.hd);
+    // parts: of the hidden units, each leaving its share of the stream, or of q, k, v
+    if (a.parts < 1 || (a.parts > 1 && (rows != 16 || (a.kv_in || a.attn ? a.parts > a.mlp_ratio || !a.part_out || a.qkv || a.kv_out : a.parts > 3))) ||
+        (a.part_in && (rows != 16 || a.kv_in || a.attn || a.n_in < 1 || a.n_in > kChainRatio)))
+        DRF_FAIL(DRF_ESHAPE, "block chain in %d parts", a.parts);
     switch (D) {
     case 256: return a.kv_in ? launch_rows<2, true>(a, rows, st) : launch_rows<2, false>(a, rows, st);
     case 384: return a.kv_in ? launch_rows<3, true>(a, rows, st) : launch_rows<3, false>(a, rows, st);

@@ -205,11 +205,16 @@ struct ChainArgs {
     // 8 quarter .. + 7.  Other memory than kv_in.  The queries go to q (a workgroup reads and writes its own rows).
     bf16_t *q, *kv_out;
     size_t plane; int heads, hd; uint32_t hd_magic; int hd_shift; float q_scale;
+    // For few rows (16 a workgroup) a block runs as two launches of several workgroups a row tile: the first deals the hidden units over
+    // `parts`, each leaving its share of the stream at part_out[part][M][D]; the second adds the n_in shares at part_in up, stores the
+    // stream, and deals q, k and v over `parts` (1: neither).
+    int parts, n_in;
+    float* part_out; const float* part_in;
 };
 bool chain_width(int D, int mlp_ratio);             // hidden sizes and ratios that have the kernel
-// How a pass uses it: rows a workgroup takes (0: the block's launches one by one are faster), and whether with the self-attention, which
-// then wants its queries scaled by chain_q_scale().
-struct ChainRoute { int rows; bool attention; };
+// How a pass uses it: rows a workgroup takes (0: the block's launches one by one are faster), whether with the self-attention, which
+// then wants its queries scaled by chain_q_scale(), and in how many parts of the hidden units and of q, k, v (1: in one launch).
+struct ChainRoute { int rows; bool attention; int parts, qkv_parts; };
 ChainRoute chain_route(int slots, int D, int mlp_ratio, int tokens, int hd);
 float chain_q_scale();
 // One D x D unit, rows n of w[n][0 .. D) at stride ld, into the kernel's layout.

@@ -425,7 +425,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         ProfScope ps(d, st, DRF_PROF_ATTN, 4.0 * slots * dm.heads * (double)dm.T * dm.T * dm.d);
         return f32 ? launch_attn_f32(aa, st) : launch_attn_bf16(aa, st);
     };
-    const ChainRoute chain = d->chain_w ? chain_route(slots, D, dm.R, dm.T, dm.d) : ChainRoute{ 0, false };
+    const ChainRoute chain = d->chain_w ? chain_route(slots, D, dm.R, dm.T, dm.d) : ChainRoute{ 0, false, 1, 1 };
     if (chain.rows) {
         // narrow models: everything of a block that works on its rows alone in one launch, and the self-attention before it too where that
         // pays; the keys and values that the launch writes for the next block are then others than those that it reads
@@ -439,6 +439,11 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         ca.q = (bf16_t*)ws.hbuf;
         for (int l = -1; l < n_blocks; ++l) {               // the launch behind block l's attention, with block l + 1's projection
             double flops = 0.0;
+            const bool next = l + 1 < n_blocks, in_parts = chain.parts > 1 && next;
+            ca.parts = 1; ca.part_out = nullptr; ca.part_in = nullptr;
+            ca.qkv = ca.kv_out = nullptr;
+            ca.mod = mod + (ptrdiff_t)l * 6 * D + 2 * D;    // gate1 | shift2 | scale2 | gate2 of block l, shift1 | scale1 of block l + 1 (of the final layer behind the last)
+            ca.weights = d->chain_w + (l >= 0 ? (size_t)l * per_block + 3 * unit : 0);
             if (l >= 0) {
                 const BlockW& b = d->blk[l];
                 if (chain.attention) {
@@ -450,11 +455,20 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
                 }
                 ca.b_proj = b.proj.b; ca.b_fc1 = b.fc1.b; ca.b_fc2 = b.fc2.b;
                 flops += 2.0 * M * D * D * (1.0 + 2.0 * dm.R);
+                if (in_parts) {
+                    ca.parts = chain.parts; ca.part_out = ws.skpart;
+                    {
+                        ProfScope ps(d, st, DRF_PROF_GEMM, flops);
+                        if ((rc = launch_block_chain(ca, D, chain.rows, st)) != DRF_OK) return rc;
+                    }
+                    flops = 0.0;
+                    ca.kv_in = nullptr; ca.attn = nullptr; ca.part_out = nullptr;
+                    ca.part_in = ws.skpart; ca.n_in = chain.parts;
+                    ca.weights += (1 + 2 * (size_t)dm.R) * unit;
+                }
             }
-            ca.mod = mod + (ptrdiff_t)l * 6 * D + 2 * D;    // gate1 | shift2 | scale2 | gate2 of block l, shift1 | scale1 of block l + 1 (of the final layer behind the last)
-            ca.weights = d->chain_w + (l >= 0 ? (size_t)l * per_block + 3 * unit : 0);
-            ca.qkv = ca.kv_out = nullptr;
-            if (l + 1 < n_blocks) {
+            if (next) {
+                if (in_parts) ca.parts = chain.qkv_parts;
                 (chain.attention ? ca.kv_out : ca.qkv) = chain.attention ? kv[(l + 1) & 1] : (bf16_t*)ws.qkv;
                 ca.b_qkv = d->blk[l + 1].qkv.b;
                 flops += 6.0 * M * D * D;
@@ -1212,5 +1226,5 @@ extern "C" int drf_probe_block_route(int slots, int tokens, int hidden, int head
 {
     if (slots < 1 || tokens < 1 || heads < 1 || mlp_ratio < 1 || hidden < 1 || hidden % heads != 0 || !chain_width(hidden, mlp_ratio)) return 0;
     const ChainRoute r = chain_route(slots, hidden, mlp_ratio, tokens, hidden / heads);
-    return r.rows + (r.attention ? 1000 : 0);
+    return r.rows + (r.attention ? 1000 : 0) + (r.parts > 1 ? 10000 * r.parts : 0);
 }

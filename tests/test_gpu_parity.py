@@ -250,7 +250,9 @@ def test_bf16_whole_and_edge_tiles_of_a_fat_pass(torch, drf, orc, cond, lat, slo
 @pytest.mark.parametrize("hidden,heads,lat,slots,ratio,route", [
     (256, 4, (10, 6), 3, 4, 16),        # 15 tokens: one part-filled row tile a slot; no room for whole key groups in the buffers
     (256, 4, (2, 2), 5, 2, 16),         # one token
-    (256, 4, (16, 16), 5, 2, 1016), (256, 4, (8, 16), 4, 3, 1016),
+    (256, 4, (16, 16), 5, 2, 21016), (256, 4, (8, 16), 4, 3, 21016), (256, 4, (16, 16), 50, 2, 1016),
+    (256, 4, (18, 14), 1, 4, 41016), (384, 6, (26, 38), 4, 4, 41016), (512, 8, (26, 38), 3, 4, 41016),
+    (384, 6, (26, 38), 5, 4, 21016), (256, 4, (26, 38), 8, 4, 21016), (512, 8, (26, 38), 7, 4, 21016),    # q, k, v in three parts, in two
     (384, 6, (26, 38), 12, 4, 1016),    # 247 tokens: a row tile and a key group of 15 and 23
     (384, 6, (26, 38), 25, 4, 1032), (256, 4, (26, 38), 30, 4, 1032), (512, 8, (26, 38), 25, 4, 1032),
     (512, 8, (26, 38), 16, 4, 1016),
@@ -260,7 +262,7 @@ def test_bf16_whole_and_edge_tiles_of_a_fat_pass(torch, drf, orc, cond, lat, slo
     (384, 6, (8, 8), 5, 4, 0)])
 def test_bf16_rows_of_a_block_in_one_launch(torch, drf, orc, hidden, heads, lat, slots, ratio, route):
     """Narrow models: the launch of a block's row-local part at 16, 32 and 64 rows, with and without the self-attention, whole and
-    part-filled row tiles and key groups, every MLP ratio; slots at both ends and in the middle against the oracle."""
+    part-filled row tiles and key groups, every MLP ratio, the hidden units in one, two and four parts; slots at both ends and in the middle against the oracle."""
     dit = small_dit(I.COND_CLASS, I.BF16, hidden=hidden, heads=heads, depth=2, mlp_ratio=ratio, lat_h=lat[0], lat_w=lat[1])
     w = I.weights(dit, 49, "loud")
     assert drf.probe_block_route(slots, lat[0] * lat[1] // 4, hidden, heads, ratio) == route
