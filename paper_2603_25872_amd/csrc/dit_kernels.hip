@@ -583,7 +583,11 @@ template <int PER4>
 void launch_ln4_inst(float* resid, const bf16_t* add, const bf16_t* add2, int write_back, const float* shift, const float* scale,
                      int mod_ld, int rows_per_slot, int M, void* out, int out_f32, hipStream_t st)
 {
-    const dim3 grid((M + 7) / 8), block(256);
+    // Rows a workgroup: eight, four up to 6144 rows and two up to 1024, so that few rows still reach all CUs and leave no round in part
+    // (whole evaluations of hidden 1152, eight | four | two: 512 rows 1929 | 1920 | 1919 us, 2048 3338 | 3323 | 3337, 3072 4299 | 4245 |
+    // 4230, 4096 4798 | 4790 | 4790, 8192 8361 | 8369 | 8381, 16384 14764 | 14779 | 14802).
+    const int rows = M <= 1024 ? 2 : M <= 6144 ? 4 : 8;
+    const dim3 grid((M + rows - 1) / rows), block(rows * 32);
 #define DRF_LN4(OUT, ADD, WB) \
     hipLaunchKernelGGL((ln_modulate4_kernel<PER4, OUT, ADD, WB>), grid, block, 0, st, resid, add, add2, shift, scale, mod_ld, \
                        rows_per_slot, M, (OUT*)out)
