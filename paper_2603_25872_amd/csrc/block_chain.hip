@@ -50,6 +50,14 @@ __device__ inline float quarters_max(float v)
     return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+__device__ inline float quarters_sum(float v)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // Self-attention of one head (width 64) for 16 MI queries of a slot over its T keys; queries are scaled to exponents of two.  q: this lane's
 // first query piece, rows of ldq; k, v: the head's keys and values in fragments of 32 keys (see ChainArgs).  The scores are computed
 // transposed, a lane holding keys 8 quarter .. + 7 of every 32 for query l16, which is the operand layout of P in O^T += V^T P^T; the
@@ -202,7 +210,7 @@ block_chain_kernel(const ChainArgs a, int tiles)
     // this workgroup's pieces of D hidden units, and of q, k, v
     const int c0 = part * a.mlp_ratio / a.parts, c1 = (part + 1) * a.mlp_ratio / a.parts, p0 = has_mlp ? 0 : part * 3 / a.parts, p1 = has_mlp ? 3 : (part + 1) * 3 / a.parts;
 
-    // every operand is asked for before the first is used, in the order of their use
+    // behind the attention, every operand is asked for before the first is used, in the order of their use
     constexpr int PIECES = ROWS * D / 8, PU = (PIECES + NT - 1) / NT;             // 16-byte pieces of a bf16 row tile
     constexpr int D4 = D / 4, MU = (6 * D4 + NT - 1) / NT, BU = ((5 + kChainRatio) * D4 + NT - 1) / NT;
     bf16x8 rows_in[ATT ? 1 : PU];
@@ -215,18 +223,6 @@ block_chain_kernel(const ChainArgs a, int tiles)
             if (PIECES % NT == 0 || id < PIECES) rows_in[u] = *reinterpret_cast<const bf16x8*>(a.attn + (size_t)(row0 + (r < left ? r : left - 1)) * D + c * 8);
         }
     }
-#pragma unroll
-    for (int u = 0; u < MU; ++u) {
-        const int id = tid + u * NT;
-        if (id < 6 * D4 && (has_mlp || id >= 4 * D4)) mod_in[u] = *reinterpret_cast<const f32x4*>(a.mod + (ptrdiff_t)slot * a.mod_ld + id * 4);
-    }
-#pragma unroll
-    for (int u = 0; u < BU; ++u) {
-        const int id = tid + u * NT;
-        const float* src = id < D4 ? a.b_proj + id * 4 : id < fc2_at ? a.b_fc1 + (id - D4) * 4 : id < fc2_at + D4 ? a.b_fc2 + (id - fc2_at) * 4 : a.b_qkv + (id - fc2_at - D4) * 4;
-        if (id < n_bias && (id < fc2_at + D4 ? has_mlp : has_qkv)) bias_in[u] = *reinterpret_cast<const f32x4*>(src);
-    }
-    __builtin_amdgcn_sched_barrier(0);
     bf16x8 ring[PD][NI];
     const auto wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.weights), 0, ((has_mlp ? 1 + 2 * a.mlp_ratio : 0) + (has_qkv ? 3 : 0)) * UNIT, 0x00020000);
     const int lane16 = lane * 16;
@@ -242,17 +238,6 @@ block_chain_kernel(const ChainArgs a, int tiles)
         const int r = j * 16 + l16;
         xp[j] = a.resid + (size_t)(row0 + (r < left ? r : left - 1)) * D + col;
     }
-    auto first_loads = [&]() {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < PD; ++s) load_step(ring[s], wp + s * NI * 1024);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-            for (int j = 0; j < MI; ++j) x[i][j] = *reinterpret_cast<const f32x4*>(xp[j] + i * 16);
-        __builtin_amdgcn_sched_barrier(0);
-    };
     const size_t part_len = (size_t)a.slots * T * D;
     if constexpr (ATT) {
         const size_t head = (size_t)((T + 31) / 32 * 32) * kChainHead;          // elements of a head's keys
@@ -266,7 +251,26 @@ block_chain_kernel(const ChainArgs a, int tiles)
             head_attention<MI>(q, k, k + a.slots * a.heads * head, T, ybuf + h * kChainHead * 2, PITCH);
         }
     }
-    first_loads();
+#pragma unroll
+    for (int u = 0; u < MU; ++u) {
+        const int id = tid + u * NT;
+        if (id < 6 * D4 && (has_mlp || id >= 4 * D4)) mod_in[u] = *reinterpret_cast<const f32x4*>(a.mod + (ptrdiff_t)slot * a.mod_ld + id * 4);
+    }
+#pragma unroll
+    for (int u = 0; u < BU; ++u) {
+        const int id = tid + u * NT;
+        const float* src = id < D4 ? a.b_proj + id * 4 : id < fc2_at ? a.b_fc1 + (id - D4) * 4 : id < fc2_at + D4 ? a.b_fc2 + (id - fc2_at) * 4 : a.b_qkv + (id - fc2_at - D4) * 4;
+        if (id < n_bias && (id < fc2_at + D4 ? has_mlp : has_qkv)) bias_in[u] = *reinterpret_cast<const f32x4*>(src);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < PD; ++s) load_step(ring[s], wp + s * NI * 1024);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j) x[i][j] = *reinterpret_cast<const f32x4*>(xp[j] + i * 16);
+    __builtin_amdgcn_sched_barrier(0);
     if (!ATT && a.attn) {
 #pragma unroll
         for (int u = 0; u < PU; ++u) {
@@ -333,15 +337,13 @@ block_chain_kernel(const ChainArgs a, int tiles)
             float s = 0.f, q = 0.f;
 #pragma unroll
             for (int i = 0; i < NI; ++i) s += (x[i][j][0] + x[i][j][1]) + (x[i][j][2] + x[i][j][3]);
-            s += __shfl_xor(s, 16, 64);
-            s += __shfl_xor(s, 32, 64);
+            s = quarters_sum(s);
             const float mean = s * (1.f / per_wave);
 #pragma unroll
             for (int i = 0; i < NI; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) { const float c = x[i][j][r] - mean; q = fmaf(c, c, q); }
-            q += __shfl_xor(q, 16, 64);
-            q += __shfl_xor(q, 32, 64);
+            q = quarters_sum(q);
             if (quarter == 0) red[wave * ROWS + j * 16 + l16] = make_float2(mean, q);
         }
         lds_barrier();
