@@ -32,7 +32,8 @@ drf_status drf_eps_trace(drf_denoiser* den, const float* x, const int32_t* t, co
  * drf_profile_read synchronises the device and returns, for family `which` (DRF_PROF_*), the
  * number of bracketed intervals, their summed duration in milliseconds and their summed
  * algorithmic work (flops for GEMM, attention and whole passes, bytes otherwise), then clears
- * that family's counters.  DRF_PROF_PASS_FULL are the passes that evaluate the drafts of a full
+ * that family's counters.  (A launch that runs a block's row-local part, with or without the self-attention, counts as
+ * GEMM with all its flops.)  DRF_PROF_PASS_FULL are the passes that evaluate the drafts of a full
  * block (n groups of slots), DRF_PROF_PASS_OTHER all other passes of the call (stand-alone
  * evaluations, cut-short last blocks); their work is slots x the flops of one slot evaluation
  * (2 M N K of every Linear of the blocks and 4 T^2 D per attention, unpadded head width).
