@@ -440,6 +440,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         for (int l = -1; l < n_blocks; ++l) {               // the launch behind block l's attention, with block l + 1's projection
             double flops = 0.0;
             const bool next = l + 1 < n_blocks, in_parts = chain.parts > 1 && next;
+            if (l < 0 && !next) break;
             ca.parts = 1; ca.part_out = nullptr; ca.part_in = nullptr;
             ca.qkv = ca.kv_out = nullptr;
             ca.mod = mod + (ptrdiff_t)l * 6 * D + 2 * D;    // gate1 | shift2 | scale2 | gate2 of block l, shift1 | scale1 of block l + 1 (of the final layer behind the last)

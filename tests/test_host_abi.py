@@ -252,6 +252,24 @@ def test_gemm_one_round_of_128_x_96_tiles(M, N, K):
     assert drf.probe_gemm_route(8192, 384, 384, 2)[0] != 7         # a short launch: 0.6 us, which the next kernels' code loads cost
 
 
+def test_block_routes_stay_inside_their_buffers():
+    """Keys and values in whole groups of 32 fit the buffers of q | k | v and of the hidden units, the shares of a dealt block the split
+    GEMMs' partial tiles (2^22 floats), the launches of a dealt block the chip; widths, head widths and ratios without the form have none."""
+    for D, heads in ((256, 4), (384, 6), (512, 8), (384, 12), (512, 16), (256, 8)):
+        for ratio in (1, 2, 3, 4):
+            for tokens in (1, 2, 15, 16, 17, 31, 32, 33, 63, 64, 65, 247, 256, 257, 1000, 4096):
+                for slots in (1, 2, 3, 5, 8, 16, 17, 64, 300):
+                    r = drf.probe_block_route(slots, tokens, D, heads, ratio)
+                    parts, attention, rows = max(r // 10000, 1), r // 1000 % 10, r % 1000
+                    assert rows in (0, 16, 32, 64) and parts <= ratio and (rows or r == 0) and (rows < 64 or D < 512)
+                    if attention:
+                        assert D // heads == 64 and rows <= 32 and 2 * ((tokens + 31) // 32 * 32) <= min(ratio, 3) * tokens
+                    if parts > 1:
+                        assert attention and rows == 16 and slots * ((tokens + 15) // 16) * parts <= 256 and parts * slots * tokens * D <= 1 << 22
+    for D, heads, ratio in ((128, 4, 4), (1152, 16, 4), (768, 12, 4), (384, 6, 5), (384, 5, 4)):
+        assert drf.probe_block_route(12, 256, D, heads, ratio) == 0
+
+
 def test_bf16_gemm_refuses_the_fp32_paths_activation():
     """SiLU is an epilogue of the fp32 GEMM only: the bf16 launch must say so (checked on the host, before anything else is looked
     at) instead of storing without it."""
