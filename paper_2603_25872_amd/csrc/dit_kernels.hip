@@ -290,16 +290,16 @@ __global__ void __launch_bounds__(256) ln_modulate4_kernel(float* __restrict__ r
 // order instead of by a reduction launch between the GEMM and this one (thin passes: 4.5 us of a 75 us block at 512
 // rows), and the branch output takes the rounding that a stored one takes, so that a sample's result does not depend on
 // the size of the pass it was part of beyond the order of those sums.  Always stores the stream, since the partials
-// do not outlive the next split launch.  A wave per row: these launches have few rows.
+// do not outlive the next split launch.  A workgroup of one wave per row: these launches have few rows (whole evaluations at two rows a
+// workgroup | one | four: 256 rows 1583 | 1574 | 1604 us, 512 1917 | 1913 | 1926, 1024 2537 | 2526 | 2527).
 template <int D, bool ADD>
-__global__ void __launch_bounds__(128) ln_partial_kernel(float* __restrict__ resid, const bf16_t* __restrict__ add, const PartialBranch br,
+__global__ void __launch_bounds__(64) ln_partial_kernel(float* __restrict__ resid, const bf16_t* __restrict__ add, const PartialBranch br,
                                                          const float* __restrict__ shift, const float* __restrict__ scale, int mod_ld,
-                                                         int rows_per_slot, int M, bf16_t* __restrict__ out)
+                                                         int rows_per_slot, bf16_t* __restrict__ out)
 {
     constexpr int D4 = D / 4, PER = (D4 + 63) / 64;                  // float4 pieces of a row, pieces per lane
     typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
-    const int lane = threadIdx.x & 63, row = blockIdx.x * 2 + (threadIdx.x >> 6);
-    if (row >= M) return;
+    const int lane = threadIdx.x, row = blockIdx.x;
     f32x4m* xr = reinterpret_cast<f32x4m*>(resid + (size_t)row * D);
     const size_t mrow = (size_t)(row / rows_per_slot) * mod_ld;
     // (a lane without a last piece repeats the row's last one, counts nothing for it and stores nothing)
@@ -640,10 +640,10 @@ drf_status launch_ln_modulate_partial(float* resid, const bf16_t* add, const Par
 {
     if (M == 0) return DRF_OK;
     if (!ln_partial_width(D) || mod_ld % 4 != 0 || br.sum.ldp % 4 != 0 || br.sum.splits < 1 || br.sum.splits > kMaxSplits) DRF_FAIL(DRF_ESHAPE, "LayerNorm of partial tiles: hidden %d", D);
-    const dim3 grid((M + 1) / 2), block(128);
+    const dim3 grid(M), block(64);
     auto go = [&](auto with, auto without) -> drf_status {
-        if (add) hipLaunchKernelGGL(with, grid, block, 0, st, resid, add, br, shift, scale, mod_ld, rows_per_slot, M, out);
-        else hipLaunchKernelGGL(without, grid, block, 0, st, resid, add, br, shift, scale, mod_ld, rows_per_slot, M, out);
+        if (add) hipLaunchKernelGGL(with, grid, block, 0, st, resid, add, br, shift, scale, mod_ld, rows_per_slot, out);
+        else hipLaunchKernelGGL(without, grid, block, 0, st, resid, add, br, shift, scale, mod_ld, rows_per_slot, out);
         DRF_HIP(hipGetLastError());
         return DRF_OK;
     };
