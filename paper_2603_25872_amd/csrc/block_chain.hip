@@ -182,7 +182,7 @@ __device__ __forceinline__ void head_attention(const bf16_t* const (&q)[MI], con
 //  - few rows leave CUs idle, each of the others streaming all weights: the hidden units are then dealt over two or four workgroups a row
 //    tile, and a second launch adds their shares of the stream and deals q, k and v over two or three (5 slots of 247 rows 525 -> 431 us an
 //    evaluation, one by one 510).
-// dit_s (3072 rows of hidden 384, 12 blocks) 11.66 -> 8.93 ms a call; passes of 6176 rows 998 -> 618 us, of 16384 1756 -> 1129.
+// A call of 16 passes of 3072 rows and two of 1024 (hidden 384, 12 blocks) 11.78 -> 8.88 ms; passes of 6175 rows 998 -> 618 us, of 16384 1756 -> 1129.
 template <int NI, int MI, bool ATT>
 __global__ void __launch_bounds__(kChainWaves * 64)
 block_chain_kernel(const ChainArgs a, int tiles)
