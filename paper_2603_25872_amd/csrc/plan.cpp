@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <limits>
 
 #include "common.h"
 
@@ -49,6 +50,12 @@ drf_status make_schedule(const drf_sched_config* sc, Schedule* out)
         before *= run[k];
     }
     for (int j = kRuns * len; j < n; ++j) ab[j] = before *= alpha(j);
+    // Below the normal range the order shows: a running product stays at some units above zero, where a factor rounds it back up,
+    // while two subnormal runs multiply to zero and the transitions would divide by it.  Such a schedule takes the running product.
+    if (!(before >= std::numeric_limits<double>::min())) {
+        before = 1.0;
+        for (int j = 0; j < n; ++j) ab[j] = before *= alpha(j);
+    }
     out->steps = sc->steps;
     out->stride = sc->train_steps / sc->steps;
     out->train_steps = sc->train_steps;

@@ -80,6 +80,26 @@ def test_stochastic_skip_matches_oracle(torch, drf, orc, shape, extra):
             assert relerr(got[j], want) < 1e-5, (s_from, s_to)
 
 
+@pytest.mark.parametrize("extra", [dict(eta=0.0), dict(eta=1.0), dict(sampler=DDPM)])
+def test_skip_where_the_cumulative_alpha_is_subnormal(torch, drf, orc, extra):
+    """100000 training steps: the running product reaches the subnormal range at step 43 of 50 and stays some thirty units above
+    zero from there on; products that take another way down reach zero, and the transitions divide by it."""
+    sd = dict(BASE, train_steps=100000, steps=50, **extra)
+    assert 0 < orc.abar_at(sd, 50) < 2e-322 and orc.abar_at(sd, 42) > 2.3e-308
+    rng = np.random.default_rng(3)
+    x, e = rng.standard_normal((2, 2, 333)).astype(np.float32)
+    for s_from, targets in [(50, [49, 46, 44, 43]), (44, [43, 42]), (40, [39, 38])]:
+        z = rng.standard_normal((len(targets),) + x.shape).astype(np.float32)
+        got = drf.skip_transition_noise(sd, dev(torch, x), dev(torch, e), s_from, targets, z=dev(torch, z)).cpu().numpy()
+        for j, s_to in enumerate(targets):
+            af, at = orc.abar_at(sd, s_from), orc.abar_at(sd, s_to)
+            if extra.get("sampler") == DDPM:
+                want = orc.ddpm_skip(x, e, z[j], af, at)
+            else:
+                want = orc.skip_eta(x, e, z[j], af, at, orc.sigma(extra["eta"], af, at))
+            assert relerr(got[j], want) < 1e-5, (s_from, s_to)
+
+
 @pytest.mark.parametrize("shape", [(2, 4, 16, 16), (3, 1021)])
 def test_generated_fields_equal_explicit_fields_bit_for_bit(torch, drf, shape):
     # vector (float4) and scalar routes of the kernel both read block q = element / 4 of the field
