@@ -205,6 +205,19 @@ block_chain_kernel(const ChainArgs a, int tiles)
     const int part = a.parts > 1 ? idx % a.parts : 0, tile = a.parts > 1 ? idx / a.parts : idx;
     const int slot = tile / tiles, t0 = (tile - slot * tiles) * ROWS, T = a.tokens, row0 = slot * T + t0;
     const int left = T - t0;                        // rows of the tile that exist
+    const size_t part_len = (size_t)a.slots * T * D;
+    if constexpr (!ATT && MI == 1) {
+        if (!a.attn && !a.qkv && !a.kv_out) {       // behind the last block only the shares are added up, in their order
+            for (int id = tid; id < ROWS * D / 4; id += NT) {
+                const size_t at = (size_t)row0 * D + id * 4;
+                if (id / (D / 4) >= left) break;
+                f32x4 v = *reinterpret_cast<const f32x4*>(a.part_in + at);
+                for (int s = 1; s < a.n_in; ++s) v += *reinterpret_cast<const f32x4*>(a.part_in + s * part_len + at);
+                *reinterpret_cast<f32x4*>(a.resid + at) = v;
+            }
+            return;
+        }
+    }
     const int col = wave * (16 * NI) + 4 * quarter;             // this lane's columns of a unit: col + 16 i .. + 3
     const bool has_mlp = ATT || a.attn, has_qkv = a.qkv || a.kv_out;
     // this workgroup's pieces of D hidden units, and of q, k, v
@@ -238,7 +251,6 @@ block_chain_kernel(const ChainArgs a, int tiles)
         const int r = j * 16 + l16;
         xp[j] = a.resid + (size_t)(row0 + (r < left ? r : left - 1)) * D + col;
     }
-    const size_t part_len = (size_t)a.slots * T * D;
     if constexpr (ATT) {
         const size_t head = (size_t)((T + 31) / 32 * 32) * kChainHead;          // elements of a head's keys
         for (int h = wave; h < a.heads; h += kChainWaves) {
@@ -614,6 +626,7 @@ drf_status launch_block_chain(const ChainArgs& a, int D, int rows, hipStream_t s
     if (a.mod_ld % 4 != 0 || !chain_width(D, a.mlp_ratio) || (a.attn && a.kv_in) || (a.qkv && a.kv_out) || ((a.kv_in || a.kv_out) && (a.hd != kChainHead || !a.q || rows > 32)))
         DRF_FAIL(DRF_ESHAPE, "block chain: hidden %d, MLP ratio %d, head width %d", D, a.mlp_ratio, a.hd);
     // parts: of the hidden units, each leaving its share of the stream, or of q, k, v
+    if (!a.attn && !a.kv_in && !a.qkv && !a.kv_out && !a.part_in) DRF_FAIL(DRF_EINVAL, "block chain with nothing to do");
     if (a.parts < 1 || (a.parts > 1 && (rows != 16 || (a.kv_in || a.attn ? a.parts > a.mlp_ratio || !a.part_out || a.qkv || a.kv_out : a.parts > 3))) ||
         (a.part_in && (rows != 16 || a.kv_in || a.attn || a.n_in < 1 || a.n_in > kChainRatio)))
         DRF_FAIL(DRF_ESHAPE, "block chain in %d parts", a.parts);

@@ -192,7 +192,7 @@ drf_status launch_attn_f32(const AttnArgs& a, hipStream_t st);
 struct ChainArgs {
     const bf16_t* attn;             // [M][D]: the attention output, or NULL
     const bf16_t* kv_in;            // keys and values that the self-attention is computed from in the launch itself (heads of 64), with the queries
-                                    // at q, or NULL; with neither, only the last part runs, of resid as it is
+                                    // at q, or NULL; with neither, only the last part runs, of resid as it is or of the shares at part_in
     float* resid;                   // [M][D]
     const bf16_t* weights;          // packed units in the order of their use (launch_chain_pack): proj, (fc1, fc2) of every D hidden units, q, k, v
     const float *b_proj, *b_fc1, *b_fc2, *b_qkv;
@@ -207,7 +207,7 @@ struct ChainArgs {
     size_t plane; int heads, hd; uint32_t hd_magic; int hd_shift; float q_scale;
     // For few rows (16 a workgroup) a block runs as two launches of several workgroups a row tile: the first deals the hidden units over
     // `parts`, each leaving its share of the stream at part_out[part][M][D]; the second adds the n_in shares at part_in up, stores the
-    // stream, and deals q, k and v over `parts` (1: neither).
+    // stream, and deals q, k and v over `parts` (1: neither); with no q, k, v to follow it only adds and stores.
     int parts, n_in;
     float* part_out; const float* part_in;
 };

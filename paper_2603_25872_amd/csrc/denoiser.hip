@@ -437,9 +437,9 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         ca.plane = h.plane; ca.heads = h.heads; ca.hd = h.hd; ca.hd_magic = h.hd_magic; ca.hd_shift = h.hd_shift;
         ca.q_scale = chain.attention ? chain_q_scale() : h.q_scale;
         ca.q = (bf16_t*)ws.hbuf;
-        for (int l = -1; l < n_blocks; ++l) {               // the launch behind block l's attention, with block l + 1's projection
+        for (int l = -1; l < n_blocks; ++l) {               // the launch behind block l's attention (in parts: two launches), with block l + 1's projection
             double flops = 0.0;
-            const bool next = l + 1 < n_blocks, in_parts = chain.parts > 1 && next;
+            const bool next = l + 1 < n_blocks, in_parts = chain.parts > 1;
             if (l < 0 && !next) break;
             ca.parts = 1; ca.part_out = nullptr; ca.part_in = nullptr;
             ca.qkv = ca.kv_out = nullptr;
@@ -463,7 +463,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
                         if ((rc = launch_block_chain(ca, D, chain.rows, st)) != DRF_OK) return rc;
                     }
                     flops = 0.0;
-                    ca.kv_in = nullptr; ca.attn = nullptr; ca.part_out = nullptr;
+                    ca.kv_in = nullptr; ca.attn = nullptr; ca.part_out = nullptr; ca.parts = 1;
                     ca.part_in = ws.skpart; ca.n_in = chain.parts;
                     ca.weights += (1 + 2 * (size_t)dm.R) * unit;
                 }

@@ -280,6 +280,32 @@ def test_bf16_rows_of_a_block_in_one_launch(torch, drf, orc, hidden, heads, lat,
     check(got[pick], orc.dit_eps(dit, w, x[pick], t[pick], c[pick]), TOL_BF16, "eps")
 
 
+@pytest.mark.parametrize("hidden,heads,lat,slots,route", [(256, 4, (18, 14), 1, 41016), (384, 6, (32, 32), 2, 41016), (512, 8, (26, 38), 7, 21016)])
+def test_bf16_every_block_of_a_dealt_pass_is_dealt(torch, drf, orc, hidden, heads, lat, slots, route):
+    """The hidden units of every block are dealt, the last one's too: an evaluation has one launch a block more than one whose blocks
+    are one launch each, at any depth.  A last block in one launch of few row tiles costs shallow models what dealing gains."""
+    rng = np.random.default_rng(61)
+    for depth in (1, 3):
+        dit = small_dit(I.COND_CLASS, I.BF16, hidden=hidden, heads=heads, depth=depth, mlp_ratio=4, lat_h=lat[0], lat_w=lat[1])
+        w = I.weights(dit, 51, "loud")
+        den = drf.Denoiser(dit, w)
+        tokens, launches = lat[0] * lat[1] // 4, {}
+        single = next(s for s in range(slots, 400) if drf.probe_block_route(s, tokens, hidden, heads) == 1016)
+        assert drf.probe_block_route(slots, tokens, hidden, heads) == route
+        for s in (slots, single):
+            x = rng.standard_normal((s, dit["in_ch"], dit["lat_h"], dit["lat_w"])).astype(np.float32)
+            t = rng.integers(0, 1000, size=s).astype(np.int32)
+            c = make_cond(dit, s, 69)
+            args = dev(torch, x), dev(torch, t), dev(torch, c)
+            den.profile_enable(True)
+            got = den.eps_batched(*args).cpu().numpy()
+            launches[s] = den.profile_read(drf.PROF_GEMM)["launches"]
+            den.profile_enable(False)
+            check(got[:1], orc.dit_eps(dit, w, x[:1], t[:1], c[:1]), TOL_BF16, "eps")
+        den.close()
+        assert launches[slots] - launches[single] == depth
+
+
 @pytest.mark.parametrize("lat", [(10, 6), (24, 24)])
 def test_bf16_text_context_of_300_rows(torch, drf, orc, lat):
     # 15 and 144 queries over 300 kv rows: the chunked kernel's forms with four and with eight waves
