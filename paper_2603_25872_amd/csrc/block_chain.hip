@@ -603,7 +603,11 @@ ChainRoute chain_route(int slots, int D, int mlp_ratio, int tokens, int hd)
             // two launches a block, each of all its workgroups at once
             const double tiles = (double)slots * ((tokens + 15) / 16);
             for (int p = 2; p <= 4; p += 2) {
-                const double t = p == 2 ? m.two + m.two_key * keys : m.four + m.four_key * keys;
+                // Three pieces in two parts take what four take, the launches one by one less: at hidden 512 they are ahead up to 256 keys
+                // (us a block, one by one | two parts: 4 x 200 rows 47.9 | 51.2, 4 x 256 48.2 | 50.9, 17 x 32 46.3 | 47.8, 12 x 64 48.2 | 47.4),
+                // not beyond, where their attention is another kernel (2 x 400 56.9 | 54.5), nor at hidden 384 (2 x 256 35.4 | 34.2).
+                const double uneven = mlp_ratio % p && D == 512 && tokens <= 256 ? 1.05 : 1.0;
+                const double t = (p == 2 ? m.two + m.two_key * keys : m.four + m.four_key * keys) * uneven;
                 if (p <= mlp_ratio && tiles * p <= 256.0 && t < us) { us = t; best = ChainRoute{ 16, true, p, tiles * 3 <= 256.0 ? 3 : 2 }; }
             }
         }

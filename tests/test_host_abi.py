@@ -270,6 +270,16 @@ def test_block_routes_stay_inside_their_buffers():
         assert drf.probe_block_route(12, 256, D, heads, ratio) == 0
 
 
+@pytest.mark.parametrize("slots,tokens", [(17, 32), (10, 64), (6, 128), (4, 256)])
+def test_block_route_of_three_pieces_of_hidden_units(slots, tokens):
+    """Three pieces do not deal evenly over two workgroups: at hidden 512 and few rows the launches one by one are the faster form; two
+    and four pieces, longer sequences and hidden 384 keep the dealt one."""
+    assert drf.probe_block_route(slots, tokens, 512, 8, 3) == 0
+    assert drf.probe_block_route(slots, tokens, 512, 8, 2) == 21016 and drf.probe_block_route(slots, tokens, 512, 8, 4) == 41016
+    for slots, tokens, hidden in ((2, 400, 512), (5, 247, 512), (2, 256, 384)):
+        assert drf.probe_block_route(slots, tokens, hidden, hidden // 64, 3) == 21016
+
+
 def test_bf16_gemm_refuses_the_fp32_paths_activation():
     """SiLU is an epilogue of the fp32 GEMM only: the bf16 launch must say so (checked on the host, before anything else is looked
     at) instead of storing without it."""
