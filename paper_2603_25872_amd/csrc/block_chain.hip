@@ -278,10 +278,12 @@ block_chain_kernel(const ChainArgs a, int tiles)
 #pragma unroll
     for (int s = 0; s < PD; ++s) load_step(ring[s], wp + s * NI * 1024);
     __builtin_amdgcn_sched_barrier(0);
+    // (not where the stream is the sum of shares: another workgroup of the row tile stores it in this launch)
+    if (ATT || MI > 1 || !a.part_in)
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < MI; ++j) x[i][j] = *reinterpret_cast<const f32x4*>(xp[j] + i * 16);
+            for (int j = 0; j < MI; ++j) x[i][j] = *reinterpret_cast<const f32x4*>(xp[j] + i * 16);
     __builtin_amdgcn_sched_barrier(0);
     if (!ATT && a.attn) {
 #pragma unroll
