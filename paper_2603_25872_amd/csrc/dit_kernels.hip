@@ -583,10 +583,14 @@ template <int PER4>
 void launch_ln4_inst(float* resid, const bf16_t* add, const bf16_t* add2, int write_back, const float* shift, const float* scale,
                      int mod_ld, int rows_per_slot, int M, void* out, int out_f32, hipStream_t st)
 {
-    // Rows a workgroup: eight, four up to 6144 rows and two up to 1024, so that few rows still reach all CUs and leave no round in part
-    // (whole evaluations of hidden 1152, eight | four | two: 512 rows 1929 | 1920 | 1919 us, 2048 3338 | 3323 | 3337, 3072 4299 | 4245 |
-    // 4230, 4096 4798 | 4790 | 4790, 8192 8361 | 8369 | 8381, 16384 14764 | 14779 | 14802).
-    const int rows = M <= 1024 ? 2 : M <= 6144 ? 4 : 8;
+    // Rows a workgroup: eight, four up to 5120 rows and two up to 1024, so that few rows still reach all CUs and leave no round in part.
+    // Times of a launch, us, eight | that many, one pending branch, then two: hidden 1152, 500 rows 4.9 | 4.4; 1000 5.3 | 4.85; 2250 9.5 |
+    // 8.8, 10.2 | 9.05; 3000 9.85 | 9.25, 11.2 | 10.0; 4000 10.6 | 10.4, 12.9 | 13.0; 6000 at four rows 12.15 | 12.4, 18.4 | 18.75.  768: 3000 8.05 |
+    // 7.55, 8.0 | 7.2; 4000 8.65 | 8.55, 9.3 | 9.6; 6000 even.  384: 2250 4.5 | 4.3, 4.7 | 4.65; 4000 4.95 | 4.95, 5.2 | 5.5; 6000 6.5 | 6.65, 7.2 |
+    // 7.6.  128: within 0.1 at all of these.  Whole evaluations of six blocks at eight | four rows: 4608 rows of 384, 768, 1024, 1152
+    // 453 | 451, 757 | 751, 1207 | 1199, 1392 | 1386; 5120 489 | 485, 775 | 771, 1250 | 1241, 1423 | 1420; 5632 513 | 514, 957 | 957, 1320 | 1320,
+    // 1522 | 1525; 6144 521 | 521, 1023 | 1025, 1391 | 1395, 1571 | 1575.
+    const int rows = M <= 1024 ? 2 : M <= 5120 ? 4 : 8;
     const dim3 grid((M + rows - 1) / rows), block(rows * 32);
 #define DRF_LN4(OUT, ADD, WB) \
     hipLaunchKernelGGL((ln_modulate4_kernel<PER4, OUT, ADD, WB>), grid, block, 0, st, resid, add, add2, shift, scale, mod_ld, \
