@@ -280,6 +280,50 @@ def test_bf16_rows_of_a_block_in_one_launch(torch, drf, orc, hidden, heads, lat,
     check(got[pick], orc.dit_eps(dit, w, x[pick], t[pick], c[pick]), TOL_BF16, "eps")
 
 
+@pytest.mark.parametrize("hidden,heads,lat,slots,route", [(256, 8, (26, 38), 17, 32), (512, 16, (26, 38), 13, 16)])
+def test_bf16_rows_of_a_block_behind_their_own_attention_launch(torch, drf, orc, hidden, heads, lat, slots, route):
+    """The forms without the self-attention at 32 rows of hidden 256 and at 16 of hidden 512, a part-filled row tile in every slot."""
+    test_bf16_rows_of_a_block_in_one_launch(torch, drf, orc, hidden, heads, lat, slots, 4, route)
+
+
+@pytest.mark.parametrize("hidden,slots,route", [(256, 12, 1016), (384, 5, 21016), (384, 4, 41016), (384, 25, 1032), (512, 12, 1016), (512, 25, 1032)])
+def test_bf16_scores_of_minus_infinity_in_the_block_launch(torch, drf, orc, hidden, slots, route):
+    """Tokens are of two kinds, told apart by one large channel each.  Keys of the second kind score below the range of fp32, those of
+    the first around 2e37: the second kind gets no weight, also where it fills the first step of 64 keys, the last or several.  Values
+    differ by kind, and hardly within one, so it does not matter which of the far-apart scores of the first kind is the largest."""
+    dit = small_dit(I.COND_CLASS, I.BF16, hidden=hidden, heads=hidden // 64, lat_h=26, lat_w=38)
+    T, D = 247, hidden
+    assert drf.probe_block_route(slots, T, D, D // 64, 4) == route
+    w = I.weights(dit, 53, "loud")
+    v = I.param_views(dit, w)
+    c1, c2 = 5, 70
+    v["patch_w"][c1, 0] = v["patch_w"][c2, 4] = 1e4             # channel 0's, channel 1's first pixel of a patch
+    v["blk0.ada_w"][:] = 0
+    v["blk0.ada_b"][:] = np.repeat(np.float32([0, 0, 1, 0, 0, 1]), D)
+    qw, qb = v["blk0.qkv_w"], v["blk0.qkv_b"]
+    qw[:D] = 0
+    qb[:D:64] = 1e19
+    qw[D:2 * D:64] = 0
+    qw[D:2 * D:64, c2] = -2.2e20                                # LN gives -1 / sqrt(D) there for the first kind, sqrt(D) for the second
+    qb[D:2 * D:64] = 0
+    qw[2 * D:] *= 3000
+    rng = np.random.default_rng(67)
+    x = rng.standard_normal((slots, 4, 13, 2, 19, 2)).astype(np.float32)
+    second = [range(0, 64), range(T - 40, T), range(64, 128), range(0, 200)]
+    for s in range(slots):
+        kind = np.isin(np.arange(T), second[s % 4]).astype(np.float32).reshape(13, 19)
+        x[s, 0, :, 0, :, 0], x[s, 1, :, 0, :, 0] = 1 - kind, kind
+    x = x.reshape(slots, 4, 26, 38)
+    t = rng.integers(0, 1000, size=slots).astype(np.int32)
+    c = make_cond(dit, slots, 71)
+    den = drf.Denoiser(dit, w)
+    args = dev(torch, x), dev(torch, t), dev(torch, c)
+    got, resid = den.eps_batched(*args).cpu().numpy(), den.eps_trace(*args, 1).cpu().numpy()
+    den.close()
+    check(resid.reshape(slots, -1)[:4], orc.dit_eps(dit, w, x[:4], t[:4], c[:4], stop_blocks=1).reshape(4, -1), TOL_BF16, "resid1")
+    check(got[:4], orc.dit_eps(dit, w, x[:4], t[:4], c[:4]), TOL_BF16, "eps")
+
+
 @pytest.mark.parametrize("hidden,heads,lat,slots,route", [(256, 4, (18, 14), 1, 41016), (384, 6, (32, 32), 2, 41016), (512, 8, (26, 38), 7, 21016)])
 def test_bf16_every_block_of_a_dealt_pass_is_dealt(torch, drf, orc, hidden, heads, lat, slots, route):
     """The hidden units of every block are dealt, the last one's too: an evaluation has one launch a block more than one whose blocks
