@@ -94,8 +94,9 @@ typedef enum { DRF_DDIM = 0, DRF_DDPM = 1, DRF_EULER = 2 } drf_sampler;
  * dtype DRF_BF16: every parameter is rounded to bf16 (round-to-nearest-even) once at
  * create; GEMM and attention operands are bf16 with fp32 accumulation; the gated branch
  * outputs (attention projection, MLP) are rounded to bf16 before they are added to the
- * residual stream; LayerNorm and softmax statistics, the residual stream itself, latents
- * and all sampler updates are fp32.
+ * residual stream, except where a pass runs a block as one or two launches (hidden 256, 384
+ * or 512, by the size of the pass): there they stay fp32; LayerNorm and softmax statistics,
+ * the residual stream itself, latents and all sampler updates are fp32.
  * dtype DRF_F32: everything in fp32.
  * Requirements: hidden % heads == 0, hidden % 4 == 0, lat_h, lat_w % patch == 0;
  * DRF_BF16 also needs hidden % 64 == 0, d % 8 == 0, d <= 96, cond_dim % 64 == 0 for text.

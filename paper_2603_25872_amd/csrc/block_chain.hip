@@ -167,22 +167,26 @@ __device__ __forceinline__ void head_attention(const bf16_t* const (&q)[MI], con
 
 // A workgroup takes 16 MI rows of one slot through the whole chain.  The rows stay on the chip: activations as bf16 tiles in LDS, the stream in
 // registers in the accumulators' layout; a wave owns 16 NI columns of every D x D unit of weights.
-// What bounds it: the weights, which every workgroup reads in full (3.5 MB a block at hidden 384) through its CU's 64 bytes a clock: 23 us
-// of the 38 that a launch of 16 rows takes, however many workgroups there are up to 256; barriers, LayerNorms and GELU take
-// the rest.  Against that stand seven launches of 5 to 13 us with their results through memory.  Hence:
+// What bounds it: the weights, which every workgroup reads in full (3.5 MB a block at hidden 384, ratio 4) through its CU's 64 bytes a
+// clock: 23 us of the 41 that a launch of 16 rows takes (with or without the attention, 192 and 224 workgroups), however many there are
+// up to 256; the attention, barriers, LayerNorms and GELU take the rest.  Against that stand seven launches of 5 to 13 us with their
+// results through memory.  Hence:
 //  - weights go from memory to registers in a layout of their own (1 KB of consecutive bytes per 16 x 32 fragment; 16 rows of 64
 //    bytes an instruction take the vector-memory path two to three times as long), each fragment read by one wave once, four k-steps
 //    ahead of their use and across the barriers (six steps ahead: no gain; each XCD's workgroups touching all lines first: no gain);
-//  - 16 rows while all workgroups run at once, since the stream costs the same for 32 (43 us) and 64 (57 us, matrix unit);
+//  - 16 rows while all workgroups run at once, since the stream costs the same for 32 (47 us without the attention, 52 with it and
+//    200 workgroups, 56 with 256) and 64 (65 with 200, 72 with 256: matrix unit, and at hidden 384 all 256 registers and 9 more in
+//    scratch, 40 bytes a lane; 64 x 256 rows are still faster so than at 32 rows a workgroup, 1129 against 1229 us an evaluation);
 //  - biases, modulation rows and the attention output are asked for together ahead of everything (asked for where they were used,
 //    they cost 64 rows 10 us);
 //  - ATT: the self-attention of these rows' queries, a head a wave, from keys and values that the launch before left as operand fragments:
-//    3 us more at 256 keys, where a launch of its own takes 10; from head-major planes, transposing values through LDS in every
-//    workgroup, it took 7.5 us.
+//    5 us at 256 keys by its clocks, 3 of them more than the form that reads an attention output takes, where a launch of its own
+//    takes 10; from head-major planes, transposing values through LDS in every workgroup, it took 7.5 us;
 //  - few rows leave CUs idle, each of the others streaming all weights: the hidden units are then dealt over two or four workgroups a row
-//    tile, and a second launch adds their shares of the stream and deals q, k and v over two or three (5 slots of 247 rows 525 -> 431 us an
-//    evaluation, one by one 510).
-// A call of 16 passes of 3072 rows and two of 1024 (hidden 384, 12 blocks) 11.78 -> 8.88 ms; passes of 6175 rows 998 -> 618 us, of 16384 1756 -> 1129.
+//    tile (projection and 2 ratio / parts units each: 19 us at 4 x 256 rows in four parts, 23 at 5 x 247 in two), and a second launch adds
+//    their shares of the stream and deals q, k and v over two or three (9 to 12 us; 5 us to add up behind the last block, and for
+//    the first q, k and v).  5 slots of 247 rows 525 us an evaluation of 12 blocks in one launch each, 422 so, one by one 510.
+// A call of 16 passes of 3072 rows and two of 1024 (hidden 384, 12 blocks) 11.78 -> 8.84 ms; passes of 6175 rows 998 -> 618 us, of 16384 1756 -> 1129.
 template <int NI, int MI, bool ATT>
 __global__ void __launch_bounds__(kChainWaves * 64)
 block_chain_kernel(const ChainArgs a, int tiles)
@@ -569,12 +573,18 @@ bool chain_width(int D, int mlp_ratio) { return (D == 256 || D == 384 || D == 51
 // launches one by one without the attention's, at 0 rows and per 1000 rows.  Fitted to whole evaluations of 1 to 64 slots of 16 to 1024
 // tokens, e.g. in us per evaluation of 12 blocks one by one | 16 rows with attention | 32 | the best plain form:
 //   hidden 256: 256 rows 422 | 323 | 378 | 357, 4096 565 | 342 | 375 | 394, 8192 792 | 583 | 403 | 510, 16384 1114 | 1060 | 739 | 678 (64 rows)
-//   hidden 384: 256 rows 408 | 535 | 622 | 560, 1024 488 | 512 | 600 | 539, 2048 591 | 514 | 597 | 554, 6176 (247 tokens a slot) 998 | 1016 | 618 | 683,
+//   hidden 384: 256 rows 408 | 535 | 622 | 560, 1024 488 | 512 | 600 | 539, 2048 591 | 514 | 597 | 554, 6175 (247 tokens a slot) 998 | 1016 | 618 | 683,
 //               16384 1756 | 2000 | 1229 | 1129 (64 rows), 64 x 1024 6453 | 10570 | 6773 | 5066 (64 rows)
 //   hidden 512: 2048 rows 701 | 829 | 912 | 861, 4096 998 | 875 | 925 | 949, 8192 1367 | 1655 | 1012 | 1063, 64 x 1024 9731 | 16532 | 10265 | 9405 (32 rows)
 // With few rows most CUs would idle while each workgroup streams all weights; the hidden units in two or four parts cost a second launch and
 // a repeated attention and projection: hidden 384, one launch | two parts | four: 1 x 256 rows 535 | 426 | 382 (one by one 410), 4 x 256 518 |
 // 421 | 390 (487), 5 x 247 525 | 431 | 563 (510), 1 x 1024 627 | 528 | 502; hidden 256, 4 x 256 322 | 300 | 288; hidden 512 825 | 625 | 567 (609).
+// Fitted while the last block and the first q, k and v were not dealt; now 1 x 256 371, 4 x 256 380, 5 x 247 422, 1 x 1024 493, hidden 256 283,
+// hidden 512 550.  At hidden 512 the launches one by one are modelled too long from 2048 rows on (8 x 256 767 us against 707), and two
+// parts too short (8 x 256 600 against 689): the choice there is between near equals.
+// The models are of ratio 4.  At ratios 1 to 3 both sides shrink: the one-launch forms by 5.0 us a unit of ratio (hidden 384), two parts by
+// 0.6 us from 4 to 3 and 5 from 3 to 2, the launches one by one by 0.4 us and 0.65 per 1000 rows.  Over 20 sizes of 1 to 64 slots of 64 to
+// 2304 tokens with heads of 32, 64 and 96 no choice at these ratios is slower than one by one beyond the spread of 1 to 2 %.
 struct ChainModel { int D; double att16, att16_key, att32, att32_key, plain16, plain32, plain64, two, two_key, four, four_key, apart, apart_row; };
 const ChainModel kChainModels[] = {
     { 256, 23.0,  9.5, 27.5, 13.5, 23.0, 29.0, 40.0, 20.3,  9.8, 18.6, 10.8, 27.0, 3.0 },

@@ -288,10 +288,11 @@ __global__ void __launch_bounds__(256) ln_modulate4_kernel(float* __restrict__ r
 
 // ln_modulate4_kernel with the output of a split GEMM as the branch to add: the partial tiles are summed here in a fixed
 // order instead of by a reduction launch between the GEMM and this one (thin passes: 4.5 us of a 75 us block at 512
-// rows), and the branch output takes the rounding that a stored one takes, so that a sample's result does not depend on
-// the size of the pass it was part of beyond the order of those sums.  Always stores the stream, since the partials
-// do not outlive the next split launch.  A workgroup of one wave per row: these launches have few rows (whole evaluations at two rows a
-// workgroup | one | four: 256 rows 1583 | 1574 | 1604 us, 512 1917 | 1913 | 1926, 1024 2537 | 2526 | 2527).
+// rows), and the branch output takes the rounding that a stored one takes, so that launch by launch a sample's result does not
+// depend on the size of the pass it was part of beyond the order of those sums (narrow models round elsewhere in passes that
+// block_chain.hip takes: there the branch outputs stay fp32).  Always stores the stream, since the partials do not outlive the
+// next split launch.  A workgroup of one wave per row: these launches have few rows (us a launch at two rows a workgroup | one: hidden
+// 1152, 250 rows 5.0 | 4.2, 500 5.3 | 4.9, 1000 7.2 | 6.75; 384, 250 3.95 | 3.3, 1000 5.2 | 4.65; four rows: whole evaluations of 256 rows 1604 us against 1583 at two).
 template <int D, bool ADD>
 __global__ void __launch_bounds__(64) ln_partial_kernel(float* __restrict__ resid, const bf16_t* __restrict__ add, const PartialBranch br,
                                                          const float* __restrict__ shift, const float* __restrict__ scale, int mod_ld,
