@@ -143,6 +143,8 @@ drf_status launch_gemm_bf16(const bf16_t* A, const bf16_t* W, int M, int N, int 
 // (no GELU with fp32 output).
 drf_status launch_gemm_wide_288(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first);
 drf_status launch_gemm_wide_256(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first);
+drf_status launch_gemm_wide_192(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first);
+drf_status launch_gemm_wide_192x288(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first);
 // The tiles of gemm_pair.h (8, 13, 16, 17) on rows m_first .. M - 1, likewise.
 drf_status launch_gemm_pair(int tile, const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first);
 size_t gemm_splitk_scratch_bytes();

@@ -585,10 +585,18 @@ drf_status launch_bf16_splitk(const bf16_t* A, const bf16_t* W, int M, int N, in
 // 128 39.8; 8192 x 384 x 1536 14.4, 128 x 128 15.8), on four waves by two (four by one: 35.7, 15.4).  Its base keeps launches of K <= 512 on
 // 128 x 128: they would gain 0.2-0.6 us, and the other launches of a block, which then find another kernel's code in the instruction
 // caches, lose as much or more (4096 rows of 256: QKV 7.1 -> 6.9, the other three 20.0 -> 21.4).
+// 21 and 22 are there for rounds that the 256-row tiles of 256 and 288 columns leave part-filled.  Inside a pass of hidden 1152, against the
+// tiles chosen before: 256 x 192 QKV of 3072 to 3584 rows 34 -> 30 us (one round of 216 to 252 tiles, 182 before), whole evaluations of
+// 8704 to 10752 rows (K = 4608 in one round; 170 to 210 tiles of 256 x 256 before) -4 to -7 %; 192 x 288 K = 4608 of 24576 rows 204 -> 180
+// (512 tiles, two whole rounds; 480 before) and of 12288 rows -3.4 to -6.6, the update of the stream at 24576 rows (K = 1152) -7, QKV of
+// 12288 rows -3.9 to -7.7.  The constants of both are fitted to those launches and to those where they lose: 256 x 192 gated K = 4608
+// of 16384 rows +33, GELU of 8192 and 16384 rows +7.4 and +5; 192 x 288 GELU of 12288 and 24576 rows +9.5 and +13.
 struct TileModel { int id, bm, bn, wk, per_cu; double base, round, lat, thr, red0, red1; };     // red0 = 0: never split
 const TileModel kTiles[] = {
     {  2, 256, 288, 1, 1, 0.00, 8.99, 1.59, 0.00, 0.0, 0.0 },
     {  3, 256, 256, 1, 1, 0.00, 7.66, 1.31, 0.00, 0.0, 0.0 },
+    { 22, 192, 288, 1, 1, 0.00, 8.50, 1.18, 0.00, 0.0, 0.0 },
+    { 21, 256, 192, 1, 1, 0.00, 8.60, 0.94, 0.00, 0.0, 0.0 },
     { 13, 256, 144, 1, 1, 0.10, 8.17, 0.94, 0.00, 0.0, 0.0 },
     { 18, 256, 144, 1, 1, 0.10, 6.50, 1.02, 0.00, 0.0, 0.0 },
     { 14, 256, 128, 1, 1, 0.24, 4.29, 0.85, 0.00, 0.0, 0.0 },
@@ -603,6 +611,20 @@ const TileModel kTiles[] = {
     {  1,  64,  64, 1, 2, 1.91, 1.40, 0.22, 0.19, 2.7, 1.8 },
     { 12,  32,  64, 2, 2, 1.98, 1.34, 0.29, 0.26, 2.9, 1.7 },
 };
+
+// Tiles 21 and 22 are for the launches they were measured ahead in: 21 a single round (of q, k, v; of other launches from 200 tiles on, so
+// that 198, 8193 to 8448 rows of hidden 1152, stay as two launches), 22 up to three rounds, but not for head-major stores whose 32 rows cross slots;
+// neither for GELU.  Beyond, and as one of two launches (pick_row_split), where the model puts them level or ahead, their larger
+// share of fragment reads and copies costs more than a part-filled last round (hidden 1152, whole evaluations: K = 4608 of 18432
+// rows in two rounds of 21 +1.3 %; 14336 and 28672 rows cut in two +2.6 %).
+bool offered(const TileModel& t, const Epilogue& e, int M, int N)
+{
+    if (t.id != 21 && t.id != 22) return true;
+    const bool heads = e.mode == EPI_STORE_HEADS;
+    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    if (e.mode == EPI_STORE_GELU) return false;
+    return t.id == 21 ? tiles <= 256 && (heads || tiles >= 200) : tiles <= 768 && (!heads || e.rows_per_slot % 32 == 0);
+}
 
 double model_us(const TileModel& t, int M, int N, int K, int splits, bool leave)
 {
@@ -643,7 +665,7 @@ int wide_form(int tile, int rows, int N, int K, const Epilogue& e)
 // Rows m_first .. M - 1 of the problem with tile v (m_first a multiple of the tile's height).
 drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first)
 {
-    if (e.mode == EPI_STORE_GELU && e.out_f32 && (v == 2 || v == 3)) v = 14;      // (the 4-wave tiles have no such store)
+    if (e.mode == EPI_STORE_GELU && e.out_f32 && (v == 2 || v == 3 || v == 21 || v == 22)) v = 14;      // (the 4-wave tiles have no such store)
     switch (v) {
     case 1: return launch_bf16_xl<64, 64, 64, 4, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 2: return launch_gemm_wide_288(A, W, M, N, K, e, st, m_first);
@@ -657,7 +679,7 @@ drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, in
     case 9: return launch_bf16_xl<64, 64, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 11: return launch_bf16_xl<64, 96, 64, 3, 2, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 12: return launch_bf16_xl<32, 64, 64, 3, 1, 2, 2>(A, W, M, N, K, e, st, m_first);
-    case 7: case 18: case 19: case 20: return launch_last_tiles(v, A, W, M, N, K, e, st, m_first);
+    case 7: case 18: case 19: case 20: case 21: case 22: return launch_last_tiles(v, A, W, M, N, K, e, st, m_first);
     case 14: return launch_bf16_xl<256, 128, 64, 3, 4, 2, 1, true>(A, W, M, N, K, e, st, m_first);
     default: return launch_bf16_xl<128, 128, 64, 4, 4, 2>(A, W, M, N, K, e, st, m_first);      // 5, or a number that names no tile
     }
@@ -673,12 +695,12 @@ int pick_row_split(int M, int N, int K, double one_us, int* id_a, int* id_b)
     int rows = 0;
     for (const TileModel& a : kTiles) {
         const long long tn = (N + a.bn - 1) / a.bn, cap = 256LL * a.per_cu, rounds = M / a.bm * tn / cap;
-        if (rounds < 1 || K % (64 * a.wk) != 0) continue;
+        if (rounds < 1 || K % (64 * a.wk) != 0 || a.id == 21 || a.id == 22) continue;
         const int ra = (int)(rounds * cap / tn) * a.bm;
         if (ra == 0 || ra >= M) continue;
         const double ua = model_us(a, ra, N, K, 1, false);
         for (const TileModel& b : kTiles) {
-            if (K % (64 * b.wk) != 0 || ra % b.bm != 0) continue;
+            if (K % (64 * b.wk) != 0 || ra % b.bm != 0 || b.id == 21 || b.id == 22) continue;
             const double us = ua + model_us(b, M - ra, N, K, 1, false);
             if (us < best) { best = us; rows = ra; *id_a = a.id; *id_b = b.id; }
         }
@@ -688,11 +710,11 @@ int pick_row_split(int M, int N, int K, double one_us, int* id_a, int* id_b)
 
 // The tile and split with the least modelled time.  Two K groups need whole pairs of k-tiles; a split leaves every
 // part at least two k-steps and its partial tiles must fit the scratch.
-double pick_tile(int M, int N, int K, bool may_split, bool leave, int* id, int* splits)
+double pick_tile(int M, int N, int K, const Epilogue& e, bool may_split, bool leave, int* id, int* splits)
 {
     double best = 1e300;
     for (const TileModel& t : kTiles) {
-        if (K % (64 * t.wk) != 0) continue;
+        if (K % (64 * t.wk) != 0 || !offered(t, e, M, N)) continue;
         const size_t tile_floats = (size_t)((M + t.bm - 1) / t.bm) * t.bm * ((size_t)((N + t.bn - 1) / t.bn) * t.bn);
         const int most = may_split && t.red0 > 0.0 && tile_floats / (t.bm * t.bn) < 512 ? kMaxSplits : 1;   // (enough tiles fill the chip unsplit)
         for (int s2 = 1; s2 <= most; ++s2) {
@@ -711,7 +733,7 @@ size_t gemm_splitk_scratch_bytes() { return kSplitKScratchFloats * sizeof(float)
 GemmRoute gemm_route(int M, int N, int K, const Epilogue& e, bool may_split, bool leave)
 {
     GemmRoute r{ 0, 1, 0, 0 };
-    const double us = pick_tile(M, N, K, may_split, leave, &r.tile, &r.splits);
+    const double us = pick_tile(M, N, K, e, may_split, leave, &r.tile, &r.splits);
     if (r.splits == 1 && M >= 2048) r.first_rows = pick_row_split(M, N, K, us, &r.first_tile, &r.tile);
     r.tile = wide_form(r.tile, M - r.first_rows, N, K, e);
     r.first_tile = wide_form(r.first_tile, r.first_rows, N, K, e);
@@ -809,7 +831,7 @@ drf_status launch_gemm_f32_ln(const float* resid, const RowNorm& ln, const float
 
 namespace {
 
-// Tiles 7, 18, 19 and 20, at the end of the file so that their code lies behind that of the others: between the kernels of small problems, whose
+// Tiles 7 and 18 to 22, at the end of the file so that their code lies behind that of the others: between the kernels of small problems, whose
 // launches are as long as a few misses of the instruction cache, it costs passes of 1500 to 2000 rows of hidden 384 1 % (six passes of 24
 // slots of 63 tokens 3.29 -> 3.26 ms, of 32 slots 3.43 -> 3.38).
 drf_status launch_last_tiles(int v, const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first)
@@ -818,6 +840,8 @@ drf_status launch_last_tiles(int v, const bf16_t* A, const bf16_t* W, int M, int
     case 7: return launch_bf16_xl<128, 96, 64, 3, 4, 2>(A, W, M, N, K, e, st, m_first);
     case 18: return launch_bf16_xl<256, 144, 64, 3, 8, 1>(A, W, M, N, K, e, st, m_first);
     case 19: return launch_bf16_xl<256, 256, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
+    case 21: return launch_gemm_wide_192(A, W, M, N, K, e, st, m_first);
+    case 22: return launch_gemm_wide_192x288(A, W, M, N, K, e, st, m_first);
     default: return launch_bf16_xl<256, 288, 64, 2, 4, 2>(A, W, M, N, K, e, st, m_first);
     }
 }

@@ -1,5 +1,5 @@
-// bf16 GEMM at tiles of 256 rows for problems that fill the chip with them: four waves, one per SIMD, each with a
-// quarter of the tile (128 x 144 or 128 x 128) and a SIMD's whole register file.
+// bf16 GEMM at tiles of 256 or 192 rows for problems that fill the chip with them: four waves, one per SIMD, each with a
+// quarter of the tile (128 x 144, 128 x 128, 128 x 96 or 96 x 144) and a SIMD's whole register file.
 //
 // Against the 8-wave form of the same tile (64 x 144 per wave) the fragment reads of a k-tile fall from 213 to 139 KB, which
 // with the 70 KB that the copies write was 96 % of what the LDS port moves in the k-tile's MFMA time and is now 70 %.  What is
@@ -103,7 +103,7 @@ gemm_bf16_wide_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W
     };
     // schedule of a k-tile (see tile below): reads every RSTEP slots; REL, LAND: slots of the two barriers; copies from LFIRST on, one every LSTEP
     // slots, the FIRST_TILE first of them in the tile whose stage they refill, the others in the next tile
-    constexpr int RSTEP = 2, REL = RSTEP * RD + 2, LAND = S + 24, LFIRST = REL + 1, LSTEP = 7;
+    constexpr int RSTEP = 2, REL = RSTEP * RD + 2, LAND = S + 24 < 2 * S - RSTEP * RD ? S + 24 : 2 * S - RSTEP * RD, LFIRST = REL + 1, LSTEP = 7;
     constexpr int FIRST_TILE = (2 * S - LFIRST + LSTEP - 1) / LSTEP < NL ? (2 * S - LFIRST + LSTEP - 1) / LSTEP : NL;
     static_assert(REL < S && LAND + RSTEP * RD <= 2 * S && LFIRST + (NL - 1) * LSTEP - 2 * S < REL, "schedule");
     auto copies_before = [](int slot) constexpr { return (slot - LFIRST + LSTEP - 1) / LSTEP < NL ? (slot - LFIRST + LSTEP - 1) / LSTEP : NL; };

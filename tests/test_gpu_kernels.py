@@ -101,6 +101,21 @@ def test_gemm_bf16_four_wave_tiles(torch, drf, orc, variant, M, N, K):
     assert err < 6e-3, err                       # bf16 rounding of the stored result: 2^-8 relative at worst
 
 
+@pytest.mark.parametrize("variant,bm,bn", [(21, 256, 192), (22, 192, 288)])
+@pytest.mark.parametrize("dm,dn,K", [(0, 0, 64), (1, 4, 128), (-1, -4, 192), (0, 0, 1088), (37, 100, 320), (-150, -180, 256)])
+def test_gemm_bf16_tiles_for_part_filled_rounds(torch, drf, orc, variant, bm, bn, K, dm, dn):
+    """Two tiles each way, whole, one row and four columns more and less, ragged, and fewer than one wave's rows and columns; 1 to 5 and 17 k-tiles."""
+    M, N = 2 * bm + dm, 2 * bn + dn
+    rng = np.random.default_rng(M + N + K)
+    A = bf16_round(torch, rng.standard_normal((M, K)))
+    W = bf16_round(torch, rng.standard_normal((N, K)) * 0.1)
+    b = rng.standard_normal(N).astype(np.float32)
+    out = drf.probe_gemm_bf16(A.cuda(), W.cuda(), torch.from_numpy(b).cuda(), variant=variant).float().cpu().numpy()
+    want = orc.linear(A.float().numpy(), W.float().numpy(), b)
+    err = np.abs(out - want).max() / np.abs(want).max()
+    assert err < 6e-3, err                       # bf16 rounding of the stored result: 2^-8 relative at worst
+
+
 @pytest.mark.parametrize("M,N,K", [(20011, 1152, 384), (12803, 1540, 384), (10957, 1540, 384)])
 def test_gemm_bf16_rows_in_two_launches(torch, drf, M, N, K):
     """Full rounds of one tile and the remaining rows with another: same sums in the same order as one launch of a

@@ -252,6 +252,23 @@ def test_gemm_one_round_of_128_x_96_tiles(M, N, K):
     assert drf.probe_gemm_route(8192, 384, 384, 2)[0] != 7         # a short launch: 0.6 us, which the next kernels' code loads cost
 
 
+@pytest.mark.parametrize("M,N,K,kind,rows_per_slot,tile", [
+    (3072, 3456, 1152, 1, 256, 21), (3276, 3456, 1152, 1, 252, 21), (10240, 1152, 4608, 2, 256, 21),
+    (24576, 1152, 4608, 2, 4096, 22), (24576, 1152, 1152, 4, 4096, 22), (12288, 3456, 1152, 1, 256, 22)])
+def test_gemm_tiles_for_part_filled_rounds(M, N, K, kind, rows_per_slot, tile):
+    """One round of 256 x 192, one to three of 192 x 288 where other tiles leave a round part-filled; neither for GELU or as one of two
+    launches, the latter not where head-major rows cross slots (times inside a pass beside the tile table)."""
+    assert drf.probe_gemm_route(M, N, K, kind, rows_per_slot) == (tile, 1, 0, 0)
+    for rows in range(2048, 65536, 512):
+        tile, _, first_tile, _ = drf.probe_gemm_route(rows, N, K, kind, rows_per_slot)
+        assert first_tile not in (21, 22)
+        if tile == 21:
+            assert -(-rows // 256) * -(-N // 192) <= 256
+        if tile == 22:
+            assert -(-rows // 192) * -(-N // 288) <= 768 and not (kind == 1 and rows_per_slot % 32)
+        assert not {21, 22} & set(drf.probe_gemm_route(rows, N, K, 3)[::2])
+
+
 def test_block_routes_stay_inside_their_buffers():
     """Keys and values in whole groups of 32 fit the buffers of q | k | v and of the hidden units, the shares of a dealt block the split
     GEMMs' partial tiles (2^22 floats), the launches of a dealt block the chip; widths, head widths and ratios without the form have none."""
