@@ -550,6 +550,11 @@ constexpr int kLongFrom[2][2][12] = {
 // rows: 51.5 against 58.0 us with 32, 91.8 chunked), at widths beyond 80 from the second round of a launch of more than 96
 // queries on (64 slots x 128 queries x 256 rows x 4 heads of 96: 15.9 against 18.9 us, 17.1 in one chunk per head; from 32 to
 // 96 queries one form or the other is ahead by up to 20 %); beyond 2^23 items the threads of its launch would not fit 32 bits.
+// Cross-attention of more than 256 queries over at most 256 rows goes to the kernel for long sequences from the second workgroup of a CU on:
+// one's loads and stores run beside another's steps, and K and V take one or two chunks.  Against the persistent chunked kernel 1.05-2.0x
+// over widths 8 to 88 and 32 to 256 rows (d = 72, 77 rows, 16 heads: 8 slots x 1024 queries 19.5 -> 15.1 us, 24 slots 50.5 -> 39.3); one workgroup
+// to a CU it is ahead at 72 and 80 only (4 slots x 1024: 11.7 -> 10.4 us over 77 rows, 11.0 -> 10.9 over 128; 64: 10.1 -> 10.5).
+// Up to 256 queries (32 slots x 256) neither is ahead everywhere (0.86-1.25x).
 AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled)
 {
     if (Nk > 256) {
@@ -562,7 +567,9 @@ AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled)
     const bool at_once = items <= attn_short_items_at_once(Nk, d);
     if (items <= 1 << 23 && (Nq <= 128 || at_once)) return items > 4096 || (d > 80 && Nq > 96 && !at_once) ? ATTN_SHORT_64 : ATTN_SHORT;
     if (Nq <= 128) return ATTN_CHUNKED_FEW;
-    return (long long)((Nq + 255) / 256) * heads * slots > kPersistGroups ? ATTN_CHUNKED_PERSIST : ATTN_CHUNKED;
+    const long long groups = (long long)((Nq + 255) / 256) * heads * slots;
+    if (Nq > 256 && d <= 88 && groups >= (d == 72 || d == 80 ? 256 : 257)) return ATTN_LONG;
+    return groups > kPersistGroups ? ATTN_CHUNKED_PERSIST : ATTN_CHUNKED;
 }
 
 bool attn_wants_scaled(int tokens, int heads, int d, int slots)

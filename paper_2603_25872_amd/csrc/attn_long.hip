@@ -87,7 +87,8 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_long_kernel(const AttnArg
     const int q0 = qb * kQpg + wave * kQpw;
     const int Nk = a.Nk, ldk = a.ldk;
 
-    // constant parts of the LDS image: pads, and the pieces of a V row behind its d columns (1, 0, 0, ...)
+    // constant parts of the LDS image: pads, and the pieces of a V row behind its d columns (1, 0, 0, ...); zeros for rows past the end of
+    // a first chunk that is not full, as other threads write there too (issue)
     const bf16x8 zero8 = { 0, 0, 0, 0, 0, 0, 0, 0 };
     if (tid < 2 * (C::PAD / 16)) {
         const int buf = tid / (C::PAD / 16), p = tid % (C::PAD / 16);
@@ -102,7 +103,7 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_long_kernel(const AttnArg
         for (int i = tid; i < 2 * KC * (VP - P8); i += NT) {
             const int buf = i / (KC * (VP - P8)), r = i % (KC * (VP - P8)), row = r / (VP - P8), p = r % (VP - P8);
             bf16x8 v = zero8;
-            if (C::ONES && p == 0) v[0] = (bf16_t)1.f;
+            if (C::ONES && p == 0 && row < Nk) v[0] = (bf16_t)1.f;
             *reinterpret_cast<bf16x8*>(attn_smem + buf * C::BUF + C::KBYTES + (row * VP + P8 + p) * 16) = v;
         }
     }
@@ -261,11 +262,14 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_long_kernel(const AttnArg
                 };
                 float m_new = C::PADM ? m_run[b] + both(rel, first ? -INFINITY : 0.f) : both(mx, first ? -INFINITY : m_run[b]);
                 if (first && __any(m_new == -INFINITY)) {
-                    // a query that scores -infinity against all of the first 32 rows takes its reference from the next 32, in
-                    // the registers of the other block's scores, which hold nothing yet; failing that, 0
-                    raw(b, 1, s[1 - b]);
-                    const float m2 = both(largest(s[1 - b]), -INFINITY);
-                    if (m_new == -INFINITY) m_new = m2 == -INFINITY ? 0.f : m2;
+                    // a query that scores -infinity against all of the first 32 rows takes its reference from the next 32 that have
+                    // a finite score, in the registers of the other block's scores, which hold nothing yet; failing that, 0
+                    for (int st = 1; st < nsteps && __any(m_new == -INFINITY); ++st) {
+                        raw(b, st, s[1 - b]);
+                        const float m2 = both(largest(s[1 - b]), -INFINITY);
+                        if (m_new == -INFINITY) m_new = m2;
+                    }
+                    if (m_new == -INFINITY) m_new = 0.f;
                 }
                 float delta = m_new - m_run[b], shift = delta;
                 // scores far above the reference have lost their low bits to it (2^-24 of the distance): formed anew

@@ -165,6 +165,28 @@ def test_scores_of_minus_infinity_in_a_step_of_64_queries(torch, drf, d, scaled,
     run(torch, drf, 7, q, kv, *args, scaled, 1.5e-2)
 
 
+@pytest.mark.parametrize("d", [w for w in WIDTHS if w <= 88])
+@pytest.mark.parametrize("Nq,Nk", [(257, 1), (300, 31), (257, 33), (513, 77), (257, 128), (600, 129), (257, 256)])
+def test_64_queries_per_wave_over_short_kv(torch, drf, d, Nq, Nk):
+    """Cross-attention of many queries over at most 256 rows: one step or less, last steps of 1 and 13 rows, one and two chunks, kv shared
+    between slots, the references of growing scores."""
+    args = (100, 5, Nq, Nk, 8, d)
+    run(torch, drf, 7, *normal(np.random.default_rng(d + Nk), *args), *args, False, 1.5e-2, look=(0, 7, 33))
+    run(torch, drf, 7, *growing(np.random.default_rng(d + Nk), *args), *args, False, 2e-2)
+
+
+@pytest.mark.parametrize("d", [w for w in WIDTHS if w <= 88])
+@pytest.mark.parametrize("rows", [range(0, 32), range(0, 96), range(32, 120)])
+def test_scores_of_minus_infinity_over_short_kv(torch, drf, d, rows):
+    """One to three steps without a finite score, the first ones or the last; the other scores are far below zero, so that the reference
+    has to come from the first step that has some."""
+    args = (34, 2, 257, 120, 8, d)
+    q, kv = overflowing(np.random.default_rng(d), *args, rows)
+    for r in set(range(120)) - set(rows):
+        kv[[r, 120 + r], :8 * d] -= 1.5e-17 * d ** -0.5
+    run(torch, drf, 7, q, kv, *args, False, 1.5e-2)
+
+
 @pytest.mark.parametrize("scaled", [False, True])
 @pytest.mark.parametrize("d", [w for w in WIDTHS if w <= 80])
 @pytest.mark.parametrize("far", [1e3, 1e5, 1e8, 1e20])

@@ -269,6 +269,15 @@ def test_gemm_tiles_for_part_filled_rounds(M, N, K, kind, rows_per_slot, tile):
         assert not {21, 22} & set(drf.probe_gemm_route(rows, N, K, 3)[::2])
 
 
+def test_cross_attention_of_many_queries_takes_the_kernel_for_long_sequences():
+    """More than 256 queries over at most 256 rows, from the second workgroup of a CU on (at widths 72 and 80 the first)."""
+    for d in range(8, 97, 8):
+        for Nk in (77, 128, 256):
+            route = [drf.probe_attn_route(slots, Nq, Nk, 16, d) for slots, Nq in ((4, 1024), (8, 1024), (5, 1025), (2, 1024), (32, 256))]
+            assert (route[0] == 7) == (d in (72, 80)) and 7 not in route[3:]
+            assert [r == 7 for r in route[1:3]] == [d <= 88] * 2
+
+
 def test_block_routes_stay_inside_their_buffers():
     """Keys and values in whole groups of 32 fit the buffers of q | k | v and of the hidden units, the shares of a dealt block the split
     GEMMs' partial tiles (2^22 floats), the launches of a dealt block the chip; widths, head widths and ratios without the form have none."""
