@@ -377,7 +377,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
     // Every pass streams all block weights from HBM (they do not fit the caches between passes), and a
     // GEMM whose k-loop waits on first-touch weight lines runs measurably slower than the same GEMM with
     // warm weights.  So each bf16 GEMM of the block chain (qkv -> proj -> fc1 -> fc2 -> next block's
-    // qkv) touches the weights of its successor while its own last round of tiles starts.
+    // qkv; with text -> proj -> xq -> xo -> fc1) touches the weights of its successor while its own last round of tiles starts.
     // In a thin pass a branch GEMM may split K across workgroups: its partial tiles are then the last pending branch
     // (part), and the LayerNorm launch that adds them stores the stream.
     const bf16_t *pend1 = nullptr, *pend2 = nullptr;
@@ -488,13 +488,13 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         if (f32) {
             if ((rc = gemm(d, ws.hbuf, b.proj, M, epi_resid(ws.resid, D, mrow + 2 * D, nm, dm.T), st)) != DRF_OK) return rc;
         } else {
-            if ((rc = gemm(d, ws.hbuf, b.proj, M, with_warm(epi_gated(ws.ybuf, D, mrow + 2 * D, nm, dm.T), text ? nullptr : &b.fc1), st, ws.skpart, may_leave ? &part.sum : nullptr)) != DRF_OK) return rc;
+            if ((rc = gemm(d, ws.hbuf, b.proj, M, with_warm(epi_gated(ws.ybuf, D, mrow + 2 * D, nm, dm.T), text ? &b.xq : &b.fc1), st, ws.skpart, may_leave ? &part.sum : nullptr)) != DRF_OK) return rc;
             part.bias = b.proj.b; part.gate = mrow + 2 * D;
             if (!part.sum.splits) pend1 = (const bf16_t*)ws.ybuf;
         }
         if (d->cfg.cond == DRF_COND_TEXT) {
             const int ctx_rows = map.cond_mod ? map.cond_mod : slots;
-            if ((rc = ln_linear(nullptr, nullptr, 0, true, b.xq, epi_store(ws.qkv, D, f32))) != DRF_OK) return rc;
+            if ((rc = ln_linear(nullptr, nullptr, 0, true, b.xq, with_warm(epi_store(ws.qkv, D, f32), &b.xo))) != DRF_OK) return rc;
             const char* kv = (const char*)ws.xkv + (size_t)l * ctx_rows * d->cfg.ctx_len * 2 * D * act;
             AttnArgs aa{};
             aa.q = ws.qkv; aa.ldq = D; aa.k = kv; aa.v = kv + (size_t)D * act; aa.ldk = 2 * D; aa.out = ws.hbuf; aa.ldo = D;
@@ -505,7 +505,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
                 ProfScope ps(d, st, DRF_PROF_ATTN, 4.0 * slots * dm.heads * (double)dm.T * d->cfg.ctx_len * dm.d);
                 if ((rc = f32 ? launch_attn_f32(aa, st) : launch_attn_bf16(aa, st)) != DRF_OK) return rc;
             }
-            if ((rc = gemm(d, ws.hbuf, b.xo, M, epi_resid(ws.resid, D, nullptr, 0, dm.T), st, ws.skpart)) != DRF_OK) return rc;
+            if ((rc = gemm(d, ws.hbuf, b.xo, M, with_warm(epi_resid(ws.resid, D, nullptr, 0, dm.T), &b.fc1), st, ws.skpart)) != DRF_OK) return rc;
         }
         const bool last = l == n_blocks - 1;
         if ((rc = ln_linear(mrow + 3 * D, mrow + 4 * D, nm, f32 || last, b.fc1, with_warm(epi_store(ws.mid, dm.R * D, f32, true), f32 ? nullptr : &b.fc2))) != DRF_OK) return rc;
