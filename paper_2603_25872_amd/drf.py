@@ -50,11 +50,12 @@ class DrfError(RuntimeError):
 
 
 _lib = None
+_skip = None            # _native.skip, once the library is loaded
 
 
 def lib():
     """Load libdrf.so (built by paper_2603_25872_amd/build.py); raises if absent."""
-    global _lib
+    global _lib, _skip
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError("libdrf.so is not built: run `python -m paper_2603_25872_amd.build`")
@@ -98,6 +99,9 @@ def lib():
         L.drf_probe_block_route.argtypes = [C.c_int] * 5
         L.drf_probe_gemm_route.argtypes = [C.c_int] * 5 + [C.c_void_p]
         L.drf_last_error.restype = C.c_char_p
+        from . import _native               # built beside the library
+        _native.bind(C.cast(L.drf_skip_transition_noise, C.c_void_p).value)
+        _skip = _native.skip
         _lib = L
     return _lib
 
@@ -162,15 +166,11 @@ def skip_transition(sched, x_from, eps_from, s_from, s_to, out=None):
     """x_from, eps_from: fp32 device tensors [batch, ...]; s_to: list of target indices.
     Returns [len(s_to), batch, ...]."""
     import torch
-    sc = sched_config(sched)
-    m = len(s_to)
-    batch = x_from.shape[0] if x_from.dim() > 0 else 1
-    elems = x_from.numel() // batch if batch else 0
     if out is None:
-        out = torch.empty((m,) + tuple(x_from.shape), dtype=torch.float32, device=x_from.device)
-    tgt = (C.c_int * max(m, 1))(*s_to)
-    _check(lib().drf_skip_transition(C.byref(sc), _dev(x_from, torch.float32), _dev(eps_from, torch.float32), s_from,
-                                     tgt, m, batch, elems, _dev(out, torch.float32), _stream()))
+        out = torch.empty((len(s_to),) + tuple(x_from.shape), dtype=torch.float32, device=x_from.device)
+    if _lib is None:
+        lib()
+    _check(_skip(sched, x_from, eps_from, s_from, s_to, None, out, torch.float32, _stream()))
     return out
 
 
@@ -178,17 +178,12 @@ def skip_transition_noise(sched, x_from, net_from, s_from, s_to, z=None, seed=No
     """Skip transitions of the configured sampler with their fresh noise: explicit fields z [len(s_to), batch, ...]
     or the library's stream (seed, field0)."""
     import torch
-    sc = sched_config(sched)
-    m = len(s_to)
-    batch = x_from.shape[0] if x_from.dim() > 0 else 1
-    elems = x_from.numel() // batch if batch else 0
     if out is None:
-        out = torch.empty((m,) + tuple(x_from.shape), dtype=torch.float32, device=x_from.device)
-    tgt = (C.c_int * max(m, 1))(*s_to)
+        out = torch.empty((len(s_to),) + tuple(x_from.shape), dtype=torch.float32, device=x_from.device)
+    if _lib is None:
+        lib()
     nz = _noise(z, seed, field0)
-    _check(lib().drf_skip_transition_noise(C.byref(sc), _dev(x_from, torch.float32), _dev(net_from, torch.float32),
-                                           s_from, tgt, m, batch, elems, C.byref(nz) if nz is not None else None,
-                                           _dev(out, torch.float32), _stream()))
+    _check(_skip(sched, x_from, net_from, s_from, s_to, None if nz is None else C.addressof(nz), out, torch.float32, _stream()))
     return out
 
 

@@ -314,3 +314,40 @@ def test_bf16_gemm_refuses_the_fp32_paths_activation():
     epilogue = (C.c_int * 128)(5)                # Epilogue starts with its mode: EPI_STORE_SILU
     assert launch(None, None, 64, 64, 64, epilogue, None, 0, None, None) == -2
     assert b"SiLU" in drf.lib().drf_last_error()
+
+
+class DeviceTensor:
+    """What the skip calls ask of a tensor, without a device."""
+    is_cuda = True
+
+    def __init__(self, shape, dtype, contiguous=True):
+        self.shape, self.dtype, self.contiguous = shape, dtype, contiguous
+
+    def is_contiguous(self):
+        return self.contiguous
+
+    def data_ptr(self):
+        return 4096
+
+
+def test_skip_calls_take_and_refuse_what_their_arguments_say():
+    """The native marshalling: mappings and sequences of every kind, defaults of absent options, the errors of bad values; nothing is
+    launched, as the batch is empty or the indices are refused."""
+    torch = pytest.importorskip("torch")
+    import collections
+    drf.lib()
+    sched = dict(train_steps=1000, beta_start=1e-4, beta_end=0.02, steps=50)
+    none, one = DeviceTensor((0, 8), torch.float32), DeviceTensor((1, 8), torch.float32)
+    skip = lambda sc, x, to, s_from=50, net=one, out=one: drf._skip(sc, x, net, s_from, to, None, out, torch.float32, 0)
+    for sc in (sched, dict(sched, eta=0.5, sampler=2, shift=3), dict(sched, eta="0.25"), collections.UserDict(sched)):
+        for to in ([1, 2], (3,), range(40), np.arange(3)):
+            assert skip(sc, none, to) == 0
+    assert skip(dict(sched, steps=0), none, [1]) != 0 and skip(dict(sched, sampler=9), none, [1]) != 0
+    assert skip(dict(sched, eta=1.5), none, [1]) != 0
+    assert skip(sched, one, [51]) != 0 and skip(sched, one, [1], s_from=51) != 0 and skip(sched, one, [1], net=None) != 0
+    for error, call in ((KeyError, lambda: skip(dict(train_steps=1000), none, [1])), (TypeError, lambda: skip(dict(sched, steps=5.0), none, [1])),
+                        (TypeError, lambda: skip(sched, none, [1.0])), (TypeError, lambda: skip(sched, none, 3)), (TypeError, lambda: skip(sched, none, [1], s_from=1.5)),
+                        (AssertionError, lambda: skip(sched, torch.zeros(1, 8), [1])), (AssertionError, lambda: skip(sched, DeviceTensor((1, 8), torch.float32, False), [1])),
+                        (AssertionError, lambda: skip(sched, one, [1], net=DeviceTensor((1, 8), torch.float16))), (ValueError, lambda: skip(dict(sched, eta="x"), none, [1]))):
+        with pytest.raises(error):
+            call()
