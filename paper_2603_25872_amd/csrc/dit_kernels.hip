@@ -435,69 +435,89 @@ __global__ void __launch_bounds__(256) final_kernel(const float* __restrict__ re
 }
 
 // Final layer for hidden sizes that are multiples of 64, on the fp32 matrix instruction: a workgroup takes 16 rows, its
-// four waves a quarter of the columns each (NS steps of 16), a row piece in the operand layout staying in registers
+// NW waves a share of the columns each (NS steps of 16), a row piece in the operand layout staying in registers
 // through the statistics (two exchanges through LDS), the modulation and the product with 16 output weights at a time;
 // the waves' partial products are added through LDS.  One chain of loads and no weights staged: with the weights in LDS
-// and a row per half wave a launch took 23 us for 512 rows and 42 us for 16384 (hidden 1152, P = 16), this one 15 and 27 us.
-template <int NS>
-__global__ void __launch_bounds__(256) final_mfma_kernel(const float* __restrict__ resid, const float* __restrict__ shift,
-                                                         const float* __restrict__ scale, int mod_ld,
-                                                         const float* __restrict__ w, const float* __restrict__ b,
-                                                         const DitDims dm, int M, float* __restrict__ eps_out)
+// and a row per half wave a launch took 23 us for 512 rows and 42 us for 16384 (hidden 1152, P = 16), four waves 15 and 27 us.
+// EARLY: a single round of workgroups is bound by latency, so modulation and the first 16 outputs' weights are asked for together
+// with the rows, ahead of the statistics, by eight waves, which have the registers for it (hidden 1152, 512 to 4096 rows:
+// 14.5-15.5 -> 8.9-9.5 us; 384, 3072 rows 5.5 -> 4.9; 128, 64 rows 3.2 -> 2.9).  Such a workgroup fills a CU: over several rounds it loses (16384 rows 33.7 us, four waves 27.4).
+template <int NS, int NW, bool EARLY>
+__global__ void __launch_bounds__(NW * 64) final_mfma_kernel(const float* __restrict__ resid, const float* __restrict__ shift,
+                                                             const float* __restrict__ scale, int mod_ld,
+                                                             const float* __restrict__ w, const float* __restrict__ b,
+                                                             const DitDims dm, int M, float* __restrict__ eps_out)
 {
-    constexpr int D = NS * 64;
-    __shared__ float s_sum[4][16], s_sq[4][16];
-    __shared__ f32x4m part[4][64];
+    constexpr int D = NS * NW * 16;
+    __shared__ float s_sum[NW][16], s_sq[NW][16];
+    __shared__ f32x4m part[NW][64];
     const int lane = threadIdx.x & 63, l16 = lane & 15, quarter = lane >> 4, wave = threadIdx.x >> 6;
     const int m0 = blockIdx.x * 16, row = m0 + l16, m = row < M ? row : M - 1;
     const size_t col0 = (size_t)wave * (NS * 16) + 4 * quarter;
-    f32x4m v[NS];
-    float sum = 0.f;
+    f32x4m v[NS], w4[NS], s4[NS], h4[NS];
 #pragma unroll
     for (int i = 0; i < NS; ++i) v[i] = *reinterpret_cast<const f32x4m*>(resid + (size_t)m * D + col0 + i * 16);
+    auto load_w = [&](int kbase) {
+        const float* wr = w + (size_t)(kbase + l16 < dm.P ? kbase + l16 : dm.P - 1) * D + col0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) w4[i] = *reinterpret_cast<const f32x4m*>(wr + i * 16);
+    };
+    auto load_mod = [&]() {
+        const size_t mod = (size_t)(m / dm.T) * mod_ld + col0;
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            s4[i] = *reinterpret_cast<const f32x4m*>(scale + mod + i * 16);
+            h4[i] = *reinterpret_cast<const f32x4m*>(shift + mod + i * 16);
+        }
+    };
+    if constexpr (EARLY) {
+        load_mod();
+        load_w(0);
+        __builtin_amdgcn_sched_barrier(0);          // (the loads would otherwise move behind the exchanges)
+    }
+    // sums of a row over its four lanes, then over the waves
+    auto total = [&](float t, float (&over)[NW][16]) {
+        t += __shfl_xor(t, 16, 64);
+        t += __shfl_xor(t, 32, 64);
+        if (quarter == 0) over[wave][l16] = t;
+        __syncthreads();
+        t = 0.f;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) t += over[k][l16];
+        return t * (1.f / (float)D);
+    };
+    float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < NS; ++i) sum += (v[i][0] + v[i][1]) + (v[i][2] + v[i][3]);
-    sum += __shfl_xor(sum, 16, 64);
-    sum += __shfl_xor(sum, 32, 64);
-    if (quarter == 0) s_sum[wave][l16] = sum;
-    __syncthreads();
-    const float mean = ((s_sum[0][l16] + s_sum[1][l16]) + (s_sum[2][l16] + s_sum[3][l16])) * (1.f / (float)D);
+    const float mean = total(sum, s_sum);
     float sq = 0.f;
 #pragma unroll
     for (int i = 0; i < NS; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) { v[i][j] -= mean; sq = fmaf(v[i][j], v[i][j], sq); }
-    sq += __shfl_xor(sq, 16, 64);
-    sq += __shfl_xor(sq, 32, 64);
-    if (quarter == 0) s_sq[wave][l16] = sq;
-    __syncthreads();
-    const float rstd = rsqrtf(((s_sq[0][l16] + s_sq[1][l16]) + (s_sq[2][l16] + s_sq[3][l16])) * (1.f / (float)D) + 1e-6f);
-    const int slot = m / dm.T;
-    const float* sh = shift + (size_t)slot * mod_ld + col0;
-    const float* sc = scale + (size_t)slot * mod_ld + col0;
+    const float rstd = rsqrtf(total(sq, s_sq) + 1e-6f);
+    if constexpr (!EARLY) load_mod();
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
-        const f32x4m s4 = *reinterpret_cast<const f32x4m*>(sc + i * 16), h4 = *reinterpret_cast<const f32x4m*>(sh + i * 16);
+    for (int i = 0; i < NS; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[i][j] = fmaf(v[i][j] * rstd, 1.f + s4[j], h4[j]);
-    }
+        for (int j = 0; j < 4; ++j) v[i][j] = fmaf(v[i][j] * rstd, 1.f + s4[i][j], h4[i][j]);
     const size_t E = (size_t)dm.C * dm.H * dm.W;
     const int pp = dm.patch * dm.patch;
     const int orow = m0 + (threadIdx.x & 15), oslot = orow / dm.T, t = orow - oslot * dm.T, py = t / dm.gw, px = t - py * dm.gw;
     for (int kbase = 0; kbase < dm.P; kbase += 16) {
-        const float* wr = w + (size_t)(kbase + l16 < dm.P ? kbase + l16 : dm.P - 1) * D + col0;
+        if (!EARLY || kbase) load_w(kbase);
         f32x4m acc[2] = { { 0.f, 0.f, 0.f, 0.f }, { 0.f, 0.f, 0.f, 0.f } };
 #pragma unroll
-        for (int i = 0; i < NS; ++i) {
-            const f32x4m w4 = *reinterpret_cast<const f32x4m*>(wr + i * 16);
+        for (int i = 0; i < NS; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[j], v[i][j], acc[j & 1], 0, 0, 0);
-        }
+            for (int j = 0; j < 4; ++j) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w4[i][j], v[i][j], acc[j & 1], 0, 0, 0);
         part[wave][lane] = acc[0] + acc[1];         // element r: output kbase + 4 quarter + r of row l16
         __syncthreads();
         const int kk = threadIdx.x >> 4, k = kbase + kk, src = (kk >> 2) * 16 + (threadIdx.x & 15);
-        if (k < dm.P && orow < M) {
-            const float tot = (part[0][src][kk & 3] + part[1][src][kk & 3]) + (part[2][src][kk & 3] + part[3][src][kk & 3]);
+        if (kk < 16 && k < dm.P && orow < M) {
+            float tot = 0.f;
+#pragma unroll
+            for (int q = 0; q < NW; ++q) tot += part[q][src][kk & 3];
             const int ch = k / pp, dy = (k % pp) / dm.patch, dx = k % dm.patch;
             eps_out[(size_t)oslot * E + ((size_t)ch * dm.H + py * dm.patch + dy) * dm.W + px * dm.patch + dx] = tot + b[k];
         }
@@ -670,18 +690,27 @@ drf_status launch_final(const float* resid, const float* shift, const float* sca
     const bool al16 = mod_ld % 4 == 0 && ((reinterpret_cast<uintptr_t>(resid) | reinterpret_cast<uintptr_t>(shift) |
                                            reinterpret_cast<uintptr_t>(scale) | reinterpret_cast<uintptr_t>(w)) & 15u) == 0;
     if (al16) {
-        auto go = [&](auto kern) -> drf_status {
-            hipLaunchKernelGGL(kern, dim3((M + 15) / 16), dim3(256), 0, st, resid, shift, scale, mod_ld, w, b, dm, M, eps_out);
+        auto go = [&](auto ns_c) -> drf_status {    // ns: column steps of a wave, of four
+            constexpr int NS = decltype(ns_c)::value;
+            const dim3 groups((M + 15) / 16);
+            if constexpr (NS % 2 == 0) {
+                if (groups.x <= 256) {
+                    hipLaunchKernelGGL((final_mfma_kernel<NS / 2, 8, true>), groups, dim3(512), 0, st, resid, shift, scale, mod_ld, w, b, dm, M, eps_out);
+                    DRF_HIP(hipGetLastError());
+                    return DRF_OK;
+                }
+            }
+            hipLaunchKernelGGL((final_mfma_kernel<NS, 4, false>), groups, dim3(256), 0, st, resid, shift, scale, mod_ld, w, b, dm, M, eps_out);
             DRF_HIP(hipGetLastError());
             return DRF_OK;
         };
         switch (dm.D) {
-        case 128: return go(final_mfma_kernel<2>);
-        case 384: return go(final_mfma_kernel<6>);
-        case 576: return go(final_mfma_kernel<9>);
-        case 768: return go(final_mfma_kernel<12>);
-        case 1024: return go(final_mfma_kernel<16>);
-        case 1152: return go(final_mfma_kernel<18>);
+        case 128: return go(std::integral_constant<int, 2>{});
+        case 384: return go(std::integral_constant<int, 6>{});
+        case 576: return go(std::integral_constant<int, 9>{});
+        case 768: return go(std::integral_constant<int, 12>{});
+        case 1024: return go(std::integral_constant<int, 16>{});
+        case 1152: return go(std::integral_constant<int, 18>{});
         default: break;
         }
     }

@@ -305,3 +305,24 @@ def test_fused_update_probe_equals_its_parts(torch, drf, orc, g, n_chain, n_draf
         anchor = guided[n_chain - 1 if n_chain else 0].contiguous()
         parts = drf.skip_transition(sd, y, anchor, s, [s - j - 1 for j in range(n_draft)])
         assert np.abs(drafts.cpu().numpy() - parts.cpu().numpy()).max() < 1e-5
+
+
+@pytest.mark.parametrize("hidden", [128, 384, 576, 768, 1024, 1152])
+@pytest.mark.parametrize("slots,in_ch", [(1, 4), (65, 5), (66, 4)])
+def test_final_layer_of_one_and_two_rounds_of_workgroups(torch, drf, orc, hidden, slots, in_ch):
+    """A model without blocks, 63 tokens a slot: 63, 4095 and 4158 rows (4, 256 and 260 workgroups of 16 rows), the last of them ragged;
+    16 and 20 outputs a token.  fp32 sums of at most 1152 products: 1152 x 2^-24 relative at worst."""
+    dit = dict(I.CONFIGS[1]["dit"], depth=0, hidden=hidden, heads=hidden // 64, lat_h=18, lat_w=14, in_ch=in_ch)
+    w = I.weights(dit, 5, "loud")
+    den = drf.Denoiser(dit, w)
+    rng = np.random.default_rng(hidden + slots)
+    x = rng.standard_normal((slots, in_ch, 18, 14)).astype(np.float32)
+    t = rng.integers(0, 1000, size=slots).astype(np.int32)
+    cond = I.conditioning(dit, slots, 5)
+    got = den.eps_batched(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda(), torch.from_numpy(cond).cuda()).cpu().numpy()
+    den.close()
+    wd = orc.prepare_weights(w)
+    for j in {0, slots // 2, slots - 1}:
+        want = orc.dit_eps(dit, wd, x[j:j + 1], t[j:j + 1], cond[j:j + 1])[0]
+        err = np.abs(got[j] - want).max() / np.abs(want).max()
+        assert err < 7e-5, (j, err)
