@@ -82,7 +82,7 @@ drf_status drf_probe_cross_attn_bf16(const void* q, const void* kv, void* out, i
  *   1 | 2  up to 256 kv rows, one wave per 64 of them, 32 | 64 queries per workgroup;
  *   3 | 4  kv rows in chunks of 64, 256 queries per workgroup, plain | persistent;
  *   5      the same with chunks of 128 for more than 256 kv rows;      6  128 queries per workgroup;
- *   7      more than 256 kv rows, 64 queries per wave.
+ *   7      more than 256 kv rows, or more than 256 queries over fewer: 64 queries per wave.
  */
 int drf_probe_attn_route(int slots, int q_rows, int kv_rows, int heads, int head_dim, int q_scaled);
 

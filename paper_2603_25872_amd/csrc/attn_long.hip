@@ -1,4 +1,4 @@
-// Multi-head attention softmax(q k^T / sqrt(d)) v for sequences of more than 256 kv rows (bf16, no mask).
+// Multi-head attention softmax(q k^T / sqrt(d)) v for sequences of more than 256 kv rows, and of many queries over fewer (bf16, no mask).
 #include <type_traits>
 
 #include "common.h"

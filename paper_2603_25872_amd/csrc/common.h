@@ -178,7 +178,7 @@ enum AttnRoute {
     ATTN_CHUNKED_PERSIST = 4,   // the same, persistent workgroups
     ATTN_CHUNKED_LONG = 5,  // 8 waves, more than 256 kv rows
     ATTN_CHUNKED_FEW = 6,   // 4 waves, up to 128 queries
-    ATTN_LONG = 7,          // more than 256 kv rows, 64 queries per wave (attn_long.hip)
+    ATTN_LONG = 7,          // more than 256 kv rows, or more than 256 queries over fewer: 64 queries per wave (attn_long.hip)
 };
 AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled);
 // Self-attention whose queries their producer should multiply by log2(e) / sqrt(d): what ATTN_LONG takes with them scaled.
