@@ -645,8 +645,9 @@ drf_status launch_last_tiles(int v, const bf16_t* A, const bf16_t* W, int M, int
 // against four, 256 x 256 | 256 x 288 tiles:
 //  - GELU: 8192 x 1536 x 384 18.1 : 20.5 | 20.1 : 22.0 us, 16384 x 4608 x 1152 163.7 : 170.2 | 155.3 : 162.1; 16384 x 6144 x 1536
 //    281.6 : 262.6 | 303.0 : 277.8, 8192 x 8192 x 2048 226.1 : 219.7 | 241.7 : 233.7.  A single round of K = 1152
-//    gains 1 us with its weights in the cache (2816 rows 32.5 : 33.6) and loses 3 with weights from HBM, which two stages wait for at
-//    every k-tile (the text model, whose MLP no launch warms: 2520 to 3276 rows 36.9 : 33.6 to 36.9 : 35.4): it stays on four;
+//    with weights from HBM loses 3 us on eight waves (33.6 : 36.9 at 2520 to 3276 rows; two stages wait for them at every k-tile), but every
+//    launch's weights are asked for by the one before: 216 to 255 tiles gain 1.6 to 2.9 us (3072 to 3584 rows; whole evaluations -0.3
+//    to -0.9 %, hidden 1024 at 224 and 240 tiles -0.9), fewer do not (208 tiles +2 %), and a full round is even (4096 rows 0 to -1.2);
 //  - head-major planes, slots of whole 32-row passes: K = 384 17.9 : 18.8 | 21.1 : 21.6, K = 512 even (19.60 : 19.56 | 21.0 : 21.9),
 //    K = 768 22.5 : 22.2 | 25.0 : 24.7, K = 1152 34.5 : 31.8 | 121.1 : 110.1;
 //  - other slot lengths: K = 768 42.9 : 43.8 | 30.3 : 32.1, K = 1152 128.6 : 138.9 | 112.4 : 118.9, K = 2048 101.9 : 96.2 | 110.9 : 106.6; a
@@ -656,8 +657,9 @@ int wide_form(int tile, int rows, int N, int K, const Epilogue& e)
 {
     if (tile != 2 && tile != 3) return tile;
     const int cols = tile == 2 ? 288 : 256;
-    const bool one_round = ((rows + 255) / 256) * (long long)((N + cols - 1) / cols) <= 256;
-    const bool eight = e.mode == EPI_STORE_GELU ? K < (one_round ? 1024 : 1536)
+    const long long tiles = ((rows + 255) / 256) * (long long)((N + cols - 1) / cols);
+    const bool one_round = tiles <= 256, part_filled = tile == 3 && tiles >= 216 && tiles < 256;
+    const bool eight = e.mode == EPI_STORE_GELU ? K < (one_round && !part_filled ? 1024 : 1536)
                                                 : e.mode == EPI_STORE_HEADS && K < (e.rows_per_slot % 32 == 0 ? 512 : tile == 3 && one_round ? 1024 : 1536);
     return !eight ? tile : tile == 2 ? 20 : 19;
 }

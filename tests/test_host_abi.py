@@ -269,6 +269,13 @@ def test_gemm_tiles_for_part_filled_rounds(M, N, K, kind, rows_per_slot, tile):
         assert not {21, 22} & set(drf.probe_gemm_route(rows, N, K, 3)[::2])
 
 
+@pytest.mark.parametrize("M,N,K,tile", [(2816, 4608, 1152, 3), (3072, 4608, 1152, 19), (3276, 4608, 1152, 19), (3584, 4608, 1152, 19),
+                                        (3328, 4096, 1024, 3), (3584, 4096, 1024, 19), (4096, 4096, 1024, 3)])
+def test_gemm_gelu_in_a_round_that_is_nearly_full_takes_eight_waves(M, N, K, tile):
+    """216 to 255 tiles of 256 x 256; fewer, and a full round, stay on four (times beside the rule)."""
+    assert drf.probe_gemm_route(M, N, K, 3) == (tile, 1, 0, 0)
+
+
 def test_cross_attention_of_many_queries_takes_the_kernel_for_long_sequences():
     """More than 256 queries over at most 256 rows, from the second workgroup of a CU on (at widths 72 and 80 the first)."""
     for d in range(8, 97, 8):
