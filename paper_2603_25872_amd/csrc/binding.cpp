@@ -119,12 +119,12 @@ PyObject* skip(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (!schedule(a[0], &sc)) return nullptr;
     PyObject* shape = PyObject_GetAttr(a[1], k_shape);
     if (!shape) return nullptr;
-    PyObject* dims = PySequence_Fast(shape, "shape is no sequence");
+    PyObject* dims = PySequence_Tuple(shape);
     Py_DECREF(shape);
     if (!dims) return nullptr;
     size_t batch = 1, elems = 1;                    // a tensor without dimensions: one sample of one element
-    for (Py_ssize_t i = 0; i < PySequence_Fast_GET_SIZE(dims); ++i) {
-        const size_t v = PyLong_AsSize_t(PySequence_Fast_GET_ITEM(dims, i));
+    for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(dims); ++i) {
+        const size_t v = PyLong_AsSize_t(PyTuple_GET_ITEM(dims, i));
         if (v == (size_t)-1 && PyErr_Occurred()) { Py_DECREF(dims); return nullptr; }
         (i == 0 ? batch : elems) *= v;
     }
@@ -132,17 +132,18 @@ PyObject* skip(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (!batch) elems = 0;
     const Py_ssize_t m = PyObject_Length(a[4]);
     if (m < 0) return nullptr;
-    PyObject* seq = PySequence_Fast(a[4], "target indices are no sequence");
+    // a tuple of our own: an element's __index__ is anybody's code (a device tensor's gives up the interpreter lock) and may change the caller's list
+    PyObject* seq = PySequence_Tuple(a[4]);
     if (!seq) return nullptr;
     int few[16];
     std::vector<int> many;
     int* to = few;
-    bool ok = PySequence_Fast_GET_SIZE(seq) == m;
+    bool ok = PyTuple_GET_SIZE(seq) == m;
     if (!ok) PyErr_SetString(PyExc_IndexError, "invalid index");
     if (ok && m > 16) {
         try { many.resize((size_t)m); to = many.data(); } catch (...) { PyErr_NoMemory(); ok = false; }
     }
-    for (Py_ssize_t i = 0; ok && i < m; ++i) ok = to_int(PySequence_Fast_GET_ITEM(seq, i), &to[i]);
+    for (Py_ssize_t i = 0; ok && i < m; ++i) ok = to_int(PyTuple_GET_ITEM(seq, i), &to[i]);
     Py_DECREF(seq);
     int s_from = 0;
     void *x = nullptr, *net = nullptr, *out = nullptr, *noise = nullptr, *stream = nullptr;

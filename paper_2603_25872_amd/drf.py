@@ -162,10 +162,19 @@ def plan_build(sched, mode, n):
     return rows
 
 
+def _targets(s_to):
+    """s_to as a tuple of the call's own: what sizes the output is what is launched, whatever becomes of the caller's list meanwhile."""
+    m, to = len(s_to), tuple(s_to)
+    if len(to) != m:
+        raise IndexError("invalid index")
+    return to
+
+
 def skip_transition(sched, x_from, eps_from, s_from, s_to, out=None):
     """x_from, eps_from: fp32 device tensors [batch, ...]; s_to: list of target indices.
     Returns [len(s_to), batch, ...]."""
     import torch
+    s_to = _targets(s_to)
     if out is None:
         out = torch.empty((len(s_to),) + tuple(x_from.shape), dtype=torch.float32, device=x_from.device)
     if _lib is None:
@@ -178,6 +187,7 @@ def skip_transition_noise(sched, x_from, net_from, s_from, s_to, z=None, seed=No
     """Skip transitions of the configured sampler with their fresh noise: explicit fields z [len(s_to), batch, ...]
     or the library's stream (seed, field0)."""
     import torch
+    s_to = _targets(s_to)
     if out is None:
         out = torch.empty((len(s_to),) + tuple(x_from.shape), dtype=torch.float32, device=x_from.device)
     if _lib is None:

@@ -358,3 +358,43 @@ def test_skip_calls_take_and_refuse_what_their_arguments_say():
                         (AssertionError, lambda: skip(sched, one, [1], net=DeviceTensor((1, 8), torch.float16))), (ValueError, lambda: skip(dict(sched, eta="x"), none, [1]))):
         with pytest.raises(error):
             call()
+
+
+def test_skip_calls_keep_target_indices_of_their_own(monkeypatch):
+    """An index is whatever has __index__, which may change the caller's list: the call goes on with the list as it was."""
+    torch = pytest.importorskip("torch")
+    drf.lib()
+    sched = dict(train_steps=1000, beta_start=1e-4, beta_end=0.02, steps=50)
+    none = DeviceTensor((0, 8), torch.float32)
+
+    class Index:
+        def __init__(self, act):
+            self.act = act
+
+        def __index__(self):
+            self.act()
+            return 1
+
+    for act in (list.clear, lambda to: to.extend([2] * 100000), lambda to: to.__setitem__(slice(1, None), ["no index"])):
+        to = []
+        to += [Index(lambda: act(to)), *(Index(lambda: None) for _ in range(40))]
+        assert drf._skip(sched, none, none, 50, to, None, none, torch.float32, 0) == 0
+        assert drf._targets(to) == tuple(to)
+
+    class Longer(list):                              # says 1, holds 2: the second would be written past an output for one
+        def __len__(self):
+            return 1
+
+    with pytest.raises(IndexError):
+        drf._targets(Longer([1, 2]))
+    with pytest.raises(IndexError):
+        drf._skip(sched, none, none, 50, Longer([1, 2]), None, none, torch.float32, 0)
+    with pytest.raises(TypeError):
+        drf._targets(i for i in (1, 2))
+    # what sizes the output is what is launched, whatever becomes of the list
+    for call in (drf.skip_transition, drf.skip_transition_noise):
+        to, handed = [1, 2], []
+        monkeypatch.setattr(drf, "_stream", lambda: to.append(3))
+        monkeypatch.setattr(drf, "_skip", lambda *a: handed.append(a[4]) or 0)
+        out = call(sched, torch.zeros(1, 8), torch.zeros(1, 8), 50, to)
+        assert out.shape == (2, 1, 8) and handed == [(1, 2)]
