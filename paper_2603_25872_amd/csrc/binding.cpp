@@ -16,20 +16,21 @@ typedef drf_status (*SkipFn)(const drf_sched_config*, const float*, const float*
 SkipFn g_skip = nullptr;
 
 PyObject *k_train_steps, *k_beta_start, *k_beta_end, *k_steps, *k_eta, *k_sampler, *k_shift, *k_get, *k_is_cuda, *k_is_contiguous, *k_dtype, *k_data_ptr, *k_shape;
+PyObject *k_zero, *k_one, *k_ddim;                   // eta, shift and sampler of a schedule that has none
 
-// New reference to d[key]; NULL with no error set where an optional key is absent.
-PyObject* item(PyObject* d, PyObject* key, bool required)
+// New reference to d[key], or to d.get(key, fallback) where there is one.
+PyObject* item(PyObject* d, PyObject* key, PyObject* fallback)
 {
     if (PyDict_CheckExact(d)) {
         PyObject* v = PyDict_GetItemWithError(d, key);
-        if (v) { Py_INCREF(v); return v; }
-        if (!PyErr_Occurred() && required) PyErr_SetObject(PyExc_KeyError, key);
-        return nullptr;
+        if (!v && !PyErr_Occurred()) {
+            v = fallback;
+            if (!v) PyErr_SetObject(PyExc_KeyError, key);
+        }
+        Py_XINCREF(v);
+        return v;
     }
-    if (required) return PyObject_GetItem(d, key);
-    PyObject* v = PyObject_CallMethodObjArgs(d, k_get, key, Py_None, nullptr);
-    if (v == Py_None) { Py_DECREF(v); v = nullptr; }
-    return v;
+    return fallback ? PyObject_CallMethodObjArgs(d, k_get, key, fallback, nullptr) : PyObject_GetItem(d, key);
 }
 
 // A C int as ctypes converts one: integers and what has __index__, the low bits of larger ones.
@@ -41,42 +42,35 @@ bool to_int(PyObject* v, int* out)
     return true;
 }
 
-bool int_item(PyObject* d, PyObject* key, int* out)
+// An integer; one with a fallback goes through int() first, a double with one through float() (which also take text).
+bool int_item(PyObject* d, PyObject* key, int* out, PyObject* fallback = nullptr)
 {
-    PyObject* v = item(d, key, true);
+    PyObject* v = item(d, key, fallback);
+    if (v && fallback) { PyObject* n = PyNumber_Long(v); Py_DECREF(v); v = n; }
     if (!v) return false;
     const bool ok = to_int(v, out);
     Py_DECREF(v);
     return ok;
 }
 
-bool double_item(PyObject* d, PyObject* key, double* out, bool required)
+bool double_item(PyObject* d, PyObject* key, double* out, PyObject* fallback = nullptr)
 {
-    PyObject* v = item(d, key, required);
-    if (!v) return !PyErr_Occurred();               // an absent optional key keeps its default
-    PyObject* f = required ? nullptr : PyNumber_Float(v);           // (float() of the optional ones: also text)
-    *out = required ? PyFloat_AsDouble(v) : f ? PyFloat_AsDouble(f) : -1.0;
-    Py_XDECREF(f);
+    PyObject* v = item(d, key, fallback);
+    if (v && fallback) { PyObject* f = PyNumber_Float(v); Py_DECREF(v); v = f; }
+    if (!v) return false;
+    *out = PyFloat_AsDouble(v);
     Py_DECREF(v);
     return !(*out == -1.0 && PyErr_Occurred());
 }
 
 bool schedule(PyObject* d, drf_sched_config* sc)
 {
-    sc->eta = 0.0; sc->sampler = DRF_DDIM; sc->shift = 1.0;
-    if (!int_item(d, k_train_steps, &sc->train_steps) || !double_item(d, k_beta_start, &sc->beta_start, true) ||
-        !double_item(d, k_beta_end, &sc->beta_end, true) || !int_item(d, k_steps, &sc->steps) || !double_item(d, k_eta, &sc->eta, false)) return false;
-    PyObject* v = item(d, k_sampler, false);
-    if (v) {
-        PyObject* n = PyNumber_Long(v);
-        int which = 0;
-        const bool ok = n && to_int(n, &which);
-        Py_XDECREF(n);
-        Py_DECREF(v);
-        if (!ok) return false;
-        sc->sampler = (decltype(sc->sampler))which;
-    } else if (PyErr_Occurred()) return false;
-    return double_item(d, k_shift, &sc->shift, false);
+    int which = 0;
+    if (!int_item(d, k_train_steps, &sc->train_steps) || !double_item(d, k_beta_start, &sc->beta_start) ||
+        !double_item(d, k_beta_end, &sc->beta_end) || !int_item(d, k_steps, &sc->steps) || !double_item(d, k_eta, &sc->eta, k_zero) ||
+        !int_item(d, k_sampler, &which, k_ddim) || !double_item(d, k_shift, &sc->shift, k_one)) return false;
+    sc->sampler = (decltype(sc->sampler))which;
+    return true;
 }
 
 // Device pointer of a contiguous device tensor of the given dtype; None: NULL.
@@ -187,5 +181,6 @@ PyMODINIT_FUNC PyInit__native()
         { &k_dtype, "dtype" }, { &k_data_ptr, "data_ptr" }, { &k_shape, "shape" } };
     for (auto& n : names)
         if (!(*n.at = PyUnicode_InternFromString(n.text))) return nullptr;
+    if (!(k_zero = PyFloat_FromDouble(0.0)) || !(k_one = PyFloat_FromDouble(1.0)) || !(k_ddim = PyLong_FromLong(DRF_DDIM))) return nullptr;
     return PyModule_Create(&kModule);
 }

@@ -398,3 +398,18 @@ def test_skip_calls_keep_target_indices_of_their_own(monkeypatch):
         monkeypatch.setattr(drf, "_skip", lambda *a: handed.append(a[4]) or 0)
         out = call(sched, torch.zeros(1, 8), torch.zeros(1, 8), 50, to)
         assert out.shape == (2, 1, 8) and handed == [(1, 2)]
+
+
+def test_skip_calls_read_a_schedules_options_as_the_other_calls_do():
+    """An option that is there and None is refused, in a dict, a class of it and another mapping; absent ones have their defaults."""
+    torch = pytest.importorskip("torch")
+    import collections
+    drf.lib()
+    sched = dict(train_steps=1000, beta_start=1e-4, beta_end=0.02, steps=50)
+    none = DeviceTensor((0, 8), torch.float32)
+    for kind in (dict, collections.UserDict, collections.OrderedDict, collections.ChainMap):
+        assert drf._skip(kind(sched), none, none, 50, [1], None, none, torch.float32, 0) == 0
+        for option in ("eta", "sampler", "shift"):
+            for read in (drf.sched_config, lambda sc: drf._skip(sc, none, none, 50, [1], None, none, torch.float32, 0)):
+                with pytest.raises(TypeError):
+                    read(kind(dict(sched, **{option: None})))
