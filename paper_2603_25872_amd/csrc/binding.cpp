@@ -105,7 +105,8 @@ bool device_pointer(PyObject* t, PyObject* dtype, void** out)
     return !(!*out && PyErr_Occurred());
 }
 
-// skip(sched, x_from, net_from, s_from, s_to, noise_address, out, float32, stream) -> status
+// skip(sched, x_from, net_from, s_from, s_to, noise_address, out, float32, stream) -> status.  stream: a handle, or what gives the current one,
+// which is asked last (it initialises the device, which a call that is refused has no need of).
 PyObject* skip(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     if (n != 9 || !g_skip) { PyErr_SetString(PyExc_TypeError, "skip() takes 9 arguments, after bind()"); return nullptr; }
@@ -144,7 +145,11 @@ PyObject* skip(PyObject*, PyObject* const* a, Py_ssize_t n)
     ok = ok && device_pointer(a[1], a[7], &x) && device_pointer(a[2], a[7], &net) && to_int(a[3], &s_from) && device_pointer(a[6], a[7], &out);
     if (!ok) return nullptr;
     if (a[5] != Py_None && !(noise = PyLong_AsVoidPtr(a[5])) && PyErr_Occurred()) return nullptr;
-    if (!(stream = PyLong_AsVoidPtr(a[8])) && PyErr_Occurred()) return nullptr;
+    PyObject* handle = PyLong_Check(a[8]) ? Py_NewRef(a[8]) : PyObject_CallNoArgs(a[8]);
+    if (!handle) return nullptr;
+    stream = PyLong_AsVoidPtr(handle);
+    Py_DECREF(handle);
+    if (!stream && PyErr_Occurred()) return nullptr;
     drf_status rc;
     Py_BEGIN_ALLOW_THREADS
     rc = g_skip(&sc, (const float*)x, (const float*)net, s_from, to, (int)m, (int)batch, elems, (const drf_noise*)noise, (float*)out, stream);

@@ -179,7 +179,7 @@ def skip_transition(sched, x_from, eps_from, s_from, s_to, out=None):
         out = torch.empty((len(s_to),) + tuple(x_from.shape), dtype=torch.float32, device=x_from.device)
     if _lib is None:
         lib()
-    _check(_skip(sched, x_from, eps_from, s_from, s_to, None, out, torch.float32, _stream()))
+    _check(_skip(sched, x_from, eps_from, s_from, s_to, None, out, torch.float32, _stream))
     return out
 
 
@@ -193,7 +193,7 @@ def skip_transition_noise(sched, x_from, net_from, s_from, s_to, z=None, seed=No
     if _lib is None:
         lib()
     nz = _noise(z, seed, field0)
-    _check(_skip(sched, x_from, net_from, s_from, s_to, None if nz is None else C.addressof(nz), out, torch.float32, _stream()))
+    _check(_skip(sched, x_from, net_from, s_from, s_to, None if nz is None else C.addressof(nz), out, torch.float32, _stream))
     return out
 
 

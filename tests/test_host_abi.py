@@ -395,7 +395,7 @@ def test_skip_calls_keep_target_indices_of_their_own(monkeypatch):
     for call in (drf.skip_transition, drf.skip_transition_noise):
         to, handed = [1, 2], []
         monkeypatch.setattr(drf, "_stream", lambda: to.append(3))
-        monkeypatch.setattr(drf, "_skip", lambda *a: handed.append(a[4]) or 0)
+        monkeypatch.setattr(drf, "_skip", lambda *a: a[8]() or handed.append(a[4]) or 0)
         out = call(sched, torch.zeros(1, 8), torch.zeros(1, 8), 50, to)
         assert out.shape == (2, 1, 8) and handed == [(1, 2)]
 
@@ -413,3 +413,19 @@ def test_skip_calls_read_a_schedules_options_as_the_other_calls_do():
             for read in (drf.sched_config, lambda sc: drf._skip(sc, none, none, 50, [1], None, none, torch.float32, 0)):
                 with pytest.raises(TypeError):
                     read(kind(dict(sched, **{option: None})))
+
+
+def test_skip_calls_refuse_host_tensors_before_they_ask_for_a_stream(monkeypatch):
+    torch = pytest.importorskip("torch")
+    sched = dict(train_steps=1000, beta_start=1e-4, beta_end=0.02, steps=50)
+    asked = []
+    monkeypatch.setattr(drf, "_stream", lambda: asked.append(1) or 0)
+    host = torch.zeros(1, 8)
+    for call in (drf.skip_transition, drf.skip_transition_noise):
+        with pytest.raises(AssertionError, match="contiguous device tensor"):
+            call(sched, host, host, 50, [1])
+        with pytest.raises(KeyError):
+            call({}, host, host, 50, [1])
+        assert not asked
+        none = DeviceTensor((0, 8), torch.float32)
+        assert call(sched, none, none, 50, [1], out=none) is none and asked.pop()
