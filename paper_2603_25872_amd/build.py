@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdrf.so")
-NATIVE = os.path.join(HERE, "_native.so")
+NATIVE = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))     # for this interpreter only
 SOURCES = ["plan.cpp", "update.hip", "dit_kernels.hip", "gemm.hip", "gemm_wide_288.hip", "gemm_wide_256.hip", "gemm_pair.hip", "attn.hip", "attn_long.hip", "attn_short.hip", "block_chain.hip", "denoiser.hip", "calibrate.hip", "gemm_wide_192.hip", "gemm_wide_192x288.hip"]
 FLAGS = ["-x", "hip", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -31,8 +31,11 @@ def build(verbose=False):
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB])
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"],
-                           os.path.join(CSRC, "binding.cpp"), "-o", NATIVE])
+    include = sysconfig.get_paths()["include"]
+    if os.path.exists(os.path.join(include, "Python.h")):
+        subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-fPIC", "-shared", "-I" + include, os.path.join(CSRC, "binding.cpp"), "-o", NATIVE])
+    else:
+        print("no Python.h in %s: the skip calls marshal their arguments with ctypes" % include)
     if verbose:
         print("built", LIB)
     return LIB
@@ -41,7 +44,7 @@ def build(verbose=False):
 def ensure_built():
     """For the test harness, the smoke entry and the benchmark: compile only when no library has been
     built yet.  The binding itself never builds: it raises when the library is missing."""
-    if not (os.path.exists(LIB) and os.path.exists(NATIVE)):
+    if not os.path.exists(LIB):
         build(verbose=True)
     return LIB
 

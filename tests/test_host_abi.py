@@ -4,6 +4,8 @@ come back as status codes."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -429,3 +431,56 @@ def test_skip_calls_refuse_host_tensors_before_they_ask_for_a_stream(monkeypatch
         assert not asked
         none = DeviceTensor((0, 8), torch.float32)
         assert call(sched, none, none, 50, [1], out=none) is none and asked.pop()
+
+
+def test_library_loads_without_the_binding_module():
+    """Another interpreter than the build's has no such module: every call is there all the same, the skip calls through ctypes."""
+    code = ("import sys; sys.modules['paper_2603_25872_amd._native'] = None\n"
+            "from paper_2603_25872_amd import drf\n"
+            "sched = dict(train_steps=1000, beta_start=1e-4, beta_end=0.02, steps=50)\n"
+            "assert len(drf.plan_build(sched, drf.CONSERVATIVE, 4)) and drf._skip is drf._skip_ctypes\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=120)
+
+
+def test_both_marshallings_of_the_skip_calls_agree():
+    """The same calls through the CPython module and through ctypes: status, message and type of error, over schedules, shapes, indices and
+    tensors that are taken and refused (nothing is launched: the batch is empty, or the call is refused)."""
+    torch = pytest.importorskip("torch")
+    import collections
+    drf.lib()
+    assert drf._skip is not drf._skip_ctypes         # built beside the library here
+    sched = dict(train_steps=1000, beta_start=1e-4, beta_end=0.02, steps=50)
+    tensor = lambda *shape, dtype=torch.float32, **kw: DeviceTensor(shape, dtype, **kw)
+    none, one = tensor(0, 8), tensor(1, 8)
+
+    def outcome(form, *args):
+        try:
+            status = form(*args)
+            return status, drf.lib().drf_last_error() if status else None
+        except Exception as e:
+            return TypeError if isinstance(e, C.ArgumentError) else type(e)      # (how ctypes reports one of its arguments)
+
+    def same(sc=sched, x=none, net=one, s_from=50, to=(1, 2), noise=None, out=one, stream=0):
+        a, b = (outcome(form, sc, x, net, s_from, to, noise, out, torch.float32, stream) for form in (drf._skip, drf._skip_ctypes))
+        assert a == b, (sc, x.shape, to, a, b)
+        return a
+
+    values = (0, 1, 3, -1, 50, 51, 2 ** 31, 2 ** 40, -2 ** 70, True, 1.0, "1", "x", None, np.int64(4), np.float64(0.5), torch.tensor(2), float("nan"))
+    for v in values:
+        for field in ("train_steps", "beta_start", "beta_end", "steps", "eta", "sampler", "shift"):
+            for kind in (dict, collections.UserDict):
+                same(kind(dict(sched, **{field: v})))
+        same(x=one, to=[v], net=None)
+        same(x=one, to=[v, v], out=None)
+        same(x=one, s_from=v, out=None)
+    for field in sched:
+        assert same({k: sched[k] for k in sched if k != field}) is KeyError
+    for to in ([], (), range(3), {1, 2}, {1: 0}, np.arange(3), torch.arange(3), list(range(40)), 3, None, "12", iter([1])):
+        same(to=to)
+    for shape in ((), (0,), (3,), (0, 0), (2, 0), (1, 0, 4), (5, 2, 3, 4)):
+        same(x=tensor(*shape), net=None)
+    for bad in (tensor(1, 8, contiguous=False), tensor(1, 8, dtype=torch.float16), torch.zeros(1, 8), 3, None):
+        same(net=bad), same(out=bad)
+        if hasattr(bad, "shape"):
+            same(x=bad)
+    same(stream=lambda: 0)
