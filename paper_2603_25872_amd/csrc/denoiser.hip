@@ -378,12 +378,18 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
     // GEMM whose k-loop waits on first-touch weight lines runs measurably slower than the same GEMM with
     // warm weights.  So each bf16 GEMM of the block chain (qkv -> proj -> fc1 -> fc2 -> next block's
     // qkv; with text -> proj -> xq -> xo -> fc1) touches the weights of its successor while its own last round of tiles starts.
+    // Around the cross-attention only from some rows on (warm_text): few workgroups take longer over 4 D^2 weights of fc1 than over their own
+    // product, and a narrow model's weights stay in the caches.  Evaluations of 28 blocks without : with these, us: hidden 1152 16 rows 2183 :
+    // 2468, 64 2192 : 2302, 128 2271 : 2280, 160 2297 : 2318, 192 2361 : 2347, 256 2457 : 2426; 768 16 rows 1866 : 2068, 160 1906 : 1924, 192 1953 :
+    // 1940, 256 1982 : 1962; 576 64 rows 2108 : 2242, 192 2098 : 2110, 1024 2397 : 2367, 4096 4122 : 4050 (12 blocks: 512 rows 907 : 914, 1024
+    // 1000 : 991); 384 and 512, 16 to 768 rows up to 5 % behind, 1024 to 4096 rows within 0.7 % either way.
     // In a thin pass a branch GEMM may split K across workgroups: its partial tiles are then the last pending branch
     // (part), and the LayerNorm launch that adds them stores the stream.
     const bf16_t *pend1 = nullptr, *pend2 = nullptr;
     PartialBranch part{};
     const bool may_leave = !f32 && ln_partial_width(D) && nm % 4 == 0;
     const bool text = d->cfg.cond == DRF_COND_TEXT;
+    const bool warm_text = D >= 768 ? M >= 192 : D > 512 && M >= 1024;
     auto ln = [&](const float* shift, const float* scale, int mod_ld, bool store) -> drf_status {
         if (part.sum.splits) {
             ProfScope ps(d, st, DRF_PROF_ELEMWISE, (double)M * D * (10.0 + 4.0 * part.sum.splits + (pend1 ? 2.0 : 0.0)));
@@ -488,13 +494,13 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
         if (f32) {
             if ((rc = gemm(d, ws.hbuf, b.proj, M, epi_resid(ws.resid, D, mrow + 2 * D, nm, dm.T), st)) != DRF_OK) return rc;
         } else {
-            if ((rc = gemm(d, ws.hbuf, b.proj, M, with_warm(epi_gated(ws.ybuf, D, mrow + 2 * D, nm, dm.T), text ? &b.xq : &b.fc1), st, ws.skpart, may_leave ? &part.sum : nullptr)) != DRF_OK) return rc;
+            if ((rc = gemm(d, ws.hbuf, b.proj, M, with_warm(epi_gated(ws.ybuf, D, mrow + 2 * D, nm, dm.T), !text ? &b.fc1 : warm_text ? &b.xq : nullptr), st, ws.skpart, may_leave ? &part.sum : nullptr)) != DRF_OK) return rc;
             part.bias = b.proj.b; part.gate = mrow + 2 * D;
             if (!part.sum.splits) pend1 = (const bf16_t*)ws.ybuf;
         }
         if (d->cfg.cond == DRF_COND_TEXT) {
             const int ctx_rows = map.cond_mod ? map.cond_mod : slots;
-            if ((rc = ln_linear(nullptr, nullptr, 0, true, b.xq, with_warm(epi_store(ws.qkv, D, f32), &b.xo))) != DRF_OK) return rc;
+            if ((rc = ln_linear(nullptr, nullptr, 0, true, b.xq, with_warm(epi_store(ws.qkv, D, f32), warm_text ? &b.xo : nullptr))) != DRF_OK) return rc;
             const char* kv = (const char*)ws.xkv + (size_t)l * ctx_rows * d->cfg.ctx_len * 2 * D * act;
             AttnArgs aa{};
             aa.q = ws.qkv; aa.ldq = D; aa.k = kv; aa.v = kv + (size_t)D * act; aa.ldk = 2 * D; aa.out = ws.hbuf; aa.ldo = D;
@@ -505,7 +511,7 @@ drf_status forward(drf_denoiser* d, const Workspace& ws, const float* x, const S
                 ProfScope ps(d, st, DRF_PROF_ATTN, 4.0 * slots * dm.heads * (double)dm.T * d->cfg.ctx_len * dm.d);
                 if ((rc = f32 ? launch_attn_f32(aa, st) : launch_attn_bf16(aa, st)) != DRF_OK) return rc;
             }
-            if ((rc = gemm(d, ws.hbuf, b.xo, M, with_warm(epi_resid(ws.resid, D, nullptr, 0, dm.T), &b.fc1), st, ws.skpart)) != DRF_OK) return rc;
+            if ((rc = gemm(d, ws.hbuf, b.xo, M, with_warm(epi_resid(ws.resid, D, nullptr, 0, dm.T), warm_text ? &b.fc1 : nullptr), st, ws.skpart)) != DRF_OK) return rc;
         }
         const bool last = l == n_blocks - 1;
         if ((rc = ln_linear(mrow + 3 * D, mrow + 4 * D, nm, f32 || last, b.fc1, with_warm(epi_store(ws.mid, dm.R * D, f32, true), f32 ? nullptr : &b.fc2))) != DRF_OK) return rc;
