@@ -554,7 +554,8 @@ constexpr int kLongFrom[2][2][12] = {
 // one's loads and stores run beside another's steps, and K and V take one or two chunks.  Against the persistent chunked kernel 1.05-2.0x
 // over widths 8 to 88 and 32 to 256 rows (d = 72, 77 rows, 16 heads: 8 slots x 1024 queries 19.5 -> 15.1 us, 24 slots 50.5 -> 39.3); one workgroup
 // to a CU it is ahead at 72 and 80 only (4 slots x 1024: 11.7 -> 10.4 us over 77 rows, 11.0 -> 10.9 over 128; 64: 10.1 -> 10.5).
-// Up to 256 queries (32 slots x 256) neither is ahead everywhere (0.86-1.25x).
+// Up to 256 queries (32 slots x 256) neither is ahead everywhere (0.86-1.25x).  From 2^24 workgroups on its threads would not fit 32 bits; persistent
+// ones take any number of items.
 AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled)
 {
     if (Nk > 256) {
@@ -568,7 +569,7 @@ AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled)
     if (items <= 1 << 23 && (Nq <= 128 || at_once)) return items > 4096 || (d > 80 && Nq > 96 && !at_once) ? ATTN_SHORT_64 : ATTN_SHORT;
     if (Nq <= 128) return ATTN_CHUNKED_FEW;
     const long long groups = (long long)((Nq + 255) / 256) * heads * slots;
-    if (Nq > 256 && d <= 88 && groups >= (d == 72 || d == 80 ? 256 : 257)) return ATTN_LONG;
+    if (Nq > 256 && d <= 88 && groups >= (d == 72 || d == 80 ? 256 : 257) && groups < 1 << 24) return ATTN_LONG;
     return groups > kPersistGroups ? ATTN_CHUNKED_PERSIST : ATTN_CHUNKED;
 }
 

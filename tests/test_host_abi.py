@@ -216,6 +216,13 @@ def test_wide_heads_share_kv_between_two_query_blocks_from_the_second_round_on(d
     assert route(64, 96, 256, 4, d) == 1 and route(8, 128, 256, 4, d) == 1
 
 
+@pytest.mark.parametrize("d", [8, 40, 72, 80, 88])
+def test_many_queries_over_short_kv_stay_within_a_grid(d):
+    """One workgroup of 256 threads to 256 queries of a head, up to 2^32 threads a launch; persistent workgroups beyond."""
+    route = drf.probe_attn_route
+    assert route(2 ** 18 - 1, 1024, 77, 16, d) == 7 and route(2 ** 18, 1024, 77, 16, d) == route(2 ** 20, 1024, 256, 16, d) == 4
+
+
 def test_gemm_routes_are_readable():
     """Small problems split K where they may, a part-filled last round goes to a second launch, bad arguments are refused."""
     tile, parts, first_tile, first_rows = drf.probe_gemm_route(512, 1152, 4608, 2)
