@@ -667,7 +667,7 @@ int wide_form(int tile, int rows, int N, int K, const Epilogue& e)
 // Rows m_first .. M - 1 of the problem with tile v (m_first a multiple of the tile's height).
 drf_status launch_tile(int v, const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first)
 {
-    if (e.mode == EPI_STORE_GELU && e.out_f32 && (v == 2 || v == 3 || v == 21 || v == 22)) v = 14;      // (the 4-wave tiles have no such store)
+    if (e.mode == EPI_STORE_GELU && e.out_f32 && (v == 2 || v == 3)) v = 14;      // (the 4-wave tiles have no such store)
     switch (v) {
     case 1: return launch_bf16_xl<64, 64, 64, 4, 2, 2>(A, W, M, N, K, e, st, m_first);
     case 2: return launch_gemm_wide_288(A, W, M, N, K, e, st, m_first);

@@ -195,12 +195,16 @@ drf_status launch_wide(const bf16_t* A, const bf16_t* W, int M, int N, int K, co
     return DRF_OK;
 }
 
-template <int BM, int BN>
+// GELU: whether the shape has instances of that store.
+template <int BM, int BN, bool GELU = true>
 drf_status launch_wide_mode(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first)
 {
+    if (!GELU && e.mode == EPI_STORE_GELU) DRF_FAIL(DRF_EINVAL, "no GELU on tiles of %d x %d", BM, BN);
     if (e.mode == EPI_RESID) return launch_wide<BM, BN, EPI_RESID, true>(A, W, M, N, K, e, st, m_first);
     if (e.out_f32) return launch_wide<BM, BN, EPI_STORE, true>(A, W, M, N, K, e, st, m_first);
-    if (e.mode == EPI_STORE_GELU) return launch_wide<BM, BN, EPI_STORE_GELU, false>(A, W, M, N, K, e, st, m_first);
+    if constexpr (GELU) {
+        if (e.mode == EPI_STORE_GELU) return launch_wide<BM, BN, EPI_STORE_GELU, false>(A, W, M, N, K, e, st, m_first);
+    }
     if (e.mode == EPI_STORE_HEADS) return launch_wide<BM, BN, EPI_STORE_HEADS, false>(A, W, M, N, K, e, st, m_first);
     if (e.mode == EPI_STORE_GATED) return launch_wide<BM, BN, EPI_STORE_GATED, false>(A, W, M, N, K, e, st, m_first);
     return launch_wide<BM, BN, EPI_STORE, false>(A, W, M, N, K, e, st, m_first);

@@ -5,7 +5,7 @@ namespace drf {
 
 drf_status launch_gemm_wide_192x288(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epilogue& e, hipStream_t st, int m_first)
 {
-    return launch_wide_mode<192, 288>(A, W, M, N, K, e, st, m_first);
+    return launch_wide_mode<192, 288, false>(A, W, M, N, K, e, st, m_first);
 }
 
 }  // namespace drf
