@@ -280,6 +280,38 @@ def test_pass_of_ragged_slots_on_every_middle_tile_sampled_slots(torch, drf, orc
         assert err < 2e-2, (j, err)
 
 
+@pytest.mark.parametrize("text,lat,slots,tiles", [
+    (False, (36, 28), 13, dict(qkv=21)), (False, (32, 32), 13, dict(qkv=21)), (False, (18, 14), 56, dict(qkv=21)),
+    (False, (36, 28), 40, dict(proj=21, fc2=21)), (False, (18, 14), 160, dict(proj=21, fc2=21)),
+    (False, (36, 28), 45, dict(proj=22, fc2=22)), (False, (18, 14), 180, dict(proj=22, fc2=22)),
+    (False, (32, 28), 17, dict(qkv=22)), (False, (8, 16), 120, dict(qkv=22)), (False, (32, 32), 48, dict(qkv=22, proj=22, fc2=22)),
+    (True, (32, 32), 34, dict(proj=21, xq=21, xo=21, fc2=21)), (True, (36, 28), 45, dict(proj=22, xq=22, xo=22, fc2=22))])
+def test_pass_on_tiles_for_part_filled_rounds_sampled_slots(torch, drf, orc, text, lat, slots, tiles):
+    """256 x 192 (21) and 192 x 288 (22) in the launches that take them: head-major planes of slots of whole 32-row passes, whose tiles begin
+    inside slots of 224 and cover several of 32, and (21) of others; one gate row, two, and more than LDS holds; the plain store and the update of the
+    stream, gated (last block) and not (behind the cross-attention).  The slots at tile edges are compared."""
+    T = lat[0] * lat[1] // 4
+    M = slots * T
+    routes = dict(block_routes(drf, M, 1152, T), xq=drf.probe_gemm_route(M, 1152, 1152, 4, T), xo=drf.probe_gemm_route(M, 1152, 1152, 4, T))
+    assert {name: routes[name] for name in tiles} == {name: (tile, 1, 0, 0) for name, tile in tiles.items()}
+    dit = dict(I.CONFIGS[4 if text else 3]["dit"], depth=2, lat_h=lat[0], lat_w=lat[1])
+    assert dit["hidden"] == 1152
+    w = I.weights(dit, 3, "loud")
+    den = drf.Denoiser(dit, w)
+    rng = np.random.default_rng(slots)
+    x = rng.standard_normal((slots, dit["in_ch"], *lat)).astype(np.float32)
+    t = rng.integers(0, 1000, size=slots).astype(np.int32)
+    cond = I.conditioning(dit, slots, 3)
+    got = den.eps_batched(torch.from_numpy(x).cuda(), torch.from_numpy(t).cuda(), torch.from_numpy(cond).cuda()).cpu().numpy()
+    den.close()
+    assert np.isfinite(got).all()
+    wd = orc.prepare_weights(w)
+    for j in sorted({r // T for r in (0, 191, 256, M // 192 * 192 - 1, M - 1)}):
+        want = orc.dit_eps(dit, wd, x[j:j + 1], t[j:j + 1], cond[j:j + 1])[0]
+        err = np.abs(got[j] - want).max() / np.abs(want).max()
+        assert err < 2e-2, (j, err)
+
+
 @pytest.mark.parametrize("g,n_chain,n_draft", [(2, 4, 4), (1, 3, 0), (2, 0, 4), (1, 1, 1)])
 def test_fused_update_probe_equals_its_parts(torch, drf, orc, g, n_chain, n_draft):
     """The measurement hook that launches the fused guidance + chain + draft update once, against the same steps
