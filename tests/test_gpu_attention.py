@@ -110,6 +110,16 @@ def test_chunks_of_64_rows(torch, drf, d, slots, T, route):
     run(torch, drf, route, *growing(np.random.default_rng(d + T), *args), *args, False, 2e-2)
 
 
+@pytest.mark.parametrize("d,slots,Nq,Nk,H,route", [(96, 17, 1024, 77, 4, 4), (96, 33, 300, 200, 8, 4), (96, 32, 513, 256, 3, 4)] +
+                         [(d, 15, 513, 256, 5, 3) for d in WIDTHS] + [(d, 8, 1000, 200, 7, 3) for d in (32, 64, 72, 88, 96)])
+def test_chunks_of_64_rows_with_several_query_blocks_a_head(torch, drf, d, slots, Nq, Nk, H, route):
+    """Cross-attention of more than 256 queries over at most 256 rows: persistent workgroups (width 96 only) and plain ones, two to four query
+    blocks to a head, the last of them of 1 to 256 queries, kv shared between slots."""
+    args = (slots, 5, Nq, Nk, H, d)
+    run(torch, drf, route, *normal(np.random.default_rng(d + Nk), *args), *args, False, 1.5e-2, look=(0, 7, slots - 1))
+    run(torch, drf, route, *growing(np.random.default_rng(d + Nk), *args), *args, False, 2e-2)
+
+
 @pytest.mark.parametrize("d", WIDTHS)
 @pytest.mark.parametrize("Nq,Nk", [(97, 97), (128, 128), (33, 192), (128, 193), (65, 256)])
 def test_64_queries_per_workgroup_of_several_waves(torch, drf, d, Nq, Nk):

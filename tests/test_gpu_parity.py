@@ -372,9 +372,10 @@ def test_bf16_text_cross_attention_77(torch, drf, orc):
 
 
 def test_bf16_attention_with_more_work_items_than_cus(torch, drf, orc):
-    # launches whose (query block, head, slot) items outnumber the CUs run persistent workgroups:
-    # self-attention over a ragged 200-token sequence, and cross-attention of 1024 queries (four
-    # query blocks per head) against a 77-row context
+    # launches whose (query block, head, slot) items outnumber the CUs: self-attention over a ragged 200-token sequence on
+    # persistent workgroups, and cross-attention of 1024 queries (four query blocks per head) against a 77-row context on
+    # workgroups of 64 queries a wave
+    assert drf.probe_attn_route(70, 200, 200, 4, 32) == 4 and drf.probe_attn_route(17, 1024, 77, 4, 32) == 7
     dit = small_dit(I.COND_CLASS, I.BF16, depth=1, lat_h=20, lat_w=40)
     check_forward(torch, drf, orc, dit, "loud", slots=70, tol=TOL_BF16, seed=41, trace=False)
     dit = small_dit(I.COND_TEXT, I.BF16, depth=1, lat_h=64, lat_w=64, ctx_len=77)
