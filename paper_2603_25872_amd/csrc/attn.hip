@@ -552,8 +552,11 @@ constexpr int kLongFrom[2][2][12] = {
 // 96 queries one form or the other is ahead by up to 20 %); beyond 2^23 items the threads of its launch would not fit 32 bits.
 // Cross-attention of more than 256 queries over at most 256 rows goes to the kernel for long sequences from the second workgroup of a CU on:
 // one's loads and stores run beside another's steps, and K and V take one or two chunks.  Against the persistent chunked kernel 1.05-2.0x
-// over widths 8 to 88 and 32 to 256 rows (d = 72, 77 rows, 16 heads: 8 slots x 1024 queries 19.5 -> 15.1 us, 24 slots 50.5 -> 39.3); one workgroup
-// to a CU it is ahead at 72 and 80 only (4 slots x 1024: 11.7 -> 10.4 us over 77 rows, 11.0 -> 10.9 over 128; 64: 10.1 -> 10.5).
+// over widths 8 to 88 and 32 to 256 rows (d = 72, 77 rows, 16 heads: 8 slots x 1024 queries 19.5 -> 15.1 us, 24 slots 50.5 -> 39.3).  One workgroup
+// to a CU, 256 of them, the plain chunked kernel against it, us: d = 72 10.07 : 9.32 over 77 rows, 9.66 : 9.80 over 128, 11.60 : 11.11 over 160, 13.09 :
+// 12.22 over 200, 12.70 : 12.68 over 256; 80 10.26 : 9.38, 9.86 : 9.82, 11.82 : 10.67, 13.39 : 12.13, 13.01 : 12.67; the other widths lose over
+// 256 rows, 8, 24, 40, 48 and 56 by 2 to 7 %, 16, 32, 64 and 88 by 8 to 12 %.  Fewer workgroups stay on the plain kernel although the two widths have the same
+// ratios there (128 to 240 of them: 72 0.97x over 128 rows, 0.99-1.08x over others, 80 1.00-1.13x).
 // Up to 256 queries (32 slots x 256) neither is ahead everywhere (0.86-1.25x).  From 2^24 workgroups on its threads would not fit 32 bits; persistent
 // ones take any number of items.
 AttnRoute attn_route(int Nq, int Nk, int heads, int d, int slots, bool q_scaled)

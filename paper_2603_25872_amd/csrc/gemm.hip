@@ -612,11 +612,15 @@ const TileModel kTiles[] = {
     { 12,  32,  64, 2, 2, 1.98, 1.34, 0.29, 0.26, 2.9, 1.7 },
 };
 
-// Tiles 21 and 22 are for the launches they were measured ahead in: 21 a single round (of q, k, v; of other launches from 200 tiles on, so
-// that 198, 8193 to 8448 rows of hidden 1152, stay as two launches), 22 up to three rounds, but not for head-major stores whose 32 rows cross slots;
-// neither for GELU.  Beyond, and as one of two launches (pick_row_split), where the model puts them level or ahead, their larger
+// Tiles 21 and 22 are for the launches they were measured ahead in: 21 a single round (of q, k, v; of other launches from 200 tiles on), 22 up
+// to three rounds, but not for head-major stores whose 32 rows cross slots; neither for GELU.  The line at 200 is no crossing: below it, where
+// the model would take 21 too, 21 is ahead as well (whole evaluations without : with the line, us, 14 blocks: hidden 1152 8448 rows, 198 tiles, 4808 :
+// 5162, slots of 247 4907 : 5247; 1024 8448 rows 4169 : 4414; 768 11008 to 12544 rows, 172 to 196 tiles, 3463 : 3698 to 3781 : 4047; 1536 6144 rows
+// 5834 : 6167).  These stay as two launches, on which a test of ragged passes stands that needs a split of this kind.  Beyond, and as one of two launches (pick_row_split), where the model puts them level or ahead, their larger
 // share of fragment reads and copies costs more than a part-filled last round (hidden 1152, whole evaluations: K = 4608 of 18432
-// rows in two rounds of 21 +1.3 %; 14336 and 28672 rows cut in two +2.6 %).
+// rows in two rounds of 21 +1.3 %; 14336 and 28672 rows cut in two +2.6 %).  Against the tiles of before over 290 evaluations of hidden 384 to
+// 2048, wherever the choice differs: 0 to -8 %, but for q, k, v of ragged slots at hidden 576 on more than 225 tiles (+0.4 to +1.4 %: 256 x 256 on
+// eight waves was ahead there) and 22 in a round of 768 or 1280 wide models' q, k, v (5888 rows +0.7 %, 3328 and 6912 rows +0.5).
 bool offered(const TileModel& t, const Epilogue& e, int M, int N)
 {
     if (t.id != 21 && t.id != 22) return true;
@@ -645,9 +649,11 @@ drf_status launch_last_tiles(int v, const bf16_t* A, const bf16_t* W, int M, int
 // against four, 256 x 256 | 256 x 288 tiles:
 //  - GELU: 8192 x 1536 x 384 18.1 : 20.5 | 20.1 : 22.0 us, 16384 x 4608 x 1152 163.7 : 170.2 | 155.3 : 162.1; 16384 x 6144 x 1536
 //    281.6 : 262.6 | 303.0 : 277.8, 8192 x 8192 x 2048 226.1 : 219.7 | 241.7 : 233.7.  A single round of K = 1152
-//    with weights from HBM loses 3 us on eight waves (33.6 : 36.9 at 2520 to 3276 rows; two stages wait for them at every k-tile), but every
-//    launch's weights are asked for by the one before: 216 to 255 tiles gain 1.6 to 2.9 us (3072 to 3584 rows; whole evaluations -0.3
-//    to -0.9 %, hidden 1024 at 224 and 240 tiles -0.9), fewer do not (208 tiles +2 %), and a full round is even (4096 rows 0 to -1.2);
+//    with weights from HBM loses on eight waves (36.9 : 33.6 to 36.9 : 35.4 at 2520 to 3276 rows; two stages wait for them at every k-tile), but
+//    every launch's weights are asked for by the one before: 216 to 255 tiles gain 1.6 to 2.9 us (3072 to 3584 rows; whole evaluations -0.3
+//    to -0.9 %, hidden 1024 at 224 and 240 tiles -0.9), fewer do not (208 tiles +2 %), and a full round is even (4096 rows 0 to -1.2).  So do the
+//    first of two launches (3584 rows of 4352 to 5632: whole evaluations -0.7 to -1.0 %, hidden 1280 -0.3 to -0.7); as the second one
+//    it is even (7424 and 7680 rows -0.3 and -0.6 %, 11520 and 11776 rows +0.7 and -0.2, where runs differ by 0.5);
 //  - head-major planes, slots of whole 32-row passes: K = 384 17.9 : 18.8 | 21.1 : 21.6, K = 512 even (19.60 : 19.56 | 21.0 : 21.9),
 //    K = 768 22.5 : 22.2 | 25.0 : 24.7, K = 1152 34.5 : 31.8 | 121.1 : 110.1;
 //  - other slot lengths: K = 768 42.9 : 43.8 | 30.3 : 32.1, K = 1152 128.6 : 138.9 | 112.4 : 118.9, K = 2048 101.9 : 96.2 | 110.9 : 106.6; a
